@@ -217,13 +217,13 @@ int hclae_online_import(hclae_ctx *ctx, const double *run_sum, const int64_t *ru
 #define HCLAE_CONTRACT_SPLIT_BF16 1   /* fp32 operands split into two bf16 terms, three bf16 MFMAs   */
 
 /*
- * Selects how the nearest-codeword kernels (Sec. 3.1 / 3.2 assignment; every entry point that assigns)
- * form the scores x'.c - ||c||^2/2.  Either way the scores only pre-select candidates within an error margin
- * (mode 0: a rigorous bound of the fp32 accumulation; mode 1: the dropped terms bounded rigorously, the
- * accumulation of a bf16 MFMA by a measured constant with a fourfold allowance) and the decision is the fp64
- * direct-form re-check, so codes, dictionaries and residues do not depend on the mode; only the number of
- * vectors that take the re-check does.  Mode 1 applies to the
- * assignments and to the multi-path scoring (hclae_beam_step, hclae_encode_beam) of every shape.
+ * Selects how the distance contraction forms the scores x'.c - ||c||^2/2 where the dictionary does not fit LDS as fp16
+ * (K = 256: D > 256), and in the multi-path scoring (hclae_beam_step, hclae_encode_beam) of every shape.  Smaller
+ * dictionaries are assigned by one kernel in either mode: fp16 matrix cores with bounds measured per vector and codeword.
+ * Whatever the arithmetic, the scores only pre-select candidates within an error margin (fp16 and mode 0: rigorous
+ * bounds; mode 1: the dropped terms bounded rigorously, the accumulation of a bf16 MFMA by a measured constant with a
+ * fourfold allowance) and the decision is a direct-form one in fp64, so codes, dictionaries and residues do not depend on
+ * the mode; only the number of vectors that take the re-check does.
  */
 int hclae_set_contraction(hclae_ctx *ctx, int mode);
 

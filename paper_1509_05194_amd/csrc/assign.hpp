@@ -66,16 +66,13 @@ struct MovedArgs {
 // k < K; -inf for the padding rows up to kpad.
 // One wave per codeword.  Also resets the two counters the assign that follows will fill
 // (refine_count[0]: re-check entries, refine_count[1]: bits of max |x'|).
-// img (or nullptr): a copy of the dictionary in the LDS order of k_assign_resident (see stage_codebook), S = k-steps
-// of a row; written here in full, zero beyond K and D, and kept up to date by k_merge, so that the assignments
-// of a stage fill their LDS with one contiguous copy instead of a gather of 16-byte pieces.
 // keep_absmax 2: max |x'| was left by the row pass that wrote x', spread over amax_parts[0..64) (block_absmax): the
 // largest word becomes refine_count[1] and the words are cleared for the next such pass.
 // entry_copy (or nullptr): receives the K x D dictionary as it is now (the carried bounds price a stage by how far
 // it moves from here); zero_word (or nullptr): a counter cleared for the kernel that follows.
 __global__ __launch_bounds__(256) void k_codeword_norms(
     const float *__restrict__ Cm, int K, int D, int ld, int kpad, float *__restrict__ hneg,
-    unsigned *__restrict__ refine_count, int keep_absmax, float *__restrict__ img, int S,
+    unsigned *__restrict__ refine_count, int keep_absmax,
     unsigned *__restrict__ amax_parts = nullptr, float *__restrict__ entry_copy = nullptr,
     unsigned *__restrict__ zero_word = nullptr)
 {
@@ -95,8 +92,6 @@ __global__ __launch_bounds__(256) void k_codeword_norms(
         if (zero_word) *zero_word = 0u;
     }
     if (k >= kpad) return;
-    if (img)
-        for (int d = lane; d < 8 * S; d += kWave) img[image_float(k, d, S)] = (k < K && d < D) ? Cm[(size_t)k * ld + d] : 0.f;
     if (k >= K) {
         if (lane == 0) hneg[k] = -__builtin_inff();
         return;
@@ -167,6 +162,12 @@ template <bool PREFIX = false>
 __device__ __forceinline__ void load_x_chunk(
     float4 (&x)[8], const float *__restrict__ xrow, int q, int h, int D, int steps = 8)
 {
+    if (!PREFIX && kChunkD * (q + 1) <= D) {               // a whole chunk (uniform): no lane masks around the loads
+        const float4 *p = reinterpret_cast<const float4 *>(xrow + kChunkD * q + 4 * h);
+#pragma unroll
+        for (int s = 0; s < 8; ++s) x[s] = p[2 * s];
+        return;
+    }
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
         const int col = kChunkD * q + 8 * s + 4 * h;
@@ -337,124 +338,6 @@ __device__ __forceinline__ void decide(
 #pragma unroll
         for (int i = 0; i < 4; ++i) it->mask[h][i] = (i < NW) ? mk[i] : 0u;
     }
-}
-
-// Assignment with the whole (padded) codebook resident in LDS: D <= 64 * NC_max dims such that
-// 32*KB * 64*NC floats fit.  Each wave owns tiles of 32 vectors, streams them from HBM straight
-// into B-operand registers in 64-dim chunks (two register sets, the next chunk in flight while
-// the current one is contracted) and keeps all 32*KB scores of a vector in accumulators.
-// PREFIX (with PRUNE 0): the last 64-dim chunk stops after the 8-dim steps that hold coordinates below D
-// (assignments on a short prefix of the coordinates, Sec. 3.2: D = 2 costs one step, not eight).
-// IMG: the LDS is filled from the image of the dictionary in its own order (k_codeword_norms, k_merge).
-template <int KB, int PRUNE = 0, bool PREFIX = false, bool IMG = false>
-__global__ __launch_bounds__(kAssignThreads) void k_assign_resident(
-    const float *__restrict__ xp, const float *__restrict__ Cm, const float *__restrict__ hneg,
-    int64_t N, int D, int ld, int K, int M, int m, int NC, float eps,
-    uint8_t *__restrict__ codes, RefineItem *__restrict__ list, unsigned *__restrict__ refine_count,
-    PruneArgs pa, const float4 *__restrict__ img = nullptr)
-{
-    extern __shared__ float4 smem4[];
-    const int S = 8 * NC;
-    float4 *lds_c = smem4;                                          // KB * S * 64 float4
-    float *lds_h = reinterpret_cast<float *>(smem4 + KB * S * kWave);   // 32*KB floats + 2
-    const int lane = lane_id();
-    const int wave = threadIdx.x >> 6;
-    const int h = lane >> 5;
-    const int r = lane & 31;
-
-    if (IMG) {                                                      // the image kept by k_codeword_norms / k_merge
-        // every block copies the same 16 * total bytes: each starts at a place of its own, so that the blocks of
-        // an XCD do not all ask the same L2 channel at the same time
-        constexpr int U = 8;
-        const int total = KB * S * kWave;
-        const int rot = (int)(blockIdx.x & 31u) * (total >> 5);
-        for (int e0 = threadIdx.x; e0 < total; e0 += U * blockDim.x) {
-            float4 v[U];
-            int at[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int e = e0 + u * blockDim.x;
-                at[u] = e + rot < total ? e + rot : e + rot - total;
-                v[u] = e < total ? img[at[u]] : make_float4(0.f, 0.f, 0.f, 0.f);
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int e = e0 + u * blockDim.x;
-                if (e < total) lds_c[at[u]] = v[u];
-            }
-        }
-    } else {
-        stage_codebook(lds_c, Cm, K, D, ld, KB, S);
-    }
-    for (int k = threadIdx.x; k < 32 * KB; k += blockDim.x) lds_h[k] = hneg[k];
-    __syncthreads();
-    // largest ||c||^2/2 over the real codewords (every thread computes the same value)
-    float hmax = 0.f;
-    for (int k = 0; k < K; ++k) hmax = fmaxf(hmax, -lds_h[k]);
-    const float cmax = sqrtf(2.f * hmax) * 1.000001f;
-
-    // Static tile schedule balanced per SIMD: waves w and w + 4 of a block share a SIMD (and its
-    // matrix pipe), so tiles are dealt round-robin to the gridDim.x * 4 SIMD slots and the two
-    // waves of a slot take alternate ones; no SIMD gets more than one tile above the average.
-    // rows of this launch: all N vectors, or the listed ones (PRUNE 2).  When nearly all are listed the launch
-    // takes all N in order instead: streaming rows beats gathering them, and a settled vector that is
-    // recomputed keeps its code (its bounds prove it) and gets fresh bounds.
-    const int64_t listed = PRUNE == 2 ? (int64_t)*pa.active_count : N;
-    const bool gather = PRUNE == 2 && listed * 32 < N * 31;
-    const int64_t rows = gather ? listed : N;
-    const int64_t ntiles = (rows + kTileVec - 1) / kTileVec;
-    const int64_t nslots = (int64_t)gridDim.x * 4;
-    const int64_t tstride = 2 * nslots;
-    const int64_t t0 = (int64_t)blockIdx.x * 4 + (wave & 3) + nslots * (wave >> 2);
-    if (t0 >= ntiles) return;
-    const int64_t my_tiles = (ntiles - t0 + tstride - 1) / tstride;
-    const int64_t G = my_tiles * NC;                                // (tile, chunk) steps of this wave
-
-    // vector behind column r of a tile; N (= "none") for the columns of the ragged tail
-    auto vec_of = [&](int64_t tile) -> int64_t {
-        const int64_t i = tile * kTileVec + r;
-        if (i >= rows) return N;
-        return gather ? (int64_t)pa.active[i] : i;
-    };
-    auto row_ptr = [&](int64_t tile) {
-        int64_t n = vec_of(tile);
-        if (n >= N) n = gather ? (int64_t)pa.active[rows - 1] : N - 1;   // tail columns re-read the last row
-        return xp + n * ld;
-    };
-
-    floatx16 acc[KB];
-    float4 xa[8], xb[8];
-    float xsq = 0.f, amax = 0.f;
-    int64_t tile = t0;
-    int q = 0;
-    const int steps_last = PREFIX ? (D - kChunkD * (NC - 1) + 7) / 8 : 8;
-    auto steps_of = [&](int qq) { return (PREFIX && qq == NC - 1) ? steps_last : 8; };
-    load_x_chunk<PREFIX>(xa, row_ptr(tile), 0, h, D, steps_of(0));
-    // Steps come in pairs so that the two register sets alternate with static names.
-    for (int64_t g = 0; g < G; g += 2) {
-        // ---- step g on xa; prefetch step g+1 into xb
-        int64_t tile1 = tile;
-        int q1 = q + 1;
-        if (q1 == NC) { q1 = 0; tile1 = tile + tstride; }
-        if (g + 1 < G) load_x_chunk<PREFIX>(xb, row_ptr(tile1), q1, h, D, steps_of(q1));
-        if (q == 0) { init_acc<KB>(acc, lds_h, h); xsq = 0.f; }
-        mfma_chunk<KB, PREFIX>(acc, xa, lds_c, q, S, lane, xsq, amax, steps_of(q));
-        if (q == NC - 1)
-            decide<KB, PRUNE>(acc, xsq, eps, hmax, cmax, lane, vec_of(tile), N, M, m, codes, list, refine_count, pa);
-        if (g + 1 >= G) break;
-        // ---- step g+1 on xb; prefetch step g+2 into xa
-        int64_t tile2 = tile1;
-        int q2 = q1 + 1;
-        if (q2 == NC) { q2 = 0; tile2 = tile1 + tstride; }
-        if (g + 2 < G) load_x_chunk<PREFIX>(xa, row_ptr(tile2), q2, h, D, steps_of(q2));
-        if (q1 == 0) { init_acc<KB>(acc, lds_h, h); xsq = 0.f; }
-        mfma_chunk<KB, PREFIX>(acc, xb, lds_c, q1, S, lane, xsq, amax, steps_of(q1));
-        if (q1 == NC - 1)
-            decide<KB, PRUNE>(acc, xsq, eps, hmax, cmax, lane, vec_of(tile1), N, M, m, codes, list, refine_count, pa);
-        tile = tile2;
-        q = q2;
-    }
-    publish_absmax(amax, refine_count + 1);
 }
 
 // Codebook in the order the D-chunked kernel stages it: float4 (q * KB * 8 + b * 8 + s) * 64 + l, l = 32 h + r,

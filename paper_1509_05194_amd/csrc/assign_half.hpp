@@ -1,0 +1,747 @@
+// Nearest-codeword assignment (Sec. 3.1/3.2; the per-dictionary step of Eq. 3 with one path) whose scores come from the
+// fp16 matrix cores (v_mfma_f32_32x32x16_f16, 16 times the rate of the fp32 MFMA on gfx950) and whose decisions are fp64.
+//
+//   argmin_k ||x - c_k||^2 = argmax_k ( (x - mu).(c_k - mu) - ||c_k - mu||^2 / 2 )          for any mu
+//
+// The scores only pre-select.  Both operands, centred on mu (the mean of a few codewords) and scaled by a power of two,
+// are rounded to fp16; what that rounding can do to a score is bounded by norms that are MEASURED, per vector and per
+// codeword, and every codeword whose score can still be the best within its own bound is a candidate.  One candidate: it
+// is the nearest codeword, whatever the rounding did.  Several: the wave itself decides among them from the fp32 data, with
+// direct-form distances (decide_items).  The codes are therefore fp64 direct-form decisions on the fp32 data, the same
+// ones an fp32 contraction with its own (narrower) margin leads to.
+//
+// Bound on the score of codeword k, in the scaled and centred units X, C (X^, C^ the fp16 values that enter the product):
+//   |X.C_k - X^.C^_k| <= ||X - X^|| ||C^_k|| + ||X|| ||C_k - C^_k||  (rounding)
+//                      + A (max||C||^2/2 + ||X|| ||C^_k||)           (accumulation),  A = (D/16 + 3) 17 2^-23:
+// an MFMA adds 16 exact products and the accumulator, and 17 2^-23 of the magnitudes it adds is what 17 addends lose
+// when each is truncated to 24 bits of the largest.  With w_k >= ||C_k||, rho = max ||C_k - C^_k|| / w_k:
+//   E_k = e w_k + h,   e = ||X - X^|| (1 + rho) + ||X|| (rho + A (1 + rho)),   h = A max||C||^2/2.
+// The matrix cores add e w_k themselves, as one more dimension of the product (X^: e, C^: w_k, both rounded up), so that the
+// accumulators end with U_k, U_k + h an upper bound of the true score; the best one's lower bound is U - 2 e w - h.
+// Per-codeword bounds instead of the largest norm for all leave a third of the undecided vectors (SIFT-shaped data, later
+// stages: 1.5 % instead of 4.5 %).
+#pragma once
+#include "assign.hpp"
+
+namespace hclae {
+
+typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
+typedef _Float16 halfx4 __attribute__((ext_vector_type(4)));
+typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
+typedef float floatv2 __attribute__((ext_vector_type(2)));
+
+constexpr int kHalfStep = 16;                       // dims per fp16 MFMA
+constexpr int kWaveMoved = 128;                     // vectors that changed cluster a wave keeps before it lists them
+constexpr int kMuRows = 8;                          // codewords whose mean centres the scores
+constexpr float kHalfMaxNorm = 64000.f;             // a scaled row beyond this may not fit fp16: all codewords are candidates
+
+// One undecided vector: its candidates (bit p of mask[h][i] is codeword 64 i + 8 (p >> 2) + 4 h + (p & 3)), a lower bound
+// on the distance to every codeword that is not among them, and the code it had.
+struct HalfItem {
+    uint32_t mask[2][4];
+    uint32_t n, old;
+    float lrest;
+    uint32_t pad;
+};
+
+// Every wave lists its undecided vectors in a stretch of its own of one array in global memory, 32 per tile of its share;
+// entries the array needs for launches over at most N vectors with `waves` waves.
+__host__ __device__ constexpr int64_t half_list_entries(int64_t N, int waves) { return N + (int64_t)waves * 2 * kTileVec; }
+
+// LDS of the resident kernel: the fp16 dictionary, then per-codeword constants, mu, and the waves' buffers.
+struct HalfLds {
+    int img, hneg, w, waug, mu, moved, misc, total; // byte offsets
+};
+__host__ __device__ constexpr HalfLds half_lds(int kb, int nc)
+{
+    HalfLds l = {};
+    l.img = 0;
+    l.hneg = kb * nc * 4096;                        // 32 kb rows of 64 nc halves
+    l.w = l.hneg + 32 * kb * 4;
+    l.waug = l.w + 32 * kb * 4;
+    l.mu = l.waug + 64 * kb * 4;
+    l.moved = l.mu + 64 * nc * 4;
+    l.misc = l.moved + kAssignWaves * kWaveMoved * 8;
+    l.total = l.misc + 256;
+    return l;
+}
+
+// Constants of a dictionary in scaled and centred units.
+struct HalfConsts {
+    float scale, inv;                               // 2^s, 2^-s
+    float h, rho, acc;                              // A max||C||^2/2, max ||C_k - C^_k|| / w_k, A
+    float cmax;                                     // max ||C||
+};
+
+__device__ __forceinline__ float uniform(float v) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v))); }
+
+// Constants the compiler does not see through: with a literal -1 it splits the mixed-precision fma below into a conversion
+// and a subtraction, and a median with a literal infinity becomes a maximum, before which it quiets NaNs one by one.
+__device__ __forceinline__ float opaque(float v)
+{
+    int b = (int)__float_as_uint(v);
+    asm("" : "+s"(b));
+    return __uint_as_float((unsigned)b);
+}
+
+// Rounds four scaled, centred coordinates to fp16; adds their squares and the squares of what the rounding left out.
+__device__ __forceinline__ halfx4 half4(const float4 &v, float &sq, float &dsq)
+{
+    const halfx2 a = __builtin_convertvector((floatv2){v.x, v.y}, halfx2);
+    const halfx2 b = __builtin_convertvector((floatv2){v.z, v.w}, halfx2);
+    const float m1 = opaque(-1.f);                   // one mixed-precision fma each: the remainder of a rounding is exact
+    const float dx = fmaf((float)a.x, m1, v.x), dy = fmaf((float)a.y, m1, v.y);
+    const float dz = fmaf((float)b.x, m1, v.z), dw = fmaf((float)b.y, m1, v.w);
+    sq = fmaf(v.x, v.x, sq);
+    sq = fmaf(v.y, v.y, sq);
+    sq = fmaf(v.z, v.z, sq);
+    sq = fmaf(v.w, v.w, sq);
+    dsq = fmaf(dx, dx, dsq);
+    dsq = fmaf(dy, dy, dsq);
+    dsq = fmaf(dz, dz, dsq);
+    dsq = fmaf(dw, dw, dsq);
+    return (halfx4){a.x, a.y, b.x, b.y};
+}
+
+__device__ __forceinline__ float4 scaled(const float4 &v, float scale, const float4 &negmu)
+{
+    return make_float4(fmaf(v.x, scale, negmu.x), fmaf(v.y, scale, negmu.y), fmaf(v.z, scale, negmu.z), fmaf(v.w, scale, negmu.w));
+}
+
+// Power of two that brings the largest codeword norm into [2^6, 2^7): rows up to 1000 times that norm stay in fp16's
+// range, and coordinates down to 2^-20 of it are normal numbers.  Every wave computes the same value; all its lanes take part.
+__device__ __forceinline__ int half_shift(const float *__restrict__ hneg, int K)
+{
+    float h = 0.f;
+    for (int k = lane_id(); k < K; k += kWave) h = fmaxf(h, -hneg[k]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) h = fmaxf(h, __shfl_xor(h, o, kWave));
+    if (!(h > 0.f) || !(h < __builtin_inff())) return 0;
+    int e;
+    (void)frexpf(sqrtf(2.f * h), &e);
+    const int s = 7 - e;
+    return s < -100 ? -100 : s > 100 ? 100 : s;
+}
+
+// Byte offset of the 16 bytes that lane (g, r) reads for k-step t (16 dims) of row block b: dims 16 t + 4 g .. + 3 and
+// 16 t + 8 + 4 g .. + 3 of codeword 32 b + r.  The slot of a row is permuted within its kilobyte by (t, g), so that the
+// stores of one row, which come from the lanes of a half wave, spread over the banks.
+__device__ __forceinline__ int half_slot(int t, int g, int r) { return (32 * g + (r ^ ((t & 3) | (g << 2)))) * 16; }
+
+// Sums NV values (a power of two, at most 32) over the 32 lanes of a half wave: NV - 1 exchanges for all of them, each
+// halving the values a lane carries.  Lane i of the half ends with the total of value i (NV < 32: the lanes that agree
+// with it in their lowest bits too).
+template <int NV>
+__device__ __forceinline__ float half_wave_sums(float (&v)[NV])
+{
+    const int lane = lane_id();
+#pragma unroll
+    for (int o = NV / 2; o > 0; o >>= 1) {
+#pragma unroll
+        for (int i = 0; i < o; ++i) {
+            float lo = v[i], hi = v[i + o];
+            asm("" : "+v"(lo), "+v"(hi));                           // two values, not one array indexed by the lane
+            const bool up = (lane & o) != 0;
+            v[i] = (up ? hi : lo) + __shfl_xor(up ? lo : hi, o, kWave);
+        }
+    }
+    float s = v[0];
+#pragma unroll
+    for (int o = NV; o < 32; o <<= 1) s += __shfl_xor(s, o, kWave);
+    return s;
+}
+
+// Fills LDS with the dictionary (first D coordinates of rows of stride ld, zero beyond) and its constants.  A half wave
+// takes a row: its loads are contiguous and its sums stay in the half wave.
+template <int KB>
+__device__ __forceinline__ HalfConsts stage_half(
+    char *lds, const HalfLds L, const float *__restrict__ Cm, const float *__restrict__ hneg, int K, int D, int ld, int NC)
+{
+    constexpr int RP = 2 * KB;                                      // rows per half wave (512 threads)
+    const int l32 = threadIdx.x & 31, hw = threadIdx.x >> 5;
+    float *lds_h = reinterpret_cast<float *>(lds + L.hneg);
+    float *lds_mu = reinterpret_cast<float *>(lds + L.mu);
+    float *red = reinterpret_cast<float *>(lds + L.misc);
+    HalfConsts c;
+    c.scale = c.inv = 1.f;
+    float sums[2 * RP];                                             // per row: squares, squares of the rounding
+#pragma unroll
+    for (int i = 0; i < 2 * RP; ++i) sums[i] = 0.f;
+    for (int p0 = 0; p0 < 16 * NC; p0 += 32) {                      // all lanes stay: half_shift exchanges between them
+        const int p = p0 + l32;
+        float4 v[RP];
+#pragma unroll
+        for (int i = 0; i < RP; ++i) v[i] = load_row_piece(Cm, hw + 16 * i, 4 * p, K, D, ld);
+        float4 mu = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int i = 0; i < kMuRows; ++i) {
+            const float4 w = load_row_piece(Cm, (int)((unsigned)(i * K) / kMuRows), 4 * p, K, D, ld);
+            mu.x += w.x;
+            mu.y += w.y;
+            mu.z += w.z;
+            mu.w += w.w;
+        }
+        if (p0 == 0) {                                              // the loads above are on their way meanwhile
+            const int s = half_shift(hneg, K);
+            c.scale = ldexpf(1.f, s);
+            c.inv = ldexpf(1.f, -s);
+        }
+        const float f = -c.scale / kMuRows;
+        const float4 neg = make_float4(mu.x * f, mu.y * f, mu.z * f, mu.w * f);
+        if (p >= 16 * NC) break;
+        if (hw == 0) reinterpret_cast<float4 *>(lds_mu)[p] = neg;
+        const int t = p >> 2, g = p & 1, hi = (p >> 1) & 1;
+#pragma unroll
+        for (int i = 0; i < RP; ++i) {
+            const int row = hw + 16 * i;
+            float4 w = scaled(v[i], c.scale, neg);
+            if (row >= K) w = make_float4(0.f, 0.f, 0.f, 0.f);
+            const halfx4 q = half4(w, sums[2 * i], sums[2 * i + 1]);
+            *reinterpret_cast<halfx4 *>(lds + ((t * KB + (row >> 5)) * 1024 + half_slot(t, g, row & 31) + 8 * hi)) = q;
+        }
+    }
+    // lane i: value i of its half wave, i.e. of row hw + 16 (i / 2) its squares (i even) or those of its rounding (i odd)
+    const float mine = half_wave_sums<2 * RP>(sums);
+    const float other = __shfl_xor(mine, 1, kWave);
+    const int row = hw + 16 * ((l32 & (2 * RP - 1)) >> 1);
+    const bool holder = l32 < 2 * RP && !(l32 & 1);
+    float hm = (l32 & 1) ? other : mine;                            // ||C_k||^2
+#pragma unroll
+    for (int o = 2; o < kWave; o <<= 1) hm = fmaxf(hm, __shfl_xor(hm, o, kWave));
+    if (lane_id() == 0) red[hw >> 1] = hm;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kAssignWaves; ++i) hm = fmaxf(hm, red[i]);
+    // the sums of squares are chains of at most 4 NC terms per lane and five additions: relative error below 2^-10 for any D
+    // allowed; the rounding of the scaled and centred fp32 values themselves is 2^-24 of them.  A codeword near mu gets a
+    // floor for its norm, so that rho stays that of ordinary rounding.
+    c.cmax = sqrtf(hm) * 1.001f;
+    const float sq = (l32 & 1) ? other : mine, dsq = (l32 & 1) ? mine : other;
+    const float wk = fmaxf(sqrtf(sq) * 1.001f, c.cmax * 0.00390625f);
+    float rho = c.cmax > 0.f ? (sqrtf(dsq) * 1.001f + wk * 1.2e-7f) / wk : 0.f;
+    if (holder) {
+        const bool real = row < K;
+        const halfx2 up = {(_Float16)(wk * 1.002f), (_Float16)0.f}; // to nearest of 1.002 w: not below w
+        lds_h[row] = real ? -0.5f * sq : -1e38f;                     // finite: index bits in an infinity would be a NaN
+        reinterpret_cast<float *>(lds + L.w)[row] = (float)up.x;
+        unsigned *aug = reinterpret_cast<unsigned *>(lds + L.waug) + 64 * (row >> 5) + (row & 31);
+        aug[0] = real ? __builtin_bit_cast(unsigned, up) : 0u;      // the operand of lane (0, r); lane (1, r) has zeros
+        aug[32] = 0u;
+    }
+#pragma unroll
+    for (int o = 2; o < kWave; o <<= 1) rho = fmaxf(rho, __shfl_xor(rho, o, kWave));
+    if (lane_id() == 0) red[kAssignWaves + (hw >> 1)] = rho;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kAssignWaves; ++i) rho = fmaxf(rho, red[kAssignWaves + i]);
+    __syncthreads();                                                // red is used again
+    c.rho = rho;
+    // two units more than the MFMAs: the norms of this function, and the index bits in a score (decide_half)
+    c.acc = (float)(4 * NC + 3) * (17.f * 1.1920929e-7f);
+    c.h = c.acc * 0.5f * hm * 1.002f;
+    // the same in every lane: scalar registers
+    c.scale = uniform(c.scale);
+    c.inv = uniform(c.inv);
+    c.h = uniform(c.h);
+    c.rho = uniform(c.rho);
+    c.cmax = uniform(c.cmax);
+    return c;
+}
+
+// One 64-dim chunk of a 32-vector tile: x as load_x_chunk leaves it (lane (g, r): dims 8 s + 4 g .. + 3 of row r for
+// s = 0..7), so k-step t takes x[2t] and x[2t + 1].  steps: k-steps of the chunk that hold coordinates (PREFIX).
+template <int KB, bool PREFIX, bool AMAX>
+__device__ __forceinline__ void mfma_chunk_half(
+    floatx16 (&acc)[KB], const float4 (&x)[8], const char *__restrict__ img, const float *__restrict__ negmu, int q, int lane,
+    float scale, float &xsq, float &dsq, float &amax, int steps)
+{
+    constexpr int GB = KB < 4 ? KB : 4;              // codeword blocks whose operands are in registers at once
+    const int g = lane >> 5, r = lane & 31;
+    const float4 *mu4 = reinterpret_cast<const float4 *>(negmu) + 16 * q + g;
+    const char *base = img + (size_t)q * 4 * KB * 1024;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        if (PREFIX && t >= steps) break;
+        const float4 u = x[2 * t], v = x[2 * t + 1];
+        if (AMAX) {
+            amax = fmaxf(fmaxf(amax, fabsf(u.x)), fabsf(u.y));
+            amax = fmaxf(fmaxf(amax, fabsf(u.z)), fabsf(u.w));
+            amax = fmaxf(fmaxf(amax, fabsf(v.x)), fabsf(v.y));
+            amax = fmaxf(fmaxf(amax, fabsf(v.z)), fabsf(v.w));
+        }
+        const char *at = base + half_slot(t, g, r);
+        const halfx4 lo = half4(scaled(u, scale, mu4[4 * t]), xsq, dsq);
+        const halfx4 hi = half4(scaled(v, scale, mu4[4 * t + 2]), xsq, dsq);
+        const halfx8 w = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+#pragma unroll
+        for (int b0 = 0; b0 < KB; b0 += GB) {
+            halfx8 a[GB];
+#pragma unroll
+            for (int b = 0; b < GB; ++b) a[b] = *reinterpret_cast<const halfx8 *>(at + (t * KB + b0 + b) * 1024);
+#pragma unroll
+            for (int b = 0; b < GB; ++b) acc[b0 + b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[b], w, acc[b0 + b], 0, 0, 0);
+        }
+    }
+}
+
+// What a wave has still to decide (in global memory) and to report (in LDS).
+struct HalfWave {
+    HalfItem *items;
+    unsigned long long *moved;                      // [kWaveMoved]
+    int nitems, nmoved;                             // wave-uniform
+};
+
+// LDS of one wave: what its lanes wrote is there for all of them (LDS operations of a wave stay in order; this keeps the
+// compiler from moving them).
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Hands the wave's moved vectors to the list in global memory: one counter add.
+__device__ __forceinline__ void flush_moved(HalfWave &w, unsigned long long *__restrict__ list, unsigned *__restrict__ count)
+{
+    wave_lds_fence();
+    unsigned base = 0;
+    if (lane_id() == 0) base = atomicAdd(count, (unsigned)w.nmoved);
+    base = __shfl(base, 0, kWave);
+    for (int i = lane_id(); i < w.nmoved; i += kWave) list[base + i] = w.moved[i];
+    w.nmoved = 0;
+    wave_lds_fence();
+}
+
+// Lanes with `yes` report that vector n went from one codeword to another.
+__device__ __forceinline__ void push_moved(HalfWave &w, bool yes, unsigned n, unsigned from, unsigned to,
+                                           unsigned long long *__restrict__ list, unsigned *__restrict__ count)
+{
+    if (w.nmoved > kWaveMoved - kWave) flush_moved(w, list, count);
+    const unsigned long long who = __ballot(yes);
+    if (yes) {
+        const int at = w.nmoved + __popcll(who & ((1ull << lane_id()) - 1ull));
+        w.moved[at] = (unsigned long long)n | ((unsigned long long)from << 32) | ((unsigned long long)to << 40);
+    }
+    w.nmoved += __popcll(who);
+}
+
+// Decides the wave's items among their candidates.
+//
+// First in fp32, direct form, eight lanes per item: the lanes share a row (contiguous pieces), two candidates at a time.  A
+// sum of n non-negative terms accumulated in fp32 is within eta = (n + 6) 2^-24 of itself relatively, so where the best two
+// are further apart than that, the smaller one is the nearest codeword.  What is left (exact and nearly exact ties) is
+// decided in fp64: direct-form squared distances summed in ascending dimension order, smallest wins, exact ties go to the
+// lowest index; kRefineLanes lanes share an item there and a lane takes one candidate at a time.
+// PRUNE: the vector's bounds become these distances (the lower one limited by the bound on the codewords left out).
+// Measured at N = 1M, D = 128, K = 256 with a fifth of the vectors undecided: 15 us of the kernel, 55 us with fp64 alone.
+template <int PRUNE>
+__device__ __forceinline__ void decide_items(
+    HalfWave &w, const float *__restrict__ xp, const float *__restrict__ Cm, int D, int ld, int M, int m,
+    uint8_t *__restrict__ codes, const PruneArgs &pa,
+    unsigned long long *__restrict__ moved_list, unsigned *__restrict__ moved_count)
+{
+    __threadfence_block();                                          // the items were written by other lanes of the wave
+    const int lane = lane_id();
+    const int d4 = D >> 2;
+    const bool want_moved = moved_list != nullptr;
+    int hard = 0;                                                   // items left for fp64, moved to the front
+    {
+        const int sub = lane & 7, first = lane & 56;
+        const int d4up = (D + 3) >> 2;
+        const float eta = (float)(4 * ((d4up + 7) >> 3) + 6) * 6.1e-8f;
+        for (int i0 = 0; i0 < w.nitems; i0 += 8) {
+            const bool live = i0 + (lane >> 3) < w.nitems;
+            const HalfItem *it = w.items + (live ? i0 + (lane >> 3) : 0);
+            const unsigned n = it->n, old = it->old;
+            const float lrest = it->lrest;
+            const uint32_t word = it->mask[sub >> 2][sub & 3];
+            uint32_t bits = live ? word : 0u;
+            const float4 *x = reinterpret_cast<const float4 *>(xp + (size_t)n * ld);
+            float best = __builtin_inff(), second = __builtin_inff();
+            int kbest = 0;
+            // next candidate of the lane's item, -1 when there is none; the same for its eight lanes
+            auto next = [&]() {
+                const unsigned have = (unsigned)(__ballot(bits != 0u) >> first) & 255u;
+                const int src = have ? __ffs(have) - 1 : 0;
+                const int p = __ffs(bits) - 1;
+                const int k = __shfl(64 * (sub & 3) + 8 * (p >> 2) + 4 * (sub >> 2) + (p & 3), first + src, kWave);
+                if (sub == src) bits &= bits - 1u;
+                return have ? k : -1;
+            };
+            while (__ballot(bits != 0u)) {
+                const int k0 = next(), k1 = next();
+                const float4 *c0 = reinterpret_cast<const float4 *>(Cm + (size_t)(k0 < 0 ? 0 : k0) * ld);
+                const float4 *c1 = reinterpret_cast<const float4 *>(Cm + (size_t)(k1 < 0 ? 0 : k1) * ld);
+                float s0 = 0.f, s1 = 0.f;
+                auto term = [](float s, const float4 &u, const float4 &v) {
+                    const float a = u.x - v.x, b = u.y - v.y, c = u.z - v.z, d = u.w - v.w;
+                    return fmaf(d, d, fmaf(c, c, fmaf(b, b, fmaf(a, a, s))));
+                };
+#pragma unroll 4
+                for (int d = sub; d < d4; d += 8) {
+                    const float4 u = x[d];
+                    s0 = term(s0, u, c0[d]);
+                    s1 = term(s1, u, c1[d]);
+                }
+                if ((D & 3) && sub == (d4 & 7)) {                   // D need not be a multiple of 4
+                    for (int d = 4 * d4; d < D; ++d) {
+                        const float u = reinterpret_cast<const float *>(x)[d];
+                        const float a = u - reinterpret_cast<const float *>(c0)[d], b = u - reinterpret_cast<const float *>(c1)[d];
+                        s0 = fmaf(a, a, s0);
+                        s1 = fmaf(b, b, s1);
+                    }
+                }
+#pragma unroll
+                for (int o = 1; o < 8; o <<= 1) {
+                    s0 += __shfl_xor(s0, o, kWave);
+                    s1 += __shfl_xor(s1, o, kWave);
+                }
+                if (k0 >= 0) {
+                    second = s0 < best ? best : fminf(second, s0);
+                    if (s0 < best) { best = s0; kbest = k0; }
+                }
+                if (k1 >= 0) {
+                    second = s1 < best ? best : fminf(second, s1);
+                    if (s1 < best) { best = s1; kbest = k1; }
+                }
+            }
+            // (the second condition keeps underflow out: a sum this large has no denormal part that counts)
+            const bool sure = best * (1.f + eta) < second * (1.f - eta) && second > 1e-25f;
+            const bool lead = live && sub == 0;
+            const unsigned long long left = __ballot(lead && !sure);
+            if (live && !sure) {
+                HalfItem *to = w.items + hard + __popcll(left & ((1ull << first) - 1ull));
+                to->mask[sub >> 2][sub & 3] = word;
+                if (sub == 0) {
+                    to->n = n;
+                    to->old = old;
+                    to->lrest = lrest;
+                }
+            }
+            hard += __popcll(left);
+            if (lead && sure) {
+                codes[(size_t)n * M + m] = (uint8_t)kbest;
+                if (PRUNE) {
+                    pa.bu[n] = sqrtf(best * (1.f + eta)) * 1.000001f;
+                    pa.bl[n] = fminf(sqrtf(second * (1.f - eta)) * 0.999999f, lrest);
+                }
+            }
+            if (want_moved) push_moved(w, lead && sure && old != (unsigned)kbest, n, old, (unsigned)kbest, moved_list, moved_count);
+            __threadfence_block();
+        }
+    }
+    const int sub = lane & (kRefineLanes - 1);
+    for (int i0 = 0; i0 < hard; i0 += kWave / kRefineLanes) {
+        const int e = i0 + lane / kRefineLanes;
+        const bool live = e < hard;
+        const HalfItem it = w.items[live ? e : 0];
+        int total = 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) total += __popc(it.mask[i >> 2][i & 3]);
+        if (!live) total = 0;
+        const float4 *x = reinterpret_cast<const float4 *>(xp + (size_t)it.n * ld);
+        double best = __builtin_inf(), second = __builtin_inf();
+        int kbest = 0x7fffffff;
+        for (int j0 = sub; j0 < total; j0 += kRefineLanes) {
+            int j = j0, k = 0;                                      // codeword of the j-th set bit
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                uint32_t bits = it.mask[i >> 2][i & 3];
+                const int c = __popc(bits);
+                if (j >= 0 && j < c) {
+                    for (int q = 0; q < j; ++q) bits &= bits - 1;
+                    const int p = __ffs(bits) - 1;
+                    k = 64 * (i & 3) + 8 * (p >> 2) + 4 * (i >> 2) + (p & 3);
+                    j = -1;
+                } else if (j >= 0) {
+                    j -= c;
+                }
+            }
+            const float4 *c4 = reinterpret_cast<const float4 *>(Cm + (size_t)k * ld);
+            double s = 0.0;
+#pragma unroll 4
+            for (int d = 0; d < d4; ++d) {                          // four rounds of loads in flight, additions in order
+                const float4 a = x[d], b = c4[d];
+                const double t0 = (double)a.x - (double)b.x, t1 = (double)a.y - (double)b.y;
+                const double t2 = (double)a.z - (double)b.z, t3 = (double)a.w - (double)b.w;
+                s += t0 * t0;
+                s += t1 * t1;
+                s += t2 * t2;
+                s += t3 * t3;
+            }
+            for (int d = 4 * d4; d < D; ++d) {
+                const double t = (double)reinterpret_cast<const float *>(x)[d] - (double)reinterpret_cast<const float *>(c4)[d];
+                s += t * t;
+            }
+            if (s < best || (s == best && k < kbest)) { second = best; best = s; kbest = k; }
+            else if (s < second) second = s;
+        }
+#pragma unroll
+        for (int o = kRefineLanes / 2; o > 0; o >>= 1) {
+            const double ob = __shfl_xor(best, o, kWave), os = __shfl_xor(second, o, kWave);
+            const int ok = __shfl_xor(kbest, o, kWave);
+            second = fmin(fmax(best, ob), fmin(second, os));
+            if (ob < best || (ob == best && ok < kbest)) { best = ob; kbest = ok; }
+        }
+        const bool lead = live && sub == 0;
+        if (lead) {
+            codes[(size_t)it.n * M + m] = (uint8_t)kbest;
+            if (PRUNE) {
+                pa.bu[it.n] = (float)sqrt(best) * 1.000001f;
+                pa.bl[it.n] = fminf((float)sqrt(second) * 0.999999f, it.lrest);
+            }
+        }
+        if (want_moved) push_moved(w, lead && it.old != (unsigned)kbest, it.n, it.old, (unsigned)kbest, moved_list, moved_count);
+    }
+}
+
+// Last step of a tile's contraction: the product's extra dimension.  Returns e, and the norms it is made of.
+template <int KB>
+__device__ __forceinline__ float mfma_bound_half(
+    floatx16 (&acc)[KB], const unsigned *__restrict__ waug, float xsq, float dsq, const HalfConsts &c, int lane, float &x2, float &xn)
+{
+    x2 = xsq + __shfl_xor(xsq, 32, kWave);
+    xn = sqrtf(x2) * 1.001f;
+    const float dx = sqrtf(dsq + __shfl_xor(dsq, 32, kWave)) * 1.001f + xn * 1.2e-7f;
+    // rounded up to fp16 (to nearest of 1.002 e), and not below its smallest normal number
+    const float e = fmaxf((dx * (1.f + c.rho) + xn * (c.rho + c.acc * (1.f + c.rho))) * 1.002f, 6.2e-5f);
+    const halfx2 eh = {(_Float16)e, (_Float16)0.f};
+    const halfx4 w = {eh.x, (_Float16)0.f, (_Float16)0.f, (_Float16)0.f};
+#pragma unroll
+    for (int b = 0; b < KB; ++b) {
+        const halfx2 u = __builtin_bit_cast(halfx2, waug[64 * b + lane]);
+        const halfx4 a = {u.x, u.y, (_Float16)0.f, (_Float16)0.f};
+        acc[b] = __builtin_amdgcn_mfma_f32_32x32x8f16(a, w, acc[b], 0, 0, 0);
+    }
+    return (float)eh.x;
+}
+
+// Decision for the wave's 32 vectors from their upper scores U_k.  old: the code the vector has now.
+//
+// The best and the second best of a lane's scores are found on keys: the score with its last four bits replaced by its
+// index in the accumulator block (2^-19 of the score, within h).  Where the second one stays below the threshold the
+// best key names the only candidate; only a tile with an undecided vector builds candidate bitmaps (see decide()).
+template <int KB, int PRUNE>
+__device__ __forceinline__ void decide_half(
+    const floatx16 (&acc)[KB], float x2, float xn, float e, const HalfConsts &c, const float *__restrict__ lds_w, int lane, int n,
+    int N, int K, int M, int m, unsigned old, uint8_t *__restrict__ codes, const PruneArgs &pa, HalfWave &w,
+    unsigned long long *__restrict__ moved_list, unsigned *__restrict__ moved_count)
+{
+    const int h = lane >> 5;
+    const float inf = opaque(__builtin_inff());
+    float mx = -__builtin_inff(), m2 = -__builtin_inff();            // best and second best key
+    int blk = 0;
+#pragma unroll
+    for (int b = 0; b < KB; ++b) {                                   // one chain: chains side by side cost registers
+        const float before = mx;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const float key = __uint_as_float((__float_as_uint(acc[b][v]) & ~15u) | (unsigned)v);
+            m2 = __builtin_amdgcn_fmed3f(mx, m2, key);               // m2 <= mx always: the median is the new second
+            mx = __builtin_amdgcn_fmed3f(mx, key, inf);              // the larger one
+        }
+        blk = mx != before ? b : blk;
+    }
+    const int v = (int)(__float_as_uint(mx) & 15u);
+    int code = 32 * blk + 8 * (v >> 2) + 4 * h + (v & 3);
+    {
+        const float mxo = __shfl_xor(mx, 32, kWave), m2o = __shfl_xor(m2, 32, kWave);
+        const int co = __shfl_xor(code, 32, kWave);
+        m2 = fmaxf(fminf(mx, mxo), fmaxf(m2, m2o));
+        if (mxo > mx || (mxo == mx && h == 1)) code = co;            // the two halves agree
+        mx = fmaxf(mx, mxo);
+    }
+    code = code < K ? code : 0;                                     // beyond K only with non-finite input
+    const float hh = c.h + 2.1e-6f * (fabsf(mx) + xn * c.cmax) + 1e-36f;   // h, and what the index bits did to the keys (to a zero, too)
+    const float low = mx - 2.f * e * lds_w[code] - hh;              // lower bound of the best one's true score
+    const float thr = low - hh;                                     // candidates: U_k + h >= low
+    const bool big = !(x2 < kHalfMaxNorm * kHalfMaxNorm && fabsf(thr) < 1e37f);   // may not fit fp16
+    const bool amb = K > 1 && n < N && (big || !(m2 < thr));
+    const bool mine = h == 0 && n < N;
+    float slack = 0.f;
+    if (PRUNE) slack = pa.slack * (x2 + 2.f * fabsf(mx) + 2.f * fabsf(m2));
+    if (mine && !amb) {
+        codes[(size_t)n * M + m] = (uint8_t)code;
+        if (PRUNE) {
+            // d^2 = ||X||^2 - 2 score; slack covers the fp32 evaluation (see decide())
+            pa.bu[n] = K > 1 ? sqrtf(fmaxf(0.f, (x2 - 2.f * low) + slack)) * 1.00001f * c.inv : __builtin_inff();
+            pa.bl[n] = K > 1 ? sqrtf(fmaxf(0.f, (x2 - 2.f * (m2 + hh)) - slack)) * 0.99999f * c.inv : 0.f;
+        }
+    }
+    if (moved_list) push_moved(w, mine && !amb && old != (unsigned)code, (unsigned)n, old, (unsigned)code, moved_list, moved_count);
+    const uint32_t who = (uint32_t)__ballot(amb && h == 0);
+    if (!who) return;
+    constexpr int NW = (KB + 1) / 2;
+    uint32_t mk[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int b = 0; b < KB; ++b) {
+        uint32_t below = 0u;
+#pragma unroll
+        for (int i = 15; i >= 0; --i)
+            below = __builtin_amdgcn_alignbit(below, __float_as_uint(acc[b][i] - thr), 31);   // (below << 1) | sign
+        mk[b >> 1] |= (~below & 0xffffu) << ((b & 1) * 16);
+    }
+    if (big) {
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            uint32_t all = 0u;
+#pragma unroll 1
+            for (int p = 0; p < 32; ++p) all |= (64 * i + 8 * (p >> 2) + 4 * h + (p & 3) < K) ? 1u << p : 0u;
+            mk[i] = all;
+        }
+    }
+    if (amb) {
+        HalfItem *it = w.items + w.nitems + __popc(who & ((1u << (lane & 31)) - 1u));
+        if (h == 0) {
+            it->n = (uint32_t)n;
+            it->old = old;
+            // codewords left out have a true score <= thr + h
+            it->lrest = PRUNE && !big ? sqrtf(fmaxf(0.f, (x2 - 2.f * (thr + hh)) - slack)) * 0.99999f * c.inv : __builtin_inff();
+        }
+        *reinterpret_cast<uint4 *>(it->mask[h]) = make_uint4(mk[0], mk[1], mk[2], mk[3]);
+    }
+    w.nitems += __popc(who);
+}
+
+// Assignment with the whole dictionary resident in LDS as fp16 (KB * NC <= 32: K = 256 up to D = 256).  Tile schedule and
+// register streaming as in the other resident kernels: a wave owns tiles of 32 vectors, streams them from HBM into operand
+// registers 64 dims at a time with the next chunk in flight, and keeps all 32 KB scores of a vector in accumulators.
+template <int KB, int PRUNE, bool PREFIX>
+__global__ __launch_bounds__(kAssignThreads) void k_assign_half(
+    const float *__restrict__ xp, const float *__restrict__ Cm, const float *__restrict__ hneg,
+    int N, int D, int ld, int K, int M, int m, int NC,
+    uint8_t *__restrict__ codes, unsigned *__restrict__ refine_count, PruneArgs pa,
+    unsigned long long *__restrict__ moved_list, unsigned *__restrict__ moved_count, unsigned long long *__restrict__ work,
+    HalfItem *__restrict__ items)
+{
+    extern __shared__ float4 smem4[];
+    char *lds = reinterpret_cast<char *>(smem4);
+    const HalfLds L = half_lds(KB, NC);
+    const int lane = lane_id();
+    const int wave = threadIdx.x >> 6;
+    const int h = lane >> 5;
+    const int r = lane & 31;
+    const float *lds_h = reinterpret_cast<const float *>(lds + L.hneg);
+    const float *lds_mu = reinterpret_cast<const float *>(lds + L.mu);
+    const bool want_moved = moved_list != nullptr;
+
+    // rows of this launch: all N vectors, or the listed ones (PRUNE 2; all in order when nearly all are listed)
+    const int listed = PRUNE == 2 ? (int)*pa.active_count : N;
+    const bool gather = PRUNE == 2 && listed < N - (N >> 5);
+    const int rows = gather ? listed : N;
+    const int ntiles = (int)(((unsigned)rows + kTileVec - 1) / kTileVec);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        work[0] += 1ull;                                            // launches on one stream follow one another
+        work[1] += (unsigned long long)listed;
+    }
+    if ((int)blockIdx.x * 4 >= ntiles) return;                  // no tile for any wave of this block
+
+    HalfWave w;
+    w.moved = reinterpret_cast<unsigned long long *>(lds + L.moved) + wave * kWaveMoved;
+    w.nitems = 0;
+    w.nmoved = 0;
+
+    const int nslots = (int)gridDim.x * 4;
+    const int tstride = 2 * nslots;
+    const int t0 = (int)blockIdx.x * 4 + (wave & 3) + nslots * (wave >> 2);
+    const int my_tiles = t0 < ntiles ? (ntiles - t0 + tstride - 1) / tstride : 0;
+    const int64_t G = (int64_t)my_tiles * NC;                       // (tile, chunk) steps of this wave
+    w.items = items + (size_t)((ntiles + tstride - 1) / tstride) * kTileVec * (blockIdx.x * kAssignWaves + wave);
+
+    // vector behind column r of a tile; N (= "none") for the columns of the ragged tail
+    auto vec_of = [&](int tile) -> int {
+        const unsigned i = (unsigned)tile * kTileVec + r;
+        if (i >= (unsigned)rows) return N;
+        return gather ? (int)pa.active[i] : (int)i;
+    };
+    auto row_ptr = [&](int n) {
+        if (n >= N) n = gather ? (int)pa.active[rows - 1] : N - 1;   // tail columns re-read the last row
+        return xp + (size_t)n * ld;
+    };
+
+    float amax = 0.f;
+    const int steps_last = PREFIX ? (D - kChunkD * (NC - 1) + kHalfStep - 1) / kHalfStep : 4;
+    auto steps_of = [&](int qq) { return (PREFIX && qq == NC - 1) ? steps_last : 4; };
+    int tile = t0, n = N;
+    unsigned old = 0u;
+    float4 xa[8], xb[8];
+    if (G > 0) {                                                    // the first chunk travels while the dictionary is staged
+        n = vec_of(t0);
+        if (want_moved && n < N) old = codes[(size_t)n * M + m];
+        load_x_chunk<PREFIX>(xa, row_ptr(n), 0, h, D, 2 * steps_of(0));
+    }
+    const HalfConsts c = stage_half<KB>(lds, L, Cm, hneg, K, D, ld, NC);
+    if (G > 0) {
+        floatx16 acc[KB];
+        float xsq = 0.f, dsq = 0.f;
+        int q = 0;
+        init_acc<KB>(acc, lds_h, h);
+        // one step: contract x (chunk q of the tile) while the next step's chunk travels into xn
+        auto step = [&](float4 (&x)[8], float4 (&xn)[8], bool more) {
+            int tile_n = tile, n_n = n;
+            unsigned old_n = old;
+            int q_n = q + 1;
+            if (q_n == NC) {
+                q_n = 0;
+                tile_n = tile + tstride;
+                if (more) {
+                    n_n = vec_of(tile_n);
+                    if (want_moved) old_n = n_n < N ? codes[(size_t)n_n * M + m] : 0u;
+                }
+            }
+            if (more) load_x_chunk<PREFIX>(xn, row_ptr(n_n), q_n, h, D, 2 * steps_of(q_n));
+            mfma_chunk_half<KB, PREFIX, PRUNE != 2>(acc, x, lds + L.img, lds_mu, q, lane, c.scale, xsq, dsq, amax, steps_of(q));
+            if (q == NC - 1) {
+                float x2, norm;
+                const float e = mfma_bound_half<KB>(acc, reinterpret_cast<const unsigned *>(lds + L.waug), xsq, dsq, c, lane, x2, norm);
+                decide_half<KB, PRUNE>(acc, x2, norm, e, c, reinterpret_cast<const float *>(lds + L.w), lane, n, N, K, M, m, old,
+                                       codes, pa, w, moved_list, moved_count);
+                init_acc<KB>(acc, lds_h, h);                        // here and not where the next tile begins: dead until now
+                xsq = 0.f;
+                dsq = 0.f;
+            }
+            tile = tile_n;
+            n = n_n;
+            old = old_n;
+            q = q_n;
+        };
+        for (int64_t g = 0; g < G; g += 2) {
+            step(xa, xb, g + 1 < G);
+            if (g + 1 >= G) break;
+            step(xb, xa, g + 2 < G);
+        }
+    }
+    if (w.nitems) decide_items<PRUNE>(w, xp, Cm, D, ld, M, m, codes, pa, moved_list, moved_count);
+
+    // what the block's waves have left, with one atomic each: moved vectors, vectors decided in fp64, max |x'|
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, kWave));
+    unsigned *tail = reinterpret_cast<unsigned *>(lds + L.misc);   // [8] moved, [8] rechecked, [8] max, [1] base
+    if (lane == 0) {
+        tail[wave] = (unsigned)w.nmoved;
+        tail[8 + wave] = (unsigned)w.nitems;
+        tail[16 + wave] = __float_as_uint(amax);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned nm = 0u, nr = 0u, mxb = 0u;
+        for (int i = 0; i < kAssignWaves; ++i) {
+            nm += tail[i];
+            nr += tail[8 + i];
+            mxb = max(mxb, tail[16 + i]);
+        }
+        if (nm) tail[24] = atomicAdd(moved_count, nm);
+        if (nr) {
+            atomicAdd(refine_count, nr);
+            atomicAdd(work + 2, (unsigned long long)nr);
+        }
+        if (PRUNE != 2) atomicMax(refine_count + 1, mxb);           // of listed vectors nobody asks: it is known from the first pass
+    }
+    __syncthreads();
+    if (w.nmoved) {
+        unsigned at = tail[24];
+        for (int i = 0; i < wave; ++i) at += tail[i];
+        for (int i = lane; i < w.nmoved; i += kWave) moved_list[at + i] = w.moved[i];
+    }
+}
+
+}  // namespace hclae

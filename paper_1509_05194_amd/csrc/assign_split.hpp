@@ -43,26 +43,11 @@ __device__ __forceinline__ void split8(const float4 &u, const float4 &v, uint4 &
 // Per-codeword constants of the split over the first D coordinates (row stride ld), as fp32 rounded up:
 //   out[2k] = || cl_k ||  (low part),   out[2k + 1] = || c_k - ch_k - cl_k ||  (what two terms miss).
 // One wave per codeword; the assign kernel takes the maxima over k.
-// img (or nullptr; the grid then covers kpad rows): the split dictionary in the LDS order of k_assign_split (see
-// stage_codebook_split), T steps of 16 dims and kb row blocks, so that the kernel fills its LDS with one copy.
 __global__ __launch_bounds__(256) void k_split_norms(
-    const float *__restrict__ Cm, int K, int D, int ld, float *__restrict__ out,
-    uint4 *__restrict__ img = nullptr, int kb = 0, int T = 0)
+    const float *__restrict__ Cm, int K, int D, int ld, float *__restrict__ out)
 {
     const int lane = lane_id();
     const int k = blockIdx.x * (256 / kWave) + (threadIdx.x >> 6);
-    if (img && k < 32 * kb) {
-        for (int j = lane; j < 2 * T; j += kWave) {                // piece (t, g): dims 16 t + 8 g .. + 7
-            const int t = j >> 1, gg = j & 1, col = kSplitStep * t + 8 * gg;
-            const float4 u = load_row_piece(Cm, k, col, K, D, ld);
-            const float4 v = load_row_piece(Cm, k, col + 4, K, D, ld);
-            uint4 hi, lo;
-            split8(u, v, hi, lo);
-            const size_t tb = (size_t)t * kb + (k >> 5);
-            img[(tb * 2 + 0) * kWave + 32 * gg + (k & 31)] = hi;
-            img[(tb * 2 + 1) * kWave + 32 * gg + (k & 31)] = lo;
-        }
-    }
     if (k >= K) return;
     const float *c = Cm + (size_t)k * ld;
     double sl = 0.0, sd = 0.0;
@@ -163,125 +148,6 @@ __device__ __forceinline__ void mfma_chunk_split(
             for (int b = 0; b < GB; ++b) acc[b0 + b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ch[b], xh, acc[b0 + b], 0, 0, 0);
         }
     }
-}
-
-// Same tile schedule, register streaming and decision as k_assign_resident; only the contraction
-// differs.  eps and cmax_eff fold the two bounds into the form the decision uses:
-//   margin = eps * (hmax + ||x'|| * cmax_eff),  eps = 2 * (accumulation bound),
-//   cmax_eff = 1.02 cmax + (split bound per unit ||x'||) / (accumulation bound)
-// (1.02: the accumulated magnitudes are those of the split operands, ||xh|| ||ch|| + ||xh|| ||cl|| + ||xl|| ||ch||).
-template <int KB, int PRUNE = 0>
-__global__ __launch_bounds__(kAssignThreads) void k_assign_split(
-    const float *__restrict__ xp, const float *__restrict__ Cm, const float *__restrict__ hneg,
-    const float *__restrict__ split_norms,
-    int64_t N, int D, int ld, int K, int M, int m, int NC, float acc_bound,
-    uint8_t *__restrict__ codes, RefineItem *__restrict__ list, unsigned *__restrict__ refine_count,
-    PruneArgs pa, const uint4 *__restrict__ img)
-{
-    extern __shared__ float4 smem4[];
-    const int T = 4 * NC;                                                // 16-dim steps
-    uint4 *lds_c = reinterpret_cast<uint4 *>(smem4);                     // KB * T * 2 * 64 uint4
-    float *lds_h = reinterpret_cast<float *>(smem4 + (size_t)KB * T * 2 * kWave);
-    const int lane = lane_id();
-    const int wave = threadIdx.x >> 6;
-    const int g = lane >> 5;
-    const int r = lane & 31;
-
-    {   // the split dictionary as k_split_norms has just laid it out: one contiguous copy
-        constexpr int U = 8;
-        const int total = KB * T * 2 * kWave;
-        for (int e0 = threadIdx.x; e0 < total; e0 += U * blockDim.x) {
-            uint4 v[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int e = e0 + u * blockDim.x;
-                v[u] = e < total ? img[e] : make_uint4(0u, 0u, 0u, 0u);
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int e = e0 + u * blockDim.x;
-                if (e < total) lds_c[e] = v[u];
-            }
-        }
-    }
-    for (int k = threadIdx.x; k < 32 * KB; k += blockDim.x) lds_h[k] = hneg[k];
-    __syncthreads();
-    float hmax = 0.f;
-    for (int k = 0; k < K; ++k) hmax = fmaxf(hmax, -lds_h[k]);
-    const float cmax = sqrtf(2.f * hmax) * 1.000001f;
-    // dropped terms per unit ||x'||:  ||xl|| ||cl|| + ||dx|| ||c|| + ||x - dx|| ||dc||
-    //   <= 2^-8 (1 + 2^-8) clmax + 2^-16 cmax + (1 + 2^-16) dcmax
-    // maxima of the per-codeword split constants: first wave reduces, everyone reads the result from LDS
-    if (wave == 0) {
-        float a = 0.f, b = 0.f;
-        for (int k = lane; k < K; k += kWave) {
-            a = fmaxf(a, split_norms[2 * k]);
-            b = fmaxf(b, split_norms[2 * k + 1]);
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            a = fmaxf(a, __shfl_xor(a, o, kWave));
-            b = fmaxf(b, __shfl_xor(b, o, kWave));
-        }
-        if (lane == 0) { lds_h[32 * KB] = a; lds_h[32 * KB + 1] = b; }
-    }
-    __syncthreads();
-    const float clmax = lds_h[32 * KB], dcmax = lds_h[32 * KB + 1];
-    const float split_bound = (0.00390625f * 1.00391f) * clmax + 1.52587890625e-5f * cmax + 1.00002f * dcmax;
-    const float eps = 2.f * acc_bound;
-    const float cmax_eff = (cmax * 1.02f + split_bound / acc_bound) * 1.0001f;
-
-    // rows of this launch: all N vectors, or the listed ones (PRUNE 2; see PruneArgs)
-    const int64_t listed = PRUNE == 2 ? (int64_t)*pa.active_count : N;
-    const bool gather = PRUNE == 2 && listed * 32 < N * 31;         // nearly all listed: all N in order
-    const int64_t rows = gather ? listed : N;
-    const int64_t ntiles = (rows + kTileVec - 1) / kTileVec;
-    const int64_t nslots = (int64_t)gridDim.x * 4;
-    const int64_t tstride = 2 * nslots;
-    const int64_t t0 = (int64_t)blockIdx.x * 4 + (wave & 3) + nslots * (wave >> 2);
-    if (t0 >= ntiles) return;
-    const int64_t my_tiles = (ntiles - t0 + tstride - 1) / tstride;
-    const int64_t G = my_tiles * NC;
-
-    auto vec_of = [&](int64_t tile) -> int64_t {
-        const int64_t i = tile * kTileVec + r;
-        if (i >= rows) return N;
-        return gather ? (int64_t)pa.active[i] : i;
-    };
-    auto row_ptr = [&](int64_t tile) {
-        int64_t n = vec_of(tile);
-        if (n >= N) n = gather ? (int64_t)pa.active[rows - 1] : N - 1;
-        return xp + n * ld;
-    };
-
-    floatx16 acc[KB];
-    float4 xa[8], xb[8];
-    float xsq = 0.f, amax = 0.f;
-    int64_t tile = t0;
-    int q = 0;
-    load_x_chunk_split(xa, row_ptr(tile), 0, g, D);
-    for (int64_t s = 0; s < G; s += 2) {
-        int64_t tile1 = tile;
-        int q1 = q + 1;
-        if (q1 == NC) { q1 = 0; tile1 = tile + tstride; }
-        if (s + 1 < G) load_x_chunk_split(xb, row_ptr(tile1), q1, g, D);
-        if (q == 0) { init_acc<KB>(acc, lds_h, g); xsq = 0.f; }
-        mfma_chunk_split<KB>(acc, xa, lds_c, q, T, lane, xsq, amax);
-        if (q == NC - 1)
-            decide<KB, PRUNE>(acc, xsq, eps, hmax, cmax_eff, lane, vec_of(tile), N, M, m, codes, list, refine_count, pa);
-        if (s + 1 >= G) break;
-        int64_t tile2 = tile1;
-        int q2 = q1 + 1;
-        if (q2 == NC) { q2 = 0; tile2 = tile1 + tstride; }
-        if (s + 2 < G) load_x_chunk_split(xa, row_ptr(tile2), q2, g, D);
-        if (q1 == 0) { init_acc<KB>(acc, lds_h, g); xsq = 0.f; }
-        mfma_chunk_split<KB>(acc, xb, lds_c, q1, T, lane, xsq, amax);
-        if (q1 == NC - 1)
-            decide<KB, PRUNE>(acc, xsq, eps, hmax, cmax_eff, lane, vec_of(tile1), N, M, m, codes, list, refine_count, pa);
-        tile = tile2;
-        q = q2;
-    }
-    publish_absmax(amax, refine_count + 1);
 }
 
 // ---- the same contraction for dimensions whose codebook does not fit LDS ---------------------------------

@@ -12,6 +12,7 @@
 #include "../../include/hclae.h"
 #include "assign.hpp"
 #include "assign_split.hpp"
+#include "assign_half.hpp"
 #include "stream.hpp"
 #include "update.hpp"
 #include "pca.hpp"
@@ -78,13 +79,11 @@ struct hclae_ctx {
     // scratch (device)
     float *hneg;             // [32*kb]
     float4 *cb_image;        // [NC][kb*8*64] codebook in staging order (k_codebook_image; D-chunked shapes only)
-    float *lds_image;        // [kb*8*NC*64*4] dictionary of the running stage in the LDS order of the resident assign kernel
-    uint4 *split_image;      // [kb*4*NC*2*64] split dictionary in the LDS order of k_assign_split (written by k_split_norms)
-    size_t split_image_bytes;
     float *split_norms;      // [K][2] split constants of the codebook in use (contraction 1)
     int contraction;         // 0: fp32 MFMA, 1: split-bf16 MFMA
     unsigned *refine_count;
     RefineItem *refine_list; // [N_max]
+    HalfItem *half_list;     // undecided vectors of k_assign_half, a stretch per wave
     uint8_t *old_codes;      // [N_max]
     long long *partial;      // [upd_blocks][K][D] fixed-point centroid sums
     int *pcount;             // [upd_blocks][K]
@@ -285,13 +284,11 @@ int launch_heat_cool(hclae_ctx *ctx, int m, int64_t N, const float *C, const uin
 }
 
 // dact: leading coordinates that count (<= ld); ld: row stride of Cm.
-// image: also write the dictionary in the LDS order of the resident assign kernel (the centroid updates that follow
-// keep it current; launch_assign then takes it when told so).
 // keep_absmax: 0 the counter of max |x'| is reset for the assignment that follows; 1 it stays; 2 it is taken from the
 // words the row pass that wrote x' left in carry_amax[64..128) (hclae_anneal).
 // With keep_absmax 2 the kernel also copies the dictionary to carry_Centry and clears the list counter of
 // k_bounds_carry (moved_count[3]).
-int launch_norms(hclae_ctx *ctx, const float *Cm, int dact = 0, int ld = 0, int keep_absmax = 0, bool image = false)
+int launch_norms(hclae_ctx *ctx, const float *Cm, int dact = 0, int ld = 0, int keep_absmax = 0)
 {
     if (dact <= 0) dact = ctx->D;
     if (ld <= 0) ld = ctx->D;
@@ -299,10 +296,39 @@ int launch_norms(hclae_ctx *ctx, const float *Cm, int dact = 0, int ld = 0, int 
     Timed t_(ctx, HCLAE_T_NORMS);
     hipLaunchKernelGGL(k_codeword_norms, dim3((kpad + 3) / 4), dim3(256), 0, ctx->stream,
                        Cm, ctx->K, dact, ld, kpad, ctx->hneg, ctx->refine_count, keep_absmax,
-                       image && ctx->resident ? ctx->lds_image : (float *)nullptr, 8 * ctx->NC,
                        keep_absmax == 2 ? ctx->carry_amax + kAmaxSlots : (unsigned *)nullptr,
                        keep_absmax == 2 ? ctx->carry_Centry : (float *)nullptr,
                        keep_absmax == 2 ? ctx->moved_count + 3 : (unsigned *)nullptr);
+    HIP_TRY(ctx, hipGetLastError());
+    return HCLAE_OK;
+}
+
+// Whether the dictionary over `dact` coordinates fits LDS as fp16 (k_assign_half).
+bool half_resident(const hclae_ctx *ctx, int dact)
+{
+    return half_lds(ctx->kb, (dact + kChunkD - 1) / kChunkD).total <= kLdsBudget;
+}
+
+// k_assign_half over all rows or the listed ones; it also decides the near-ties and lists the moved vectors (prune 3).
+template <int KB, int PRUNE, bool PREFIX>
+int launch_assign_half(hclae_ctx *ctx, int m, int64_t N, const float *xp, const float *Cm, uint8_t *codes, int dact, int ld,
+                       const PruneArgs &pa, bool want_moved)
+{
+    const int NC = (dact + kChunkD - 1) / kChunkD;
+    const int64_t ntiles = (N + kTileVec - 1) / kTileVec;
+    int64_t blocks = (ntiles + 3) / 4;                      // few tiles: one per SIMD before any SIMD gets two
+    if (blocks > ctx->cus) blocks = ctx->cus;
+    auto kern = &k_assign_half<KB, PRUNE, PREFIX>;
+    const uint64_t attr_set = 1ull << (16 + 2 * PRUNE + (PREFIX ? 1 : 0));   // this instance's bit in ctx->attr_done
+    if (!(ctx->attr_done & attr_set)) {
+        HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget));
+        ctx->attr_done |= attr_set;
+    }
+    Timed t_(ctx, PRUNE == 2 ? HCLAE_T_ASSIGN_ACTIVE : HCLAE_T_ASSIGN);
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kAssignThreads), (size_t)half_lds(KB, NC).total, ctx->stream,
+                       xp, Cm, ctx->hneg, (int)N, dact, ld, ctx->K, ctx->M, m, NC, codes, ctx->refine_count, pa,
+                       want_moved ? ctx->moved_list : (unsigned long long *)nullptr, ctx->moved_count, ctx->work,
+                       ctx->half_list);
     HIP_TRY(ctx, hipGetLastError());
     return HCLAE_OK;
 }
@@ -311,11 +337,27 @@ int launch_norms(hclae_ctx *ctx, const float *Cm, int dact = 0, int ld = 0, int 
 // (over all D coordinates only; the caller checks).
 template <int KB>
 int launch_assign_kb(hclae_ctx *ctx, int m, int64_t N, const float *xp, const float *Cm, uint8_t *codes, int dact, int ld,
-                     int prune, bool use_image)
+                     int prune)
 {
     PruneArgs pa;
     pa.bu = ctx->cur_u; pa.bl = ctx->cur_l;
     pa.active = ctx->active; pa.active_count = ctx->moved_count + 3;
+    const int NC = (dact + kChunkD - 1) / kChunkD;
+    const int dpad = kChunkD * NC;
+    pa.slack = (float)(dpad / 2 + 16) * 1.1920929e-7f;
+    if (half_resident(ctx, dact)) {
+        // the last chunk holds fewer than four 16-dim steps with coordinates that count: stop after them
+        const bool prefix = (dact % kChunkD) != 0 && (dact % kChunkD) <= kChunkD - kHalfStep;
+        const bool moved = prune == 3;
+        switch ((prune == 3 ? 2 : prune) * 2 + (prefix ? 1 : 0)) {
+        case 0: return launch_assign_half<KB, 0, false>(ctx, m, N, xp, Cm, codes, dact, ld, pa, false);
+        case 1: return launch_assign_half<KB, 0, true>(ctx, m, N, xp, Cm, codes, dact, ld, pa, false);
+        case 2: return launch_assign_half<KB, 1, false>(ctx, m, N, xp, Cm, codes, dact, ld, pa, false);
+        case 3: return launch_assign_half<KB, 1, true>(ctx, m, N, xp, Cm, codes, dact, ld, pa, false);
+        case 4: return launch_assign_half<KB, 2, false>(ctx, m, N, xp, Cm, codes, dact, ld, pa, moved);
+        default: return launch_assign_half<KB, 2, true>(ctx, m, N, xp, Cm, codes, dact, ld, pa, moved);
+        }
+    }
     // prune 3 = 2, and the re-check kernel lists the vectors that changed cluster (moved_count[0] is zero: the
     // merge of the previous centroid update of this stage reset it)
     MovedArgs mv = {};
@@ -324,41 +366,12 @@ int launch_assign_kb(hclae_ctx *ctx, int m, int64_t N, const float *xp, const fl
         mv.cand = ctx->active; mv.cand_count = ctx->moved_count + 3; mv.bl = ctx->cur_l;
         prune = 2;
     }
-    const int NC = (dact + kChunkD - 1) / kChunkD;
-    const int dpad = kChunkD * NC;
-    pa.slack = (float)(dpad / 2 + 16) * 1.1920929e-7f;
-    const bool resident = (size_t)32 * KB * dpad * sizeof(float) + 4096 <= (size_t)kLdsBudget;
     // twice the worst-case rounding error of a score: (dpad + 1) roundings of relative size 2^-23
     // on partial sums bounded by h + ||x'|| ||c||, plus the rounding of h itself
     const float eps = 2.02f * (float)(dpad + 2) * 1.1920929e-7f;
     {
     Timed t_(ctx, prune == 2 ? HCLAE_T_ASSIGN_ACTIVE : HCLAE_T_ASSIGN);
-    if (resident && ctx->contraction == 1) {
-        const size_t lds = (size_t)KB * 8 * NC * kWave * sizeof(float4) + (32 * KB + 4) * sizeof(float);
-        const int64_t ntiles = (N + kTileVec - 1) / kTileVec;
-        int64_t blocks = (ntiles + 3) / 4;                      // few tiles: one per SIMD before any SIMD gets two
-        if (blocks > ctx->cus) blocks = ctx->cus;
-        const uint64_t attr_set = 1ull << 0;        // this call site's bit in ctx->attr_done
-        if (!(ctx->attr_done & attr_set)) {
-            HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_assign_split<KB, 0>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget));
-            HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_assign_split<KB, 1>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget));
-            HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_assign_split<KB, 2>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget));
-            ctx->attr_done |= attr_set;
-        }
-        // 3 MFMAs per 16 dims, each within 2^-21 of the magnitudes it adds; one more for the rounding of the norm
-        const float acc_bound = (float)(3 * (dpad / kSplitStep) + 1) * 4.76837158203125e-7f;
-        if ((size_t)KB * 4 * NC * 2 * kWave * sizeof(uint4) > ctx->split_image_bytes)
-            return fail(ctx, HCLAE_EINVAL, "assign: split dictionary image too small for this shape");
-        hipLaunchKernelGGL(k_split_norms, dim3((32 * KB + 3) / 4), dim3(256), 0, ctx->stream, Cm, ctx->K, dact, ld, ctx->split_norms,
-                           ctx->split_image, KB, 4 * NC);
-        auto kern = prune == 1 ? &k_assign_split<KB, 1> : prune == 2 ? &k_assign_split<KB, 2> : &k_assign_split<KB, 0>;
-        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kAssignThreads), lds, ctx->stream,
-                           xp, Cm, ctx->hneg, ctx->split_norms, N, dact, ld, ctx->K, ctx->M, m, NC, acc_bound,
-                           codes, ctx->refine_list, ctx->refine_count, pa, ctx->split_image);
-    } else if (ctx->contraction == 1) {
+    if (ctx->contraction == 1) {
         // D-chunked, split-bf16: two slices of 64 dims in LDS, one block per CU
         const size_t lds = (size_t)2 * KB * 8 * kWave * sizeof(float4) + (32 * KB + 4) * sizeof(float);
         const int64_t nbt = (N + kTileVec * kAssignWaves - 1) / (kTileVec * kAssignWaves);
@@ -385,47 +398,6 @@ int launch_assign_kb(hclae_ctx *ctx, int m, int64_t N, const float *xp, const fl
         hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kAssignThreads), lds, ctx->stream,
                            xp, reinterpret_cast<const uint4 *>(ctx->cb_image), ctx->hneg, ctx->split_norms, N, dact, ld,
                            ctx->K, ctx->M, m, NC, acc_bound, codes, ctx->refine_list, ctx->refine_count, pa);
-    } else if (resident) {
-        const size_t lds = (size_t)KB * 8 * NC * kWave * sizeof(float4) + (32 * KB + 4) * sizeof(float);
-        const int64_t ntiles = (N + kTileVec - 1) / kTileVec;
-        int64_t blocks = (ntiles + 3) / 4;                      // few tiles: one per SIMD before any SIMD gets two
-        if (blocks > ctx->cus) blocks = ctx->cus;
-        const uint64_t attr_set = 1ull << 2;        // this call site's bit in ctx->attr_done
-        if (!(ctx->attr_done & attr_set)) {
-            HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_assign_resident<KB, 0>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget));
-            HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_assign_resident<KB, 1>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget));
-            HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_assign_resident<KB, 2>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget));
-            ctx->attr_done |= attr_set;
-        }
-        // the last chunk holds fewer than eight 8-dim steps with coordinates that count: stop after them
-        const bool prefix = prune == 0 && (dact % kChunkD) != 0 && (dact % kChunkD) <= kChunkD - 8;
-        const uint64_t attr_set_p = 1ull << 3;        // this call site's bit in ctx->attr_done
-        if (prefix && !(ctx->attr_done & attr_set_p)) {
-            HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_assign_resident<KB, 0, true>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget));
-            ctx->attr_done |= attr_set_p;
-        }
-        const uint64_t attr_set_i = 1ull << 4;        // this call site's bit in ctx->attr_done
-        if (use_image && !(ctx->attr_done & attr_set_i)) {
-            HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_assign_resident<KB, 0, false, true>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget));
-            HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_assign_resident<KB, 1, false, true>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget));
-            HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_assign_resident<KB, 2, false, true>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget));
-            ctx->attr_done |= attr_set_i;
-        }
-        auto kern = prefix ? &k_assign_resident<KB, 0, true>
-                  : use_image ? (prune == 1 ? &k_assign_resident<KB, 1, false, true>
-                                 : prune == 2 ? &k_assign_resident<KB, 2, false, true> : &k_assign_resident<KB, 0, false, true>)
-                  : prune == 1 ? &k_assign_resident<KB, 1> : prune == 2 ? &k_assign_resident<KB, 2> : &k_assign_resident<KB, 0>;
-        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kAssignThreads), lds, ctx->stream,
-                           xp, Cm, ctx->hneg, N, dact, ld, ctx->K, ctx->M, m, NC, eps,
-                           codes, ctx->refine_list, ctx->refine_count, pa,
-                           use_image && !prefix ? reinterpret_cast<const float4 *>(ctx->lds_image) : (const float4 *)nullptr);
     } else {
         // two slices of 64 dims in LDS: one block per CU
         const size_t lds = (size_t)2 * KB * 8 * kWave * sizeof(float4) + (32 * KB + 4) * sizeof(float);
@@ -462,18 +434,17 @@ int launch_assign_kb(hclae_ctx *ctx, int m, int64_t N, const float *xp, const fl
 }
 
 // Assumes hneg holds the norms of Cm (over the same dact coordinates) and the re-check counter is zero.
-// use_image: the dictionary image kept by launch_norms(image) and the centroid updates since is that of Cm.
 int launch_assign(hclae_ctx *ctx, int m, int64_t N, const float *xp, const float *Cm, uint8_t *codes,
-                  int dact = 0, int ld = 0, int prune = 0, bool use_image = false)
+                  int dact = 0, int ld = 0, int prune = 0)
 {
     if (dact <= 0) dact = ctx->D;
     if (ld <= 0) ld = ctx->D;
-    if (dact != ctx->D || ld != ctx->D) { prune = 0; use_image = false; }
+    if (dact != ctx->D || ld != ctx->D) prune = 0;
     switch (ctx->kb) {
-    case 1: return launch_assign_kb<1>(ctx, m, N, xp, Cm, codes, dact, ld, prune, use_image);
-    case 2: return launch_assign_kb<2>(ctx, m, N, xp, Cm, codes, dact, ld, prune, use_image);
-    case 4: return launch_assign_kb<4>(ctx, m, N, xp, Cm, codes, dact, ld, prune, use_image);
-    default: return launch_assign_kb<8>(ctx, m, N, xp, Cm, codes, dact, ld, prune, use_image);
+    case 1: return launch_assign_kb<1>(ctx, m, N, xp, Cm, codes, dact, ld, prune);
+    case 2: return launch_assign_kb<2>(ctx, m, N, xp, Cm, codes, dact, ld, prune);
+    case 4: return launch_assign_kb<4>(ctx, m, N, xp, Cm, codes, dact, ld, prune);
+    default: return launch_assign_kb<8>(ctx, m, N, xp, Cm, codes, dact, ld, prune);
     }
 }
 
@@ -538,10 +509,9 @@ int launch_update(hclae_ctx *ctx, int m, int64_t N, const float *xp, float *Cm, 
                        online ? ctx->run_sum + (size_t)m * K * D : (double *)nullptr,
                        online ? ctx->run_cnt + (size_t)m * K : (long long *)nullptr,
                        keep_totals ? ctx->tot_sum : (long long *)nullptr, keep_totals ? ctx->tot_cnt : (int *)nullptr, 0,
-                       keep_totals ? ctx->moved_count : (unsigned *)nullptr, keep_totals ? ctx->drift : (float *)nullptr,
-                       ctx->resident ? ctx->lds_image : (float *)nullptr, 8 * ctx->NC);
+                       keep_totals ? ctx->moved_count : (unsigned *)nullptr, keep_totals ? ctx->drift : (float *)nullptr);
     HIP_TRY(ctx, hipGetLastError());
-    if (keep_totals) {
+    if (keep_totals && !half_resident(ctx, D)) {           // k_refine compares with it; k_assign_half has the code it replaces
         hipLaunchKernelGGL(k_save_column, dim3(stream_blocks(ctx, N, 256)), dim3(256), 0, ctx->stream,
                            codes, N, ctx->M, m, ctx->upd_col);
         HIP_TRY(ctx, hipGetLastError());
@@ -574,7 +544,7 @@ int launch_update_moved(hclae_ctx *ctx, int m, int64_t N, const float *xp, float
     hipLaunchKernelGGL(k_merge, dim3(K), dim3(256), 0, ctx->stream,
                        ctx->partial, ctx->pcount, nb, K, D, D, Cm, ctx->hneg, ctx->nk, (int *)nullptr,
                        ctx->refine_count, (double *)nullptr, (long long *)nullptr, ctx->tot_sum, ctx->tot_cnt, 1,
-                       ctx->moved_count, ctx->drift, ctx->resident ? ctx->lds_image : (float *)nullptr, 8 * ctx->NC);
+                       ctx->moved_count, ctx->drift);
     HIP_TRY(ctx, hipGetLastError());
     return HCLAE_OK;
 }
@@ -618,7 +588,7 @@ int enqueue_stage(hclae_ctx *ctx, int m, int64_t N, float *C, uint8_t *codes, fl
         hipLaunchKernelGGL(k_seed, dim3(K), dim3(256), 0, ctx->stream, residue, seed_dev, K, D, Cm);
         HIP_TRY(ctx, hipGetLastError());
     }
-    if ((rc = launch_norms(ctx, Cm, 0, 0, carry ? 2 : 0, true)) != HCLAE_OK) return rc;
+    if ((rc = launch_norms(ctx, Cm, 0, 0, carry ? 2 : 0)) != HCLAE_OK) return rc;
     if (carry == 2) {
         Timed t_(ctx, HCLAE_T_BOUNDS);
         // (8M + 16) 2^-24 sqrt(D), times the largest coordinate seen: the roundings of the passes since the last visit
@@ -636,14 +606,14 @@ int enqueue_stage(hclae_ctx *ctx, int m, int64_t N, float *C, uint8_t *codes, fl
     const bool prune = ctx->pruning && iters > 0;
     for (int t = 0; t < iters; ++t) {
         if (prune && t > 0 && (rc = launch_bounds_step(ctx, m, N, codes, residue, Cm)) != HCLAE_OK) return rc;
-        if ((rc = launch_assign(ctx, m, N, residue, Cm, codes, 0, 0, prune ? (t == 0 ? (carry == 2 ? 2 : 1) : 3) : 0, true)) != HCLAE_OK) return rc;
+        if ((rc = launch_assign(ctx, m, N, residue, Cm, codes, 0, 0, prune ? (t == 0 ? (carry == 2 ? 2 : 1) : 3) : 0)) != HCLAE_OK) return rc;
         rc = (t == 0 || !ctx->pruning)
                  ? launch_update(ctx, m, N, residue, Cm, codes, nullptr, true, false, 0, ctx->pruning && (iters > 1 || prune))
                  : launch_update_moved(ctx, m, N, residue, Cm);
         if (rc != HCLAE_OK) return rc;
     }
     if (prune && (rc = launch_bounds_step(ctx, m, N, codes, residue, Cm)) != HCLAE_OK) return rc;
-    if ((rc = launch_assign(ctx, m, N, residue, Cm, codes, 0, 0, prune ? 2 : 0, true)) != HCLAE_OK) return rc;
+    if ((rc = launch_assign(ctx, m, N, residue, Cm, codes, 0, 0, prune ? 2 : 0)) != HCLAE_OK) return rc;
     if (carry) {
         // how far this visit moved every vector's part of the reconstruction (old_codes still holds the column as the
         // stage found it: the row pass below is the one that replaces it)
@@ -749,10 +719,6 @@ int hclae_create(hclae_ctx **out, int64_t N_max, int D, int M, int K, void *hip_
     ctx->kb = K <= 32 ? 1 : K <= 64 ? 2 : K <= 128 ? 4 : 8;
     ctx->NC = (D + kChunkD - 1) / kChunkD;
     ctx->resident = (size_t)32 * ctx->kb * kChunkD * ctx->NC * sizeof(float) + 4096 <= (size_t)kLdsBudget;
-    {   // the split image serves every LDS-resident assignment, those on a prefix of a long row included
-        const int nc_res = (int)(((size_t)kLdsBudget - 4096) / ((size_t)32 * ctx->kb * kChunkD * sizeof(float)));
-        ctx->split_image_bytes = sizeof(uint4) * (size_t)ctx->kb * 4 * (ctx->NC < nc_res ? ctx->NC : nc_res) * 2 * kWave;
-    }
 
     hipError_t e = hipGetDevice(&ctx->device);
     hipDeviceProp_t prop;
@@ -787,11 +753,10 @@ int hclae_create(hclae_ctx **out, int64_t N_max, int D, int M, int K, void *hip_
     struct { void **p; size_t bytes; } allocs[] = {
         {(void **)&ctx->hneg, sizeof(float) * 32 * ctx->kb},
         {(void **)&ctx->cb_image, ctx->resident ? 256 : sizeof(float4) * (size_t)ctx->NC * ctx->kb * 8 * kWave},
-        {(void **)&ctx->lds_image, ctx->resident ? sizeof(float4) * (size_t)ctx->NC * ctx->kb * 8 * kWave : 256},
-        {(void **)&ctx->split_image, ctx->split_image_bytes},
         {(void **)&ctx->split_norms, sizeof(float) * 2 * HCLAE_MAX_K},
         {(void **)&ctx->refine_count, 256},
         {(void **)&ctx->refine_list, sizeof(RefineItem) * (size_t)N_max},
+        {(void **)&ctx->half_list, sizeof(HalfItem) * (size_t)half_list_entries(N_max, ctx->cus * kAssignWaves)},
         {(void **)&ctx->old_codes, (size_t)N_max},
         {(void **)&ctx->partial, per * ub},
         {(void **)&ctx->pcount, sizeof(int) * (size_t)K * ub},
@@ -841,7 +806,7 @@ int hclae_create(hclae_ctx **out, int64_t N_max, int D, int M, int K, void *hip_
 int hclae_destroy(hclae_ctx *ctx)
 {
     if (!ctx) return HCLAE_EINVAL;
-    void *dev[] = {ctx->hneg, ctx->cb_image, ctx->lds_image, ctx->split_image, ctx->split_norms, ctx->refine_count, ctx->refine_list, ctx->old_codes, ctx->partial, ctx->pcount,
+    void *dev[] = {ctx->hneg, ctx->cb_image, ctx->split_norms, ctx->refine_count, ctx->refine_list, ctx->half_list, ctx->old_codes, ctx->partial, ctx->pcount,
                    ctx->nk, ctx->tot_sum, ctx->tot_cnt, ctx->upd_col, ctx->moved_list, ctx->moved_count, ctx->bnd_u, ctx->bnd_l, ctx->drift, ctx->active, ctx->work, ctx->seed_idx, ctx->part_a, ctx->part_b, ctx->part_chg, ctx->rec,
                    ctx->run_sum, ctx->run_cnt, ctx->n0_dev, ctx->pca_rt, ctx->pca_crot, ctx->pca_colpart,
                    ctx->pca_grampart, ctx->pca_mean, ctx->pca_mean32, ctx->pca_cov, ctx->pca_R, ctx->pca_xr,
@@ -1273,15 +1238,15 @@ int hclae_online_chunk(hclae_ctx *ctx, const uint8_t *Xu8, int64_t n, int D, flo
     HIP_TRY(ctx, hipGetLastError());
     for (int m = 0; m < M; ++m) {
         float *Cm = C + (size_t)m * K * D;
-        if ((rc = launch_norms(ctx, Cm, 0, 0, false, true)) != HCLAE_OK) return rc;
-        if ((rc = launch_assign(ctx, m, n, residue, Cm, codes, 0, 0, 0, true)) != HCLAE_OK) return rc;
+        if ((rc = launch_norms(ctx, Cm)) != HCLAE_OK) return rc;
+        if ((rc = launch_assign(ctx, m, n, residue, Cm, codes)) != HCLAE_OK) return rc;
         if (codes_first) {
             hipLaunchKernelGGL(k_copy_column, dim3(stream_blocks(ctx, n, kFlatThreads)), dim3(kFlatThreads), 0, ctx->stream,
                                codes_first, codes, n, M, m);
             HIP_TRY(ctx, hipGetLastError());
         }
         if ((rc = launch_update(ctx, m, n, residue, Cm, codes, nullptr, true, true)) != HCLAE_OK) return rc;
-        if ((rc = launch_assign(ctx, m, n, residue, Cm, codes, 0, 0, 0, true)) != HCLAE_OK) return rc;
+        if ((rc = launch_assign(ctx, m, n, residue, Cm, codes)) != HCLAE_OK) return rc;
         const bool last = (m == M - 1) && err;
         const int b = last ? launch_heat_cool<-1, true>(ctx, m, n, C, codes, residue, ctx->part_b)
                            : launch_heat_cool<-1, false>(ctx, m, n, C, codes, residue, nullptr);
