@@ -217,9 +217,8 @@ int hclae_online_import(hclae_ctx *ctx, const double *run_sum, const int64_t *ru
 #define HCLAE_CONTRACT_SPLIT_BF16 1   /* fp32 operands split into two bf16 terms, three bf16 MFMAs   */
 
 /*
- * Selects how the distance contraction forms the scores x'.c - ||c||^2/2 where the dictionary does not fit LDS as fp16
- * (K = 256: D > 256), and in the multi-path scoring (hclae_beam_step, hclae_encode_beam) of every shape.  Smaller
- * dictionaries are assigned by one kernel in either mode: fp16 matrix cores with bounds measured per vector and codeword.
+ * Selects how the multi-path scoring (hclae_beam_step, hclae_encode_beam) forms the scores x'.c - ||c||^2/2.  The
+ * nearest-codeword assignments use fp16 matrix cores with bounds measured per vector and codeword in either mode.
  * Whatever the arithmetic, the scores only pre-select candidates within an error margin (fp16 and mode 0: rigorous
  * bounds; mode 1: the dropped terms bounded rigorously, the accumulation of a bf16 MFMA by a measured constant with a
  * fourfold allowance) and the decision is a direct-form one in fp64, so codes, dictionaries and residues do not depend on

@@ -1,17 +1,9 @@
-// Nearest-codeword assignment (the assignment half of the k-means that cools a dictionary,
-// Sec. 3.1/3.2; equally the per-dictionary step of Eq. 3 with one path).
+// What the nearest-codeword assignments share (assign_half.hpp holds their kernels), the fp32 contraction that the multi-path
+// scoring and the rotation use, and the distance bounds of a stage.
 //
-// argmin_k ||x' - c_k||^2 = argmax_k ( x'.c_k - ||c_k||^2/2 ).  The right-hand score is a dense
-// K x D by D x N contraction and runs on the fp32 matrix cores (v_mfma_f32_32x32x2_f32), with
-// the accumulators started at -||c_k||^2/2.  The product is oriented codewords x vectors, so a
-// lane ends up holding scores of many codewords for ONE vector and the argmax never leaves
-// the wave (one exchange between lane l and lane l+32 at the end).
-//
-// fp32 rounding of the expanded form can reorder two codewords whose distances differ by less
-// than the rounding error, which is far larger than the error of the direct form.  Each wave
-// therefore bounds that error rigorously, collects every codeword whose score is within the
-// bound of the best, and when more than one remains hands the vector to k_refine, which decides
-// among the candidates with direct-form distances in fp64 (lowest index on exact ties).
+// argmin_k ||x' - c_k||^2 = argmax_k ( x'.c_k - ||c_k||^2/2 ).  The right-hand score is a dense K x D by D x N contraction.
+// The product is oriented codewords x vectors, so a lane ends up holding scores of many codewords for ONE vector and the
+// argmax never leaves the wave (one exchange between lane l and lane l+32 at the end).
 #pragma once
 #include "common.hpp"
 
@@ -21,14 +13,6 @@ constexpr int kAssignThreads = 512;                 // 8 waves: 2 per SIMD
 constexpr int kAssignWaves = kAssignThreads / kWave;
 constexpr int kTileVec = 32;                        // vectors per wave tile (N side of the MFMA)
 constexpr int kChunkD = 64;                         // dims per register-resident chunk of x'
-
-// One entry of the re-check list: the vector and the bitmap of its candidate codewords in the
-// layout the wave produces it in.  Bit p of word mask[h][i] stands for codeword
-// 64 i + 8 (p >> 2) + 4 h + (p & 3).
-struct RefineItem {
-    uint32_t n;
-    uint32_t mask[2][4];
-};
 
 // Exact pruning of the assignments of one stage (x' fixed, only the dictionary moves).  For every vector
 // the stage keeps an upper bound bu on the distance to its own codeword and a lower bound bl on the
@@ -45,21 +29,6 @@ struct PruneArgs {
     const uint32_t *active;            // [*active_count] vector indices (PRUNE 2)
     const unsigned *active_count;
     float slack;                       // rounding of ||x'||^2 and of the bound arithmetic, relative: grows with D
-};
-// Lower bound stored for a vector that goes to the fp64 re-check: no distance is negative, so the value
-// keeps the vector listed and tells it from all others.
-constexpr float kAmbiguousL = -2.f;
-
-// Which vectors changed cluster since the last centroid update of the stage, found by the re-check kernel that
-// follows a PRUNE 2 assignment (prev == nullptr: not wanted).  Only a vector that assignment recomputed can
-// have changed code.  Entry = n | old code << 32 | new code << 40; order is free.
-struct MovedArgs {
-    uint8_t *prev;                     // [N] code column at the last update; brought up to date
-    unsigned long long *list;
-    unsigned *count;                   // zero on entry
-    const uint32_t *cand;              // [*cand_count] the vectors the assignment recomputed
-    const unsigned *cand_count;
-    const float *bl;                   // [N] kAmbiguousL marks the ones on the re-check list
 };
 
 // -||c_k||^2 / 2 in fp32 (computed in fp64) over the first D coordinates of rows of stride ld, for
@@ -176,16 +145,6 @@ __device__ __forceinline__ void load_x_chunk(
     }
 }
 
-// max |x'| over everything the wave has read, merged into *slot (bit pattern of a non-negative
-// float: integer max is float max, and an integer atomic is order-free).  The centroid-sum kernel
-// that follows derives its fixed-point scale from it.
-__device__ __forceinline__ void publish_absmax(float amax, unsigned *slot)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, kWave));
-    if (lane_id() == 0) atomicMax(slot, __float_as_uint(amax));
-}
-
 // PREFIX: the chunk ends after `steps` of its eight 8-dim steps (a short prefix of the coordinates counts;
 // the codebook image is zero beyond it, so the steps left out would add nothing).
 template <int KB, bool PREFIX = false>
@@ -232,111 +191,6 @@ __device__ __forceinline__ void init_acc(floatx16 (&acc)[KB], const float *hneg_
             acc[b][4 * g + 2] = t.z;
             acc[b][4 * g + 3] = t.w;
         }
-    }
-}
-
-// Per-vector decision from the wave's scores.  `eps` * (hmax + ||x'|| * cmax) bounds twice the
-// rounding error of any score, so the true nearest codeword is among those within that
-// margin of the best score.
-template <int KB, int PRUNE = 0>
-__device__ __forceinline__ void decide(
-    const floatx16 (&acc)[KB], float xsq, float eps, float hmax, float cmax, int lane,
-    int64_t n, int64_t N, int M, int m, uint8_t *__restrict__ codes,
-    RefineItem *__restrict__ list, unsigned *__restrict__ refine_count, PruneArgs pa = PruneArgs())
-{
-    const int h = lane >> 5;
-    float mx = -__builtin_inff(), m2 = -__builtin_inff();            // best and second best score
-    if (PRUNE) {
-        // top two per accumulator block (independent chains), then merged
-        float bm[KB], b2[KB];
-#pragma unroll
-        for (int b = 0; b < KB; ++b) {
-            bm[b] = acc[b][0];
-            b2[b] = -__builtin_inff();
-#pragma unroll
-            for (int v = 1; v < 16; ++v) {
-                b2[b] = __builtin_amdgcn_fmed3f(bm[b], b2[b], acc[b][v]);   // b2 <= bm always: the median is the new second
-                bm[b] = fmaxf(bm[b], acc[b][v]);
-            }
-        }
-#pragma unroll
-        for (int b = 0; b < KB; ++b) {
-            m2 = fmaxf(fminf(mx, bm[b]), fmaxf(m2, b2[b]));
-            mx = fmaxf(mx, bm[b]);
-        }
-        const float mxo = __shfl_xor(mx, 32, kWave), m2o = __shfl_xor(m2, 32, kWave);
-        m2 = fmaxf(fminf(mx, mxo), fmaxf(m2, m2o));
-    } else {
-#pragma unroll
-        for (int b = 0; b < KB; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) mx = fmaxf(mx, acc[b][v]);
-    }
-    mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
-    const float x2 = xsq + __shfl_xor(xsq, 32, kWave);
-    const float margin = eps * (hmax + sqrtf(x2) * cmax);
-    const float thr = mx - margin;
-
-    // Candidate bitmaps without compare-and-select chains: the sign of acc - thr is shifted into a word
-    // (v_alignbit), one subtraction and one shift-in per score; the 16 bits of a block end up "1 = below".
-    constexpr int NW = (KB + 1) / 2;
-    uint32_t mk[NW];
-#pragma unroll
-    for (int i = 0; i < NW; ++i) mk[i] = 0u;
-#pragma unroll
-    for (int b = 0; b < KB; ++b) {
-        uint32_t below = 0u;
-#pragma unroll
-        for (int v = 15; v >= 0; --v)
-            below = __builtin_amdgcn_alignbit(below, __float_as_uint(acc[b][v] - thr), 31);   // (below << 1) | sign
-        mk[b >> 1] |= (~below & 0xffffu) << ((b & 1) * 16);
-    }
-
-    // bit p of word i is codeword 64 i + 8 (p >> 2) + 4 h + (p & 3): ascending in (i, p)
-    int cnt = 0, lo = 0x7fffffff;
-#pragma unroll
-    for (int i = NW - 1; i >= 0; --i) {
-        cnt += __popc(mk[i]);
-        if (mk[i]) {
-            const int p = __ffs(mk[i]) - 1;
-            lo = 64 * i + 8 * (p >> 2) + 4 * h + (p & 3);
-        }
-    }
-    cnt += __shfl_xor(cnt, 32, kWave);
-    lo = min(lo, __shfl_xor(lo, 32, kWave));
-
-    if (PRUNE) {
-        // d^2 = ||x'||^2 - 2 score.  With E the rounding bound of a score (half the margin): the own codeword
-        // has true score >= mx - E and every other one <= m2 + E.  A vector that goes to the re-check (or has
-        // no candidate) gets bounds that keep it active.  slack covers the fp32 evaluation of these lines: x2 is a
-        // chain of D/2 fused multiply-adds per lane (relative error <= (D/2 + 1) 2^-24, all terms positive) and the
-        // few operations below add a handful of roundings of the magnitudes involved; pa.slack = (D/2 + 16) 2^-23.
-        const float E = 0.5001f * margin;
-        const float slack = pa.slack * (x2 + 2.f * fabsf(mx) + 2.f * fabsf(m2));
-        float u = __builtin_inff(), l = cnt >= 2 ? kAmbiguousL : 0.f;
-        if (cnt == 1) {
-            u = sqrtf(fmaxf(0.f, (x2 - 2.f * (mx - E)) + slack)) * 1.00001f;
-            l = sqrtf(fmaxf(0.f, (x2 - 2.f * (m2 + E)) - slack)) * 0.99999f;
-        }
-        if (h == 0 && n < N) {
-            pa.bu[n] = u;
-            pa.bl[n] = l;
-        }
-    }
-
-    // provisional code: the lowest candidate (final when it is the only one)
-    unsigned slot = 0;
-    const bool amb = (cnt >= 2) && (n < N);
-    if (h == 0 && n < N) {
-        codes[n * M + m] = (uint8_t)(cnt == 0 ? 0 : lo);     // cnt == 0 only with non-finite input
-        if (amb) slot = atomicAdd(refine_count, 1u);
-    }
-    slot = __shfl(slot, lane & 31, kWave);                    // the h = 1 partner learns the slot
-    if (amb) {
-        RefineItem *it = list + slot;
-        if (h == 0) it->n = (uint32_t)n;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) it->mask[h][i] = (i < NW) ? mk[i] : 0u;
     }
 }
 
@@ -400,81 +254,6 @@ __device__ __forceinline__ void mfma_chunk_refill(
 #pragma unroll
         for (int b = 0; b < KB; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[b].w, xv.w, acc[b], 0, 0, 0);
     }
-}
-
-// Assignment for dimensions whose codebook does not fit LDS: the block walks the D axis in 64-dim chunks for
-// every tile of 8 x 32 vectors, the accumulators persisting across chunks.  Two LDS buffers hold the slice in
-// use and the one being brought in from the codebook image (k_codebook_image), one barrier per chunk; the
-// refills run under the MFMAs (mfma_chunk_refill), across tile boundaries too.
-template <int KB, int PRUNE = 0>
-__global__ __launch_bounds__(kAssignThreads) void k_assign_chunked(
-    const float *__restrict__ xp, const float4 *__restrict__ img, const float *__restrict__ hneg,
-    int64_t N, int D, int ld, int K, int M, int m, int NC, float eps,
-    uint8_t *__restrict__ codes, RefineItem *__restrict__ list, unsigned *__restrict__ refine_count,
-    PruneArgs pa)
-{
-    extern __shared__ float4 smem4[];
-    constexpr int CH = KB * 8 * kWave;                              // float4 per slice
-    float4 *buf0 = smem4, *buf1 = smem4 + CH;
-    float *lds_h = reinterpret_cast<float *>(smem4 + 2 * CH);
-    const int lane = lane_id();
-    const int wave = threadIdx.x >> 6;
-    const int h = lane >> 5;
-    const int r = lane & 31;
-
-    for (int k = threadIdx.x; k < 32 * KB; k += blockDim.x) lds_h[k] = hneg[k];
-    // slice 0 (the same for every tile)
-    const float4 *mine = img + wave * kWave + lane;
-#pragma unroll
-    for (int p = 0; p < KB; ++p) buf0[(p * 8 + wave) * kWave + lane] = mine[p * 8 * kWave];
-    __syncthreads();
-    float hmax = 0.f;
-    for (int k = 0; k < K; ++k) hmax = fmaxf(hmax, -lds_h[k]);
-    const float cmax = sqrtf(2.f * hmax) * 1.000001f;
-
-    // rows of this launch: all N vectors, or the listed ones (PRUNE 2; see PruneArgs)
-    // (nearly all listed: all N in order, as in k_assign_resident)
-    const int64_t listed = PRUNE == 2 ? (int64_t)*pa.active_count : N;
-    const bool gather = PRUNE == 2 && listed * 32 < N * 31;
-    const int64_t rows = gather ? listed : N;
-    const int64_t nbt = (rows + kTileVec * kAssignWaves - 1) / (kTileVec * kAssignWaves);   // block tiles
-    float amax = 0.f;
-    if ((int64_t)blockIdx.x < nbt) {
-        // row of x' this lane feeds for block tile bt (tail columns re-read the last row); vec = N for "none"
-        auto tile_row = [&](int64_t bt, int64_t &vec) -> const float * {
-            const int64_t i = (bt * kAssignWaves + wave) * kTileVec + r;
-            const int64_t ic = i < rows ? i : rows - 1;
-            const int64_t nrow = gather ? (int64_t)pa.active[ic] : ic;
-            vec = i < rows ? nrow : N;
-            return xp + nrow * ld;
-        };
-        int64_t vec;
-        const float *xrow = tile_row(blockIdx.x, vec);
-        float4 x[8];
-#pragma unroll
-        for (int s = 0; s < 8; ++s) x[s] = *reinterpret_cast<const float4 *>(xrow + min(8 * s + 4 * h, last_piece(D)));
-        int par = 0;
-        for (int64_t bt = blockIdx.x; bt < nbt; bt += gridDim.x) {
-            int64_t vec_next = vec;
-            const float *xrow_next = xrow;                          // the last tile refills with itself: unused
-            if (bt + gridDim.x < nbt) xrow_next = tile_row(bt + gridDim.x, vec_next);
-            floatx16 acc[KB];
-            float xsq = 0.f;
-            init_acc<KB>(acc, lds_h, h);
-            for (int q = 0; q < NC; ++q) {
-                const bool last = q + 1 == NC;
-                const int qn = last ? 0 : q + 1;
-                mfma_chunk_refill<KB>(acc, x, par ? buf1 : buf0, par ? buf0 : buf1, mine + (size_t)qn * CH,
-                                      last ? xrow_next : xrow, q, qn, D, lane, wave, xsq, amax);
-                __syncthreads();                                    // slice q consumed by all, slice qn complete
-                par ^= 1;
-            }
-            decide<KB, PRUNE>(acc, xsq, eps, hmax, cmax, lane, vec, N, M, m, codes, list, refine_count, pa);
-            xrow = xrow_next;
-            vec = vec_next;
-        }
-    }
-    publish_absmax(amax, refine_count + 1);
 }
 
 // Between two assignments of a stage: age the bounds by the drift of the dictionary (drift[k] >= the
@@ -722,146 +501,6 @@ __global__ void k_zero_words(unsigned *__restrict__ p, int n)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0u;
-}
-
-constexpr int kMovedSpan = 1024;
-// fp64 re-check of the vectors whose fp32 scores were too close to call: direct-form squared
-// distances summed in ascending dimension order, smallest wins, exact ties go to the lowest
-// index.  A group of kRefineLanes lanes takes one list entry and gives each candidate its own lane (most
-// entries have two or three candidates; more take further rounds).
-constexpr int kRefineLanes = 4;
-__global__ __launch_bounds__(256) void k_refine(
-    const float *__restrict__ xp, const float *__restrict__ Cm, int D, int ld, int M, int m,
-    uint8_t *__restrict__ codes, const RefineItem *__restrict__ list,
-    const unsigned *__restrict__ refine_count, MovedArgs mv,
-    unsigned long long *__restrict__ work, unsigned long long rows, const unsigned *__restrict__ rows_listed)
-{
-    __shared__ unsigned long long found[kMovedSpan];
-    __shared__ unsigned nfound, base;
-    const unsigned count = *refine_count;
-    // Work counters of the ctx (read by hclae_work_counters): assignments run, vectors they recomputed, vectors that
-    // went to this re-check.  Launches on one stream follow one another, so one thread may add without atomics.
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        work[0] += 1ull;
-        work[1] += rows_listed ? (unsigned long long)*rows_listed : rows;
-        work[2] += count;
-    }
-    // With the moved-vector list wanted, the two jobs run side by side: the first half of the blocks re-checks,
-    // the second half scans the other recomputed vectors (below).
-    const unsigned nr = mv.prev ? gridDim.x / 2 : gridDim.x;        // blocks that re-check
-    const bool scans = blockIdx.x >= nr;
-    // re-checked vectors that changed cluster are staged in LDS like the others while a block's share fits
-    const bool staged = count <= nr * (unsigned)kMovedSpan;
-    if (mv.prev) {
-        if (threadIdx.x == 0) nfound = 0u;
-        __syncthreads();
-    }
-    const int l16 = threadIdx.x & (kRefineLanes - 1);
-    const unsigned groups = nr * (256 / kRefineLanes);
-    const int d4 = D >> 2;
-    for (unsigned e = scans ? count : blockIdx.x * (256 / kRefineLanes) + threadIdx.x / kRefineLanes; e < count;
-         e += groups) {
-        const RefineItem it = list[e];
-        int total = 0;
-#pragma unroll
-        for (int w = 0; w < 8; ++w) total += __popc(it.mask[w >> 2][w & 3]);
-        const float4 *x = reinterpret_cast<const float4 *>(xp + (size_t)it.n * ld);
-        double best = __builtin_inf();
-        int kbest = 0x7fffffff;
-        for (int first = 0; first < total; first += kRefineLanes) {
-            int j = first + l16;
-            if (j < total) {
-                // codeword of the j-th set bit
-                int k = 0;
-#pragma unroll
-                for (int w = 0; w < 8; ++w) {
-                    uint32_t bits = it.mask[w >> 2][w & 3];
-                    const int c = __popc(bits);
-                    if (j >= 0 && j < c) {
-                        for (int q = 0; q < j; ++q) bits &= bits - 1;
-                        const int p = __ffs(bits) - 1;
-                        k = 64 * (w & 3) + 8 * (p >> 2) + 4 * (w >> 2) + (p & 3);
-                        j = -1;
-                    } else if (j >= 0) {
-                        j -= c;
-                    }
-                }
-                const float4 *c4 = reinterpret_cast<const float4 *>(Cm + (size_t)k * ld);
-                double s = 0.0;
-                // unrolled so that eight rounds of loads are in flight; the additions keep their order
-#pragma unroll 8
-                for (int d = 0; d < d4; ++d) {
-                    const float4 a = x[d], b = c4[d];
-                    const double t0 = (double)a.x - (double)b.x, t1 = (double)a.y - (double)b.y;
-                    const double t2 = (double)a.z - (double)b.z, t3 = (double)a.w - (double)b.w;
-                    s += t0 * t0;
-                    s += t1 * t1;
-                    s += t2 * t2;
-                    s += t3 * t3;
-                }
-                for (int d = 4 * d4; d < D; ++d) {                  // D need not be a multiple of 4
-                    const double t = (double)reinterpret_cast<const float *>(x)[d] - (double)reinterpret_cast<const float *>(c4)[d];
-                    s += t * t;
-                }
-                if (s < best || (s == best && k < kbest)) { best = s; kbest = k; }
-            }
-        }
-#pragma unroll
-        for (int o = kRefineLanes / 2; o > 0; o >>= 1) {
-            const double ob = __shfl_xor(best, o, kWave);
-            const int ok = __shfl_xor(kbest, o, kWave);
-            if (ob < best || (ob == best && ok < kbest)) { best = ob; kbest = ok; }
-        }
-        if (l16 == 0) {
-            codes[(size_t)it.n * M + m] = (uint8_t)kbest;
-            if (mv.prev) {
-                const unsigned co = mv.prev[it.n];
-                if (co != (unsigned)kbest) {
-                    mv.prev[it.n] = (uint8_t)kbest;
-                    const unsigned long long ent =
-                        (unsigned long long)it.n | ((unsigned long long)co << 32) | ((unsigned long long)kbest << 40);
-                    if (staged) found[atomicAdd(&nfound, 1u)] = ent;
-                    else mv.list[atomicAdd(mv.count, 1u)] = ent;
-                }
-            }
-        }
-    }
-    if (!mv.prev) return;
-    if (!scans) {
-        __syncthreads();
-        if (threadIdx.x == 0 && nfound) base = atomicAdd(mv.count, nfound);
-        __syncthreads();
-        for (unsigned i = threadIdx.x; i < nfound; i += 256) mv.list[base + i] = found[i];
-        return;
-    }
-    // The other recomputed vectors have their final code already.  A block takes kMovedSpan list entries at a
-    // time, stages what it finds in LDS and claims its stretch of the output with one counter add.
-    const int64_t total = (int64_t)*mv.cand_count;
-    const int64_t ns = gridDim.x - nr;                              // blocks that scan
-    for (int64_t i0 = (int64_t)(blockIdx.x - nr) * kMovedSpan; i0 < total; i0 += ns * kMovedSpan) {
-        if (threadIdx.x == 0) nfound = 0u;
-        __syncthreads();
-#pragma unroll
-        for (int i = threadIdx.x; i < kMovedSpan; i += 256) {
-            const int64_t j = i0 + i;
-            if (j < total) {
-                const int64_t n = mv.cand[j];
-                if (mv.bl[n] != kAmbiguousL) {
-                    const unsigned cn = codes[n * M + m], co = mv.prev[n];
-                    if (cn != co) {
-                        mv.prev[n] = (uint8_t)cn;
-                        found[atomicAdd(&nfound, 1u)] =
-                            (unsigned long long)(uint32_t)n | ((unsigned long long)co << 32) | ((unsigned long long)cn << 40);
-                    }
-                }
-            }
-        }
-        __syncthreads();
-        if (threadIdx.x == 0 && nfound) base = atomicAdd(mv.count, nfound);
-        __syncthreads();
-        for (unsigned i = threadIdx.x; i < nfound; i += 256) mv.list[base + i] = found[i];
-        __syncthreads();
-    }
 }
 
 }  // namespace hclae

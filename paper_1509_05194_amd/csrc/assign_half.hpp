@@ -32,6 +32,7 @@ typedef float floatv2 __attribute__((ext_vector_type(2)));
 
 constexpr int kHalfStep = 16;                       // dims per fp16 MFMA
 constexpr int kWaveMoved = 128;                     // vectors that changed cluster a wave keeps before it lists them
+constexpr int kRefineLanes = 4;                     // lanes that share an undecided vector in the fp64 decision
 constexpr int kMuRows = 8;                          // codewords whose mean centres the scores
 constexpr float kHalfMaxNorm = 64000.f;             // a scaled row beyond this may not fit fp16: all codewords are candidates
 
@@ -48,15 +49,16 @@ struct HalfItem {
 // entries the array needs for launches over at most N vectors with `waves` waves.
 __host__ __device__ constexpr int64_t half_list_entries(int64_t N, int waves) { return N + (int64_t)waves * 2 * kTileVec; }
 
-// LDS of the resident kernel: the fp16 dictionary, then per-codeword constants, mu, and the waves' buffers.
+// LDS of the kernels: the fp16 dictionary (or two slices of it), then per-codeword constants, mu, and the waves' buffers.
 struct HalfLds {
     int img, hneg, w, waug, mu, moved, misc, total; // byte offsets
 };
-__host__ __device__ constexpr HalfLds half_lds(int kb, int nc)
+// slices: 64-dim slices of the dictionary held at a time (all nc of them, or the two of k_assign_half_chunked).
+__host__ __device__ constexpr HalfLds half_lds(int kb, int nc, int slices)
 {
     HalfLds l = {};
     l.img = 0;
-    l.hneg = kb * nc * 4096;                        // 32 kb rows of 64 nc halves
+    l.hneg = kb * slices * 4096;                    // 32 kb rows of 64 halves per slice
     l.w = l.hneg + 32 * kb * 4;
     l.waug = l.w + 32 * kb * 4;
     l.mu = l.waug + 64 * kb * 4;
@@ -151,6 +153,56 @@ __device__ __forceinline__ float half_wave_sums(float (&v)[NV])
     return s;
 }
 
+// Constants of a dictionary from its codewords' sums: every thread brings the squares (sq) of a scaled, centred codeword and
+// those of its rounding (dsq), or zeros; `holder` threads, one per row below 32 KB, write the row's entries.  Needs all
+// threads of the block.
+template <int KB>
+__device__ __forceinline__ HalfConsts half_constants(
+    char *lds, const HalfLds L, float sq, float dsq, int row, bool holder, int K, int NC, float scale, float inv)
+{
+    float *red = reinterpret_cast<float *>(lds + L.misc);
+    const int wave = threadIdx.x >> 6;
+    HalfConsts c;
+    float hm = sq;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) hm = fmaxf(hm, __shfl_xor(hm, o, kWave));
+    if (lane_id() == 0) red[wave] = hm;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kAssignWaves; ++i) hm = fmaxf(hm, red[i]);
+    // the sums of squares are chains of at most 4 NC terms per lane and five or six additions: relative error below 2^-10 for
+    // any D allowed; the rounding of the scaled and centred fp32 values themselves is 2^-24 of them.  A codeword near mu
+    // gets a floor for its norm, so that rho stays that of ordinary rounding.
+    c.cmax = sqrtf(hm) * 1.001f;
+    const float wk = fmaxf(sqrtf(sq) * 1.001f, c.cmax * 0.00390625f);
+    float rho = c.cmax > 0.f ? (sqrtf(dsq) * 1.001f + wk * 1.2e-7f) / wk : 0.f;
+    if (holder) {
+        const bool real = row < K;
+        const halfx2 up = {(_Float16)(wk * 1.002f), (_Float16)0.f}; // to nearest of 1.002 w: not below w
+        reinterpret_cast<float *>(lds + L.hneg)[row] = real ? -0.5f * sq : -1e38f;   // finite: index bits in an infinity would be a NaN
+        reinterpret_cast<float *>(lds + L.w)[row] = (float)up.x;
+        unsigned *aug = reinterpret_cast<unsigned *>(lds + L.waug) + 64 * (row >> 5) + (row & 31);
+        aug[0] = real ? __builtin_bit_cast(unsigned, up) : 0u;      // the operand of lane (0, r); lane (1, r) has zeros
+        aug[32] = 0u;
+    }
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) rho = fmaxf(rho, __shfl_xor(rho, o, kWave));
+    if (lane_id() == 0) red[kAssignWaves + wave] = rho;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kAssignWaves; ++i) rho = fmaxf(rho, red[kAssignWaves + i]);
+    __syncthreads();                                                // red is used again
+    // two units more than the MFMAs: the norms of this function, and the index bits in a score (decide_half)
+    c.acc = (float)(4 * NC + 3) * (17.f * 1.1920929e-7f);
+    // the same in every lane: scalar registers
+    c.scale = uniform(scale);
+    c.inv = uniform(inv);
+    c.h = uniform(c.acc * 0.5f * hm * 1.002f);
+    c.rho = uniform(rho);
+    c.cmax = uniform(c.cmax);
+    return c;
+}
+
 // Fills LDS with the dictionary (first D coordinates of rows of stride ld, zero beyond) and its constants.  A half wave
 // takes a row: its loads are contiguous and its sums stay in the half wave.
 template <int KB>
@@ -159,11 +211,8 @@ __device__ __forceinline__ HalfConsts stage_half(
 {
     constexpr int RP = 2 * KB;                                      // rows per half wave (512 threads)
     const int l32 = threadIdx.x & 31, hw = threadIdx.x >> 5;
-    float *lds_h = reinterpret_cast<float *>(lds + L.hneg);
     float *lds_mu = reinterpret_cast<float *>(lds + L.mu);
-    float *red = reinterpret_cast<float *>(lds + L.misc);
-    HalfConsts c;
-    c.scale = c.inv = 1.f;
+    float scale = 1.f, inv = 1.f;
     float sums[2 * RP];                                             // per row: squares, squares of the rounding
 #pragma unroll
     for (int i = 0; i < 2 * RP; ++i) sums[i] = 0.f;
@@ -183,10 +232,10 @@ __device__ __forceinline__ HalfConsts stage_half(
         }
         if (p0 == 0) {                                              // the loads above are on their way meanwhile
             const int s = half_shift(hneg, K);
-            c.scale = ldexpf(1.f, s);
-            c.inv = ldexpf(1.f, -s);
+            scale = ldexpf(1.f, s);
+            inv = ldexpf(1.f, -s);
         }
-        const float f = -c.scale / kMuRows;
+        const float f = -scale / kMuRows;
         const float4 neg = make_float4(mu.x * f, mu.y * f, mu.z * f, mu.w * f);
         if (p >= 16 * NC) break;
         if (hw == 0) reinterpret_cast<float4 *>(lds_mu)[p] = neg;
@@ -194,7 +243,7 @@ __device__ __forceinline__ HalfConsts stage_half(
 #pragma unroll
         for (int i = 0; i < RP; ++i) {
             const int row = hw + 16 * i;
-            float4 w = scaled(v[i], c.scale, neg);
+            float4 w = scaled(v[i], scale, neg);
             if (row >= K) w = make_float4(0.f, 0.f, 0.f, 0.f);
             const halfx4 q = half4(w, sums[2 * i], sums[2 * i + 1]);
             *reinterpret_cast<halfx4 *>(lds + ((t * KB + (row >> 5)) * 1024 + half_slot(t, g, row & 31) + 8 * hi)) = q;
@@ -204,48 +253,8 @@ __device__ __forceinline__ HalfConsts stage_half(
     const float mine = half_wave_sums<2 * RP>(sums);
     const float other = __shfl_xor(mine, 1, kWave);
     const int row = hw + 16 * ((l32 & (2 * RP - 1)) >> 1);
-    const bool holder = l32 < 2 * RP && !(l32 & 1);
-    float hm = (l32 & 1) ? other : mine;                            // ||C_k||^2
-#pragma unroll
-    for (int o = 2; o < kWave; o <<= 1) hm = fmaxf(hm, __shfl_xor(hm, o, kWave));
-    if (lane_id() == 0) red[hw >> 1] = hm;
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kAssignWaves; ++i) hm = fmaxf(hm, red[i]);
-    // the sums of squares are chains of at most 4 NC terms per lane and five additions: relative error below 2^-10 for any D
-    // allowed; the rounding of the scaled and centred fp32 values themselves is 2^-24 of them.  A codeword near mu gets a
-    // floor for its norm, so that rho stays that of ordinary rounding.
-    c.cmax = sqrtf(hm) * 1.001f;
-    const float sq = (l32 & 1) ? other : mine, dsq = (l32 & 1) ? mine : other;
-    const float wk = fmaxf(sqrtf(sq) * 1.001f, c.cmax * 0.00390625f);
-    float rho = c.cmax > 0.f ? (sqrtf(dsq) * 1.001f + wk * 1.2e-7f) / wk : 0.f;
-    if (holder) {
-        const bool real = row < K;
-        const halfx2 up = {(_Float16)(wk * 1.002f), (_Float16)0.f}; // to nearest of 1.002 w: not below w
-        lds_h[row] = real ? -0.5f * sq : -1e38f;                     // finite: index bits in an infinity would be a NaN
-        reinterpret_cast<float *>(lds + L.w)[row] = (float)up.x;
-        unsigned *aug = reinterpret_cast<unsigned *>(lds + L.waug) + 64 * (row >> 5) + (row & 31);
-        aug[0] = real ? __builtin_bit_cast(unsigned, up) : 0u;      // the operand of lane (0, r); lane (1, r) has zeros
-        aug[32] = 0u;
-    }
-#pragma unroll
-    for (int o = 2; o < kWave; o <<= 1) rho = fmaxf(rho, __shfl_xor(rho, o, kWave));
-    if (lane_id() == 0) red[kAssignWaves + (hw >> 1)] = rho;
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kAssignWaves; ++i) rho = fmaxf(rho, red[kAssignWaves + i]);
-    __syncthreads();                                                // red is used again
-    c.rho = rho;
-    // two units more than the MFMAs: the norms of this function, and the index bits in a score (decide_half)
-    c.acc = (float)(4 * NC + 3) * (17.f * 1.1920929e-7f);
-    c.h = c.acc * 0.5f * hm * 1.002f;
-    // the same in every lane: scalar registers
-    c.scale = uniform(c.scale);
-    c.inv = uniform(c.inv);
-    c.h = uniform(c.h);
-    c.rho = uniform(c.rho);
-    c.cmax = uniform(c.cmax);
-    return c;
+    const bool odd = (l32 & 1) != 0;
+    return half_constants<KB>(lds, L, odd ? other : mine, odd ? mine : other, row, l32 < 2 * RP && !odd, K, NC, scale, inv);
 }
 
 // One 64-dim chunk of a 32-vector tile: x as load_x_chunk leaves it (lane (g, r): dims 8 s + 4 g .. + 3 of row r for
@@ -519,7 +528,8 @@ __device__ __forceinline__ float mfma_bound_half(
 //
 // The best and the second best of a lane's scores are found on keys: the score with its last four bits replaced by its
 // index in the accumulator block (2^-19 of the score, within h).  Where the second one stays below the threshold the
-// best key names the only candidate; only a tile with an undecided vector builds candidate bitmaps (see decide()).
+// best key names the only candidate; only a tile with an undecided vector builds candidate bitmaps, without compare-and-
+// select chains: the sign of score - threshold is shifted into a word (v_alignbit), two instructions per score.
 template <int KB, int PRUNE>
 __device__ __forceinline__ void decide_half(
     const floatx16 (&acc)[KB], float x2, float xn, float e, const HalfConsts &c, const float *__restrict__ lds_w, int lane, int n,
@@ -562,7 +572,8 @@ __device__ __forceinline__ void decide_half(
     if (mine && !amb) {
         codes[(size_t)n * M + m] = (uint8_t)code;
         if (PRUNE) {
-            // d^2 = ||X||^2 - 2 score; slack covers the fp32 evaluation (see decide())
+            // d^2 = ||X||^2 - 2 score.  slack covers the fp32 evaluation: x2 is a chain of D/2 fused multiply-adds per lane
+            // (relative error <= (D/2 + 1) 2^-24, all terms positive), the rest a handful of roundings; pa.slack = (D/2 + 16) 2^-23
             pa.bu[n] = K > 1 ? sqrtf(fmaxf(0.f, (x2 - 2.f * low) + slack)) * 1.00001f * c.inv : __builtin_inff();
             pa.bl[n] = K > 1 ? sqrtf(fmaxf(0.f, (x2 - 2.f * (m2 + hh)) - slack)) * 0.99999f * c.inv : 0.f;
         }
@@ -602,6 +613,44 @@ __device__ __forceinline__ void decide_half(
     w.nitems += __popc(who);
 }
 
+// End of a block: what its waves have left, with one atomic each: moved vectors, vectors decided again, max |x'|.
+template <int PRUNE>
+__device__ __forceinline__ void half_finish(
+    char *lds, const HalfLds L, const HalfWave &w, float amax, unsigned *__restrict__ refine_count,
+    unsigned long long *__restrict__ moved_list, unsigned *__restrict__ moved_count, unsigned long long *__restrict__ work)
+{
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, kWave));
+    unsigned *tail = reinterpret_cast<unsigned *>(lds + L.misc);   // [8] moved, [8] decided again, [8] max, [1] base
+    if (lane == 0) {
+        tail[wave] = (unsigned)w.nmoved;
+        tail[8 + wave] = (unsigned)w.nitems;
+        tail[16 + wave] = __float_as_uint(amax);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned nm = 0u, nr = 0u, mxb = 0u;
+        for (int i = 0; i < kAssignWaves; ++i) {
+            nm += tail[i];
+            nr += tail[8 + i];
+            mxb = max(mxb, tail[16 + i]);
+        }
+        if (nm) tail[24] = atomicAdd(moved_count, nm);
+        if (nr) {
+            atomicAdd(refine_count, nr);
+            atomicAdd(work + 2, (unsigned long long)nr);
+        }
+        if (PRUNE != 2) atomicMax(refine_count + 1, mxb);           // of listed vectors nobody asks: it is known from the first pass
+    }
+    __syncthreads();
+    if (w.nmoved) {
+        unsigned at = tail[24];
+        for (int i = 0; i < wave; ++i) at += tail[i];
+        for (int i = lane; i < w.nmoved; i += kWave) moved_list[at + i] = w.moved[i];
+    }
+}
+
 // Assignment with the whole dictionary resident in LDS as fp16 (KB * NC <= 32: K = 256 up to D = 256).  Tile schedule and
 // register streaming as in the other resident kernels: a wave owns tiles of 32 vectors, streams them from HBM into operand
 // registers 64 dims at a time with the next chunk in flight, and keeps all 32 KB scores of a vector in accumulators.
@@ -615,7 +664,7 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign_half(
 {
     extern __shared__ float4 smem4[];
     char *lds = reinterpret_cast<char *>(smem4);
-    const HalfLds L = half_lds(KB, NC);
+    const HalfLds L = half_lds(KB, NC, NC);
     const int lane = lane_id();
     const int wave = threadIdx.x >> 6;
     const int h = lane >> 5;
@@ -712,36 +761,203 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign_half(
     }
     if (w.nitems) decide_items<PRUNE>(w, xp, Cm, D, ld, M, m, codes, pa, moved_list, moved_count);
 
-    // what the block's waves have left, with one atomic each: moved vectors, vectors decided in fp64, max |x'|
+    half_finish<PRUNE>(lds, L, w, amax, refine_count, moved_list, moved_count, work);
+}
+
+// The fp16 dictionary for k_assign_half_chunked, slice by slice in the order its LDS holds them, with the sums its
+// constants come from.  A wave per row of the padded dictionary.
+__global__ __launch_bounds__(256) void k_half_image(
+    const float *__restrict__ Cm, const float *__restrict__ hneg, int K, int D, int ld, int kb, int NC,
+    char *__restrict__ img, float *__restrict__ sums, float *__restrict__ negmu)
+{
+    const int lane = lane_id();
+    const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const float scale = ldexpf(1.f, half_shift(hneg, K));
+    float sq = 0.f, dsq = 0.f;
+    for (int p = lane; p < 16 * NC; p += kWave) {
+        const float4 v = load_row_piece(Cm, row, 4 * p, K, D, ld);
+        float4 mu = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, kWave));
-    unsigned *tail = reinterpret_cast<unsigned *>(lds + L.misc);   // [8] moved, [8] rechecked, [8] max, [1] base
+        for (int i = 0; i < kMuRows; ++i) {
+            const float4 w = load_row_piece(Cm, (int)((unsigned)(i * K) / kMuRows), 4 * p, K, D, ld);
+            mu.x += w.x;
+            mu.y += w.y;
+            mu.z += w.z;
+            mu.w += w.w;
+        }
+        const float f = -scale / kMuRows;
+        const float4 neg = make_float4(mu.x * f, mu.y * f, mu.z * f, mu.w * f);
+        if (row == 0) reinterpret_cast<float4 *>(negmu)[p] = neg;
+        float4 w = scaled(v, scale, neg);
+        if (row >= K) w = make_float4(0.f, 0.f, 0.f, 0.f);
+        const halfx4 q = half4(w, sq, dsq);
+        const int t = p >> 2, g = p & 1, hi = (p >> 1) & 1;
+        *reinterpret_cast<halfx4 *>(img + (size_t)(t * kb + (row >> 5)) * 1024 + half_slot(t, g, row & 31) + 8 * hi) = q;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        sq += __shfl_xor(sq, o, kWave);
+        dsq += __shfl_xor(dsq, o, kWave);
+    }
     if (lane == 0) {
-        tail[wave] = (unsigned)w.nmoved;
-        tail[8 + wave] = (unsigned)w.nitems;
-        tail[16 + wave] = __float_as_uint(amax);
+        sums[2 * row] = sq;
+        sums[2 * row + 1] = dsq;
     }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned nm = 0u, nr = 0u, mxb = 0u;
-        for (int i = 0; i < kAssignWaves; ++i) {
-            nm += tail[i];
-            nr += tail[8 + i];
-            mxb = max(mxb, tail[16 + i]);
+}
+
+// One 64-dim slice of k_assign_half_chunked: contracts x (the slice's chunk in registers) with the dictionary slice in `cur`
+// and brings in what the next one needs: k-step t refills x[2t], x[2t + 1] from xnext as soon as it has converted them, and
+// fetches a piece of the next dictionary slice at its start and stores it to `nxt` behind its MFMAs.
+// EXACT: D is a multiple of 64.  Otherwise the refill clamps its addresses into the row and what lies past D is multiplied by
+// zero at use (mu and the dictionary are zero there).
+template <int KB, bool AMAX, bool EXACT>
+__device__ __forceinline__ void mfma_slice_half_refill(
+    floatx16 (&acc)[KB], float4 (&x)[8], const char *__restrict__ cur, char *__restrict__ nxt, const char *__restrict__ src,
+    const float *__restrict__ xnext, const float *__restrict__ negmu, int q, int qn, int D, int lane, float scale,
+    float &xsq, float &dsq, float &amax)
+{
+    constexpr int GB = KB < 4 ? KB : 4;
+    constexpr int PIECES = KB * 256;                                // uint4 of a slice
+    const int g = lane >> 5, r = lane & 31;
+    const float4 *mu4 = reinterpret_cast<const float4 *>(negmu) + 16 * q + g;
+    const float4 *xn4 = reinterpret_cast<const float4 *>(xnext + (EXACT ? kChunkD * qn + 4 * g : 0));
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const int at = t * kAssignThreads + (int)threadIdx.x;
+        uint4 piece = make_uint4(0u, 0u, 0u, 0u);
+        if ((t + 1) * kAssignThreads <= PIECES || (t * kAssignThreads < PIECES && at < PIECES)) piece = reinterpret_cast<const uint4 *>(src)[at];
+        const float4 u = x[2 * t], v = x[2 * t + 1];
+        float su = scale, sv = scale;
+        if (EXACT) {
+            x[2 * t] = xn4[4 * t];
+            x[2 * t + 1] = xn4[4 * t + 2];
+        } else {
+            const int col = kChunkD * q + 16 * t + 4 * g, coln = kChunkD * qn + 16 * t + 4 * g;
+            su = col < D ? scale : 0.f;
+            sv = col + 8 < D ? scale : 0.f;
+            x[2 * t] = *reinterpret_cast<const float4 *>(xnext + min(coln, last_piece(D)));
+            x[2 * t + 1] = *reinterpret_cast<const float4 *>(xnext + min(coln + 8, last_piece(D)));
         }
-        if (nm) tail[24] = atomicAdd(moved_count, nm);
-        if (nr) {
-            atomicAdd(refine_count, nr);
-            atomicAdd(work + 2, (unsigned long long)nr);
+        if (AMAX) {
+            amax = fmaxf(fmaxf(amax, fabsf(u.x)), fabsf(u.y));
+            amax = fmaxf(fmaxf(amax, fabsf(u.z)), fabsf(u.w));
+            amax = fmaxf(fmaxf(amax, fabsf(v.x)), fabsf(v.y));
+            amax = fmaxf(fmaxf(amax, fabsf(v.z)), fabsf(v.w));
         }
-        if (PRUNE != 2) atomicMax(refine_count + 1, mxb);           // of listed vectors nobody asks: it is known from the first pass
+        const char *base = cur + half_slot(t, g, r);
+        const halfx4 lo = half4(scaled(u, su, mu4[4 * t]), xsq, dsq);
+        const halfx4 hi = half4(scaled(v, sv, mu4[4 * t + 2]), xsq, dsq);
+        const halfx8 w = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+#pragma unroll
+        for (int b0 = 0; b0 < KB; b0 += GB) {
+            halfx8 a[GB];
+#pragma unroll
+            for (int b = 0; b < GB; ++b) a[b] = *reinterpret_cast<const halfx8 *>(base + (t * KB + b0 + b) * 1024);
+#pragma unroll
+            for (int b = 0; b < GB; ++b) acc[b0 + b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[b], w, acc[b0 + b], 0, 0, 0);
+        }
+        // the store (and the wait for its load) stays behind the step's MFMAs
+        __builtin_amdgcn_sched_barrier(0x10f);
+        if ((t + 1) * kAssignThreads <= PIECES || (t * kAssignThreads < PIECES && at < PIECES)) reinterpret_cast<uint4 *>(nxt)[at] = piece;
     }
-    __syncthreads();
-    if (w.nmoved) {
-        unsigned at = tail[24];
-        for (int i = 0; i < wave; ++i) at += tail[i];
-        for (int i = lane; i < w.nmoved; i += kWave) moved_list[at + i] = w.moved[i];
+}
+
+// The same assignment for dictionaries that do not fit LDS even as fp16: a block walks the D axis in 64-dim slices for every
+// tile of 8 x 32 vectors, the accumulators persisting across slices.  Two LDS buffers hold the slice in use and the one
+// being brought in from k_half_image's array, one barrier per slice; the refills run under the MFMAs, across tiles too.
+template <int KB, int PRUNE, bool EXACT>
+__global__ __launch_bounds__(kAssignThreads) void k_assign_half_chunked(
+    const float *__restrict__ xp, const float *__restrict__ Cm, const float *__restrict__ hneg,
+    const char *__restrict__ img, const float *__restrict__ sums, const float *__restrict__ negmu,
+    int N, int D, int ld, int K, int M, int m, int NC,
+    uint8_t *__restrict__ codes, unsigned *__restrict__ refine_count, PruneArgs pa,
+    unsigned long long *__restrict__ moved_list, unsigned *__restrict__ moved_count, unsigned long long *__restrict__ work,
+    HalfItem *__restrict__ items)
+{
+    extern __shared__ float4 smem4[];
+    char *lds = reinterpret_cast<char *>(smem4);
+    const HalfLds L = half_lds(KB, NC, 2);
+    constexpr int SLICE = KB * 4096;
+    const int lane = lane_id();
+    const int wave = threadIdx.x >> 6;
+    const int h = lane >> 5, r = lane & 31;
+    const float *lds_h = reinterpret_cast<const float *>(lds + L.hneg);
+    float *lds_mu = reinterpret_cast<float *>(lds + L.mu);
+
+    const int listed = PRUNE == 2 ? (int)*pa.active_count : N;
+    const bool gather = PRUNE == 2 && listed < N - (N >> 5);
+    const int rows = gather ? listed : N;
+    const int nbt = (int)(((unsigned)rows + kTileVec * kAssignWaves - 1) / (kTileVec * kAssignWaves));   // block tiles
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        work[0] += 1ull;                                            // launches on one stream follow one another
+        work[1] += (unsigned long long)listed;
     }
+    if ((int)blockIdx.x >= nbt) return;
+
+    // vector this lane's column of block tile bt stands for; N (= "none") in the ragged tail
+    auto vec_of = [&](int bt) -> int {
+        const unsigned i = ((unsigned)bt * kAssignWaves + wave) * kTileVec + r;
+        if (i >= (unsigned)rows) return N;
+        return gather ? (int)pa.active[i] : (int)i;
+    };
+    auto row_ptr = [&](int n) {
+        if (n >= N) n = gather ? (int)pa.active[rows - 1] : N - 1;  // tail columns re-read the last row
+        return xp + (size_t)n * ld;
+    };
+    int n = vec_of(blockIdx.x);
+    const float *xrow = row_ptr(n);
+    unsigned old = moved_list && n < N ? codes[(size_t)n * M + m] : 0u;
+    float4 x[8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) x[s] = *reinterpret_cast<const float4 *>(xrow + min(8 * s + 4 * h, last_piece(D)));
+
+    // slice 0 (the same for every tile), mu and the constants
+    for (int e = threadIdx.x; e < SLICE / 16; e += kAssignThreads)
+        reinterpret_cast<uint4 *>(lds)[e] = reinterpret_cast<const uint4 *>(img)[e];
+    for (int d = threadIdx.x; d < kChunkD * NC; d += kAssignThreads) lds_mu[d] = negmu[d];
+    const int s = half_shift(hneg, K);
+    const bool holder = (int)threadIdx.x < 32 * KB;
+    const HalfConsts c = half_constants<KB>(lds, L, holder ? sums[2 * threadIdx.x] : 0.f, holder ? sums[2 * threadIdx.x + 1] : 0.f,
+                                            threadIdx.x, holder, K, NC, ldexpf(1.f, s), ldexpf(1.f, -s));
+    HalfWave w;
+    w.moved = reinterpret_cast<unsigned long long *>(lds + L.moved) + wave * kWaveMoved;
+    w.nitems = 0;
+    w.nmoved = 0;
+    w.items = items + (size_t)((nbt + gridDim.x - 1) / gridDim.x) * kTileVec * (blockIdx.x * kAssignWaves + wave);
+
+    floatx16 acc[KB];
+    float amax = 0.f;
+    int par = 0;
+    for (int bt = blockIdx.x; bt < nbt; bt += gridDim.x) {
+        int n_n = n;
+        const float *xrow_n = xrow;                                 // the last tile refills with itself: unused
+        unsigned old_n = old;
+        if (bt + (int)gridDim.x < nbt) {
+            n_n = vec_of(bt + gridDim.x);
+            xrow_n = row_ptr(n_n);
+            if (moved_list) old_n = n_n < N ? codes[(size_t)n_n * M + m] : 0u;
+        }
+        float xsq = 0.f, dsq = 0.f;
+        init_acc<KB>(acc, lds_h, h);
+#pragma unroll 1
+        for (int q = 0; q < NC; ++q) {
+            const bool last = q + 1 == NC;
+            const int qn = last ? 0 : q + 1;
+            mfma_slice_half_refill<KB, PRUNE != 2, EXACT>(acc, x, lds + par * SLICE, lds + (par ^ 1) * SLICE, img + (size_t)qn * SLICE,
+                                                   last ? xrow_n : xrow, lds_mu, q, qn, D, lane, c.scale, xsq, dsq, amax);
+            __syncthreads();                                        // slice q consumed by all, slice qn complete
+            par ^= 1;
+        }
+        float x2, norm;
+        const float e = mfma_bound_half<KB>(acc, reinterpret_cast<const unsigned *>(lds + L.waug), xsq, dsq, c, lane, x2, norm);
+        decide_half<KB, PRUNE>(acc, x2, norm, e, c, reinterpret_cast<const float *>(lds + L.w), lane, n, N, K, M, m, old, codes, pa,
+                               w, moved_list, moved_count);
+        n = n_n;
+        xrow = xrow_n;
+        old = old_n;
+    }
+    if (w.nitems) decide_items<PRUNE>(w, xp, Cm, D, ld, M, m, codes, pa, moved_list, moved_count);
+    half_finish<PRUNE>(lds, L, w, amax, refine_count, moved_list, moved_count, work);
 }
 
 }  // namespace hclae

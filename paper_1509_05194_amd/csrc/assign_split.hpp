@@ -260,95 +260,4 @@ __device__ __forceinline__ void mfma_chunk_split_refill(
     }
 }
 
-// k_assign_chunked with the split-bf16 contraction: tiles, slices, refills and decision as there; margin as
-// in k_assign_split.  img = k_codebook_image_split of the codebook in use.
-template <int KB, int PRUNE = 0>
-__global__ __launch_bounds__(kAssignThreads) void k_assign_split_chunked(
-    const float *__restrict__ xp, const uint4 *__restrict__ img, const float *__restrict__ hneg,
-    const float *__restrict__ split_norms,
-    int64_t N, int D, int ld, int K, int M, int m, int NC, float acc_bound,
-    uint8_t *__restrict__ codes, RefineItem *__restrict__ list, unsigned *__restrict__ refine_count,
-    PruneArgs pa)
-{
-    extern __shared__ float4 smem4[];
-    constexpr int CH = KB * 8 * kWave;                              // uint4 per slice
-    uint4 *buf0 = reinterpret_cast<uint4 *>(smem4), *buf1 = buf0 + CH;
-    float *lds_h = reinterpret_cast<float *>(smem4 + 2 * CH);
-    const int lane = lane_id();
-    const int wave = threadIdx.x >> 6;
-    const int g = lane >> 5;
-    const int r = lane & 31;
-
-    for (int k = threadIdx.x; k < 32 * KB; k += blockDim.x) lds_h[k] = hneg[k];
-    const uint4 *mine = img + wave * kWave + lane;
-#pragma unroll
-    for (int p = 0; p < KB; ++p) buf0[(p * 8 + wave) * kWave + lane] = mine[p * 8 * kWave];
-    __syncthreads();
-    float hmax = 0.f;
-    for (int k = 0; k < K; ++k) hmax = fmaxf(hmax, -lds_h[k]);
-    const float cmax = sqrtf(2.f * hmax) * 1.000001f;
-    if (wave == 0) {
-        float a = 0.f, b = 0.f;
-        for (int k = lane; k < K; k += kWave) {
-            a = fmaxf(a, split_norms[2 * k]);
-            b = fmaxf(b, split_norms[2 * k + 1]);
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            a = fmaxf(a, __shfl_xor(a, o, kWave));
-            b = fmaxf(b, __shfl_xor(b, o, kWave));
-        }
-        if (lane == 0) { lds_h[32 * KB] = a; lds_h[32 * KB + 1] = b; }
-    }
-    __syncthreads();
-    const float clmax = lds_h[32 * KB], dcmax = lds_h[32 * KB + 1];
-    const float split_bound = (0.00390625f * 1.00391f) * clmax + 1.52587890625e-5f * cmax + 1.00002f * dcmax;
-    const float eps = 2.f * acc_bound;
-    const float cmax_eff = (cmax * 1.02f + split_bound / acc_bound) * 1.0001f;
-
-    const int64_t listed = PRUNE == 2 ? (int64_t)*pa.active_count : N;
-    const bool gather = PRUNE == 2 && listed * 32 < N * 31;         // nearly all listed: all N in order
-    const int64_t rows = gather ? listed : N;
-    const int64_t nbt = (rows + kTileVec * kAssignWaves - 1) / (kTileVec * kAssignWaves);
-    float amax = 0.f;
-    if ((int64_t)blockIdx.x < nbt) {
-        auto tile_row = [&](int64_t bt, int64_t &vec) -> const float * {
-            const int64_t i = (bt * kAssignWaves + wave) * kTileVec + r;
-            const int64_t ic = i < rows ? i : rows - 1;
-            const int64_t nrow = gather ? (int64_t)pa.active[ic] : ic;
-            vec = i < rows ? nrow : N;
-            return xp + nrow * ld;
-        };
-        int64_t vec;
-        const float *xrow = tile_row(blockIdx.x, vec);
-        float4 x[8];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            x[2 * t] = *reinterpret_cast<const float4 *>(xrow + min(kSplitStep * t + 8 * g, last_piece(D)));
-            x[2 * t + 1] = *reinterpret_cast<const float4 *>(xrow + min(kSplitStep * t + 8 * g + 4, last_piece(D)));
-        }
-        int par = 0;
-        for (int64_t bt = blockIdx.x; bt < nbt; bt += gridDim.x) {
-            int64_t vec_next = vec;
-            const float *xrow_next = xrow;
-            if (bt + gridDim.x < nbt) xrow_next = tile_row(bt + gridDim.x, vec_next);
-            floatx16 acc[KB];
-            float xsq = 0.f;
-            init_acc<KB>(acc, lds_h, g);
-            for (int q = 0; q < NC; ++q) {
-                const bool last = q + 1 == NC;
-                const int qn = last ? 0 : q + 1;
-                mfma_chunk_split_refill<KB>(acc, x, par ? buf1 : buf0, par ? buf0 : buf1, mine + (size_t)qn * CH,
-                                            last ? xrow_next : xrow, q, qn, D, lane, wave, xsq, amax);
-                __syncthreads();
-                par ^= 1;
-            }
-            decide<KB, PRUNE>(acc, xsq, eps, hmax, cmax_eff, lane, vec, N, M, m, codes, list, refine_count, pa);
-            xrow = xrow_next;
-            vec = vec_next;
-        }
-    }
-    publish_absmax(amax, refine_count + 1);
-}
-
 }  // namespace hclae

@@ -82,8 +82,9 @@ struct hclae_ctx {
     float *split_norms;      // [K][2] split constants of the codebook in use (contraction 1)
     int contraction;         // 0: fp32 MFMA, 1: split-bf16 MFMA
     unsigned *refine_count;
-    RefineItem *refine_list; // [N_max]
     HalfItem *half_list;     // undecided vectors of k_assign_half, a stretch per wave
+    float *half_sums;        // [32*kb][2] what k_half_image leaves for the constants of k_assign_half_chunked
+    float *half_negmu;       // [64*NC]
     uint8_t *old_codes;      // [N_max]
     long long *partial;      // [upd_blocks][K][D] fixed-point centroid sums
     int *pcount;             // [upd_blocks][K]
@@ -91,7 +92,6 @@ struct hclae_ctx {
     // exact incremental centroid update within a stage (see k_merge)
     long long *tot_sum;      // [K][D] fixed-point sums of the stage
     int *tot_cnt;            // [K]
-    uint8_t *upd_col;        // [N_max] code column as of the last centroid pass
     unsigned long long *moved_list;  // [N_max]
     unsigned *moved_count;
     // exact pruning of the assignments of a stage (see PruneArgs)
@@ -306,7 +306,8 @@ int launch_norms(hclae_ctx *ctx, const float *Cm, int dact = 0, int ld = 0, int 
 // Whether the dictionary over `dact` coordinates fits LDS as fp16 (k_assign_half).
 bool half_resident(const hclae_ctx *ctx, int dact)
 {
-    return half_lds(ctx->kb, (dact + kChunkD - 1) / kChunkD).total <= kLdsBudget;
+    const int NC = (dact + kChunkD - 1) / kChunkD;
+    return half_lds(ctx->kb, NC, NC).total <= kLdsBudget;
 }
 
 // k_assign_half over all rows or the listed ones; it also decides the near-ties and lists the moved vectors (prune 3).
@@ -325,10 +326,39 @@ int launch_assign_half(hclae_ctx *ctx, int m, int64_t N, const float *xp, const 
         ctx->attr_done |= attr_set;
     }
     Timed t_(ctx, PRUNE == 2 ? HCLAE_T_ASSIGN_ACTIVE : HCLAE_T_ASSIGN);
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kAssignThreads), (size_t)half_lds(KB, NC).total, ctx->stream,
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kAssignThreads), (size_t)half_lds(KB, NC, NC).total, ctx->stream,
                        xp, Cm, ctx->hneg, (int)N, dact, ld, ctx->K, ctx->M, m, NC, codes, ctx->refine_count, pa,
                        want_moved ? ctx->moved_list : (unsigned long long *)nullptr, ctx->moved_count, ctx->work,
                        ctx->half_list);
+    HIP_TRY(ctx, hipGetLastError());
+    return HCLAE_OK;
+}
+
+// The same where the dictionary does not fit LDS (k_half_image lays it out first).
+template <int KB, int PRUNE>
+int launch_assign_half_chunked(hclae_ctx *ctx, int m, int64_t N, const float *xp, const float *Cm, uint8_t *codes, int dact, int ld,
+                               const PruneArgs &pa, bool want_moved)
+{
+    const int NC = (dact + kChunkD - 1) / kChunkD;
+    if (NC > ctx->NC || KB != ctx->kb)
+        return fail(ctx, HCLAE_EINVAL, "assign: codebook image too small for this shape");
+    const int64_t nbt = (N + kTileVec * kAssignWaves - 1) / (kTileVec * kAssignWaves);
+    const int64_t blocks = nbt < ctx->cus ? nbt : ctx->cus;
+    const bool exact = dact % kChunkD == 0;
+    auto kern = exact ? &k_assign_half_chunked<KB, PRUNE, true> : &k_assign_half_chunked<KB, PRUNE, false>;
+    const uint64_t attr_set = 1ull << (24 + 2 * PRUNE + (exact ? 1 : 0));   // this instance's bit in ctx->attr_done
+    if (!(ctx->attr_done & attr_set)) {
+        HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget));
+        ctx->attr_done |= attr_set;
+    }
+    Timed t_(ctx, PRUNE == 2 ? HCLAE_T_ASSIGN_ACTIVE : HCLAE_T_ASSIGN);
+    char *img = reinterpret_cast<char *>(ctx->cb_image);
+    hipLaunchKernelGGL(k_half_image, dim3(8 * KB), dim3(256), 0, ctx->stream, Cm, ctx->hneg, ctx->K, dact, ld, KB, NC,
+                       img, ctx->half_sums, ctx->half_negmu);
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kAssignThreads), (size_t)half_lds(KB, NC, 2).total, ctx->stream,
+                       xp, Cm, ctx->hneg, img, ctx->half_sums, ctx->half_negmu, (int)N, dact, ld, ctx->K, ctx->M, m, NC, codes,
+                       ctx->refine_count, pa, want_moved ? ctx->moved_list : (unsigned long long *)nullptr, ctx->moved_count,
+                       ctx->work, ctx->half_list);
     HIP_TRY(ctx, hipGetLastError());
     return HCLAE_OK;
 }
@@ -358,79 +388,11 @@ int launch_assign_kb(hclae_ctx *ctx, int m, int64_t N, const float *xp, const fl
         default: return launch_assign_half<KB, 2, true>(ctx, m, N, xp, Cm, codes, dact, ld, pa, moved);
         }
     }
-    // prune 3 = 2, and the re-check kernel lists the vectors that changed cluster (moved_count[0] is zero: the
-    // merge of the previous centroid update of this stage reset it)
-    MovedArgs mv = {};
-    if (prune == 3) {
-        mv.prev = ctx->upd_col; mv.list = ctx->moved_list; mv.count = ctx->moved_count;
-        mv.cand = ctx->active; mv.cand_count = ctx->moved_count + 3; mv.bl = ctx->cur_l;
-        prune = 2;
+    switch (prune == 3 ? 2 : prune) {
+    case 0: return launch_assign_half_chunked<KB, 0>(ctx, m, N, xp, Cm, codes, dact, ld, pa, false);
+    case 1: return launch_assign_half_chunked<KB, 1>(ctx, m, N, xp, Cm, codes, dact, ld, pa, false);
+    default: return launch_assign_half_chunked<KB, 2>(ctx, m, N, xp, Cm, codes, dact, ld, pa, prune == 3);
     }
-    // twice the worst-case rounding error of a score: (dpad + 1) roundings of relative size 2^-23
-    // on partial sums bounded by h + ||x'|| ||c||, plus the rounding of h itself
-    const float eps = 2.02f * (float)(dpad + 2) * 1.1920929e-7f;
-    {
-    Timed t_(ctx, prune == 2 ? HCLAE_T_ASSIGN_ACTIVE : HCLAE_T_ASSIGN);
-    if (ctx->contraction == 1) {
-        // D-chunked, split-bf16: two slices of 64 dims in LDS, one block per CU
-        const size_t lds = (size_t)2 * KB * 8 * kWave * sizeof(float4) + (32 * KB + 4) * sizeof(float);
-        const int64_t nbt = (N + kTileVec * kAssignWaves - 1) / (kTileVec * kAssignWaves);
-        int64_t blocks = nbt < ctx->cus ? nbt : ctx->cus;
-        const uint64_t attr_set = 1ull << 1;        // this call site's bit in ctx->attr_done
-        if (!(ctx->attr_done & attr_set)) {
-            HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_assign_split_chunked<KB, 0>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget));
-            HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_assign_split_chunked<KB, 1>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget));
-            HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_assign_split_chunked<KB, 2>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget));
-            ctx->attr_done |= attr_set;
-        }
-        if (NC > ctx->NC || KB != ctx->kb)
-            return fail(ctx, HCLAE_EINVAL, "assign: codebook image too small for this shape");
-        const float acc_bound = (float)(3 * (dpad / kSplitStep) + 1) * 4.76837158203125e-7f;
-        const int img_total = NC * 4 * KB * kWave;
-        hipLaunchKernelGGL(k_split_norms, dim3((ctx->K + 3) / 4), dim3(256), 0, ctx->stream, Cm, ctx->K, dact, ld, ctx->split_norms);
-        hipLaunchKernelGGL(k_codebook_image_split, dim3((img_total + 255) / 256), dim3(256), 0, ctx->stream,
-                           Cm, ctx->K, dact, ld, KB, NC, reinterpret_cast<uint4 *>(ctx->cb_image));
-        auto kern = prune == 1 ? &k_assign_split_chunked<KB, 1> : prune == 2 ? &k_assign_split_chunked<KB, 2>
-                                                                              : &k_assign_split_chunked<KB, 0>;
-        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kAssignThreads), lds, ctx->stream,
-                           xp, reinterpret_cast<const uint4 *>(ctx->cb_image), ctx->hneg, ctx->split_norms, N, dact, ld,
-                           ctx->K, ctx->M, m, NC, acc_bound, codes, ctx->refine_list, ctx->refine_count, pa);
-    } else {
-        // two slices of 64 dims in LDS: one block per CU
-        const size_t lds = (size_t)2 * KB * 8 * kWave * sizeof(float4) + (32 * KB + 4) * sizeof(float);
-        const int64_t nbt = (N + kTileVec * kAssignWaves - 1) / (kTileVec * kAssignWaves);
-        int64_t blocks = nbt < ctx->cus ? nbt : ctx->cus;
-        const uint64_t attr_set = 1ull << 5;        // this call site's bit in ctx->attr_done
-        if (!(ctx->attr_done & attr_set)) {
-            HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_assign_chunked<KB, 0>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget));
-            HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_assign_chunked<KB, 1>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget));
-            HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_assign_chunked<KB, 2>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget));
-            ctx->attr_done |= attr_set;
-        }
-        if (NC > ctx->NC || KB != ctx->kb)
-            return fail(ctx, HCLAE_EINVAL, "assign: codebook image too small for this shape");
-        const int img_total = NC * KB * 8 * kWave;
-        hipLaunchKernelGGL(k_codebook_image, dim3((img_total + 255) / 256), dim3(256), 0, ctx->stream,
-                           Cm, ctx->K, dact, ld, KB, NC, ctx->cb_image);
-        auto kern = prune == 1 ? &k_assign_chunked<KB, 1> : prune == 2 ? &k_assign_chunked<KB, 2> : &k_assign_chunked<KB, 0>;
-        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kAssignThreads), lds, ctx->stream,
-                           xp, ctx->cb_image, ctx->hneg, N, dact, ld, ctx->K, ctx->M, m, NC, eps,
-                           codes, ctx->refine_list, ctx->refine_count, pa);
-    }
-    }
-    HIP_TRY(ctx, hipGetLastError());
-    Timed t_(ctx, HCLAE_T_REFINE);
-    hipLaunchKernelGGL(k_refine, dim3(ctx->cus * 4), dim3(256), 0, ctx->stream,
-                       xp, Cm, dact, ld, ctx->M, m, codes, ctx->refine_list, ctx->refine_count, mv,
-                       ctx->work, (unsigned long long)N, prune == 2 ? ctx->moved_count + 3 : (const unsigned *)nullptr);
-    HIP_TRY(ctx, hipGetLastError());
-    return HCLAE_OK;
 }
 
 // Assumes hneg holds the norms of Cm (over the same dact coordinates) and the re-check counter is zero.
@@ -511,11 +473,6 @@ int launch_update(hclae_ctx *ctx, int m, int64_t N, const float *xp, float *Cm, 
                        keep_totals ? ctx->tot_sum : (long long *)nullptr, keep_totals ? ctx->tot_cnt : (int *)nullptr, 0,
                        keep_totals ? ctx->moved_count : (unsigned *)nullptr, keep_totals ? ctx->drift : (float *)nullptr);
     HIP_TRY(ctx, hipGetLastError());
-    if (keep_totals && !half_resident(ctx, D)) {           // k_refine compares with it; k_assign_half has the code it replaces
-        hipLaunchKernelGGL(k_save_column, dim3(stream_blocks(ctx, N, 256)), dim3(256), 0, ctx->stream,
-                           codes, N, ctx->M, m, ctx->upd_col);
-        HIP_TRY(ctx, hipGetLastError());
-    }
     return HCLAE_OK;
 }
 
@@ -755,7 +712,8 @@ int hclae_create(hclae_ctx **out, int64_t N_max, int D, int M, int K, void *hip_
         {(void **)&ctx->cb_image, ctx->resident ? 256 : sizeof(float4) * (size_t)ctx->NC * ctx->kb * 8 * kWave},
         {(void **)&ctx->split_norms, sizeof(float) * 2 * HCLAE_MAX_K},
         {(void **)&ctx->refine_count, 256},
-        {(void **)&ctx->refine_list, sizeof(RefineItem) * (size_t)N_max},
+        {(void **)&ctx->half_sums, sizeof(float) * 2 * 32 * ctx->kb},
+        {(void **)&ctx->half_negmu, sizeof(float) * kChunkD * ctx->NC},
         {(void **)&ctx->half_list, sizeof(HalfItem) * (size_t)half_list_entries(N_max, ctx->cus * kAssignWaves)},
         {(void **)&ctx->old_codes, (size_t)N_max},
         {(void **)&ctx->partial, per * ub},
@@ -763,7 +721,6 @@ int hclae_create(hclae_ctx **out, int64_t N_max, int D, int M, int K, void *hip_
         {(void **)&ctx->nk, sizeof(int) * K},
         {(void **)&ctx->tot_sum, sizeof(long long) * (size_t)K * D},
         {(void **)&ctx->tot_cnt, sizeof(int) * K},
-        {(void **)&ctx->upd_col, (size_t)N_max},
         {(void **)&ctx->moved_list, sizeof(unsigned long long) * (size_t)N_max},
         {(void **)&ctx->moved_count, 256},
         {(void **)&ctx->bnd_u, sizeof(float) * (size_t)N_max},
@@ -806,8 +763,8 @@ int hclae_create(hclae_ctx **out, int64_t N_max, int D, int M, int K, void *hip_
 int hclae_destroy(hclae_ctx *ctx)
 {
     if (!ctx) return HCLAE_EINVAL;
-    void *dev[] = {ctx->hneg, ctx->cb_image, ctx->split_norms, ctx->refine_count, ctx->refine_list, ctx->half_list, ctx->old_codes, ctx->partial, ctx->pcount,
-                   ctx->nk, ctx->tot_sum, ctx->tot_cnt, ctx->upd_col, ctx->moved_list, ctx->moved_count, ctx->bnd_u, ctx->bnd_l, ctx->drift, ctx->active, ctx->work, ctx->seed_idx, ctx->part_a, ctx->part_b, ctx->part_chg, ctx->rec,
+    void *dev[] = {ctx->hneg, ctx->cb_image, ctx->split_norms, ctx->refine_count, ctx->half_list, ctx->half_sums, ctx->half_negmu, ctx->old_codes, ctx->partial, ctx->pcount,
+                   ctx->nk, ctx->tot_sum, ctx->tot_cnt, ctx->moved_list, ctx->moved_count, ctx->bnd_u, ctx->bnd_l, ctx->drift, ctx->active, ctx->work, ctx->seed_idx, ctx->part_a, ctx->part_b, ctx->part_chg, ctx->rec,
                    ctx->run_sum, ctx->run_cnt, ctx->n0_dev, ctx->pca_rt, ctx->pca_crot, ctx->pca_colpart,
                    ctx->pca_grampart, ctx->pca_mean, ctx->pca_mean32, ctx->pca_cov, ctx->pca_R, ctx->pca_xr,
                    ctx->stats_buf, ctx->order_var, ctx->order_idx, ctx->order_tmp,

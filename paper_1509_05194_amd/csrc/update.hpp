@@ -107,16 +107,6 @@ __global__ __launch_bounds__(kUpdThreads) void k_accumulate(
         for (int k = threadIdx.x; k < K; k += kUpdThreads) pcount[blockIdx.x * K + k] = (int)cnt[k];
 }
 
-// prev[n] = codes[n][m]: the column as the full centroid pass saw it.  (A kernel of its own: as a by-product of
-// k_accumulate the byte stores sat in the row loop of the blocks of the first window and made those blocks, and with
-// them the pass, 18 % slower at D = 960.)
-__global__ __launch_bounds__(256) void k_save_column(
-    const uint8_t *__restrict__ codes, int64_t N, int M, int m, uint8_t *__restrict__ prev)
-{
-    for (int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x; n < N; n += (int64_t)gridDim.x * 256)
-        prev[n] = codes[n * M + m];
-}
-
 // Blocks (of the x dimension) that the pass over `total` moved vectors uses: 160 rows per block measured best
 // on one MI355X (N = 1M, D = 128: the gather of the rows wants many blocks, the flush of 128 KB of partial sums
 // per block and the merge that reads them want few).  The merge that follows computes the same number.
@@ -190,7 +180,7 @@ __global__ __launch_bounds__(kUpdThreads) void k_accumulate_moved(
         for (int k = threadIdx.x; k < K; k += kUpdThreads) pcount[blockIdx.x * K + k] = cnt[k];
 }
 
-// max |x'| over an array (bits of the float, see publish_absmax); used when the centroid update is
+// max |x'| over an array (bits of a non-negative float: integer max is float max); used when the centroid update is
 // called on its own, without the assign kernel that normally provides it.  *slot must start at 0.
 __global__ __launch_bounds__(256) void k_absmax(const float4 *__restrict__ x, int64_t n4, unsigned *__restrict__ slot)
 {
@@ -206,7 +196,7 @@ __global__ __launch_bounds__(256) void k_absmax(const float4 *__restrict__ x, in
 
 // Exact incremental form (tot_sum int64 [K][D], tot_cnt int [K]; both may be null): a full pass stores the
 // integer sums and counts of the stage; while x' stays as it is, a later pass over only the vectors that
-// changed cluster (listed by k_refine; k_accumulate_moved: +q into the new cluster, -q out of the old one) advances
+// changed cluster (listed by the assignment; k_accumulate_moved: +q into the new cluster, -q out of the old one) advances
 // them with delta != 0.  Integer addition being exact, the totals -- and so the centroids -- are the very
 // numbers a full pass would give.
 //
