@@ -1190,7 +1190,7 @@ int hclae_online_chunk(hclae_ctx *ctx, const uint8_t *Xu8, int64_t n, int D, flo
     if (reinterpret_cast<uintptr_t>(Xu8) % 16 != 0)
         return fail(ctx, HCLAE_EINVAL, "hclae_online_chunk: Xu8 must be 16-byte aligned");
     const int64_t total = n * (int64_t)D;
-    hipLaunchKernelGGL(k_convert_u8, dim3(stream_blocks(ctx, (total >> 4) + 1, kFlatThreads * 2)), dim3(kFlatThreads), 0,
+    hipLaunchKernelGGL(k_convert_u8, dim3(stream_blocks(ctx, total >> 2, kFlatThreads * 8)), dim3(kFlatThreads), 0,
                        ctx->stream, residue, Xu8, total);
     HIP_TRY(ctx, hipGetLastError());
     for (int m = 0; m < M; ++m) {
@@ -1818,8 +1818,11 @@ int hclae_code_stats(hclae_ctx *ctx, const uint8_t *codes, int64_t N, int M, int
     hipLaunchKernelGGL(k_zero_u64, dim3(stream_blocks(ctx, (int64_t)(nh + nj), 256)), dim3(256), 0, ctx->stream, dev, nh + nj);
     e = hipGetLastError();
     if (e == hipSuccess && N > 0) {
-        hipLaunchKernelGGL(k_code_histograms, dim3(stream_blocks(ctx, N, 256)), dim3(256), 0, ctx->stream,
-                           codes, N, M, K, a, b, dev, joint ? dev + nh : (unsigned long long *)nullptr);
+        const int cols = std::min(M, kHistLds / (4 * K));           // columns whose counters fit a block's LDS
+        const int wide = cols == M && 16 % M == 0 && (reinterpret_cast<uintptr_t>(codes) & 15u) == 0;
+        const int blocks = (int)std::min<int64_t>(kHistBlocks, (N + kHistThreads - 1) / kHistThreads);
+        hipLaunchKernelGGL(k_code_histograms, dim3(blocks, (M + cols - 1) / cols), dim3(kHistThreads), (size_t)cols * K * 4, ctx->stream,
+                           codes, N, M, K, cols, a, b, wide, dev, joint ? dev + nh : (unsigned long long *)nullptr);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipMemcpyAsync(hist, dev, sizeof(int64_t) * nh, hipMemcpyDeviceToHost, ctx->stream);
