@@ -110,6 +110,37 @@ __device__ __forceinline__ float4 scaled(const float4 &v, float scale, const flo
     return make_float4(fmaf(v.x, scale, negmu.x), fmaf(v.y, scale, negmu.y), fmaf(v.z, scale, negmu.z), fmaf(v.w, scale, negmu.w));
 }
 
+// The exponent of half_shift for a largest ||c||^2/2.
+__device__ __forceinline__ int half_exponent(float h)
+{
+    if (!(h > 0.f) || !(h < __builtin_inff())) return 0;
+    int e;
+    (void)frexpf(sqrtf(2.f * h), &e);
+    const int s = 7 - e;
+    return s < -100 ? -100 : s > 100 ? 100 : s;
+}
+
+// w_k of a codeword from its squares: its norm, with a floor for one near mu, so that rho stays that of ordinary rounding.
+__device__ __forceinline__ float half_floor(float sq, float cmax) { return fmaxf(sqrtf(sq) * 1.001f, cmax * 0.00390625f); }
+
+// Its share of rho: the measured rounding, and that of the scaled and centred fp32 values themselves (2^-24 of them).  The sums
+// of squares are chains of at most 4 NC terms per lane and a few additions: relative error below 2^-10 for any D allowed.
+__device__ __forceinline__ float half_rho(float dsq, float wk, float cmax)
+{
+    return cmax > 0.f ? (sqrtf(dsq) * 1.001f + wk * 1.2e-7f) / wk : 0.f;
+}
+
+// A: two units more than the MFMAs, for the norms and for the index bits in a score (decide_half).
+__device__ __forceinline__ float half_acc(int NC) { return (float)(4 * NC + 3) * (17.f * 1.1920929e-7f); }
+
+// e of a vector, rounded up to fp16 (to nearest of 1.002 e), and not below its smallest normal number.
+__device__ __forceinline__ float half_bound(float x2, float dsq, float xn, const HalfConsts &c)
+{
+    const float dx = sqrtf(dsq) * 1.001f + xn * 1.2e-7f;
+    const float e = fmaxf((dx * (1.f + c.rho) + xn * (c.rho + c.acc * (1.f + c.rho))) * 1.002f, 6.2e-5f);
+    return (float)(_Float16)e;
+}
+
 // Power of two that brings the largest codeword norm into [2^6, 2^7): rows up to 1000 times that norm stay in fp16's
 // range, and coordinates down to 2^-20 of it are normal numbers.  Every wave computes the same value; all its lanes take part.
 __device__ __forceinline__ int half_shift(const float *__restrict__ hneg, int K)
@@ -118,11 +149,7 @@ __device__ __forceinline__ int half_shift(const float *__restrict__ hneg, int K)
     for (int k = lane_id(); k < K; k += kWave) h = fmaxf(h, -hneg[k]);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) h = fmaxf(h, __shfl_xor(h, o, kWave));
-    if (!(h > 0.f) || !(h < __builtin_inff())) return 0;
-    int e;
-    (void)frexpf(sqrtf(2.f * h), &e);
-    const int s = 7 - e;
-    return s < -100 ? -100 : s > 100 ? 100 : s;
+    return half_exponent(h);
 }
 
 // Byte offset of the 16 bytes that lane (g, r) reads for k-step t (16 dims) of row block b: dims 16 t + 4 g .. + 3 and
@@ -130,11 +157,11 @@ __device__ __forceinline__ int half_shift(const float *__restrict__ hneg, int K)
 // stores of one row, which come from the lanes of a half wave, spread over the banks.
 __device__ __forceinline__ int half_slot(int t, int g, int r) { return (32 * g + (r ^ ((t & 3) | (g << 2)))) * 16; }
 
-// Sums NV values (a power of two, at most 32) over the 32 lanes of a half wave: NV - 1 exchanges for all of them, each
-// halving the values a lane carries.  Lane i of the half ends with the total of value i (NV < 32: the lanes that agree
-// with it in their lowest bits too).
-template <int NV>
-__device__ __forceinline__ float half_wave_sums(float (&v)[NV])
+// Sums NV values (a power of two, at most W) over groups of W lanes: NV - 1 exchanges for all of them, each halving the values
+// a lane carries.  Lane i of the group ends with the total of value i (NV < W: the lanes that agree with it in their lowest
+// bits too).
+template <int NV, int W>
+__device__ __forceinline__ float group_sums(float (&v)[NV])
 {
     const int lane = lane_id();
 #pragma unroll
@@ -149,7 +176,7 @@ __device__ __forceinline__ float half_wave_sums(float (&v)[NV])
     }
     float s = v[0];
 #pragma unroll
-    for (int o = NV; o < 32; o <<= 1) s += __shfl_xor(s, o, kWave);
+    for (int o = NV; o < W; o <<= 1) s += __shfl_xor(s, o, kWave);
     return s;
 }
 
@@ -170,12 +197,9 @@ __device__ __forceinline__ HalfConsts half_constants(
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < kAssignWaves; ++i) hm = fmaxf(hm, red[i]);
-    // the sums of squares are chains of at most 4 NC terms per lane and five or six additions: relative error below 2^-10 for
-    // any D allowed; the rounding of the scaled and centred fp32 values themselves is 2^-24 of them.  A codeword near mu
-    // gets a floor for its norm, so that rho stays that of ordinary rounding.
     c.cmax = sqrtf(hm) * 1.001f;
-    const float wk = fmaxf(sqrtf(sq) * 1.001f, c.cmax * 0.00390625f);
-    float rho = c.cmax > 0.f ? (sqrtf(dsq) * 1.001f + wk * 1.2e-7f) / wk : 0.f;
+    const float wk = half_floor(sq, c.cmax);
+    float rho = half_rho(dsq, wk, c.cmax);
     if (holder) {
         const bool real = row < K;
         const halfx2 up = {(_Float16)(wk * 1.002f), (_Float16)0.f}; // to nearest of 1.002 w: not below w
@@ -192,8 +216,7 @@ __device__ __forceinline__ HalfConsts half_constants(
 #pragma unroll
     for (int i = 0; i < kAssignWaves; ++i) rho = fmaxf(rho, red[kAssignWaves + i]);
     __syncthreads();                                                // red is used again
-    // two units more than the MFMAs: the norms of this function, and the index bits in a score (decide_half)
-    c.acc = (float)(4 * NC + 3) * (17.f * 1.1920929e-7f);
+    c.acc = half_acc(NC);
     // the same in every lane: scalar registers
     c.scale = uniform(scale);
     c.inv = uniform(inv);
@@ -250,7 +273,7 @@ __device__ __forceinline__ HalfConsts stage_half(
         }
     }
     // lane i: value i of its half wave, i.e. of row hw + 16 (i / 2) its squares (i even) or those of its rounding (i odd)
-    const float mine = half_wave_sums<2 * RP>(sums);
+    const float mine = group_sums<2 * RP, 32>(sums);
     const float other = __shfl_xor(mine, 1, kWave);
     const int row = hw + 16 * ((l32 & (2 * RP - 1)) >> 1);
     const bool odd = (l32 & 1) != 0;
@@ -510,18 +533,15 @@ __device__ __forceinline__ float mfma_bound_half(
 {
     x2 = xsq + __shfl_xor(xsq, 32, kWave);
     xn = sqrtf(x2) * 1.001f;
-    const float dx = sqrtf(dsq + __shfl_xor(dsq, 32, kWave)) * 1.001f + xn * 1.2e-7f;
-    // rounded up to fp16 (to nearest of 1.002 e), and not below its smallest normal number
-    const float e = fmaxf((dx * (1.f + c.rho) + xn * (c.rho + c.acc * (1.f + c.rho))) * 1.002f, 6.2e-5f);
-    const halfx2 eh = {(_Float16)e, (_Float16)0.f};
-    const halfx4 w = {eh.x, (_Float16)0.f, (_Float16)0.f, (_Float16)0.f};
+    const float e = half_bound(x2, dsq + __shfl_xor(dsq, 32, kWave), xn, c);
+    const halfx4 w = {(_Float16)e, (_Float16)0.f, (_Float16)0.f, (_Float16)0.f};
 #pragma unroll
     for (int b = 0; b < KB; ++b) {
         const halfx2 u = __builtin_bit_cast(halfx2, waug[64 * b + lane]);
         const halfx4 a = {u.x, u.y, (_Float16)0.f, (_Float16)0.f};
         acc[b] = __builtin_amdgcn_mfma_f32_32x32x8f16(a, w, acc[b], 0, 0, 0);
     }
-    return (float)eh.x;
+    return e;
 }
 
 // Decision for the wave's 32 vectors from their upper scores U_k.  old: the code the vector has now.

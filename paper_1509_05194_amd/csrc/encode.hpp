@@ -1,10 +1,11 @@
 // Greedy encoding (Sec. 3.3, Eq. 3 with one path) of dictionaries that fit fp16 operand registers, in one kernel: a block
 // takes 32 vectors through ALL M dictionaries, the residual rows staying in registers in between.
 //
-// Dictionary by dictionary (assign, subtract, and a copy to begin with) the greedy encoder reads and writes every row M + 1
-// times and launches 3 M + 1 kernels: 2606 us for N = 1M, D = 128, M = 8, of which 1440 us are those row passes, and 160 us for
-// 64 vectors, all of it launches.  Here a row is read once and written once, and the two launches are k_encode_prep, which
-// lays out the fp16 dictionaries, and k_encode_fused.
+// Dictionary by dictionary the greedy encoder launches 3 M kernels and reads and writes every row M times; a few thousand
+// vectors pay for nothing but launches that way (D = 128, M = 8: 158 us for 64 vectors, 202 us for 10k).  Here a row is read
+// and written once, and the two launches are k_encode_prep, which lays out the fp16 dictionaries, and k_encode_fused: 51 us
+// and 90 us.  What bounds it is the chain of a dictionary's steps (round, contract, decide, subtract, with two or four
+// barriers): about 4.5 us each, eight waves waiting for each other, which is why large calls do not come here (encode_fused()).
 //
 // Wave b of the block keeps codewords 32 b .. 32 b + 31 of the running dictionary as MFMA operands in registers (its next
 // operands travel while the vectors are decided); the 32 rows are rounded to fp16 once by all threads and shared through
@@ -25,55 +26,64 @@ __global__ __launch_bounds__(kPrepThreads) void k_encode_prep(
     float *__restrict__ wtab, float *__restrict__ negmu, float *__restrict__ consts, unsigned *__restrict__ refine_count)
 {
     __shared__ float s_sq[256], s_dsq[256], s_red[2][kPrepThreads / kWave];
-    const int m = blockIdx.x, lane = lane_id(), wave = threadIdx.x >> 6, waves = kPrepThreads / kWave;
+    constexpr int waves = kPrepThreads / kWave;
+    const int m = blockIdx.x, lane = lane_id(), wave = threadIdx.x >> 6;
     const int kpad = 32 * kb;
     const float *Cm = C + (size_t)m * K * D;
     img += (size_t)m * NC * kb * 4096;
     if (m == 0 && threadIdx.x == 0) refine_count[0] = 0u;
+    // a lane keeps its float4 column (NC <= 4), a wave takes rows wave, wave + 16, ..., eight of them in flight
+    constexpr int U = 8;
+    const int p = lane;
+    const bool live = p < 16 * NC;
+    float4 mu = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int i = 0; i < kMuRows; ++i) {
+        const float4 w = load_row_piece(Cm, (int)((unsigned)(i * K) / kMuRows), 4 * p, K, D, D);
+        mu.x += w.x;
+        mu.y += w.y;
+        mu.z += w.z;
+        mu.w += w.w;
+    }
     // the largest norm sets the scale (see half_shift)
     float big = 0.f;
-    for (int row = wave; row < K; row += waves) {
-        float s = 0.f;
-        for (int p = lane; p < D / 4; p += kWave) {
-            const float4 v = *reinterpret_cast<const float4 *>(Cm + (size_t)row * D + 4 * p);
-            s += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-        }
+    for (int r0 = wave; r0 < K; r0 += U * waves) {
+        float s[U];
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, kWave);
-        big = fmaxf(big, s);
+        for (int u = 0; u < U; ++u) {
+            const float4 v = load_row_piece(Cm, r0 + u * waves, 4 * p, K, D, D);
+            s[u] = v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+        }
+        big = fmaxf(big, group_sums<U, 64>(s));
     }
+#pragma unroll
+    for (int o = 1; o < U; o <<= 1) big = fmaxf(big, __shfl_xor(big, o, kWave));
     if (lane == 0) s_red[0][wave] = big;
     __syncthreads();
     for (int i = 0; i < waves; ++i) big = fmaxf(big, s_red[0][i]);
     const float scale = ldexpf(1.f, half_exponent(0.5f * big));
-    for (int row = wave; row < kpad; row += waves) {
-        float sq = 0.f, dsq = 0.f;
-        for (int p = lane; p < 16 * NC; p += kWave) {
-            const float4 v = load_row_piece(Cm, row, 4 * p, K, D, D);
-            float4 mu = make_float4(0.f, 0.f, 0.f, 0.f);
+    const float f = -scale / kMuRows;
+    const float4 neg = make_float4(mu.x * f, mu.y * f, mu.z * f, mu.w * f);
+    if (wave == 0 && live) reinterpret_cast<float4 *>(negmu + (size_t)m * kChunkD * NC)[p] = neg;
+    for (int r0 = wave; r0 < kpad; r0 += U * waves) {
+        float4 v[U];
+        float s[2 * U];
 #pragma unroll
-            for (int i = 0; i < kMuRows; ++i) {
-                const float4 w = load_row_piece(Cm, (int)((unsigned)(i * K) / kMuRows), 4 * p, K, D, D);
-                mu.x += w.x;
-                mu.y += w.y;
-                mu.z += w.z;
-                mu.w += w.w;
-            }
-            const float f = -scale / kMuRows;
-            const float4 neg = make_float4(mu.x * f, mu.y * f, mu.z * f, mu.w * f);
-            if (row == 0) reinterpret_cast<float4 *>(negmu + (size_t)m * kChunkD * NC)[p] = neg;
-            float4 w = scaled(v, scale, neg);
-            if (row >= K) w = make_float4(0.f, 0.f, 0.f, 0.f);
-            const halfx4 q = half4(w, sq, dsq);
+        for (int u = 0; u < U; ++u) v[u] = load_row_piece(Cm, r0 + u * waves, 4 * p, K, D, D);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int row = r0 + u * waves;
+            float4 w = scaled(v[u], scale, neg);
+            if (row >= K || !live) w = make_float4(0.f, 0.f, 0.f, 0.f);
+            s[2 * u] = s[2 * u + 1] = 0.f;
+            const halfx4 q = half4(w, s[2 * u], s[2 * u + 1]);
             const int t = p >> 2, g = p & 1, hi = (p >> 1) & 1;
-            *reinterpret_cast<halfx4 *>(img + (size_t)(t * kb + (row >> 5)) * 1024 + half_slot(t, g, row & 31) + 8 * hi) = q;
+            if (live && row < kpad)
+                *reinterpret_cast<halfx4 *>(img + (size_t)(t * kb + (row >> 5)) * 1024 + half_slot(t, g, row & 31) + 8 * hi) = q;
         }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            sq += __shfl_xor(sq, o, kWave);
-            dsq += __shfl_xor(dsq, o, kWave);
-        }
-        if (lane == 0) { s_sq[row] = sq; s_dsq[row] = dsq; }
+        const float mine = group_sums<2 * U, 64>(s);                // lane i: value i
+        const int row = r0 + (lane >> 1) * waves;
+        if (lane < 2 * U && row < kpad) ((lane & 1) ? s_dsq : s_sq)[row] = mine;
     }
     __syncthreads();
     float hm = 0.f;
@@ -103,6 +113,88 @@ __global__ __launch_bounds__(kPrepThreads) void k_encode_prep(
     }
 }
 
+// The nearest of a vector's candidates (bit i of mask[b]: codeword 32 b + i), by one wave; row: its fp32 residual in LDS.
+// As decide_items: fp32 direct form where the two best are further apart than its error, then fp64 in ascending dimension
+// order, lowest index on exact ties.
+template <int KB>
+__device__ __forceinline__ int encode_decide(const float *__restrict__ row, const float *__restrict__ Cm, const unsigned *mask, int D, int lane)
+{
+    const int d4 = D >> 2;
+    // fp32: a half wave per candidate
+    const int half = lane >> 5, l32 = lane & 31;
+    const float eta = (float)(4 * ((d4 + 31) >> 5) + 8) * 6.1e-8f;
+    float best = __builtin_inff(), second = __builtin_inff();
+    int kbest = 0, total = 0;
+    for (int b = 0; b < KB; ++b) total += __popc(mask[b]);
+    int b = 0;
+    unsigned bits = mask[0];
+    auto next = [&]() {                                             // candidates in ascending order, -1 at the end; uniform
+        while (!bits && b + 1 < KB) bits = mask[++b];
+        if (!bits) return -1;
+        const int k = 32 * b + __ffs(bits) - 1;
+        bits &= bits - 1u;
+        return k;
+    };
+    for (int i = 0; i < total; i += 2) {
+        const int k0 = next(), k1 = next();
+        const int k = half ? k1 : k0;
+        const float4 *c4 = reinterpret_cast<const float4 *>(Cm + (size_t)(k < 0 ? 0 : k) * D);
+        float s = 0.f;
+        for (int d = l32; d < d4; d += 32) {
+            const float4 u = reinterpret_cast<const float4 *>(row)[d], v = c4[d];
+            const float e0 = u.x - v.x, e1 = u.y - v.y, e2 = u.z - v.z, e3 = u.w - v.w;
+            s = fmaf(e3, e3, fmaf(e2, e2, fmaf(e1, e1, fmaf(e0, e0, s))));
+        }
+#pragma unroll
+        for (int o = 16; o > 0; o >>= 1) s += __shfl_xor(s, o, kWave);
+        const float o = __shfl_xor(s, 32, kWave);
+        const float s0 = half ? o : s, s1 = half ? s : o;
+        second = s0 < best ? best : fminf(second, s0);
+        if (s0 < best) { best = s0; kbest = k0; }
+        if (k1 >= 0) {
+            second = s1 < best ? best : fminf(second, s1);
+            if (s1 < best) { best = s1; kbest = k1; }
+        }
+    }
+    if (best * (1.f + eta) < second * (1.f - eta) && second > 1e-25f) return kbest;
+    // fp64: a lane per candidate
+    double dbest = __builtin_inf();
+    int k64 = 0x7fffffff;
+    for (int j0 = 0; j0 < total; j0 += kWave) {
+        int j = j0 + lane, k = -1;
+        for (int w = 0; w < KB && k < 0; ++w) {
+            unsigned q = mask[w];
+            const int c = __popc(q);
+            if (j < c) {
+                for (int i = 0; i < j; ++i) q &= q - 1u;
+                k = 32 * w + __ffs(q) - 1;
+            }
+            j -= c;
+        }
+        if (k < 0) continue;
+        const float4 *c4 = reinterpret_cast<const float4 *>(Cm + (size_t)k * D);
+        double s = 0.0;
+#pragma unroll 4
+        for (int d = 0; d < d4; ++d) {
+            const float4 u = reinterpret_cast<const float4 *>(row)[d], v = c4[d];
+            const double t0 = (double)u.x - (double)v.x, t1 = (double)u.y - (double)v.y;
+            const double t2 = (double)u.z - (double)v.z, t3 = (double)u.w - (double)v.w;
+            s += t0 * t0;
+            s += t1 * t1;
+            s += t2 * t2;
+            s += t3 * t3;
+        }
+        if (s < dbest || (s == dbest && k < k64)) { dbest = s; k64 = k; }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const double os = __shfl_xor(dbest, o, kWave);
+        const int ok = __shfl_xor(k64, o, kWave);
+        if (os < dbest || (os == dbest && ok < k64)) { dbest = os; k64 = ok; }
+    }
+    return k64 == 0x7fffffff ? 0 : k64;
+}
+
 // LDS of k_encode_fused.
 struct EncodeLds {
     int rows16, rows32, best, w, rsq, mask, code, misc, total;      // byte offsets
@@ -124,7 +216,7 @@ __host__ __device__ constexpr EncodeLds encode_lds(int kb, int nc)
 
 // NC: 64-dim chunks, 1, 2 or 4 (a row length between rounds up).  A block is KB waves.
 template <int KB, int NC>
-__global__ __launch_bounds__(64 * KB, NC == 4 ? 2 : 4) void k_encode_fused(
+__global__ __launch_bounds__(64 * KB, 2) void k_encode_fused(
     const float *__restrict__ X, const float *__restrict__ C, int N, int D, int K, int M,
     const char *__restrict__ img, const float *__restrict__ hn, const float *__restrict__ wtab, const float *__restrict__ negmu,
     const float *__restrict__ consts, uint8_t *__restrict__ codes, float *__restrict__ residue,
@@ -182,19 +274,16 @@ __global__ __launch_bounds__(64 * KB, NC == 4 ? 2 : 4) void k_encode_fused(
             c.cmax = cc[4];
             // ---- the rows as fp16 operands, with their norms
             const int t16 = p >> 2, g16 = p & 1, hi = (p >> 1) & 1;
+            float s[2 * R];
 #pragma unroll
             for (int i = 0; i < R; ++i) {
                 const int row = row0 + i * RSTEP;
-                float sq = 0.f, dsq = 0.f;
-                const halfx4 q = half4(scaled(x[i], c.scale, mu), sq, dsq);
+                s[2 * i] = s[2 * i + 1] = 0.f;
+                const halfx4 q = half4(scaled(x[i], c.scale, mu), s[2 * i], s[2 * i + 1]);
                 *reinterpret_cast<halfx4 *>(lds + L.rows16 + t16 * 1024 + half_slot(t16, g16, row) + 8 * hi) = q;
-#pragma unroll
-                for (int o = 1; o < COLS; o <<= 1) {
-                    sq += __shfl_xor(sq, o, kWave);
-                    dsq += __shfl_xor(dsq, o, kWave);
-                }
-                if (p == 0) { rsq[2 * row] = sq; rsq[2 * row + 1] = dsq; }
             }
+            const float mine = group_sums<2 * R, COLS>(s);          // lane i of a row's lanes: value i
+            if (p < 2 * R) rsq[2 * (row0 + (p >> 1) * RSTEP) + (p & 1)] = mine;
             __syncthreads();
             // ---- scores of this wave's 32 codewords
             floatx16 acc;

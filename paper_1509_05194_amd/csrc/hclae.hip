@@ -13,6 +13,7 @@
 #include "assign.hpp"
 #include "assign_split.hpp"
 #include "assign_half.hpp"
+#include "encode.hpp"
 #include "stream.hpp"
 #include "update.hpp"
 #include "pca.hpp"
@@ -85,6 +86,7 @@ struct hclae_ctx {
     HalfItem *half_list;     // undecided vectors of k_assign_half, a stretch per wave
     float *half_sums;        // [32*kb][2] what k_half_image leaves for the constants of k_assign_half_chunked
     float *half_negmu;       // [64*NC]
+    char *enc_buf;           // dictionaries of the fused encoder as k_encode_prep lays them out
     uint8_t *old_codes;      // [N_max]
     long long *partial;      // [upd_blocks][K][D] fixed-point centroid sums
     int *pcount;             // [upd_blocks][K]
@@ -254,8 +256,9 @@ RowGeom row_geom(int D)
 // amax (heat only): the pass also publishes max |x'| in refine_count[1] (see k_row_pass).
 template <int SIGN, bool STATS>
 int launch_heat_cool(hclae_ctx *ctx, int m, int64_t N, const float *C, const uint8_t *codes, float *r,
-                     double *part_err, bool amax = false)
+                     double *part_err, bool amax = false, const float *src = nullptr)
 {
+    if (!src) src = r;                                      // in place
     const RowGeom g = row_geom(ctx->D);
     const int rows = kStreamThreads >> g.lcw;
     const int blocks = heat_cool_blocks(N, ctx->D, ctx->cus);
@@ -269,7 +272,7 @@ int launch_heat_cool(hclae_ctx *ctx, int m, int64_t N, const float *C, const uin
     if (ctx->D >= kWideMinD) {
         auto kern = (amax && kCanAmax) ? &k_row_pass_wide<SIGN, STATS, kCanAmax> : &k_row_pass_wide<SIGN, STATS, false>;
         hipLaunchKernelGGL(kern, dim3(blocks), dim3(kStreamThreads), 0, ctx->stream,
-                           r, codes, Cm, (const float *)nullptr, N, ctx->D, ctx->M, m, 0, ctx->old_codes, part_err,
+                           r, src, codes, Cm, (const float *)nullptr, N, ctx->D, ctx->M, m, 0, ctx->old_codes, part_err,
                            ctx->part_chg, amax ? ctx->carry_amax + kAmaxSlots : (unsigned *)nullptr);
         HIP_TRY(ctx, hipGetLastError());
         return blocks;
@@ -277,7 +280,7 @@ int launch_heat_cool(hclae_ctx *ctx, int m, int64_t N, const float *C, const uin
     auto kern = (amax && kCanAmax) ? (ctx->D == 128 ? &k_row_pass<SIGN, STATS, 128, kCanAmax> : &k_row_pass<SIGN, STATS, 0, kCanAmax>)
                                    : (ctx->D == 128 ? &k_row_pass<SIGN, STATS, 128, false> : &k_row_pass<SIGN, STATS, 0, false>);
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(kStreamThreads), 0, ctx->stream,
-                       r, codes, Cm, (const float *)nullptr, N, ctx->D, ctx->M, m, 0, g, ctx->old_codes, part_err,
+                       r, src, codes, Cm, (const float *)nullptr, N, ctx->D, ctx->M, m, 0, g, ctx->old_codes, part_err,
                        ctx->part_chg, amax ? ctx->carry_amax + kAmaxSlots : (unsigned *)nullptr);
     HIP_TRY(ctx, hipGetLastError());
     return blocks;
@@ -591,14 +594,14 @@ int enqueue_stage(hclae_ctx *ctx, int m, int64_t N, float *C, uint8_t *codes, fl
         if (D >= kWideMinD) {
             auto kern = next_amax ? &k_row_pass_wide<0, true, true> : &k_row_pass_wide<0, true, false>;
             hipLaunchKernelGGL(kern, dim3(pa), dim3(kStreamThreads), 0, ctx->stream,
-                               residue, codes, Cm, C + (size_t)next * K * D, N, D, ctx->M, m, next,
+                               residue, residue, codes, Cm, C + (size_t)next * K * D, N, D, ctx->M, m, next,
                                ctx->old_codes, ctx->part_b, ctx->part_chg,
                                next_amax ? ctx->carry_amax + kAmaxSlots : (unsigned *)nullptr);
         } else {
             auto kern = next_amax ? (D == 128 ? &k_row_pass<0, true, 128, true> : &k_row_pass<0, true, 0, true>)
                                   : (D == 128 ? &k_row_pass<0, true, 128, false> : &k_row_pass<0, true, 0, false>);
             hipLaunchKernelGGL(kern, dim3(pa), dim3(kStreamThreads), 0, ctx->stream,
-                               residue, codes, Cm, C + (size_t)next * K * D, N, D, ctx->M, m, next, g,
+                               residue, residue, codes, Cm, C + (size_t)next * K * D, N, D, ctx->M, m, next, g,
                                ctx->old_codes, ctx->part_b, ctx->part_chg,
                                next_amax ? ctx->carry_amax + kAmaxSlots : (unsigned *)nullptr);
         }
@@ -618,19 +621,71 @@ int enqueue_stage(hclae_ctx *ctx, int m, int64_t N, float *C, uint8_t *codes, fl
     return HCLAE_OK;
 }
 
+// Chunks of the fused encoder's rows, or 0: rows longer than its registers take go dictionary by dictionary (K <= 32 leaves
+// one wave to a block, whose threads then hold 8 NC float4 of the rows).
+int encode_chunks(const hclae_ctx *ctx)
+{
+    const int nc = ctx->NC == 3 ? 4 : ctx->NC;
+    return nc <= 4 && 8 * nc <= 16 * ctx->kb ? nc : 0;
+}
+
+// Which encoder: eight waves that decide 32 vectors in lockstep leave a CU waiting, so for more than 128 codewords the fused
+// encoder is the better one only while a CU has few tiles (K = 256, D = 128, M = 8: 51 us against 158 for 64 vectors, 90 / 202
+// for 10k, 216 / 277 for 40k, 409 / 368 for 80k; the lines cross between 40k and 80k at D = 64 and 256 too).  With fewer
+// waves to a block it always is (K = 100, D = 100, M = 8: 46 / 152 for 10k, 1817 / 2650 for 1M; K = 16: 23 / 60, 251 / 243).
+bool encode_fused(const hclae_ctx *ctx, int64_t N)
+{
+    return encode_chunks(ctx) != 0 && (ctx->kb < 8 || N <= (int64_t)ctx->cus * 6 * kTileVec);
+}
+
+template <int KB, int NC>
+int launch_encode_fused(hclae_ctx *ctx, const float *X, int64_t N, const float *C, uint8_t *codes, float *residue)
+{
+    if (8 * NC > 16 * KB) return fail(ctx, HCLAE_EINVAL, "encode: shape not covered by the fused encoder");
+    const int kpad = 32 * KB;
+    char *img = ctx->enc_buf;
+    float *hn = reinterpret_cast<float *>(img + (size_t)ctx->M * NC * KB * 4096);
+    float *wtab = hn + (size_t)ctx->M * kpad, *negmu = wtab + (size_t)ctx->M * kpad;
+    float *consts = negmu + (size_t)ctx->M * kChunkD * NC;
+    {
+        Timed t_(ctx, HCLAE_T_NORMS);
+        hipLaunchKernelGGL(k_encode_prep, dim3(ctx->M), dim3(kPrepThreads), 0, ctx->stream, C, ctx->K, ctx->D, KB, NC,
+                           img, hn, wtab, negmu, consts, ctx->refine_count);
+        HIP_TRY(ctx, hipGetLastError());
+    }
+    const int64_t ntiles = (N + kTileVec - 1) / kTileVec;
+    Timed t_(ctx, HCLAE_T_ASSIGN);
+    hipLaunchKernelGGL((k_encode_fused<KB, NC>), dim3((unsigned)ntiles), dim3(64 * KB),
+                       (size_t)encode_lds(KB, NC).total, ctx->stream,
+                       X, C, (int)N, ctx->D, ctx->K, ctx->M, img, hn, wtab, negmu, consts, codes, residue, ctx->refine_count, ctx->work);
+    HIP_TRY(ctx, hipGetLastError());
+    return HCLAE_OK;
+}
+
 int enqueue_encode(hclae_ctx *ctx, const float *X, int64_t N, const float *C, uint8_t *codes, float *residue)
 {
     const int D = ctx->D, K = ctx->K;
-    const int64_t n4 = N * (D / 4);
+    switch (encode_fused(ctx, N) ? encode_chunks(ctx) * 16 + ctx->kb : 0) {
+    case 16 + 1: return launch_encode_fused<1, 1>(ctx, X, N, C, codes, residue);
+    case 16 + 2: return launch_encode_fused<2, 1>(ctx, X, N, C, codes, residue);
+    case 16 + 4: return launch_encode_fused<4, 1>(ctx, X, N, C, codes, residue);
+    case 16 + 8: return launch_encode_fused<8, 1>(ctx, X, N, C, codes, residue);
+    case 32 + 1: return launch_encode_fused<1, 2>(ctx, X, N, C, codes, residue);
+    case 32 + 2: return launch_encode_fused<2, 2>(ctx, X, N, C, codes, residue);
+    case 32 + 4: return launch_encode_fused<4, 2>(ctx, X, N, C, codes, residue);
+    case 32 + 8: return launch_encode_fused<8, 2>(ctx, X, N, C, codes, residue);
+    case 64 + 2: return launch_encode_fused<2, 4>(ctx, X, N, C, codes, residue);
+    case 64 + 4: return launch_encode_fused<4, 4>(ctx, X, N, C, codes, residue);
+    case 64 + 8: return launch_encode_fused<8, 4>(ctx, X, N, C, codes, residue);
+    default: break;
+    }
     int rc;
-    hipLaunchKernelGGL(k_copy, dim3(stream_blocks(ctx, n4, kFlatThreads * 4)), dim3(kFlatThreads), 0, ctx->stream,
-                       reinterpret_cast<floatx4 *>(residue), reinterpret_cast<const floatx4 *>(X), n4);
-    HIP_TRY(ctx, hipGetLastError());
     for (int m = 0; m < ctx->M; ++m) {
         const float *Cm = C + (size_t)m * K * D;
+        const float *src = m == 0 ? X : residue;            // the first dictionary's passes read X itself
         if ((rc = launch_norms(ctx, Cm)) != HCLAE_OK) return rc;
-        if ((rc = launch_assign(ctx, m, N, residue, Cm, codes)) != HCLAE_OK) return rc;
-        const int b = launch_heat_cool<-1, false>(ctx, m, N, C, codes, residue, nullptr);
+        if ((rc = launch_assign(ctx, m, N, src, Cm, codes)) != HCLAE_OK) return rc;
+        const int b = launch_heat_cool<-1, false>(ctx, m, N, C, codes, residue, nullptr, false, src);
         if (b < 0) return b;
     }
     return HCLAE_OK;
@@ -707,6 +762,9 @@ int hclae_create(hclae_ctx **out, int64_t N_max, int D, int M, int K, void *hip_
     ctx->nparts = heat_cool_blocks(N_max, D, ctx->cus);
     if (ctx->nparts < kFlatParts) ctx->nparts = kFlatParts;
 
+    const size_t enc_nc = (size_t)encode_chunks(ctx);
+    const size_t encode_bytes = enc_nc == 0 ? 256 : (size_t)M * (enc_nc * ctx->kb * 4096 + sizeof(float) *
+                                (2 * 32 * ctx->kb + kChunkD * enc_nc + kEncodeConsts));
     struct { void **p; size_t bytes; } allocs[] = {
         {(void **)&ctx->hneg, sizeof(float) * 32 * ctx->kb},
         {(void **)&ctx->cb_image, ctx->resident ? 256 : sizeof(float4) * (size_t)ctx->NC * ctx->kb * 8 * kWave},
@@ -714,6 +772,7 @@ int hclae_create(hclae_ctx **out, int64_t N_max, int D, int M, int K, void *hip_
         {(void **)&ctx->refine_count, 256},
         {(void **)&ctx->half_sums, sizeof(float) * 2 * 32 * ctx->kb},
         {(void **)&ctx->half_negmu, sizeof(float) * kChunkD * ctx->NC},
+        {(void **)&ctx->enc_buf, encode_bytes},
         {(void **)&ctx->half_list, sizeof(HalfItem) * (size_t)half_list_entries(N_max, ctx->cus * kAssignWaves)},
         {(void **)&ctx->old_codes, (size_t)N_max},
         {(void **)&ctx->partial, per * ub},
@@ -763,7 +822,7 @@ int hclae_create(hclae_ctx **out, int64_t N_max, int D, int M, int K, void *hip_
 int hclae_destroy(hclae_ctx *ctx)
 {
     if (!ctx) return HCLAE_EINVAL;
-    void *dev[] = {ctx->hneg, ctx->cb_image, ctx->split_norms, ctx->refine_count, ctx->half_list, ctx->half_sums, ctx->half_negmu, ctx->old_codes, ctx->partial, ctx->pcount,
+    void *dev[] = {ctx->hneg, ctx->cb_image, ctx->split_norms, ctx->refine_count, ctx->half_list, ctx->half_sums, ctx->half_negmu, ctx->enc_buf, ctx->old_codes, ctx->partial, ctx->pcount,
                    ctx->nk, ctx->tot_sum, ctx->tot_cnt, ctx->moved_list, ctx->moved_count, ctx->bnd_u, ctx->bnd_l, ctx->drift, ctx->active, ctx->work, ctx->seed_idx, ctx->part_a, ctx->part_b, ctx->part_chg, ctx->rec,
                    ctx->run_sum, ctx->run_cnt, ctx->n0_dev, ctx->pca_rt, ctx->pca_crot, ctx->pca_colpart,
                    ctx->pca_grampart, ctx->pca_mean, ctx->pca_mean32, ctx->pca_cov, ctx->pca_R, ctx->pca_xr,

@@ -46,6 +46,7 @@ __device__ __forceinline__ void block_absmax(float amax, float *scratch, unsigne
 //            as if it had been stored and reloaded, so the result equals the two passes bit for bit.  By-products:
 //            sum ||e_x||^2 (error after stage m = error before stage j), codes of stage m changed since its entry,
 //            and the code column of stage j saved for its own change count.
+// The rows are read from src, which is r itself in place, or the vectors the greedy encoder starts from.
 // part_err[blockIdx.x], part_chg[blockIdx.x] receive this block's partial sums (fixed order); STATS false: no by-products.
 //
 // A thread works on kStreamUnroll rows at a time, one float4 column of each, in steps (row group, column chunk).
@@ -60,7 +61,7 @@ __device__ __forceinline__ void block_absmax(float amax, float *scratch, unsigne
 // a stage whose first assignment does not read every row and so cannot provide it.
 template <int MODE, bool STATS, int DT = 0, bool AMAX = false>
 __global__ __launch_bounds__(kStreamThreads) void k_row_pass(
-    float *__restrict__ r, const uint8_t *__restrict__ codes, const float *__restrict__ Cm, const float *__restrict__ Cj,
+    float *__restrict__ r, const float *src, const uint8_t *__restrict__ codes, const float *__restrict__ Cm, const float *__restrict__ Cj,
     int64_t N, int D_rt, int M, int m, int j_stage, RowGeom g_rt,
     uint8_t *__restrict__ old_codes, double *__restrict__ part_err, long long *__restrict__ part_chg,
     unsigned *__restrict__ absmax_slot = nullptr)
@@ -99,7 +100,7 @@ __global__ __launch_bounds__(kStreamThreads) void k_row_pass(
         for (int u = 0; u < U; ++u) {
             const int64_t n = n0 + (int64_t)u * rows;
             const int64_t nn = n < N ? n : N - 1;
-            v[u] = __builtin_nontemporal_load(reinterpret_cast<const floatx4 *>(r + nn * D) + cc);
+            v[u] = __builtin_nontemporal_load(reinterpret_cast<const floatx4 *>(src + nn * D) + cc);
         }
     };
 
@@ -195,7 +196,7 @@ constexpr int kWideMinD = 768;
 constexpr int kWideRows = 2;
 template <int MODE, bool STATS, bool AMAX = false>
 __global__ __launch_bounds__(kStreamThreads) void k_row_pass_wide(
-    float *__restrict__ r, const uint8_t *__restrict__ codes, const float *__restrict__ Cm, const float *__restrict__ Cj,
+    float *__restrict__ r, const float *src, const uint8_t *__restrict__ codes, const float *__restrict__ Cm, const float *__restrict__ Cj,
     int64_t N, int D, int M, int m, int j_stage,
     uint8_t *__restrict__ old_codes, double *__restrict__ part_err, long long *__restrict__ part_chg,
     unsigned *__restrict__ absmax_slot = nullptr)
@@ -225,7 +226,7 @@ __global__ __launch_bounds__(kStreamThreads) void k_row_pass_wide(
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int c = (group * U + u) * kWave + lane;
-                v[q][u] = __builtin_nontemporal_load(reinterpret_cast<const floatx4 *>(r + nn * D) + (c < d4 ? c : d4 - 1));
+                v[q][u] = __builtin_nontemporal_load(reinterpret_cast<const floatx4 *>(src + nn * D) + (c < d4 ? c : d4 - 1));
             }
         }
     };
@@ -309,23 +310,6 @@ __global__ __launch_bounds__(kStreamThreads) void k_row_pass_wide(
         }
     }
     if (AMAX && MODE >= 0) block_absmax(amax, reinterpret_cast<float *>(red), absmax_slot);
-}
-
-// r <- X (first step of the greedy encoder): four float4 per thread in flight.
-__global__ __launch_bounds__(kFlatThreads) void k_copy(
-    floatx4 *__restrict__ dst, const floatx4 *__restrict__ src, int64_t n4)
-{
-    constexpr int U = 4;
-    const int64_t stride = (int64_t)gridDim.x * kFlatThreads;
-    for (int64_t i = (int64_t)blockIdx.x * kFlatThreads + threadIdx.x; i < n4; i += U * stride) {
-        floatx4 v[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (i + u * stride < n4) v[u] = __builtin_nontemporal_load(src + i + u * stride);
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (i + u * stride < n4) __builtin_nontemporal_store(v[u], dst + i + u * stride);
-    }
 }
 
 // r <- float(X) for descriptors stored as bytes (online chunks), over the flat array of `total` bytes (a multiple of 4): a

@@ -1,0 +1,47 @@
+"""The fused greedy encoder (Eq. 3 with one path) against the same steps taken one by one -- assign, subtract, dictionary by
+dictionary -- bit for bit, at the edges of its tiles, waves and chunks and with ties."""
+import numpy as np
+import pytest
+
+from parity_util import to_dev
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+# K: 1, 2, 4 and 8 waves to a block; D: 1, 2 and 4 chunks (one that rounds up) and rows too long for the fused kernel;
+# N: one vector, the edges of a 32-vector tile, and above the line where K > 128 goes dictionary by dictionary
+@pytest.mark.parametrize("kind", ["plain", "ties"])
+@pytest.mark.parametrize("N,D,M,K", [(1, 4, 1, 1), (31, 16, 4, 16), (33, 64, 3, 32), (65, 100, 2, 20), (95, 60, 3, 33),
+                                     (1000, 128, 4, 64), (777, 200, 2, 50), (513, 68, 3, 65), (600, 128, 8, 128),
+                                     (64, 256, 2, 100), (1, 128, 8, 256), (2050, 128, 8, 256), (300, 36, 5, 200),
+                                     (129, 132, 3, 256), (260, 256, 2, 129), (100, 260, 2, 256), (70, 512, 2, 17),
+                                     (49152 + 33, 16, 2, 140)])
+def test_encode_equals_its_steps(kind, N, D, M, K):
+    from paper_1509_05194_amd import hclae
+    rng = np.random.default_rng(N + D + K)
+    C = rng.standard_normal((M, K, D)).astype(np.float32) / np.float32(3) ** np.arange(M, dtype=np.float32)[:, None, None]
+    X = sum(C[m][rng.integers(0, K, N)] for m in range(M)) + np.float32(0.05) * rng.standard_normal((N, D)).astype(np.float32)
+    if kind == "ties":
+        C[:, K // 2:2 * (K // 2)] = C[:, :K // 2]            # every codeword twice
+        X[::5] = 0.0
+        X[1::9] *= np.float32(1e5)                           # rows beyond the range the dictionaries set
+        C[M - 1] = 0.0                                       # every score ties
+    X = X.astype(np.float32)
+    Xg, Cg = to_dev(X), to_dev(C)
+    ctx = hclae.Context(N, D, M, K)
+    codes = torch.full((N, M), 9, dtype=torch.uint8, device="cuda:0")
+    r = torch.empty_like(Xg)
+    for _ in range(2):
+        ctx.encode(Xg, Cg, codes, r)
+    want, rw = torch.full_like(codes, 9), Xg.clone()
+    for m in range(M):
+        ctx.assign(m, rw, Cg, want)
+        ctx.cool(m, Cg, want, rw)
+    assert torch.equal(codes, want)
+    assert torch.equal(r, rw)
+    ctx.work_counters(reset=True)
+    ctx.encode(Xg, Cg, codes, r)
+    a, v, f = ctx.work_counters()
+    assert (a, v) == (M, M * N) and 0 <= ctx.last_refined() <= f <= v
+    ctx.close()
