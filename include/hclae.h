@@ -213,16 +213,15 @@ int hclae_online_import(hclae_ctx *ctx, const double *run_sum, const int64_t *ru
 
 /* ---- choice of the matrix-core arithmetic of the distance contraction ------------------------- */
 
-#define HCLAE_CONTRACT_F32        0   /* fp32 MFMA (default)                                         */
-#define HCLAE_CONTRACT_SPLIT_BF16 1   /* fp32 operands split into two bf16 terms, three bf16 MFMAs   */
+#define HCLAE_CONTRACT_F32        0
+#define HCLAE_CONTRACT_SPLIT_BF16 1
 
 /*
- * Selects how the multi-path scoring (hclae_beam_step, hclae_encode_beam) forms the scores x'.c - ||c||^2/2.  The
- * nearest-codeword assignments use fp16 matrix cores with bounds measured per vector and codeword in either mode.
- * Whatever the arithmetic, the scores only pre-select candidates within an error margin (fp16 and mode 0: rigorous
- * bounds; mode 1: the dropped terms bounded rigorously, the accumulation of a bf16 MFMA by a measured constant with a
- * fourfold allowance) and the decision is a direct-form one in fp64, so codes, dictionaries and residues do not depend on
- * the mode; only the number of vectors that take the re-check does.
+ * Kept for callers: both modes are accepted and give what they always gave, the same codes, dictionaries and residues.
+ * The scores x'.c - ||c||^2/2 of the nearest-codeword kernels (Sec. 3.1 / 3.2 assignment, Eq. 3) only pre-select
+ * candidates within an error margin, and the decision is a direct-form one in fp64, so no result depends on how they are
+ * formed.  One contraction serves both modes: fp16 matrix cores on centred, scaled operands, whose rounding is bounded
+ * rigorously by norms measured per vector and per codeword.
  */
 int hclae_set_contraction(hclae_ctx *ctx, int mode);
 
@@ -253,7 +252,7 @@ int hclae_set_pruning(hclae_ctx *ctx, int on);
  *   parent / code DEVICE uint8[N][Ln] = l / k.  err_next, parent and code may be NULL.
  * Cm: DEVICE float[K][D].  1 <= Lc <= L <= HCLAE_MAX_L, N * L < 2^31.
  * Decisions are taken on fp64 direct-form errors of the fp32 rows (candidates pre-selected on the
- * fp32 matrix cores with a rigorous rounding margin).
+ * fp16 matrix cores with a rigorous rounding margin).
  */
 int hclae_beam_step(hclae_ctx *ctx, const float *rows, const double *err, const float *Cm,
                     int64_t N, int D, int K, int Lc, int L,
@@ -363,8 +362,8 @@ int hclae_work_counters(hclae_ctx *ctx, int64_t *out, int reset);
 enum {
     HCLAE_T_HEAT = 0,   /* heat pass (Sec. 3.1, x' = e_x + c)                              */
     HCLAE_T_COOL,       /* new-residue pass                                                 */
-    HCLAE_T_ASSIGN,     /* fp32-MFMA distance contraction + argmin                          */
-    HCLAE_T_REFINE,     /* fp64 re-check of near-ties                                       */
+    HCLAE_T_ASSIGN,     /* distance contraction + argmin, near-ties decided                 */
+    HCLAE_T_REFINE,     /* (part of HCLAE_T_ASSIGN: no launches of its own)                 */
     HCLAE_T_ACCUM,      /* centroid sums and counts                                         */
     HCLAE_T_MERGE,      /* merge of the block partials, division, codeword norms            */
     HCLAE_T_NORMS,      /* codeword norms alone                                             */
@@ -372,7 +371,7 @@ enum {
     HCLAE_T_TRANSITION, /* fused stage boundary of hclae_sweep: new residue of m + heat of m+1 */
     HCLAE_T_ROTATE,     /* projection y = R x (Sec. 3.2)                                    */
     HCLAE_T_MOMENTS,    /* mean and covariance of x' (Sec. 3.2)                             */
-    HCLAE_T_BEAM_SCORE, /* multi-path encoding: fp32-MFMA scoring and candidate bitmaps     */
+    HCLAE_T_BEAM_SCORE, /* multi-path encoding: scoring and candidate bitmaps               */
     HCLAE_T_BEAM_EXPAND,/* multi-path encoding: fp64 evaluation, top-L, next beam           */
     HCLAE_T_ACCUM_MOVED,/* centroid sums advanced by the vectors that changed cluster       */
     HCLAE_T_ASSIGN_ACTIVE, /* assignment of the vectors the distance bounds could not settle  */

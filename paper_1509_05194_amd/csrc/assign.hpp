@@ -97,33 +97,6 @@ __device__ __forceinline__ float4 load_row_piece(const float *__restrict__ base,
     return v;
 }
 
-__device__ __forceinline__ void stage_codebook(
-    float4 *lds, const float *__restrict__ Cm, int K, int D, int ld, int kb, int S)
-{
-    const int total = kb * S * kWave;
-    constexpr int U = 8;                                   // gathers in flight per thread
-    for (int e0 = threadIdx.x; e0 < total; e0 += U * blockDim.x) {
-        float4 v[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int e = e0 + u * blockDim.x;
-            const int l = e & 63;
-            const int bs = e >> 6;
-            const int s = bs % S;
-            const int b = bs / S;
-            const int row = 32 * b + (l & 31);
-            const int col = 8 * s + 4 * (l >> 5);
-            v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (e < total) v[u] = load_row_piece(Cm, row, col, K, D, ld);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int e = e0 + u * blockDim.x;
-            if (e < total) lds[e] = v[u];
-        }
-    }
-}
-
 // Loads the 64-dim chunk q of the wave's 32-vector tile into B-operand order:
 // lane (h, r) gets x'[row r][64q + 8s + 4h .. +3] for s = 0..7.
 // PREFIX: only the first `steps` 8-dim steps of the chunk are wanted (the others are not contracted either).
@@ -191,68 +164,6 @@ __device__ __forceinline__ void init_acc(floatx16 (&acc)[KB], const float *hneg_
             acc[b][4 * g + 2] = t.z;
             acc[b][4 * g + 3] = t.w;
         }
-    }
-}
-
-// Codebook in the order the D-chunked kernel stages it: float4 (q * KB * 8 + b * 8 + s) * 64 + l, l = 32 h + r,
-// holds C[32 b + r][64 q + 8 s + 4 h .. + 3] (zero beyond K and D), so that the slice of 64-dim chunk q is one
-// contiguous piece already in MFMA operand order (see stage_codebook).
-__global__ __launch_bounds__(256) void k_codebook_image(
-    const float *__restrict__ Cm, int K, int D, int ld, int kb, int NC, float4 *__restrict__ img)
-{
-    const int total = NC * kb * 8 * kWave;
-    for (int e = blockIdx.x * 256 + threadIdx.x; e < total; e += gridDim.x * 256) {
-        const int l = e & 63;
-        int bs = e >> 6;
-        const int s = bs & 7;
-        bs >>= 3;
-        const int b = bs % kb, q = bs / kb;
-        img[e] = load_row_piece(Cm, 32 * b + (l & 31), kChunkD * q + 8 * s + 4 * (l >> 5), K, D, ld);
-    }
-}
-
-// One 64-dim chunk of the D-chunked kernel: contracts x (the chunk in registers) with the slice in `cur`, and
-// meanwhile brings in what the next chunk needs: k-step s refills x[s] from xnext (the same columns of the
-// next chunk, or of the next tile's first one) as soon as it has used it, and fetches piece s of the next
-// slice (src: this thread's float4 of piece 0; pieces are 8 * 64 float4 apart) at its start and stores it to
-// `nxt` at its end, with the step's MFMAs between the load and its use.
-template <int KB>
-__device__ __forceinline__ void mfma_chunk_refill(
-    floatx16 (&acc)[KB], float4 (&x)[8], const float4 *__restrict__ cur, float4 *__restrict__ nxt,
-    const float4 *__restrict__ src, const float *__restrict__ xnext, int q, int qn, int D, int lane, int wave,
-    float &xsq, float &amax)
-{
-    const int h = lane >> 5;
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-        float4 piece = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (s < KB) piece = src[s * 8 * kWave];
-        float4 a[KB];
-#pragma unroll
-        for (int b = 0; b < KB; ++b) a[b] = cur[(b * 8 + s) * kWave + lane];
-        // columns past D (last chunk only) are zeroed here, at use: the refill itself is unconditional (its
-        // address clamped into the row), so that no branch hides from the compiler which loads are in flight
-        float4 xv = x[s];
-        if (kChunkD * q + 8 * s + 4 * h >= D) xv = make_float4(0.f, 0.f, 0.f, 0.f);
-        x[s] = *reinterpret_cast<const float4 *>(xnext + min(kChunkD * qn + 8 * s + 4 * h, last_piece(D)));
-        xsq = fmaf(xv.x, xv.x, xsq);
-        xsq = fmaf(xv.y, xv.y, xsq);
-        xsq = fmaf(xv.z, xv.z, xsq);
-        xsq = fmaf(xv.w, xv.w, xsq);
-        amax = fmaxf(fmaxf(amax, fabsf(xv.x)), fabsf(xv.y));
-        amax = fmaxf(fmaxf(amax, fabsf(xv.z)), fabsf(xv.w));
-#pragma unroll
-        for (int b = 0; b < KB; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[b].x, xv.x, acc[b], 0, 0, 0);
-#pragma unroll
-        for (int b = 0; b < KB; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[b].y, xv.y, acc[b], 0, 0, 0);
-#pragma unroll
-        for (int b = 0; b < KB; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[b].z, xv.z, acc[b], 0, 0, 0);
-        // the store (and the wait for its load) stays behind three quarters of the step's MFMAs; arithmetic,
-        // MFMAs and LDS reads of the next step may still move across
-        __builtin_amdgcn_sched_barrier(0x10f);
-        if (s < KB) nxt[(s * 8 + wave) * kWave + lane] = piece;
-#pragma unroll
-        for (int b = 0; b < KB; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[b].w, xv.w, acc[b], 0, 0, 0);
     }
 }
 

@@ -2,20 +2,17 @@
 // of the dictionaries seen so far; for the next dictionary score all K * L sums a_l + c(k) by
 // || x - a_l - c(k) ||^2 and keep the L smallest.
 //
-// The beam is stored as residuals r_l = x - a_l (fp32 rows), so a candidate's error is
-// || r_l - c(k) ||^2 = e_l - 2 ( r_l . c(k) - ||c(k)||^2 / 2 ) and scoring a dictionary is the same
-// codewords x vectors contraction as the nearest-codeword assignment, over N * L rows.  Two
-// kernels per dictionary:
-//   k_beam_score_*  fp32 matrix cores; per vector finds a threshold that at least L candidates
-//                   reach and writes, per beam row, the bitmap of codewords that reach it minus
-//                   twice the fp32 rounding bound (so the L best in exact arithmetic are in it);
-//   k_beam_expand   evaluates the listed candidates in fp64 in the direct form, sorts them by
-//                   (error, l, k), keeps the first L and writes their residuals, errors and
-//                   code prefixes.
+// The beam is stored as residuals r_l = x - a_l (fp32 rows), so a candidate's error is || r_l - c(k) ||^2 and scoring a
+// dictionary is the same codewords x vectors contraction as the nearest-codeword assignment, over N * L rows.  Two kernels per
+// dictionary:
+//   k_beam_score_*  fp16 matrix cores with the bounds of assign_half.hpp; per vector finds a value that the lower bounds of
+//                   at least L candidates reach and writes, per beam row, the bitmap of codewords whose upper bound reaches
+//                   it (so the L best in exact arithmetic are in it);
+//   k_beam_expand   evaluates the listed candidates in fp64 in the direct form, sorts them by (error, l, k), keeps the first
+//                   L and writes their residuals, errors and code prefixes.
 // The decision is therefore an fp64 direct-form decision, as in the assignment kernels.
 #pragma once
-#include "assign.hpp"
-#include "assign_split.hpp"
+#include "assign_half.hpp"
 
 namespace hclae {
 
@@ -26,52 +23,53 @@ struct BeamMask {
     uint32_t w[2][4];
 };
 
-// Threshold and bitmaps from a wave's scores.  Lane (h, r) holds the scores g = r_l.c - ||c||^2/2
-// of beam row r of the tile against half of the codewords; a candidate's error is e_l - 2 g, so
-// candidates are ranked by g - e_l / 2 (larger is better).
-//   1. per lane, the maximum of each 16-score accumulator block (8 values, shifted by -e_l/2);
-//   2. Ln rounds of "take the largest block maximum of the vector's group of lanes and strike it
-//      out": the value taken in the last round is reached by at least Ln distinct candidates
-//      (ties struck together only lower it);
-//   3. every score within twice the rounding bound of that value is marked.
-// gamma * (hmax + ||r|| cmax + ||r||^2) bounds the rounding error of a shifted score.
+// Threshold and bitmaps from a wave's upper scores U_k (assign_half.hpp).  Lane (h, r) holds those of beam row r of the tile
+// for half of the codewords.  Half a candidate's squared distance is ||X||^2/2 - S_k, so candidates of one vector are ranked
+// by S_k - ||X||^2/2 of their own row X (larger is better).
+//   1. per lane, the maximum of each 16-score accumulator block, taken down to a lower bound of that candidate's rank
+//      value: less 2 e cmax, h and the rounding of ||X||^2/2;
+//   2. Ln rounds of "take the largest value of the vector's group of lanes and strike it out": the value taken in the last
+//      round is reached by at least Ln distinct candidates (ties struck together only lower it);
+//   3. every candidate whose upper bound reaches that value is marked.
+// slack: rounding of ||X||^2 relative to it.  next[i]: lane that is 2^i rows further round the vector's group of Lc lanes.
+constexpr int kBeamHops = 5;                        // 2^5 >= kBeamMaxL
 template <int KB>
 __device__ __forceinline__ void beam_select(
-    const floatx16 (&acc)[KB], float xsq, float e_l, float gamma, float hmax, float cmax,
-    int lane, int gbase, int Lc, int Ln, bool valid, BeamMask *__restrict__ out)
+    const floatx16 (&acc)[KB], float x2, float xn, float e, const HalfConsts &c, float slack, int K,
+    int lane, const int (&next)[kBeamHops], int hops, int Ln, bool valid, BeamMask *__restrict__ out)
 {
-    const int h = lane >> 5;
     const float ninf = -__builtin_inff();
-    const float shift = 0.5f * e_l;
-    float bm[KB];
+    const float inf = opaque(__builtin_inff());
+    const float half_x2 = 0.5f * x2;
+    float bm[KB], top = ninf;
 #pragma unroll
     for (int b = 0; b < KB; ++b) {
-        float t = acc[b][0];
+        bm[b] = acc[b][0];
 #pragma unroll
-        for (int v = 1; v < 16; ++v) t = fmaxf(t, acc[b][v]);
-        bm[b] = valid ? t - shift : ninf;
+        for (int v = 1; v < 16; ++v) bm[b] = __builtin_amdgcn_fmed3f(bm[b], acc[b][v], inf);   // the larger one, see opaque()
+        top = fmaxf(top, bm[b]);
     }
-    const float x2 = xsq + __shfl_xor(xsq, 32, kWave);
-    const float el = fmaxf(e_l, x2) * 1.00001f;
-    const float bound = valid ? gamma * (hmax + sqrtf(el) * cmax + el) : 0.f;
+    const float round = c.h + 2.4e-7f * (fabsf(top) + xn * c.cmax) + slack * x2 + 1e-36f;
+    const float down = half_x2 + 2.f * e * c.cmax * 1.01f + round;
+    const bool big = !(x2 < kHalfMaxNorm * kHalfMaxNorm && down < 1e37f);     // may not fit fp16: all codewords are candidates
+#pragma unroll
+    for (int b = 0; b < KB; ++b) bm[b] = valid && !big ? bm[b] - down : ninf;
 
     float tau = ninf;
     for (int it = 0; it < Ln; ++it) {
-        float top = bm[0];
+        float g = bm[0];
 #pragma unroll
-        for (int b = 1; b < KB; ++b) top = fmaxf(top, bm[b]);
-        top = fmaxf(top, __shfl_xor(top, 32, kWave));
-        float g = top;
-        for (int j = 0; j < Lc; ++j) g = fmaxf(g, __shfl(top, gbase + j, kWave));
+        for (int b = 1; b < KB; ++b) g = fmaxf(g, bm[b]);
+        g = fmaxf(g, __shfl_xor(g, 32, kWave));
+#pragma unroll
+        for (int i = 0; i < kBeamHops; ++i)
+            if (i < hops) g = fmaxf(g, __shfl(g, next[i], kWave));
         tau = g;
 #pragma unroll
         for (int b = 0; b < KB; ++b) bm[b] = (bm[b] == g) ? ninf : bm[b];
     }
-    float gb = bound;
-    for (int j = 0; j < Lc; ++j) gb = fmaxf(gb, __shfl(bound, gbase + j, kWave));
-    const float thr = (tau - 2.f * gb) + shift;          // back to the lane's unshifted scores
+    const float thr = (tau - round) + half_x2;           // back to the lane's scores
 
-    constexpr int NW = (KB + 1) / 2;
     uint32_t mk[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
     for (int b = 0; b < KB; ++b) {
@@ -81,360 +79,149 @@ __device__ __forceinline__ void beam_select(
             below = __builtin_amdgcn_alignbit(below, __float_as_uint(acc[b][v] - thr), 31);
         mk[b >> 1] |= (~below & 0xffffu) << ((b & 1) * 16);
     }
-    (void)NW;
-    if (valid) *reinterpret_cast<uint4 *>(&out->w[h][0]) = make_uint4(mk[0], mk[1], mk[2], mk[3]);
+    if (big || !(thr > ninf))                            // (bits of codewords beyond K are dropped by the reader)
+        mk[0] = mk[1] = mk[2] = mk[3] = ~0u;
+    (void)K;
+    if (valid) *reinterpret_cast<uint4 *>(&out->w[lane >> 5][0]) = make_uint4(mk[0], mk[1], mk[2], mk[3]);
 }
 
-// Scoring with the whole padded codebook resident in LDS (same staging, operand order and
-// two-register-set streaming as k_assign_resident).  A tile holds V = 32 / Lc whole vectors =
-// V * Lc consecutive beam rows; the remaining columns idle.
+// What the scoring kernels share: tiles of V = 32 / Lc whole vectors = V Lc consecutive beam rows; the remaining columns of
+// the 32 idle.
+struct BeamTile {
+    int rt, hops;                                       // beam rows per tile; doublings that cover a group
+    int next[kBeamHops];
+    __device__ __forceinline__ BeamTile(int lane, int Lc)
+    {
+        const int r = lane & 31;
+        rt = (kTileVec / Lc) * Lc;
+        const int base = r < rt ? (r / Lc) * Lc : 0, at = r < rt ? r - base : 0;
+        hops = 0;
+        while ((1 << hops) < Lc) ++hops;
+#pragma unroll
+        for (int i = 0; i < kBeamHops; ++i) next[i] = (lane & 32) + base + (at + (1 << i)) % Lc;
+    }
+};
+
+// Scoring with the dictionary resident in LDS as fp16: staging, streaming and bounds of k_assign_half.
 template <int KB>
-__global__ __launch_bounds__(kAssignThreads) void k_beam_score_resident(
-    const float *__restrict__ rows, const double *__restrict__ err, const float *__restrict__ Cm,
-    const float *__restrict__ hneg, int64_t N, int Lc, int Ln, int D, int ld, int K, int NC, float gamma,
-    BeamMask *__restrict__ masks)
+__global__ __launch_bounds__(kAssignThreads) void k_beam_score_half(
+    const float *__restrict__ rows, const float *__restrict__ Cm, const float *__restrict__ hneg,
+    int64_t N, int Lc, int Ln, int D, int K, int NC, float slack, BeamMask *__restrict__ masks)
 {
     extern __shared__ float4 smem4[];
-    const int S = 8 * NC;
-    float4 *lds_c = smem4;
-    float *lds_h = reinterpret_cast<float *>(smem4 + KB * S * kWave);
-    const int lane = lane_id();
-    const int wave = threadIdx.x >> 6;
-    const int h = lane >> 5;
-    const int r = lane & 31;
-
-    stage_codebook(lds_c, Cm, K, D, ld, KB, S);
-    for (int k = threadIdx.x; k < 32 * KB; k += blockDim.x) lds_h[k] = hneg[k];
-    __syncthreads();
-    float hmax = 0.f;
-    for (int k = 0; k < K; ++k) hmax = fmaxf(hmax, -lds_h[k]);
-    const float cmax = sqrtf(2.f * hmax) * 1.000001f;
-
-    const int V = kTileVec / Lc;                       // vectors per tile
-    const int RT = V * Lc;                             // beam rows per tile
-    const int gbase = (r < RT) ? (r / Lc) * Lc : 0;
+    char *lds = reinterpret_cast<char *>(smem4);
+    const HalfLds L = half_lds(KB, NC, NC);
+    const int lane = lane_id(), wave = threadIdx.x >> 6, h = lane >> 5, r = lane & 31;
+    const float *lds_h = reinterpret_cast<const float *>(lds + L.hneg);
+    const float *lds_mu = reinterpret_cast<const float *>(lds + L.mu);
+    const BeamTile bt(lane, Lc);
     const int64_t nrows = N * Lc;
-    const int64_t ntiles = (N + V - 1) / V;
-    const int64_t nslots = (int64_t)gridDim.x * 4;
-    const int64_t tstride = 2 * nslots;
+    const int64_t ntiles = (nrows + bt.rt - 1) / bt.rt;
+    const int64_t nslots = (int64_t)gridDim.x * 4, tstride = 2 * nslots;
     const int64_t t0 = (int64_t)blockIdx.x * 4 + (wave & 3) + nslots * (wave >> 2);
-    if (t0 >= ntiles) return;
-    const int64_t my_tiles = (ntiles - t0 + tstride - 1) / tstride;
+    const int64_t my_tiles = t0 < ntiles ? (ntiles - t0 + tstride - 1) / tstride : 0;
     const int64_t G = my_tiles * NC;
-
-    auto row_of = [&](int64_t tile) { return tile * RT + r; };
     auto row_ptr = [&](int64_t tile) {
-        int64_t n = row_of(tile);
-        if (r >= RT || n >= nrows) n = nrows - 1;      // idle columns re-read the last row
-        return rows + n * ld;
+        int64_t n = tile * bt.rt + r;
+        if (r >= bt.rt || n >= nrows) n = nrows - 1;     // idle columns re-read the last row
+        return rows + n * D;
     };
-    auto e_of = [&](int64_t tile) {
-        int64_t n = row_of(tile);
-        if (r >= RT || n >= nrows) n = nrows - 1;
-        return err ? (float)err[n] : 0.f;
-    };
-
-    floatx16 acc[KB];
     float4 xa[8], xb[8];
-    float xsq = 0.f, amax = 0.f, e_l = 0.f;
+    if (G > 0) load_x_chunk(xa, row_ptr(t0), 0, h, D);   // travels while the dictionary is staged
+    const HalfConsts c = stage_half<KB>(lds, L, Cm, hneg, K, D, D, NC);
+    if (G == 0) return;
+    floatx16 acc[KB];
+    float xsq = 0.f, dsq = 0.f, unused = 0.f;
     int64_t tile = t0;
     int q = 0;
-    load_x_chunk(xa, row_ptr(tile), 0, h, D);
-    for (int64_t g = 0; g < G; g += 2) {
-        int64_t tile1 = tile;
-        int q1 = q + 1;
-        if (q1 == NC) { q1 = 0; tile1 = tile + tstride; }
-        if (g + 1 < G) load_x_chunk(xb, row_ptr(tile1), q1, h, D);
-        if (q == 0) { init_acc<KB>(acc, lds_h, h); xsq = 0.f; e_l = e_of(tile); }
-        mfma_chunk<KB>(acc, xa, lds_c, q, S, lane, xsq, amax);
+    init_acc<KB>(acc, lds_h, h);
+    auto step = [&](float4 (&x)[8], float4 (&xn)[8], bool more) {
+        const int q_n = q + 1 == NC ? 0 : q + 1;
+        const int64_t tile_n = q_n ? tile : tile + tstride;
+        if (more) load_x_chunk(xn, row_ptr(tile_n), q_n, h, D);
+        mfma_chunk_half<KB, false, false>(acc, x, lds + L.img, lds_mu, q, lane, c.scale, xsq, dsq, unused, 4);
         if (q == NC - 1) {
-            const int64_t row = row_of(tile);
-            const bool valid = r < RT && row < nrows;
-            beam_select<KB>(acc, xsq, e_l, gamma, hmax, cmax, lane, gbase, Lc, Ln, valid, masks + (valid ? row : 0));
+            float x2, norm;
+            const float e = mfma_bound_half<KB>(acc, reinterpret_cast<const unsigned *>(lds + L.waug), xsq, dsq, c, lane, x2, norm);
+            const int64_t row = tile * bt.rt + r;
+            const bool valid = r < bt.rt && row < nrows;
+            beam_select<KB>(acc, x2, norm, e, c, slack, K, lane, bt.next, bt.hops, Ln, valid, masks + (valid ? row : 0));
+            init_acc<KB>(acc, lds_h, h);
+            xsq = 0.f;
+            dsq = 0.f;
         }
+        tile = tile_n;
+        q = q_n;
+    };
+    for (int64_t g = 0; g < G; g += 2) {
+        step(xa, xb, g + 1 < G);
         if (g + 1 >= G) break;
-        int64_t tile2 = tile1;
-        int q2 = q1 + 1;
-        if (q2 == NC) { q2 = 0; tile2 = tile1 + tstride; }
-        if (g + 2 < G) load_x_chunk(xa, row_ptr(tile2), q2, h, D);
-        if (q1 == 0) { init_acc<KB>(acc, lds_h, h); xsq = 0.f; e_l = e_of(tile1); }
-        mfma_chunk<KB>(acc, xb, lds_c, q1, S, lane, xsq, amax);
-        if (q1 == NC - 1) {
-            const int64_t row = row_of(tile1);
-            const bool valid = r < RT && row < nrows;
-            beam_select<KB>(acc, xsq, e_l, gamma, hmax, cmax, lane, gbase, Lc, Ln, valid, masks + (valid ? row : 0));
-        }
-        tile = tile2;
-        q = q2;
+        step(xb, xa, g + 2 < G);
     }
 }
 
-// The same with the split-bf16 contraction of k_assign_split (operands as two bf16 terms, three bf16
-// MFMAs per 16 dims).  gamma is then the accumulation bound and the bound on the dropped terms enters
-// through the effective codeword norm, exactly as in k_assign_split.
-template <int KB>
-__global__ __launch_bounds__(kAssignThreads) void k_beam_score_split(
-    const float *__restrict__ rows, const double *__restrict__ err, const float *__restrict__ Cm,
-    const float *__restrict__ hneg, const float *__restrict__ split_norms,
-    int64_t N, int Lc, int Ln, int D, int ld, int K, int NC, float gamma,
-    BeamMask *__restrict__ masks)
+// Scoring for dictionaries that do not fit LDS: the slices of k_assign_half_chunked (laid out by k_half_image).
+template <int KB, bool EXACT>
+__global__ __launch_bounds__(kAssignThreads) void k_beam_score_half_chunked(
+    const float *__restrict__ rows, const float *__restrict__ hneg, const char *__restrict__ img, const float *__restrict__ sums,
+    const float *__restrict__ negmu, int64_t N, int Lc, int Ln, int D, int K, int NC, float slack, BeamMask *__restrict__ masks)
 {
     extern __shared__ float4 smem4[];
-    const int T = 4 * NC;                                                // 16-dim steps
-    uint4 *lds_c = reinterpret_cast<uint4 *>(smem4);                     // KB * T * 2 * 64 uint4
-    float *lds_h = reinterpret_cast<float *>(smem4 + (size_t)KB * T * 2 * kWave);
-    const int lane = lane_id();
-    const int wave = threadIdx.x >> 6;
-    const int h = lane >> 5;
-    const int r = lane & 31;
-
-    stage_codebook_split(lds_c, Cm, K, D, ld, KB, T);
-    for (int k = threadIdx.x; k < 32 * KB; k += blockDim.x) lds_h[k] = hneg[k];
-    __syncthreads();
-    float hmax = 0.f;
-    for (int k = 0; k < K; ++k) hmax = fmaxf(hmax, -lds_h[k]);
-    float cmax = sqrtf(2.f * hmax) * 1.000001f;
-    if (wave == 0) {
-        float a = 0.f, b = 0.f;
-        for (int k = lane; k < K; k += kWave) {
-            a = fmaxf(a, split_norms[2 * k]);
-            b = fmaxf(b, split_norms[2 * k + 1]);
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            a = fmaxf(a, __shfl_xor(a, o, kWave));
-            b = fmaxf(b, __shfl_xor(b, o, kWave));
-        }
-        if (lane == 0) { lds_h[32 * KB] = a; lds_h[32 * KB + 1] = b; }
-    }
-    __syncthreads();
-    {   // dropped terms per unit ||r||, folded into the norm the margin multiplies (see k_assign_split)
-        const float clmax = lds_h[32 * KB], dcmax = lds_h[32 * KB + 1];
-        const float split_bound = (0.00390625f * 1.00391f) * clmax + 1.52587890625e-5f * cmax + 1.00002f * dcmax;
-        cmax = (cmax * 1.02f + split_bound / gamma) * 1.0001f;
-    }
-
-    const int V = kTileVec / Lc;                       // vectors per tile
-    const int RT = V * Lc;                             // beam rows per tile
-    const int gbase = (r < RT) ? (r / Lc) * Lc : 0;
+    char *lds = reinterpret_cast<char *>(smem4);
+    const HalfLds L = half_lds(KB, NC, 2);
+    constexpr int SLICE = KB * 4096;
+    const int lane = lane_id(), wave = threadIdx.x >> 6, h = lane >> 5, r = lane & 31;
+    const float *lds_h = reinterpret_cast<const float *>(lds + L.hneg);
+    float *lds_mu = reinterpret_cast<float *>(lds + L.mu);
+    const BeamTile bt(lane, Lc);
     const int64_t nrows = N * Lc;
-    const int64_t ntiles = (N + V - 1) / V;
-    const int64_t nslots = (int64_t)gridDim.x * 4;
-    const int64_t tstride = 2 * nslots;
-    const int64_t t0 = (int64_t)blockIdx.x * 4 + (wave & 3) + nslots * (wave >> 2);
-    if (t0 >= ntiles) return;
-    const int64_t my_tiles = (ntiles - t0 + tstride - 1) / tstride;
-    const int64_t G = my_tiles * NC;
-
-    auto row_of = [&](int64_t tile) { return tile * RT + r; };
-    auto row_ptr = [&](int64_t tile) {
-        int64_t n = row_of(tile);
-        if (r >= RT || n >= nrows) n = nrows - 1;      // idle columns re-read the last row
-        return rows + n * ld;
-    };
-    auto e_of = [&](int64_t tile) {
-        int64_t n = row_of(tile);
-        if (r >= RT || n >= nrows) n = nrows - 1;
-        return err ? (float)err[n] : 0.f;
-    };
-
-    floatx16 acc[KB];
-    float4 xa[8], xb[8];
-    float xsq = 0.f, amax = 0.f, e_l = 0.f;
-    int64_t tile = t0;
-    int q = 0;
-    load_x_chunk_split(xa, row_ptr(tile), 0, h, D);
-    for (int64_t g = 0; g < G; g += 2) {
-        int64_t tile1 = tile;
-        int q1 = q + 1;
-        if (q1 == NC) { q1 = 0; tile1 = tile + tstride; }
-        if (g + 1 < G) load_x_chunk_split(xb, row_ptr(tile1), q1, h, D);
-        if (q == 0) { init_acc<KB>(acc, lds_h, h); xsq = 0.f; e_l = e_of(tile); }
-        mfma_chunk_split<KB>(acc, xa, lds_c, q, T, lane, xsq, amax);
-        if (q == NC - 1) {
-            const int64_t row = row_of(tile);
-            const bool valid = r < RT && row < nrows;
-            beam_select<KB>(acc, xsq, e_l, gamma, hmax, cmax, lane, gbase, Lc, Ln, valid, masks + (valid ? row : 0));
-        }
-        if (g + 1 >= G) break;
-        int64_t tile2 = tile1;
-        int q2 = q1 + 1;
-        if (q2 == NC) { q2 = 0; tile2 = tile1 + tstride; }
-        if (g + 2 < G) load_x_chunk_split(xa, row_ptr(tile2), q2, h, D);
-        if (q1 == 0) { init_acc<KB>(acc, lds_h, h); xsq = 0.f; e_l = e_of(tile1); }
-        mfma_chunk_split<KB>(acc, xb, lds_c, q1, T, lane, xsq, amax);
-        if (q1 == NC - 1) {
-            const int64_t row = row_of(tile1);
-            const bool valid = r < RT && row < nrows;
-            beam_select<KB>(acc, xsq, e_l, gamma, hmax, cmax, lane, gbase, Lc, Ln, valid, masks + (valid ? row : 0));
-        }
-        tile = tile2;
-        q = q2;
-    }
-}
-
-// Scoring for dimensions whose codebook does not fit LDS: as k_assign_chunked, the block walks the D axis in
-// 64-dim slices of the codebook image (k_codebook_image), two LDS buffers alternating, the next slice and the
-// next chunk of the residual rows arriving under the MFMAs (mfma_chunk_refill).
-template <int KB>
-__global__ __launch_bounds__(kAssignThreads) void k_beam_score_chunked(
-    const float *__restrict__ rows, const double *__restrict__ err, const float4 *__restrict__ img,
-    const float *__restrict__ hneg, int64_t N, int Lc, int Ln, int D, int ld, int K, int NC, float gamma,
-    BeamMask *__restrict__ masks)
-{
-    extern __shared__ float4 smem4[];
-    constexpr int CH = KB * 8 * kWave;                              // float4 per slice
-    float4 *buf0 = smem4, *buf1 = smem4 + CH;
-    float *lds_h = reinterpret_cast<float *>(smem4 + 2 * CH);
-    const int lane = lane_id();
-    const int wave = threadIdx.x >> 6;
-    const int h = lane >> 5;
-    const int r = lane & 31;
-
-    for (int k = threadIdx.x; k < 32 * KB; k += blockDim.x) lds_h[k] = hneg[k];
-    const float4 *mine = img + wave * kWave + lane;
-#pragma unroll
-    for (int p = 0; p < KB; ++p) buf0[(p * 8 + wave) * kWave + lane] = mine[p * 8 * kWave];
-    __syncthreads();
-    float hmax = 0.f;
-    for (int k = 0; k < K; ++k) hmax = fmaxf(hmax, -lds_h[k]);
-    const float cmax = sqrtf(2.f * hmax) * 1.000001f;
-
-    const int V = kTileVec / Lc;
-    const int RT = V * Lc;
-    const int gbase = (r < RT) ? (r / Lc) * Lc : 0;
-    const int64_t nrows = N * Lc;
-    const int64_t ntiles = (N + V - 1) / V;
+    const int64_t ntiles = (nrows + bt.rt - 1) / bt.rt;
     const int64_t nbt = (ntiles + kAssignWaves - 1) / kAssignWaves;
     if ((int64_t)blockIdx.x >= nbt) return;
-    // residual row this lane feeds for block tile bt (idle lanes and waves re-read the last row)
-    auto tile_row = [&](int64_t bt, bool &valid) -> int64_t {
-        const int64_t row = (bt * kAssignWaves + wave) * RT + r;
-        valid = r < RT && row < nrows;
+    // beam row this lane feeds for block tile i (idle lanes and waves re-read the last row)
+    auto tile_row = [&](int64_t i, bool &valid) -> int64_t {
+        const int64_t row = (i * kAssignWaves + wave) * bt.rt + r;
+        valid = r < bt.rt && row < nrows;
         return valid ? row : nrows - 1;
     };
-    float amax = 0.f;
     bool valid;
     int64_t row = tile_row(blockIdx.x, valid);
-    const float *xrow = rows + row * ld;
+    const float *xrow = rows + row * D;
     float4 x[8];
 #pragma unroll
     for (int s = 0; s < 8; ++s) x[s] = *reinterpret_cast<const float4 *>(xrow + min(8 * s + 4 * h, last_piece(D)));
+    for (int i = threadIdx.x; i < SLICE / 16; i += kAssignThreads)
+        reinterpret_cast<uint4 *>(lds)[i] = reinterpret_cast<const uint4 *>(img)[i];
+    for (int d = threadIdx.x; d < kChunkD * NC; d += kAssignThreads) lds_mu[d] = negmu[d];
+    const int s = half_shift(hneg, K);
+    const bool holder = (int)threadIdx.x < 32 * KB;
+    const HalfConsts c = half_constants<KB>(lds, L, holder ? sums[2 * threadIdx.x] : 0.f, holder ? sums[2 * threadIdx.x + 1] : 0.f,
+                                            threadIdx.x, holder, K, NC, ldexpf(1.f, s), ldexpf(1.f, -s));
+    floatx16 acc[KB];
+    float unused = 0.f;
     int par = 0;
-    for (int64_t bt = blockIdx.x; bt < nbt; bt += gridDim.x) {
-        bool valid_next = valid;
-        int64_t row_next = row;
-        if (bt + gridDim.x < nbt) row_next = tile_row(bt + gridDim.x, valid_next);
-        const float *xrow_next = rows + row_next * ld;
-        const float e_l = err ? (float)err[row] : 0.f;
-        floatx16 acc[KB];
-        float xsq = 0.f;
+    for (int64_t i = blockIdx.x; i < nbt; i += gridDim.x) {
+        bool valid_n = valid;
+        int64_t row_n = row;
+        if (i + gridDim.x < nbt) row_n = tile_row(i + gridDim.x, valid_n);
+        const float *xrow_n = rows + row_n * D;
+        float xsq = 0.f, dsq = 0.f;
         init_acc<KB>(acc, lds_h, h);
+#pragma unroll 1
         for (int q = 0; q < NC; ++q) {
             const bool last = q + 1 == NC;
             const int qn = last ? 0 : q + 1;
-            mfma_chunk_refill<KB>(acc, x, par ? buf1 : buf0, par ? buf0 : buf1, mine + (size_t)qn * CH,
-                                  last ? xrow_next : xrow, q, qn, D, lane, wave, xsq, amax);
+            mfma_slice_half_refill<KB, false, EXACT>(acc, x, lds + par * SLICE, lds + (par ^ 1) * SLICE, img + (size_t)qn * SLICE,
+                                                     last ? xrow_n : xrow, lds_mu, q, qn, D, lane, c.scale, xsq, dsq, unused);
             __syncthreads();
             par ^= 1;
         }
-        beam_select<KB>(acc, xsq, e_l, gamma, hmax, cmax, lane, gbase, Lc, Ln, valid, masks + (valid ? row : 0));
-        row = row_next;
-        valid = valid_next;
-        xrow = xrow_next;
-    }
-}
-
-// k_beam_score_chunked with the split-bf16 contraction (see k_assign_split_chunked and k_beam_score_split):
-// img = k_codebook_image_split of the codebook in use; gamma is the accumulation bound.
-template <int KB>
-__global__ __launch_bounds__(kAssignThreads) void k_beam_score_split_chunked(
-    const float *__restrict__ rows, const double *__restrict__ err, const uint4 *__restrict__ img,
-    const float *__restrict__ hneg, const float *__restrict__ split_norms,
-    int64_t N, int Lc, int Ln, int D, int ld, int K, int NC, float gamma,
-    BeamMask *__restrict__ masks)
-{
-    extern __shared__ float4 smem4[];
-    constexpr int CH = KB * 8 * kWave;                              // uint4 per slice
-    uint4 *buf0 = reinterpret_cast<uint4 *>(smem4), *buf1 = buf0 + CH;
-    float *lds_h = reinterpret_cast<float *>(smem4 + 2 * CH);
-    const int lane = lane_id();
-    const int wave = threadIdx.x >> 6;
-    const int h = lane >> 5;
-    const int r = lane & 31;
-
-    for (int k = threadIdx.x; k < 32 * KB; k += blockDim.x) lds_h[k] = hneg[k];
-    const uint4 *mine = img + wave * kWave + lane;
-#pragma unroll
-    for (int p = 0; p < KB; ++p) buf0[(p * 8 + wave) * kWave + lane] = mine[p * 8 * kWave];
-    __syncthreads();
-    float hmax = 0.f;
-    for (int k = 0; k < K; ++k) hmax = fmaxf(hmax, -lds_h[k]);
-    float cmax = sqrtf(2.f * hmax) * 1.000001f;
-    if (wave == 0) {
-        float a = 0.f, b = 0.f;
-        for (int k = lane; k < K; k += kWave) {
-            a = fmaxf(a, split_norms[2 * k]);
-            b = fmaxf(b, split_norms[2 * k + 1]);
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            a = fmaxf(a, __shfl_xor(a, o, kWave));
-            b = fmaxf(b, __shfl_xor(b, o, kWave));
-        }
-        if (lane == 0) { lds_h[32 * KB] = a; lds_h[32 * KB + 1] = b; }
-    }
-    __syncthreads();
-    {   // dropped terms per unit ||r||, folded into the norm the margin multiplies (see k_assign_split)
-        const float clmax = lds_h[32 * KB], dcmax = lds_h[32 * KB + 1];
-        const float split_bound = (0.00390625f * 1.00391f) * clmax + 1.52587890625e-5f * cmax + 1.00002f * dcmax;
-        cmax = (cmax * 1.02f + split_bound / gamma) * 1.0001f;
-    }
-
-    const int V = kTileVec / Lc;
-    const int RT = V * Lc;
-    const int gbase = (r < RT) ? (r / Lc) * Lc : 0;
-    const int64_t nrows = N * Lc;
-    const int64_t ntiles = (N + V - 1) / V;
-    const int64_t nbt = (ntiles + kAssignWaves - 1) / kAssignWaves;
-    if ((int64_t)blockIdx.x >= nbt) return;
-    auto tile_row = [&](int64_t bt, bool &valid) -> int64_t {
-        const int64_t row = (bt * kAssignWaves + wave) * RT + r;
-        valid = r < RT && row < nrows;
-        return valid ? row : nrows - 1;
-    };
-    float amax = 0.f;
-    bool valid;
-    int64_t row = tile_row(blockIdx.x, valid);
-    const float *xrow = rows + row * ld;
-    float4 x[8];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        x[2 * t] = *reinterpret_cast<const float4 *>(xrow + min(kSplitStep * t + 8 * h, last_piece(D)));
-        x[2 * t + 1] = *reinterpret_cast<const float4 *>(xrow + min(kSplitStep * t + 8 * h + 4, last_piece(D)));
-    }
-    int par = 0;
-    for (int64_t bt = blockIdx.x; bt < nbt; bt += gridDim.x) {
-        bool valid_next = valid;
-        int64_t row_next = row;
-        if (bt + gridDim.x < nbt) row_next = tile_row(bt + gridDim.x, valid_next);
-        const float *xrow_next = rows + row_next * ld;
-        const float e_l = err ? (float)err[row] : 0.f;
-        floatx16 acc[KB];
-        float xsq = 0.f;
-        init_acc<KB>(acc, lds_h, h);
-        for (int q = 0; q < NC; ++q) {
-            const bool last = q + 1 == NC;
-            const int qn = last ? 0 : q + 1;
-            mfma_chunk_split_refill<KB>(acc, x, par ? buf1 : buf0, par ? buf0 : buf1, mine + (size_t)qn * CH,
-                                        last ? xrow_next : xrow, q, qn, D, lane, wave, xsq, amax);
-            __syncthreads();
-            par ^= 1;
-        }
-        beam_select<KB>(acc, xsq, e_l, gamma, hmax, cmax, lane, gbase, Lc, Ln, valid, masks + (valid ? row : 0));
-        row = row_next;
-        valid = valid_next;
-        xrow = xrow_next;
+        float x2, norm;
+        const float e = mfma_bound_half<KB>(acc, reinterpret_cast<const unsigned *>(lds + L.waug), xsq, dsq, c, lane, x2, norm);
+        beam_select<KB>(acc, x2, norm, e, c, slack, K, lane, bt.next, bt.hops, Ln, valid, masks + (valid ? row : 0));
+        row = row_n;
+        valid = valid_n;
+        xrow = xrow_n;
     }
 }
 

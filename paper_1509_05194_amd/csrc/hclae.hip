@@ -11,7 +11,6 @@
 
 #include "../../include/hclae.h"
 #include "assign.hpp"
-#include "assign_split.hpp"
 #include "assign_half.hpp"
 #include "encode.hpp"
 #include "stream.hpp"
@@ -73,15 +72,12 @@ struct hclae_ctx {
     int D, M, K;
     int kb;                  // 32-codeword blocks of the padded codebook: 1, 2, 4 or 8
     int NC;                  // 64-dim chunks of the padded D
-    bool resident;           // whole padded codebook fits LDS
     int cus;
     hipStream_t stream;
     int device;
     // scratch (device)
     float *hneg;             // [32*kb]
-    float4 *cb_image;        // [NC][kb*8*64] codebook in staging order (k_codebook_image; D-chunked shapes only)
-    float *split_norms;      // [K][2] split constants of the codebook in use (contraction 1)
-    int contraction;         // 0: fp32 MFMA, 1: split-bf16 MFMA
+    char *cb_image;          // [NC][kb*4096] fp16 dictionary slices (k_half_image; dictionaries beyond LDS only)
     unsigned *refine_count;
     HalfItem *half_list;     // undecided vectors of k_assign_half, a stretch per wave
     float *half_sums;        // [32*kb][2] what k_half_image leaves for the constants of k_assign_half_chunked
@@ -355,7 +351,7 @@ int launch_assign_half_chunked(hclae_ctx *ctx, int m, int64_t N, const float *xp
         ctx->attr_done |= attr_set;
     }
     Timed t_(ctx, PRUNE == 2 ? HCLAE_T_ASSIGN_ACTIVE : HCLAE_T_ASSIGN);
-    char *img = reinterpret_cast<char *>(ctx->cb_image);
+    char *img = ctx->cb_image;
     hipLaunchKernelGGL(k_half_image, dim3(8 * KB), dim3(256), 0, ctx->stream, Cm, ctx->hneg, ctx->K, dact, ld, KB, NC,
                        img, ctx->half_sums, ctx->half_negmu);
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kAssignThreads), (size_t)half_lds(KB, NC, 2).total, ctx->stream,
@@ -730,7 +726,6 @@ int hclae_create(hclae_ctx **out, int64_t N_max, int D, int M, int K, void *hip_
     ctx->cooldown_phases = 10;               // I = 10 (Sec. 3.2)
     ctx->kb = K <= 32 ? 1 : K <= 64 ? 2 : K <= 128 ? 4 : 8;
     ctx->NC = (D + kChunkD - 1) / kChunkD;
-    ctx->resident = (size_t)32 * ctx->kb * kChunkD * ctx->NC * sizeof(float) + 4096 <= (size_t)kLdsBudget;
 
     hipError_t e = hipGetDevice(&ctx->device);
     hipDeviceProp_t prop;
@@ -767,8 +762,7 @@ int hclae_create(hclae_ctx **out, int64_t N_max, int D, int M, int K, void *hip_
                                 (2 * 32 * ctx->kb + kChunkD * enc_nc + kEncodeConsts));
     struct { void **p; size_t bytes; } allocs[] = {
         {(void **)&ctx->hneg, sizeof(float) * 32 * ctx->kb},
-        {(void **)&ctx->cb_image, ctx->resident ? 256 : sizeof(float4) * (size_t)ctx->NC * ctx->kb * 8 * kWave},
-        {(void **)&ctx->split_norms, sizeof(float) * 2 * HCLAE_MAX_K},
+        {(void **)&ctx->cb_image, half_resident(ctx, D) ? 256 : (size_t)ctx->NC * ctx->kb * 4096},
         {(void **)&ctx->refine_count, 256},
         {(void **)&ctx->half_sums, sizeof(float) * 2 * 32 * ctx->kb},
         {(void **)&ctx->half_negmu, sizeof(float) * kChunkD * ctx->NC},
@@ -822,7 +816,7 @@ int hclae_create(hclae_ctx **out, int64_t N_max, int D, int M, int K, void *hip_
 int hclae_destroy(hclae_ctx *ctx)
 {
     if (!ctx) return HCLAE_EINVAL;
-    void *dev[] = {ctx->hneg, ctx->cb_image, ctx->split_norms, ctx->refine_count, ctx->half_list, ctx->half_sums, ctx->half_negmu, ctx->enc_buf, ctx->old_codes, ctx->partial, ctx->pcount,
+    void *dev[] = {ctx->hneg, ctx->cb_image, ctx->refine_count, ctx->half_list, ctx->half_sums, ctx->half_negmu, ctx->enc_buf, ctx->old_codes, ctx->partial, ctx->pcount,
                    ctx->nk, ctx->tot_sum, ctx->tot_cnt, ctx->moved_list, ctx->moved_count, ctx->bnd_u, ctx->bnd_l, ctx->drift, ctx->active, ctx->work, ctx->seed_idx, ctx->part_a, ctx->part_b, ctx->part_chg, ctx->rec,
                    ctx->run_sum, ctx->run_cnt, ctx->n0_dev, ctx->pca_rt, ctx->pca_crot, ctx->pca_colpart,
                    ctx->pca_grampart, ctx->pca_mean, ctx->pca_mean32, ctx->pca_cov, ctx->pca_R, ctx->pca_xr,
@@ -1033,8 +1027,7 @@ int hclae_set_contraction(hclae_ctx *ctx, int mode)
     if (!ctx) return HCLAE_EINVAL;
     if (mode != HCLAE_CONTRACT_F32 && mode != HCLAE_CONTRACT_SPLIT_BF16)
         return fail(ctx, HCLAE_EINVAL, "hclae_set_contraction: unknown mode");
-    ctx->contraction = mode;
-    return HCLAE_OK;
+    return HCLAE_OK;                             // one contraction serves both (see hclae.h)
 }
 
 int hclae_set_beam_width(hclae_ctx *ctx, int L)
@@ -1325,84 +1318,42 @@ static int beam_scratch(hclae_ctx *ctx, int64_t cap, int L, bool with_state)
 
 extern "C++" {
 template <int KB>
-static int launch_beam_score_kb(hclae_ctx *ctx, const float *rows, const double *err, const float *Cm,
-                                int64_t N, int Lc, int Ln, BeamMask *masks)
+static int launch_beam_score_kb(hclae_ctx *ctx, const float *rows, const float *Cm, int64_t N, int Lc, int Ln, BeamMask *masks)
 {
     const int D = ctx->D;
     const int NC = ctx->NC;
-    const int dpad = kChunkD * NC;
-    // bound on the rounding error of a shifted score, relative to hmax + ||r|| cmax + ||r||^2:
-    // dpad + 1 accumulation steps of relative size 2^-23, plus the roundings of the norm, the
-    // shift by the beam error, the threshold arithmetic and of the residual rows themselves
-    const float gamma = 1.01f * (float)(dpad + 8) * 1.1920929e-7f;
+    // rounding of ||X||^2 (a chain of D/2 fused multiply-adds per lane) and of the arithmetic of the ranking
+    const float slack = (float)(kChunkD * NC / 2 + 16) * 1.1920929e-7f;
     const int V = kTileVec / Lc;
     const int64_t ntiles = (N + V - 1) / V;
     Timed t_(ctx, HCLAE_T_BEAM_SCORE);
-    if (ctx->resident && ctx->contraction == 1) {
-        const size_t lds = (size_t)KB * 8 * NC * kWave * sizeof(float4) + (32 * KB + 4) * sizeof(float);
+    if (half_resident(ctx, D)) {
         int64_t blocks = (ntiles + 3) / 4;                      // few tiles: one per SIMD before any SIMD gets two
         if (blocks > ctx->cus) blocks = ctx->cus;
         const uint64_t attr_set = 1ull << 9;        // this call site's bit in ctx->attr_done
         if (!(ctx->attr_done & attr_set)) {
-            HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_beam_score_split<KB>),
+            HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_beam_score_half<KB>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget));
             ctx->attr_done |= attr_set;
         }
-        // accumulation bound of the split contraction (see launch_assign_kb) plus the roundings of the shift
-        const float acc_bound = (float)(3 * (dpad / kSplitStep) + 9) * 4.76837158203125e-7f;
-        hipLaunchKernelGGL(k_split_norms, dim3((ctx->K + 3) / 4), dim3(256), 0, ctx->stream, Cm, ctx->K, D, D, ctx->split_norms);
-        hipLaunchKernelGGL((k_beam_score_split<KB>), dim3((unsigned)blocks), dim3(kAssignThreads), lds, ctx->stream,
-                           rows, err, Cm, ctx->hneg, ctx->split_norms, N, Lc, Ln, D, D, ctx->K, NC, acc_bound, masks);
-    } else if (ctx->contraction == 1) {
-        // D-chunked, split-bf16: two slices of 64 dims in LDS, one block per CU
-        const size_t lds = (size_t)2 * KB * 8 * kWave * sizeof(float4) + (32 * KB + 4) * sizeof(float);
-        const int64_t nbt = (ntiles + kAssignWaves - 1) / kAssignWaves;
-        int64_t blocks = nbt < ctx->cus ? nbt : ctx->cus;
-        const uint64_t attr_set = 1ull << 10;        // this call site's bit in ctx->attr_done
-        if (!(ctx->attr_done & attr_set)) {
-            HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_beam_score_split_chunked<KB>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget));
-            ctx->attr_done |= attr_set;
-        }
-        if (NC > ctx->NC || KB != ctx->kb)
-            return fail(ctx, HCLAE_EINVAL, "beam: codebook image too small for this shape");
-        const float acc_bound = (float)(3 * (dpad / kSplitStep) + 9) * 4.76837158203125e-7f;
-        const int img_total = NC * 4 * KB * kWave;
-        hipLaunchKernelGGL(k_split_norms, dim3((ctx->K + 3) / 4), dim3(256), 0, ctx->stream, Cm, ctx->K, D, D, ctx->split_norms);
-        hipLaunchKernelGGL(k_codebook_image_split, dim3((img_total + 255) / 256), dim3(256), 0, ctx->stream,
-                           Cm, ctx->K, D, D, KB, NC, reinterpret_cast<uint4 *>(ctx->cb_image));
-        hipLaunchKernelGGL((k_beam_score_split_chunked<KB>), dim3((unsigned)blocks), dim3(kAssignThreads), lds, ctx->stream,
-                           rows, err, reinterpret_cast<const uint4 *>(ctx->cb_image), ctx->hneg, ctx->split_norms,
-                           N, Lc, Ln, D, D, ctx->K, NC, acc_bound, masks);
-    } else if (ctx->resident) {
-        const size_t lds = (size_t)KB * 8 * NC * kWave * sizeof(float4) + (32 * KB + 4) * sizeof(float);
-        int64_t blocks = (ntiles + 3) / 4;                      // few tiles: one per SIMD before any SIMD gets two
-        if (blocks > ctx->cus) blocks = ctx->cus;
-        const uint64_t attr_set = 1ull << 11;        // this call site's bit in ctx->attr_done
-        if (!(ctx->attr_done & attr_set)) {
-            HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_beam_score_resident<KB>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget));
-            ctx->attr_done |= attr_set;
-        }
-        hipLaunchKernelGGL((k_beam_score_resident<KB>), dim3((unsigned)blocks), dim3(kAssignThreads), lds, ctx->stream,
-                           rows, err, Cm, ctx->hneg, N, Lc, Ln, D, D, ctx->K, NC, gamma, masks);
+        hipLaunchKernelGGL((k_beam_score_half<KB>), dim3((unsigned)blocks), dim3(kAssignThreads), (size_t)half_lds(KB, NC, NC).total,
+                           ctx->stream, rows, Cm, ctx->hneg, N, Lc, Ln, D, ctx->K, NC, slack, masks);
     } else {
-        const size_t lds = (size_t)2 * KB * 8 * kWave * sizeof(float4) + (32 * KB + 4) * sizeof(float);
         const int64_t nbt = (ntiles + kAssignWaves - 1) / kAssignWaves;
-        int64_t blocks = nbt < ctx->cus ? nbt : ctx->cus;
-        const uint64_t attr_set = 1ull << 12;        // this call site's bit in ctx->attr_done
+        const int64_t blocks = nbt < ctx->cus ? nbt : ctx->cus;
+        const bool exact = D % kChunkD == 0;
+        auto kern = exact ? &k_beam_score_half_chunked<KB, true> : &k_beam_score_half_chunked<KB, false>;
+        const uint64_t attr_set = 1ull << 10;       // this call site's bit in ctx->attr_done (D is the ctx's)
         if (!(ctx->attr_done & attr_set)) {
-            HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_beam_score_chunked<KB>),
+            HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget));
             ctx->attr_done |= attr_set;
         }
-        if (NC > ctx->NC || KB != ctx->kb)
-            return fail(ctx, HCLAE_EINVAL, "beam: codebook image too small for this shape");
-        const int img_total = NC * KB * 8 * kWave;
-        hipLaunchKernelGGL(k_codebook_image, dim3((img_total + 255) / 256), dim3(256), 0, ctx->stream,
-                           Cm, ctx->K, D, D, KB, NC, ctx->cb_image);
-        hipLaunchKernelGGL((k_beam_score_chunked<KB>), dim3((unsigned)blocks), dim3(kAssignThreads), lds, ctx->stream,
-                           rows, err, ctx->cb_image, ctx->hneg, N, Lc, Ln, D, D, ctx->K, NC, gamma, masks);
+        char *img = ctx->cb_image;
+        hipLaunchKernelGGL(k_half_image, dim3(8 * KB), dim3(256), 0, ctx->stream, Cm, ctx->hneg, ctx->K, D, D, KB, NC,
+                           img, ctx->half_sums, ctx->half_negmu);
+        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kAssignThreads), (size_t)half_lds(KB, NC, 2).total, ctx->stream,
+                           rows, ctx->hneg, img, ctx->half_sums, ctx->half_negmu, N, Lc, Ln, D, ctx->K, NC, slack, masks);
     }
     HIP_TRY(ctx, hipGetLastError());
     return HCLAE_OK;
@@ -1410,17 +1361,17 @@ static int launch_beam_score_kb(hclae_ctx *ctx, const float *rows, const double 
 }  // extern "C++"
 
 // One dictionary of the beam for N vectors: norms, scoring, exact expansion.  rows_c has stride D.
-static int enqueue_beam_step(hclae_ctx *ctx, const float *rows_c, const double *err_c, const float *Cm,
+static int enqueue_beam_step(hclae_ctx *ctx, const float *rows_c, const float *Cm,
                              int64_t N, int Lc, int Ln, const uint8_t *pre_c, uint8_t *pre_n, int m,
                              float *rows_n, double *err_n, uint8_t *parent, uint8_t *code)
 {
     int rc;
     if ((rc = launch_norms(ctx, Cm)) != HCLAE_OK) return rc;
     switch (ctx->kb) {
-    case 1: rc = launch_beam_score_kb<1>(ctx, rows_c, err_c, Cm, N, Lc, Ln, ctx->beam_mask); break;
-    case 2: rc = launch_beam_score_kb<2>(ctx, rows_c, err_c, Cm, N, Lc, Ln, ctx->beam_mask); break;
-    case 4: rc = launch_beam_score_kb<4>(ctx, rows_c, err_c, Cm, N, Lc, Ln, ctx->beam_mask); break;
-    default: rc = launch_beam_score_kb<8>(ctx, rows_c, err_c, Cm, N, Lc, Ln, ctx->beam_mask); break;
+    case 1: rc = launch_beam_score_kb<1>(ctx, rows_c, Cm, N, Lc, Ln, ctx->beam_mask); break;
+    case 2: rc = launch_beam_score_kb<2>(ctx, rows_c, Cm, N, Lc, Ln, ctx->beam_mask); break;
+    case 4: rc = launch_beam_score_kb<4>(ctx, rows_c, Cm, N, Lc, Ln, ctx->beam_mask); break;
+    default: rc = launch_beam_score_kb<8>(ctx, rows_c, Cm, N, Lc, Ln, ctx->beam_mask); break;
     }
     if (rc != HCLAE_OK) return rc;
     int64_t blocks = N < (int64_t)ctx->cus * 32 ? N : (int64_t)ctx->cus * 32;
@@ -1457,7 +1408,6 @@ static int enqueue_encode_beam(hclae_ctx *ctx, const float *X, int64_t N, const 
     for (int64_t n0 = 0; n0 < N; n0 += cap) {
         const int64_t nb = N - n0 < cap ? N - n0 : cap;
         const float *rows_c = X + n0 * D;
-        const double *err_c = nullptr;
         const uint8_t *pre_c = nullptr;
         int Lc = 1;
         for (int m = 0; m < M; ++m) {
@@ -1466,10 +1416,10 @@ static int enqueue_encode_beam(hclae_ctx *ctx, const float *X, int64_t N, const 
             float *rows_n = last ? residue + n0 * D : ctx->beam_rows[m & 1];
             double *err_n = last ? (err ? err + n0 : nullptr) : ctx->beam_err[m & 1];
             uint8_t *pre_n = last ? codes + n0 * M : ctx->beam_pre[m & 1];
-            rc = enqueue_beam_step(ctx, rows_c, err_c, C + (size_t)m * K * D, nb, Lc, Ln, pre_c, pre_n, m,
+            rc = enqueue_beam_step(ctx, rows_c, C + (size_t)m * K * D, nb, Lc, Ln, pre_c, pre_n, m,
                                    rows_n, err_n, nullptr, nullptr);
             if (rc != HCLAE_OK) return rc;
-            rows_c = rows_n; err_c = err_n; pre_c = pre_n; Lc = Ln;
+            rows_c = rows_n; pre_c = pre_n; Lc = Ln;
         }
     }
     return HCLAE_OK;
@@ -1489,7 +1439,8 @@ int hclae_beam_step(hclae_ctx *ctx, const float *rows, const double *err, const 
     if (misaligned(rows, Cm, rows_next)) return fail(ctx, HCLAE_EINVAL, "hclae_beam_step: float arrays must be 16-byte aligned");
     if (N * (int64_t)L >= ((int64_t)1 << 31)) return fail(ctx, HCLAE_EINVAL, "hclae_beam_step: N * L too large");
     if ((rc = beam_scratch(ctx, N, L, false)) != HCLAE_OK) return rc;
-    return enqueue_beam_step(ctx, rows, err, Cm, N, Lc, beam_next_width(K, Lc, L), nullptr, nullptr, 0,
+    (void)err;                                   // the candidates are ranked from the rows themselves
+    return enqueue_beam_step(ctx, rows, Cm, N, Lc, beam_next_width(K, Lc, L), nullptr, nullptr, 0,
                              rows_next, err_next, parent, code);
 }
 
