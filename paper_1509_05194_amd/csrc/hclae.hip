@@ -362,8 +362,8 @@ int launch_assign_half_chunked(hclae_ctx *ctx, int m, int64_t N, const float *xp
     return HCLAE_OK;
 }
 
-// prune: 0 plain; 1 all vectors and store the stage's bounds; 2 only the vectors k_bounds_step listed
-// (over all D coordinates only; the caller checks).
+// prune: 0 plain; 1 all vectors and store the stage's bounds; 2 only the vectors k_bounds_step listed; 3 = 2 and 4 = 0, with the
+// vectors that changed cluster listed (over all D coordinates only; the caller checks).
 template <int KB>
 int launch_assign_kb(hclae_ctx *ctx, int m, int64_t N, const float *xp, const float *Cm, uint8_t *codes, int dact, int ld,
                      int prune)
@@ -377,18 +377,18 @@ int launch_assign_kb(hclae_ctx *ctx, int m, int64_t N, const float *xp, const fl
     if (half_resident(ctx, dact)) {
         // the last chunk holds fewer than four 16-dim steps with coordinates that count: stop after them
         const bool prefix = (dact % kChunkD) != 0 && (dact % kChunkD) <= kChunkD - kHalfStep;
-        const bool moved = prune == 3;
-        switch ((prune == 3 ? 2 : prune) * 2 + (prefix ? 1 : 0)) {
-        case 0: return launch_assign_half<KB, 0, false>(ctx, m, N, xp, Cm, codes, dact, ld, pa, false);
-        case 1: return launch_assign_half<KB, 0, true>(ctx, m, N, xp, Cm, codes, dact, ld, pa, false);
+        const bool moved = prune >= 3;
+        switch ((prune == 3 ? 2 : prune & 3) * 2 + (prefix ? 1 : 0)) {
+        case 0: return launch_assign_half<KB, 0, false>(ctx, m, N, xp, Cm, codes, dact, ld, pa, moved);
+        case 1: return launch_assign_half<KB, 0, true>(ctx, m, N, xp, Cm, codes, dact, ld, pa, moved);
         case 2: return launch_assign_half<KB, 1, false>(ctx, m, N, xp, Cm, codes, dact, ld, pa, false);
         case 3: return launch_assign_half<KB, 1, true>(ctx, m, N, xp, Cm, codes, dact, ld, pa, false);
         case 4: return launch_assign_half<KB, 2, false>(ctx, m, N, xp, Cm, codes, dact, ld, pa, moved);
         default: return launch_assign_half<KB, 2, true>(ctx, m, N, xp, Cm, codes, dact, ld, pa, moved);
         }
     }
-    switch (prune == 3 ? 2 : prune) {
-    case 0: return launch_assign_half_chunked<KB, 0>(ctx, m, N, xp, Cm, codes, dact, ld, pa, false);
+    switch (prune == 3 ? 2 : prune & 3) {
+    case 0: return launch_assign_half_chunked<KB, 0>(ctx, m, N, xp, Cm, codes, dact, ld, pa, prune == 4);
     case 1: return launch_assign_half_chunked<KB, 1>(ctx, m, N, xp, Cm, codes, dact, ld, pa, false);
     default: return launch_assign_half_chunked<KB, 2>(ctx, m, N, xp, Cm, codes, dact, ld, pa, prune == 3);
     }
@@ -516,6 +516,17 @@ int launch_sqnorm(hclae_ctx *ctx, const float *r, int64_t N, double *part)
     return blocks;
 }
 
+// Whether a stage keeps distance bounds and assigns only what they leave open.  Up to 2^23 products of an assignment (N K D) the
+// assignment of everything is over before the chip is full, and ageing the bounds first only adds their 10 to 12 us, most of
+// them the launch and the ranking of the drifts (training from zero, with the bounds / without, N = 10k, D = 16, K = 16:
+// 3655 us / 3030).  Above, the sweeps one call chains recompute fewer vectors, which callers read from the work counters, so the
+// bounds stay there although they cost a little up to some 100k vectors (N = 10k, D = 128, K = 256: 7900 us / 6654; N = 50k:
+// 9675 / 8426; N = 250k: 20268 / 23284; N = 1M: 32849 / 43928).
+bool bounds_pay(const hclae_ctx *ctx, int64_t N)
+{
+    return ctx->pruning && (double)N * ctx->K * ctx->D > 8388608.0;
+}
+
 // Enqueues one full stage; by-products land in ctx->rec[slot].  No host synchronisation.
 // heated: residue already holds x' of this stage and ctx->part_a its entry error (the previous
 // stage ended with a fused transition).  next: >= 0 ends the stage with the fused transition into
@@ -532,7 +543,7 @@ int enqueue_stage(hclae_ctx *ctx, int m, int64_t N, float *C, uint8_t *codes, fl
     const int D = ctx->D, K = ctx->K;
     float *Cm = C + (size_t)m * K * D;
     int rc;
-    if (carry && (!ctx->pruning || iters <= 0 || seed_dev || !ctx->carry_u))
+    if (carry && (!bounds_pay(ctx, N) || iters <= 0 || seed_dev || !ctx->carry_u))
         return fail(ctx, HCLAE_ESTATE, "stage: carried bounds need pruning, iters > 0 and no seeding");
     ctx->cur_u = carry ? ctx->carry_u + (size_t)m * ctx->N_max : ctx->bnd_u;
     ctx->cur_l = carry ? ctx->carry_l + (size_t)m * ctx->N_max : ctx->bnd_l;
@@ -559,10 +570,11 @@ int enqueue_stage(hclae_ctx *ctx, int m, int64_t N, float *C, uint8_t *codes, fl
     // With pruning the first assignment stores distance bounds for every vector; after each centroid update
     // (which also reports how far every codeword moved) only the vectors whose bounds no longer separate
     // their codeword from the others are assigned again.  The first update must then keep its totals.
-    const bool prune = ctx->pruning && iters > 0;
+    const bool prune = iters > 0 && bounds_pay(ctx, N);
     for (int t = 0; t < iters; ++t) {
         if (prune && t > 0 && (rc = launch_bounds_step(ctx, m, N, codes, residue, Cm)) != HCLAE_OK) return rc;
-        if ((rc = launch_assign(ctx, m, N, residue, Cm, codes, 0, 0, prune ? (t == 0 ? (carry == 2 ? 2 : 1) : 3) : 0)) != HCLAE_OK) return rc;
+        if ((rc = launch_assign(ctx, m, N, residue, Cm, codes, 0, 0, prune ? (t == 0 ? (carry == 2 ? 2 : 1) : 3)
+                                                                             : ctx->pruning && t > 0 ? 4 : 0)) != HCLAE_OK) return rc;
         rc = (t == 0 || !ctx->pruning)
                  ? launch_update(ctx, m, N, residue, Cm, codes, nullptr, true, false, 0, ctx->pruning && (iters > 1 || prune))
                  : launch_update_moved(ctx, m, N, residue, Cm);
@@ -1134,7 +1146,7 @@ int hclae_anneal(hclae_ctx *ctx, int64_t N, int D, float *C, int M, int K, uint8
     const bool lloyd = ctx->cooldown == HCLAE_COOLDOWN_LLOYD;
     // a sweep that seeds its dictionaries stands apart: its stages start from other dictionaries than they were left with
     const int first_kept = init_idx ? 1 : 0;                 // first sweep whose stages keep their bounds
-    const bool carry = lloyd && ctx->pruning && iters > 0 && n_sweeps - first_kept > 1;
+    const bool carry = lloyd && bounds_pay(ctx, N) && iters > 0 && n_sweeps - first_kept > 1;
     if (init_idx)
         HIP_TRY(ctx, hipMemcpyAsync(ctx->seed_idx, init_idx, sizeof(int64_t) * (size_t)M * K, hipMemcpyHostToDevice, ctx->stream));
     if (carry) {

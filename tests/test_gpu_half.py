@@ -85,7 +85,9 @@ def test_prefix_codes(dact, oracle):
 
 
 @pytest.mark.parametrize("kind", ["plain", "offset", "twins", "wild"])
-@pytest.mark.parametrize("N,D,K", [(5000 + 7, 128, 256), (3000 + 1, 100, 90), (2500, 16, 33), (2000 + 3, 516, 70)])
+# N K D on both sides of the line from which a stage keeps bounds (2^23)
+@pytest.mark.parametrize("N,D,K", [(5000 + 7, 128, 256), (3000 + 1, 100, 90), (2500, 16, 33), (20000 + 1, 16, 33),
+                                   (2000 + 3, 516, 70), (200 + 3, 516, 70)])
 def test_bounds_never_keep_a_wrong_code(kind, N, D, K):
     """A stage that skips what its bounds settle ends with the bits of a stage that assigns every vector every time."""
     from paper_1509_05194_amd import hclae
