@@ -493,7 +493,7 @@ int launch_update_moved(hclae_ctx *ctx, int m, int64_t N, const float *xp, float
         Timed t_(ctx, HCLAE_T_ACCUM_MOVED);
         hipLaunchKernelGGL(k_accumulate_moved, dim3((unsigned)nb, (unsigned)windows), dim3(kUpdThreads), upd_lds_bytes(K),
                            ctx->stream, xp, ctx->moved_list, ctx->moved_count, D, K, ctx->refine_count + 1,
-                           ctx->partial, ctx->pcount);
+                           ctx->partial, ctx->pcount, ctx->tot_sum, ctx->tot_cnt);
         HIP_TRY(ctx, hipGetLastError());
     }
     Timed t_(ctx, HCLAE_T_MERGE);

@@ -116,12 +116,22 @@ __device__ __forceinline__ int moved_blocks(unsigned total, int max_blocks)
     return (int)(want < 1u ? 1u : (want > (unsigned)max_blocks ? (unsigned)max_blocks : want));
 }
 
+// A short list goes into the totals themselves, with 64-bit integer atomics (2 D per moved vector): the partial sums cost 128 KB
+// of LDS cleared and flushed per block whatever the list holds.  All updates of a training (8 dictionaries of 256, D = 128, two
+// or three sweeps) through partial sums only / with this line: N = 10k 1.83 ms / 1.23, N = 50k 1.98 / 1.55, N = 250k 3.26 /
+// 2.53, N = 1M 4.90 / 4.67.  A line at 2^19 is no better there (1.24, 1.52, 2.49, 4.67), and where few sums take many
+// additions the atomics queue up: K = 64, D = 32, N = 300k 0.84 ms / 0.93, with 2^19 2.86, with 2^21 5.61.
+// Whether `total` moved vectors of D coordinates are a short list; the merge asks the same.
+constexpr unsigned kMovedDirect = 1u << 17;         // most additions of one sign
+__device__ __forceinline__ bool moved_direct(unsigned total, int D) { return (unsigned long long)total * (unsigned)D <= kMovedDirect; }
+
 // k_accumulate over the moved vectors only: +q into the new cluster, -q out of the old one, counts likewise.
 // Same grid roles, scale, rounding and partial layout as k_accumulate; the first moved_blocks(count)
 // blocks stride over the list, the others leave at once.
 __global__ __launch_bounds__(kUpdThreads) void k_accumulate_moved(
     const float *__restrict__ xp, const unsigned long long *__restrict__ list, const unsigned *__restrict__ count,
-    int D, int K, const unsigned *__restrict__ xmax_bits, long long *__restrict__ partial, int *__restrict__ pcount)
+    int D, int K, const unsigned *__restrict__ xmax_bits, long long *__restrict__ partial, int *__restrict__ pcount,
+    long long *__restrict__ tot_sum, int *__restrict__ tot_cnt)
 {
     extern __shared__ float4 smem4[];
     unsigned long long *acc = reinterpret_cast<unsigned long long *>(smem4);   // [K][64]
@@ -133,6 +143,24 @@ __global__ __launch_bounds__(kUpdThreads) void k_accumulate_moved(
     const bool counting = blockIdx.y == 0;
     const int shift = fixed_point_shift(*xmax_bits);
     const unsigned total = *count;
+    if (moved_direct(total, D)) {
+        unsigned long long *sum = reinterpret_cast<unsigned long long *>(tot_sum);
+        const unsigned waves = gridDim.x * kUpdWaves;
+        for (unsigned e = blockIdx.x + gridDim.x * wave; e < total; e += waves) {   // neighbours on different CUs
+            const unsigned long long ent = list[e];
+            const unsigned n = (unsigned)ent, ko = (unsigned)(ent >> 32) & 255u, kn = (unsigned)(ent >> 40) & 255u;
+            if (live) {
+                const long long q = (long long)(int)__builtin_rintf(ldexpf(xp[(size_t)n * D + d], shift));
+                atomicAdd(sum + (size_t)kn * D + d, (unsigned long long)q);
+                atomicAdd(sum + (size_t)ko * D + d, (unsigned long long)(-q));
+            }
+            if (counting && lane == 0) {
+                atomicAdd(tot_cnt + kn, 1);
+                atomicAdd(tot_cnt + ko, -1);
+            }
+        }
+        return;
+    }
     const int used = moved_blocks(total, (int)gridDim.x);
     if ((int)blockIdx.x >= used) return;
 
@@ -222,7 +250,7 @@ __global__ __launch_bounds__(256) void k_merge(
     if (k == 0 && threadIdx.x == 0) refine_count[0] = 0u;
     // after a pass over the moved vectors only the blocks that pass used hold partials; the list counter is
     // handed back empty (every block reads it before the last one to arrive resets it)
-    if (delta) nblk = moved_blocks(*moved_count, nblk);
+    if (delta) nblk = moved_direct(*moved_count, D) ? 0 : moved_blocks(*moved_count, nblk);
     // moved_count[3]: the list counter of the pruning step that follows (k_bounds_step)
     if (moved_count) {
         __syncthreads();
