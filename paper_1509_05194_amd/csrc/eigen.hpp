@@ -4,23 +4,137 @@
 // on the tridiagonal matrix with every plane rotation applied to the accumulated transformation.  The
 // transformation is kept TRANSPOSED (row i = i-th basis vector), so a rotation works on two contiguous rows and
 // the result already has the axes as rows, which is how the rotation kernels take R.
+//
+// What bounds it is arithmetic, 6 operations per element of Vt and rotation (about 14,000 rotations at D = 128), so the four
+// loops over rows run in blocks of columns that stay in registers and are compiled for each width of the host's vector unit.
+// The rotations of several QR sweeps are queued and applied one block of columns after the other, which keeps the block in
+// the first-level cache.  Every element sees the operations of the plain loops in their order, without contraction to fused
+// multiply-adds: the same bits.  D = 128 (covariance of SIFT-like rows, one core of an EPYC): 1969 us as plain loops,
+// 854 us (1020 with 256-bit vectors).
 #pragma once
 #include <math.h>
 #include <stddef.h>
+#include <string.h>
 #include <algorithm>
 #include <numeric>
 #include <vector>
 
 namespace hclae {
 
+#pragma clang fp contract(off)
+
+// One QR sweep: plane rotations (k, k+1) for k = lo..hi-1, in this order; their (c, s) start at pair `at` of the queue.
+struct EigenSweep {
+    int lo, hi;
+    size_t at;
+};
+
+// W columns of a row-major matrix in registers.
+template <int W>
+struct EigenCols {
+    typedef double vec __attribute__((vector_size(8 * W), aligned(8)));
+    static __attribute__((always_inline)) inline vec get(const double *p) { return *reinterpret_cast<const vec *>(p); }
+    static __attribute__((always_inline)) inline void put(double *p, const vec &v) { *reinterpret_cast<vec *>(p) = v; }
+};
+
+// y[j] = sum_i v[i] B[i][j] for i in ascending order, from zero; columns [j, j + W).
+template <int W>
+__attribute__((always_inline)) inline int eigen_mul(const double *B, int n, int len, const double *v, double *y, int j)
+{
+    using C = EigenCols<W>;
+    for (; j + W <= len; j += W) {
+        typename C::vec s = {};
+        for (int i = 0; i < len; ++i) s += C::get(B + (size_t)i * n + j) * v[i];
+        C::put(y + j, s);
+    }
+    return j;
+}
+
+// B[i][j] -= v[i] p[j] + q[i] x[j]
+__attribute__((always_inline)) inline void eigen_rank2(double *B, int n, int len, const double *x, const double *p)
+{
+    for (int i = 0; i < len; ++i) {
+        double *bi = B + (size_t)i * n;
+        const double vi = x[i], qi = p[i];
+#pragma clang loop vectorize(assume_safety)
+        for (int j = 0; j < len; ++j) bi[j] -= vi * p[j] + qi * x[j];
+    }
+}
+
+// Q[i][j] -= (b v[i]) u[j]
+__attribute__((always_inline)) inline void eigen_rank1(double *Q, int n, int len, double b, const double *v, const double *u)
+{
+    for (int i = 0; i < len; ++i) {
+        double *qi = Q + (size_t)i * n;
+        const double bv = b * v[i];
+#pragma clang loop vectorize(assume_safety)
+        for (int j = 0; j < len; ++j) qi[j] -= bv * u[j];
+    }
+}
+
+// The queued sweeps on columns [j, j + W) of V: row k is finished and row k+1 carried to the next rotation in registers.
+template <int W>
+__attribute__((always_inline)) inline int eigen_rotate(double *V, int n, const EigenSweep *sw, size_t nsw, const double *cs, int j)
+{
+    using C = EigenCols<W>;
+    for (; j + W <= n; j += W)
+        for (size_t q = 0; q < nsw; ++q) {
+            const double *r = cs + 2 * sw[q].at;
+            double *row = V + (size_t)sw[q].lo * n + j;
+            typename C::vec t0 = C::get(row);
+            for (int k = sw[q].lo; k < sw[q].hi; ++k, r += 2, row += n) {
+                const typename C::vec t1 = C::get(row + n);
+                C::put(row, t0 * r[0] - t1 * r[1]);
+                t0 = t0 * r[1] + t1 * r[0];
+            }
+            C::put(row, t0);
+        }
+    return j;
+}
+
+// The four loops for one vector unit.
+#define HCLAE_EIGEN_LOOPS(name, target_)                                                                                  \
+    struct name {                                                                                                         \
+        target_ static void mul(const double *B, int n, int len, const double *v, double *y)                              \
+        {                                                                                                                 \
+            eigen_mul<1>(B, n, len, v, y, eigen_mul<8>(B, n, len, v, y, eigen_mul<32>(B, n, len, v, y, 0)));              \
+        }                                                                                                                 \
+        target_ static void rank2(double *B, int n, int len, const double *x, const double *p)                            \
+        {                                                                                                                 \
+            eigen_rank2(B, n, len, x, p);                                                                                 \
+        }                                                                                                                 \
+        target_ static void rank1(double *Q, int n, int len, double b, const double *v, const double *u)                  \
+        {                                                                                                                 \
+            eigen_rank1(Q, n, len, b, v, u);                                                                              \
+        }                                                                                                                 \
+        target_ static void rotate(double *V, int n, const EigenSweep *sw, size_t nsw, const double *cs)                  \
+        {                                                                                                                 \
+            eigen_rotate<1>(V, n, sw, nsw, cs,                                                                            \
+                            eigen_rotate<8>(V, n, sw, nsw, cs, eigen_rotate<32>(V, n, sw, nsw, cs, 0)));                  \
+        }                                                                                                                 \
+    };
+HCLAE_EIGEN_LOOPS(EigenBase, )
+#if defined(__x86_64__) && !defined(__HIP_DEVICE_COMPILE__)
+HCLAE_EIGEN_LOOPS(EigenAvx2, __attribute__((target("avx2"))))
+HCLAE_EIGEN_LOOPS(EigenAvx512, __attribute__((target("avx512f"))))
+#endif
+#undef HCLAE_EIGEN_LOOPS
+
 // A: n x n symmetric, row-major; destroyed.  On return w[0] >= ... >= w[n-1] are the eigenvalues and row i of
 // Vt (n x n, row-major) is a unit eigenvector of w[i], signed so that its entry of largest magnitude (the
 // first one among equals) is positive.  Returns 0, or -1 when the iteration did not converge (never seen).
-inline int symmetric_eigen(double *A, int n, double *w, double *Vt)
+template <typename Loops>
+inline int symmetric_eigen_with(double *A, int n, double *w, double *Vt)
 {
     if (n <= 0) return 0;
     std::vector<double> d(n), e(n > 1 ? n - 1 : 1, 0.0), beta(n, 0.0), p(n), u(n);
     auto row = [&](int i) { return A + (size_t)i * n; };
+
+    // a matrix that is symmetric to the last bit stays so (both triangles get the same two products), and then a product with
+    // a column is the product with a row: the sums of several rows at once
+    bool exact = true;
+    for (int i = 0; i < n && exact; ++i)
+        for (int j = 0; j < i; ++j) exact = exact && memcmp(row(i) + j, row(j) + i, sizeof(double)) == 0;
 
     // ---- Householder reduction: H_k = I - beta_k v_k v_k^T acts on coordinates k+1..n-1 and clears column k
     // below the sub-diagonal.  v_k is kept in row k of A (columns k+1..), which is no longer needed then.
@@ -44,20 +158,23 @@ inline int symmetric_eigen(double *A, int n, double *w, double *Vt)
         beta[k] = b;
         // trailing block B = A[k+1.., k+1..]:  B <- B - v q^T - q v^T  with  pv = b B v,  q = pv - (b/2)(v.pv) v
         double vp = 0.0;
+        if (exact) {
+            Loops::mul(row(k + 1) + k + 1, n, len, x, u.data());
+        } else {
+            for (int i = 0; i < len; ++i) {
+                const double *bi = row(k + 1 + i) + k + 1;
+                double s = 0.0;
+                for (int j = 0; j < len; ++j) s += bi[j] * x[j];
+                u[i] = s;
+            }
+        }
         for (int i = 0; i < len; ++i) {
-            const double *bi = row(k + 1 + i) + k + 1;
-            double s = 0.0;
-            for (int j = 0; j < len; ++j) s += bi[j] * x[j];
-            p[i] = b * s;
+            p[i] = b * u[i];
             vp += x[i] * p[i];
         }
         const double kc = 0.5 * b * vp;
         for (int i = 0; i < len; ++i) p[i] -= kc * x[i];
-        for (int i = 0; i < len; ++i) {
-            double *bi = row(k + 1 + i) + k + 1;
-            const double vi = x[i], qi = p[i];
-            for (int j = 0; j < len; ++j) bi[j] -= vi * p[j] + qi * x[j];
-        }
+        Loops::rank2(row(k + 1) + k + 1, n, len, x, p.data());
     }
     if (n >= 2) {
         d[n - 2] = row(n - 2)[n - 2];
@@ -73,17 +190,9 @@ inline int symmetric_eigen(double *A, int n, double *w, double *Vt)
         if (beta[k] == 0.0) continue;
         const double *v = row(k) + k + 1;
         const int len = n - k - 1;
-        for (int j = 0; j < len; ++j) u[j] = 0.0;
-        for (int i = 0; i < len; ++i) {
-            const double *qi = Vt + (size_t)(k + 1 + i) * n + k + 1;
-            const double vi = v[i];
-            for (int j = 0; j < len; ++j) u[j] += vi * qi[j];
-        }
-        for (int i = 0; i < len; ++i) {
-            double *qi = Vt + (size_t)(k + 1 + i) * n + k + 1;
-            const double bv = beta[k] * v[i];
-            for (int j = 0; j < len; ++j) qi[j] -= bv * u[j];
-        }
+        double *Q = Vt + (size_t)(k + 1) * n + k + 1;
+        Loops::mul(Q, n, len, v, u.data());
+        Loops::rank1(Q, n, len, beta[k], v, u.data());
     }
     for (int i = 0; i < n; ++i)
         for (int j = i + 1; j < n; ++j) std::swap(Vt[(size_t)i * n + j], Vt[(size_t)j * n + i]);
@@ -91,6 +200,15 @@ inline int symmetric_eigen(double *A, int n, double *w, double *Vt)
     // ---- implicit-shift QR on the tridiagonal matrix (d, e); rotation of the plane (k, k+1) turns rows k, k+1 of Vt
     const double eps = 2.220446049250313e-16;
     int budget = 64 * n;
+    constexpr size_t kQueue = 4096;                                 // rotations applied to Vt in one go, and one sweep more
+    std::vector<EigenSweep> sweeps;
+    std::vector<double> cs(2 * (kQueue + n));
+    size_t queued = 0;
+    auto apply = [&]() {
+        Loops::rotate(Vt, n, sweeps.data(), sweeps.size(), cs.data());
+        sweeps.clear();
+        queued = 0;
+    };
     for (;;) {
         for (int i = 0; i + 1 < n; ++i)
             if (fabs(e[i]) <= eps * (fabs(d[i]) + fabs(d[i + 1]))) e[i] = 0.0;
@@ -105,6 +223,7 @@ inline int symmetric_eigen(double *A, int n, double *w, double *Vt)
         const double den = dd + (dd >= 0.0 ? 1.0 : -1.0) * hypot(dd, off);
         const double mu = d[hi] - (den != 0.0 ? off * off / den : 0.0);
         double x = d[lo] - mu, z = e[lo];
+        sweeps.push_back({lo, hi, queued});
         for (int k = lo; k < hi; ++k) {
             // c, s with [c s; -s c]^T [x; z] = [r; 0]
             const double r = hypot(x, z);
@@ -119,14 +238,13 @@ inline int symmetric_eigen(double *A, int n, double *w, double *Vt)
                 z = -s * e[k + 1];                                  // the bulge at (k, k+2)
                 e[k + 1] = c * e[k + 1];
             }
-            double *rk = Vt + (size_t)k * n, *rk1 = rk + n;
-            for (int j = 0; j < n; ++j) {
-                const double t0 = rk[j], t1 = rk1[j];
-                rk[j] = c * t0 - s * t1;
-                rk1[j] = s * t0 + c * t1;
-            }
+            cs[2 * queued] = c;
+            cs[2 * queued + 1] = s;
+            ++queued;
         }
+        if (queued >= kQueue) apply();
     }
+    apply();
 
     // ---- descending order (equal values keep their order), sign convention
     std::vector<int> order(n);
@@ -145,6 +263,15 @@ inline int symmetric_eigen(double *A, int n, double *w, double *Vt)
     }
     std::copy(tmp.begin(), tmp.end(), Vt);
     return 0;
+}
+
+inline int symmetric_eigen(double *A, int n, double *w, double *Vt)
+{
+#if defined(__x86_64__) && !defined(__HIP_DEVICE_COMPILE__)
+    if (__builtin_cpu_supports("avx512f")) return symmetric_eigen_with<EigenAvx512>(A, n, w, Vt);
+    if (__builtin_cpu_supports("avx2")) return symmetric_eigen_with<EigenAvx2>(A, n, w, Vt);
+#endif
+    return symmetric_eigen_with<EigenBase>(A, n, w, Vt);
 }
 
 }  // namespace hclae
