@@ -1493,34 +1493,37 @@ static int pca_scratch(hclae_ctx *ctx)
     return HCLAE_OK;
 }
 
-// out = x R^T (rows), R given as is; the caller passes the transposed matrix for R^T.
-static int launch_project(hclae_ctx *ctx, const float *x, int64_t N, const float *R, float *out)
+// out = x R^T (rows), R given as is; the caller passes the transposed matrix for R^T.  absmax: null, or a zeroed slot for max |out|.
+// Up to 128 coordinates all of R stays in LDS (64 KB, two blocks per CU) and a block is 128 outputs wide.
+static int launch_project(hclae_ctx *ctx, const float *x, int64_t N, const float *R, float *out, unsigned *absmax = nullptr)
 {
     const int D = ctx->D;
-    const size_t lds = (size_t)8 * 8 * kWave * sizeof(float4);
-    const uint64_t attr_set = 1ull << 13;        // this call site's bit in ctx->attr_done
-    if (!(ctx->attr_done & attr_set)) {
-        HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_project),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget));
-        ctx->attr_done |= attr_set;
-    }
-    const int64_t nbt = (N + kTileVec * kAssignWaves - 1) / (kTileVec * kAssignWaves);
-    const int groups = (D + 255) / 256;
-    int64_t blocks = nbt < 2 * ctx->cus ? nbt : 2 * ctx->cus;
-    Timed t_(ctx, HCLAE_T_ROTATE);
-    hipLaunchKernelGGL(k_project, dim3((unsigned)blocks, (unsigned)groups), dim3(kAssignThreads), lds, ctx->stream,
-                       x, R, N, D, out);
-    HIP_TRY(ctx, hipGetLastError());
-    return HCLAE_OK;
+    auto launch = [&](auto kernel, int KB, int slices, uint64_t attr_set) -> int {
+        if (!(ctx->attr_done & attr_set)) {
+            HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget));
+            ctx->attr_done |= attr_set;
+        }
+        const int64_t nbt = (N + kTileVec * kAssignWaves - 1) / (kTileVec * kAssignWaves);
+        const int64_t blocks = nbt < 2 * ctx->cus ? nbt : 2 * ctx->cus;
+        Timed t_(ctx, HCLAE_T_ROTATE);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks, (unsigned)((D + 32 * KB - 1) / (32 * KB))), dim3(kAssignThreads),
+                           (size_t)slices * KB * 8 * kWave * sizeof(float4), ctx->stream, x, R, N, D, out, absmax);
+        HIP_TRY(ctx, hipGetLastError());
+        return HCLAE_OK;
+    };
+    if (D <= 128) return launch(&k_project<4, true>, 4, (D + kChunkD - 1) / kChunkD, 1ull << 11);
+    return launch(&k_project<8, false>, 8, 1, 1ull << 13);
 }
 
-static int launch_rotate(hclae_ctx *ctx, const float *x, int64_t N, const float *R, int transpose, float *out)
+static int launch_rotate(hclae_ctx *ctx, const float *x, int64_t N, const float *R, int transpose, float *out,
+                         unsigned *absmax = nullptr)
 {
-    if (!transpose) return launch_project(ctx, x, N, R, out);
+    if (!transpose) return launch_project(ctx, x, N, R, out, absmax);
     const int D = ctx->D;
     hipLaunchKernelGGL(k_transpose, dim3((D * D + 255) / 256), dim3(256), 0, ctx->stream, R, D, ctx->pca_rt);
     HIP_TRY(ctx, hipGetLastError());
-    return launch_project(ctx, x, N, ctx->pca_rt, out);
+    return launch_project(ctx, x, N, ctx->pca_rt, out, absmax);
 }
 
 int hclae_rotate(hclae_ctx *ctx, const float *x, int64_t N, int D, const float *R, int transpose, float *out)
@@ -1553,8 +1556,7 @@ static int enqueue_covariance(hclae_ctx *ctx, const float *xp, int64_t N, double
     if (ng > ctx->pca_ngram) ng = ctx->pca_ngram;
     const int64_t rpg = (N + ng - 1) / ng;
     ng = (int)((N + rpg - 1) / rpg);
-    const int tiles = (D + 127) / 128;
-    hipLaunchKernelGGL(k_gram_tile, dim3(ng, tiles, tiles), dim3(512), 0, ctx->stream,
+    hipLaunchKernelGGL(k_gram_tile, dim3(ng, (D + 127) / 128, (D + 63) / 64), dim3(256), 0, ctx->stream,
                        xp, ctx->pca_mean32, N, D, rpg, ctx->pca_grampart);
     HIP_TRY(ctx, hipGetLastError());
     hipLaunchKernelGGL(k_cov_finish, dim3(stream_blocks(ctx, (int64_t)D * D, 256)), dim3(256), 0, ctx->stream,
@@ -1670,17 +1672,11 @@ static int enqueue_stage_pca(hclae_ctx *ctx, int m, int64_t N, float *C, uint8_t
         R = ctx->pca_R;
     }
     // into the PCA space: x^r = R x', C' = R C_m (C[m] holds C' until it is rotated back)
-    if ((rc = launch_rotate(ctx, residue, N, R, 0, xr)) != HCLAE_OK) return rc;
     if ((rc = launch_rotate(ctx, Cm, K, R, 0, ctx->pca_crot)) != HCLAE_OK) return rc;
     HIP_TRY(ctx, hipMemcpyAsync(Cm, ctx->pca_crot, cbytes, hipMemcpyDeviceToDevice, ctx->stream));
-    // max |x^r| over ALL coordinates for the fixed-point centroid sums: a prefix assignment reads only part of a row
     if ((rc = launch_norms(ctx, Cm, dims[0], D, false)) != HCLAE_OK) return rc;    // zeroes the slot
-    {
-        const int64_t n4 = N * (D / 4);
-        hipLaunchKernelGGL(k_absmax, dim3(stream_blocks(ctx, n4, 256 * 4)), dim3(256), 0, ctx->stream,
-                           reinterpret_cast<const float4 *>(xr), n4, ctx->refine_count + 1);
-        HIP_TRY(ctx, hipGetLastError());
-    }
+    // max |x^r| over ALL coordinates for the fixed-point centroid sums: a prefix assignment reads only part of a row
+    if ((rc = launch_rotate(ctx, residue, N, R, 0, xr, ctx->refine_count + 1)) != HCLAE_OK) return rc;
     int iters_run = 0;
     for (int i = 0; i < n_dims; ++i) {
         if (iters_per_dim > 0 && (rc = launch_norms(ctx, Cm, dims[i], D, true)) != HCLAE_OK) return rc;

@@ -7,15 +7,19 @@
 namespace hclae {
 
 // ---------------------------------------------------------------------------------------------
-// out[n][o] = sum_j x[n][j] * R[o][j]  for o in [o0, o0 + 256), i.e. y = R x row by row.
-// Same structure as k_assign_chunked: a block owns tiles of 8 x 32 vectors, walks the D axis in 64-dim
-// chunks restaging that slice of (up to 256 rows of) R in LDS in MFMA operand order, keeps the 256
-// outputs of a vector in accumulators, and stores them instead of taking an argmax.
-// grid: (vector tiles, groups of 256 outputs).
-__global__ __launch_bounds__(kAssignThreads) void k_project(
-    const float *__restrict__ x, const float *__restrict__ R, int64_t N, int D, float *__restrict__ out)
+// out[n][o] = sum_j x[n][j] * R[o][j]  for o in [o0, o0 + 32 KB), i.e. y = R x row by row; absmax (may be null, must start at
+// 0): max |out| is accumulated there, as float bits.
+// A block owns tiles of 8 x 32 vectors and keeps the 32 KB outputs of a vector in accumulators.  Bound by the fp32 matrix
+// cores (2 N D^2 operations against 8 N D bytes), so the block is no wider than R: KB = 4 up to 128 coordinates, where R
+// stays in LDS (RES); beyond, KB = 8 and R passes through LDS in slices of 64 dims, restaged for every tile.  The largest
+// output is taken from the registers that store it instead of in a pass of its own.  N = 300k, D = 128: 102 us at KB = 8
+// with restaging and 111 us for the separate maximum, 115 us as it is.
+// grid: (vector tiles, groups of 32 KB outputs).
+template <int KB, bool RES>
+__global__ __launch_bounds__(kAssignThreads, RES ? 4 : 2) void k_project(
+    const float *__restrict__ x, const float *__restrict__ R, int64_t N, int D, float *__restrict__ out, unsigned *absmax)
 {
-    constexpr int KB = 8, S = 8;
+    constexpr int S = 8;
     extern __shared__ float4 smem4[];
     float4 *lds_c = smem4;
     const int lane = lane_id();
@@ -26,6 +30,22 @@ __global__ __launch_bounds__(kAssignThreads) void k_project(
     const int rows = min(32 * KB, D - o0);                          // live rows of R in this group
     const float *Rg = R + (size_t)o0 * D;
     const int NC = (D + kChunkD - 1) / kChunkD;
+    auto stage = [&](int q, float4 *dst) {
+#pragma unroll
+        for (int i = 0; i < KB * S * kWave / kAssignThreads; ++i) {
+            const int e = i * kAssignThreads + (int)threadIdx.x;
+            const int l = e & 63;
+            const int bs = e >> 6;
+            const int s = bs & 7;
+            const int b = bs >> 3;
+            dst[e] = load_row_piece(Rg, 32 * b + (l & 31), kChunkD * q + 8 * s + 4 * (l >> 5), rows, D, D);
+        }
+    };
+    if (RES) {
+        for (int q = 0; q < NC; ++q) stage(q, lds_c + q * KB * S * kWave);
+        __syncthreads();
+    }
+    float amax = 0.f;
     const int64_t nbt = (N + kTileVec * kAssignWaves - 1) / (kTileVec * kAssignWaves);
     for (int64_t bt = blockIdx.x; bt < nbt; bt += gridDim.x) {
         const int64_t n_raw = (bt * kAssignWaves + wave) * kTileVec + r;
@@ -40,16 +60,12 @@ __global__ __launch_bounds__(kAssignThreads) void k_project(
         float unused_sq = 0.f, unused_max = 0.f;
         for (int q = 0; q < NC; ++q) {
             load_x_chunk(xc, xrow, q, h, D);
-            __syncthreads();
-            for (int e = threadIdx.x; e < KB * S * kWave; e += blockDim.x) {
-                const int l = e & 63;
-                const int bs = e >> 6;
-                const int s = bs & 7;
-                const int b = bs >> 3;
-                lds_c[e] = load_row_piece(Rg, 32 * b + (l & 31), kChunkD * q + 8 * s + 4 * (l >> 5), rows, D, D);
+            if (!RES) {
+                __syncthreads();
+                stage(q, lds_c);
+                __syncthreads();
             }
-            __syncthreads();
-            mfma_chunk<KB>(acc, xc, lds_c, 0, S, lane, unused_sq, unused_max);
+            mfma_chunk<KB>(acc, xc, lds_c + (RES ? q * KB * S * kWave : 0), 0, S, lane, unused_sq, unused_max);
         }
         if (n_raw < N) {
             float *orow = out + n_raw * D + o0;
@@ -58,10 +74,24 @@ __global__ __launch_bounds__(kAssignThreads) void k_project(
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     const int o = 32 * b + 8 * g + 4 * h;           // acc[b][4g..4g+3] are outputs o..o+3
-                    if (o < rows)
-                        *reinterpret_cast<float4 *>(orow + o) =
-                            make_float4(acc[b][4 * g], acc[b][4 * g + 1], acc[b][4 * g + 2], acc[b][4 * g + 3]);
+                    if (o < rows) {
+                        const float4 v = make_float4(acc[b][4 * g], acc[b][4 * g + 1], acc[b][4 * g + 2], acc[b][4 * g + 3]);
+                        *reinterpret_cast<float4 *>(orow + o) = v;
+                        amax = fmaxf(fmaxf(amax, fmaxf(fabsf(v.x), fabsf(v.y))), fmaxf(fabsf(v.z), fabsf(v.w)));
+                    }
                 }
+        }
+    }
+    if (absmax) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, kWave));
+        float *lds_m = reinterpret_cast<float *>(smem4);
+        __syncthreads();                                            // every wave is done with R
+        if (lane == 0) lds_m[wave] = amax;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int w = 1; w < kAssignWaves; ++w) amax = fmaxf(amax, lds_m[w]);
+            atomicMax(absmax, __float_as_uint(amax));
         }
     }
 }
@@ -77,8 +107,9 @@ __global__ __launch_bounds__(256) void k_transpose(const float *__restrict__ src
 
 // ---------------------------------------------------------------------------------------------
 // Column sums of x in fp64: part[blockIdx.x][d] over a contiguous range of rows.  A block is
-// (1 << lcw) float4-column threads by (256 >> lcw) row groups; four rows per thread in flight; the row
-// groups are combined through LDS in ascending order.
+// (1 << lcw) float4-column threads by (256 >> lcw) row groups; the row groups are combined through LDS in ascending order.
+// One pass over x, with about one block per CU for N = 300k: eight rows per thread in flight cover the latency (62 us with
+// four, 36 us now with loads that no branch guards, 154 MB).
 __global__ __launch_bounds__(256) void k_colsum(
     const float *__restrict__ x, int64_t N, int D, int64_t rows_per_block, int lcw, double *__restrict__ part)
 {
@@ -92,15 +123,17 @@ __global__ __launch_bounds__(256) void k_colsum(
         const int c4 = c0 + tx;
         double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
         if (c4 < d4) {
-            for (int64_t n = r0 + ty; n < r1; n += 4 * groups) {
-                float4 v[4];
+            for (int64_t n = r0 + ty; n < r1; n += 8 * groups) {
+                float4 v[8];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
+                for (int u = 0; u < 8; ++u) {
                     const int64_t row = n + (int64_t)u * groups;
-                    v[u] = (row < r1) ? *(reinterpret_cast<const float4 *>(x + row * D) + c4) : make_float4(0.f, 0.f, 0.f, 0.f);
+                    v[u] = *(reinterpret_cast<const float4 *>(x + (row < r1 ? row : r1 - 1) * D) + c4);   // no branch around a load
                 }
 #pragma unroll
-                for (int u = 0; u < 4; ++u) { s0 += (double)v[u].x; s1 += (double)v[u].y; s2 += (double)v[u].z; s3 += (double)v[u].w; }
+                for (int u = 0; u < 8; ++u) if (n + (int64_t)u * groups < r1) {
+                    s0 += (double)v[u].x; s1 += (double)v[u].y; s2 += (double)v[u].z; s3 += (double)v[u].w;
+                }
             }
         }
         comb[threadIdx.x][0] = s0; comb[threadIdx.x][1] = s1; comb[threadIdx.x][2] = s2; comb[threadIdx.x][3] = s3;
@@ -118,20 +151,24 @@ __global__ __launch_bounds__(256) void k_colsum(
     }
 }
 
-// One 128 x 128 tile of the Gram matrix sum_n x_n x_n^T over a contiguous range of rows, fp32 MFMA.
+// One 128 x 64 tile of the Gram matrix sum_n x_n x_n^T over a contiguous range of rows, fp32 MFMA.
 // The contraction index is the row n: A = x[n][i0..], B = x[n][j0..].  Wave w owns 32 rows of the tile
-// (i-block w & 3) and two 32-column blocks (2 (w >> 2), +1).  fp32 accumulation runs over 256 rows at
-// a time and is then added to fp64 sums; the merge across ranges is in fp64 as well.
+// and its two 32-column blocks.  fp32 accumulation runs over 256 rows at a time and is then added to fp64 sums; the merge
+// across ranges is in fp64 as well.
+// Bound by the fp32 matrix cores at one or two waves per SIMD.  A wave holds too many registers for two blocks of 8 waves on
+// a CU, so a grid of a few more than 256 of them took two rounds; blocks of 4 share the CUs (N = 300k, D = 128, 293 ranges:
+// 238 us in blocks of 8, 181 us in blocks of 4;
+// held to the registers of three blocks per CU it spills: 189 us).
 // grid: (row ranges, tiles along i, tiles along j); part: double [range][D][D].
-__global__ __launch_bounds__(512) void k_gram_tile(
+__global__ __launch_bounds__(256) void k_gram_tile(
     const float *__restrict__ x, const float *__restrict__ mean32, int64_t N, int D, int64_t rows_per_block,
     double *__restrict__ part)
 {
     const int lane = lane_id();
     const int wave = threadIdx.x >> 6;
     const int h = lane >> 5, c = lane & 31;
-    const int i0 = blockIdx.y * 128 + 32 * (wave & 3);
-    const int j0 = blockIdx.z * 128 + 64 * (wave >> 2);
+    const int i0 = blockIdx.y * 128 + 32 * wave;
+    const int j0 = blockIdx.z * 64;
     const int64_t r0 = (int64_t)blockIdx.x * rows_per_block;
     const int64_t r1 = (r0 + rows_per_block < N) ? r0 + rows_per_block : N;
     const bool ai = (i0 + c) < D, bj0 = (j0 + c) < D, bj1 = (j0 + 32 + c) < D;
@@ -200,11 +237,13 @@ __global__ __launch_bounds__(512) void k_gram_tile(
 }
 
 // mean[d] = (sum of column partials) / N in fp64 (ascending range order) and its fp32 rounding.
+// A chain of additions on one block: the loads of 16 are in flight together (293 ranges: 62 us one by one, 9 us now).
 __global__ __launch_bounds__(256) void k_mean_finish(
     const double *__restrict__ colpart, int ncol, int64_t N, int D, double *__restrict__ mean, float *__restrict__ mean32)
 {
     for (int d = blockIdx.x * 256 + threadIdx.x; d < D; d += gridDim.x * 256) {
         double s = 0.0;
+#pragma unroll 16
         for (int b = 0; b < ncol; ++b) s += colpart[(size_t)b * D + d];
         s /= (double)N;
         mean[d] = s;
