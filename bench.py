@@ -22,19 +22,15 @@ import time
 
 import numpy as np
 
-PEAK_FP32_MFMA_TFLOPS = 157.3     # MI355X dense fp32 matrix peak
-PEAK_BF16_MFMA_TFLOPS = 2500.0    # MI355X dense bf16 matrix peak
+PEAK_FP16_MFMA_TFLOPS = 2500.0    # MI355X dense fp16 matrix peak: the unit that scores the codewords
 PEAK_HBM_GBS = 8000.0             # MI355X HBM3E peak
 CONVERGED_AFTER = 8                # sweeps before the one `converged_sweep` times
 MANY_SWEEPS = 20                   # annealing sweeps of the hclae_anneal figure
 
-# HBM bytes per N=1M launch of the assign kernel from two rocprofv3 --pmc runs (FETCH_SIZE 250,672.6 KiB
-# x 2.000, WRITE_SIZE 16,135.5 KiB x 1.000; factors from a 512 MB device copy in the same runs), recorded
-# in profiles/da_sweep_sift1m_counters.md: the launches that also store the distance bounds.  Algorithmic
-# bytes are 521e6 (x', codes, bounds).
-ASSIGN_TRAFFIC_BYTES = 5.299e8   # (250672.6 * 2.000 + 16135.5) KiB
-# the same for the D-chunked kernel at N=1M, D=960 (profiles/da_sweep_gist1m_counters.md); algorithmic 3.841e9
-ASSIGN_TRAFFIC_BYTES_GIST = 4.035e9   # (1962277.4 * 2.000 + 16313.4) KiB
+# HBM bytes per launch of the assign kernel over all vectors, from rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE runs recorded in
+# profiles/da_sweep_sift1m_counters.md (FETCH_SIZE x 2.000, WRITE_SIZE x 1.000; factors from a 512 MB device copy).
+ASSIGN_TRAFFIC_BYTES = 5.3e8   # N=1M, D=128: algorithmic 521e6 (x', codes, bounds)
+ASSIGN_TRAFFIC_BYTES_GIST = 4.0e9   # N=1M, D=960: algorithmic 3.849e9
 
 
 class State:
@@ -92,8 +88,7 @@ def sweep_bench(args, torch, hclae, synth, dev, gist, extras):
     qcodes = torch.zeros((Q, M), dtype=torch.uint8, device=dev)
     qres = torch.empty((Q, D), dtype=torch.float32, device=dev)
     ctx = hclae.Context(N, D, M, K)
-    split = args.contraction == "split"
-    ctx.set_contraction(1 if split else 0)
+    ctx.set_contraction(1 if args.contraction == "split" else 0)
     ctx.set_pruning(not args.no_pruning)
     steps, warmup = args.steps, max(args.warmup, 1)
     side_steps = max(1, min(steps, 5))                       # steps of the figures reported beside the headline
@@ -130,10 +125,8 @@ def sweep_bench(args, torch, hclae, synth, dev, gist, extras):
     # launches of the warm-up steps are in the sums too: same kernel on the same state
     assign_ms = a_ms / max(a_n, 1)
     flops = 2.0 * N * K * D                               # algorithmic flops of one assign launch over all N
-    # the split contraction issues three bf16 MFMAs per product: its roofline counts those against the bf16 peak
-    mfma_flops = 3.0 * flops if split else flops
-    peak = PEAK_BF16_MFMA_TFLOPS if split else PEAK_FP32_MFMA_TFLOPS
-    achieved = mfma_flops / (assign_ms * 1e-3) / 1e12
+    peak = PEAK_FP16_MFMA_TFLOPS
+    achieved = flops / (assign_ms * 1e-3) / 1e12
 
     out = {
         "metric": "DA sweep vectors/sec per stage (D=%d,K=256)" % D,
@@ -146,7 +139,7 @@ def sweep_bench(args, torch, hclae, synth, dev, gist, extras):
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "bf16" if split else "f32",
+        "dtype": "f32",
         "data": "synthetic",
         "config": {"workload": "%s-shaped: N=%d, D=%d, M=%d, K=256, T=%d Lloyd iterations per stage; one step = the "
                                "first annealing DA sweep after a sweep from all-zero dictionaries (every step "
@@ -155,20 +148,17 @@ def sweep_bench(args, torch, hclae, synth, dev, gist, extras):
                    "N": N, "D": D, "M": M, "K": K, "iters": T, "queries": Q,
                    "timed_sweep": "first_anneal_sweep",
                    "quant_error_after": E_first},
-        "roofline": {"bound": "mfma", "kernel": ("%s (fp32 MFMA distance contraction + argmin; the launches over "
-                                                 "all N vectors: with the exact shortcuts on, the first assignment "
-                                                 "of each stage, which also stores the distance bounds)"
-                                                 % ("k_assign_chunked<8>" if gist else "k_assign_resident<8>")
-                                                 if not split else
-                                                 "%s (split-bf16 MFMA distance contraction + argmin: three bf16 "
-                                                 "MFMAs per product, 6NKD flop per launch against the bf16 peak)"
-                                                 % ("k_assign_split_chunked<8>" if gist else "k_assign_split<8>")),
+        "roofline": {"bound": "mfma", "kernel": "%s (distance contraction on the fp16 matrix cores with rigorous bounds, "
+                                                 "argmin, and the exact decision of what the bounds leave open; the "
+                                                 "launches over all N vectors: with the exact shortcuts on, the first "
+                                                 "assignment of each stage, which also stores the distance bounds)"
+                                                 % ("k_assign_half_chunked<8>" if gist else "k_assign_half<8>"),
                      "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                      "frac": achieved / peak,
                      "traffic": (ASSIGN_TRAFFIC_BYTES if (N, D, K) == (1_000_000, 128, 256) else
                                  ASSIGN_TRAFFIC_BYTES_GIST if (N, D, K) == (1_000_000, 960, 256) else None)
-                                if not split and not args.no_pruning else None,
-                     "avg_launch_ms": assign_ms, "launches": a_n, "flops_per_launch": mfma_flops},
+                                if not args.no_pruning else None,
+                     "avg_launch_ms": assign_ms, "launches": a_n, "flops_per_launch": flops},
     }
 
     if not args.no_breakdown:
@@ -238,7 +228,7 @@ def sweep_bench(args, torch, hclae, synth, dev, gist, extras):
         share["vectors_recomputed"] = n_vec
         share["vectors_recomputed_vs_unpruned"] = n_vec / float((T + 1) * M * N)
         share["vectors_rechecked_fp64"] = n_refined
-        scale = (3.0 if split else 1.0) * 2.0 * K * D
+        scale = 2.0 * K * D
         if act_ms > 0 and act_vec > 0:
             tf = scale * act_vec / (act_ms * 1e-3) / 1e12
             share["assign_active_TFLOPs"] = tf
@@ -274,7 +264,7 @@ def sweep_bench(args, torch, hclae, synth, dev, gist, extras):
                 gbs = alg_bytes[cls] / (ms / n * 1e-3) / 1e9
                 e.update(achieved_GBs=gbs, frac_hbm=gbs / PEAK_HBM_GBS)
             if cls == "assign":
-                tf = mfma_flops / (ms / n * 1e-3) / 1e12
+                tf = flops / (ms / n * 1e-3) / 1e12
                 e.update(achieved_TFLOPs=tf, frac_mfma=tf / peak)
             kernels[cls] = e
         out["kernels"] = kernels
@@ -296,22 +286,10 @@ def sweep_bench(args, torch, hclae, synth, dev, gist, extras):
             out["unpruned"] = {
                 "value": N * M / ts, "unit": "vectors/s per stage", "ms_per_step": ts * 1e3, "steps": side_steps,
                 "assign_avg_launch_ms": a_ms1,
-                ("assign_frac_fp32_mfma_peak" if not split else "assign_algorithmic_TFLOPs"):
-                    (tf / PEAK_FP32_MFMA_TFLOPS if not split else tf),
+                "assign_frac_mfma": tf / peak,
                 "note": "hclae_set_pruning(0): all (T+1) assignments and all T centroid sums of a stage over all N "
                         "vectors -- work that does not depend on the state; the same sweep from the same state, "
                         "same dictionaries, codes and residues"}
-        if not split:
-            # the same step with the optional split-bf16 contraction (hclae_set_contraction 1): identical results
-            # by construction (same fp64 decisions), another matrix-core arithmetic
-            ts, s_avg = variant(lambda: ctx.set_contraction(1), lambda: ctx.set_contraction(0))
-            out["split_bf16_contraction"] = {
-                "value": N * M / ts, "unit": "vectors/s per stage", "ms_per_step": ts * 1e3, "steps": side_steps,
-                "assign_avg_launch_ms": s_avg,
-                "assign_algorithmic_TFLOPs": flops / (s_avg * 1e-3) / 1e12,
-                "assign_frac_bf16_mfma_peak": 3.0 * flops / (s_avg * 1e-3) / 1e12 / PEAK_BF16_MFMA_TFLOPS,
-                "note": "fp32 operands split into two bf16 terms, three bf16 MFMAs per product, fp32 accumulation; the "
-                        "same sweep from the same state, same codes, dictionaries and residues as the fp32 kernel"}
 
     if extras and not gist:
         out["improved_kmeans_stage"] = pca_stage_bench(torch, hclae, synth, ctx, st, idx, N, D, M, K)
@@ -449,12 +427,9 @@ def beam_bench(args, torch, hclae, synth, dev, steps=None):
         "config": {"workload": "SIFT-shaped: N=%d, D=128, M=%d, K=256; dictionaries from one fresh DA sweep (T=%d); "
                                "one step = multi-path encoding of all N vectors with L=%d" % (N, M, T, L),
                    "quant_error_greedy": e_greedy, "quant_error_multipath": e_beam},
-        "roofline": {"bound": "mfma", "kernel": ("k_beam_score_resident<8> (fp32 MFMA scoring of N*L beam rows)"
-                                                 if args.contraction == "f32" else
-                                                 "k_beam_score_split<8> (split-bf16 MFMA scoring; algorithmic flop "
-                                                 "against the fp32 peak for comparison)"),
-                     "achieved": achieved, "peak": PEAK_FP32_MFMA_TFLOPS, "unit": "TFLOP/s",
-                     "frac": achieved / PEAK_FP32_MFMA_TFLOPS if achieved else None, "traffic": None,
+        "roofline": {"bound": "mfma", "kernel": "k_beam_score_half<8> (scoring of N*L beam rows on the fp16 matrix cores)",
+                     "achieved": achieved, "peak": PEAK_FP16_MFMA_TFLOPS, "unit": "TFLOP/s",
+                     "frac": achieved / PEAK_FP16_MFMA_TFLOPS if achieved else None, "traffic": None,
                      "flops_per_step": flops},
         "kernels": {"beam_score": {"ms_per_step": s_ms / steps, "launches": s_n},
                     "beam_expand": {"ms_per_step": x_ms / steps, "launches": x_n}},
@@ -535,8 +510,8 @@ def online_bench(args, torch, hclae, synth, dev, nchunks=None):
         "h2d_copy_ms_per_chunk": tc * 1e3, "h2d_GBs": N * D / tc / 1e9,
         "compute_only_ms_per_chunk": tk * 1e3,
         "copy_hidden_fraction": min(1.0, max(0.0, 1.0 - (per_chunk - tk) / tc)),
-        "roofline": {"bound": "mfma", "kernel": "k_assign_resident<8>", "achieved": tf, "peak": PEAK_FP32_MFMA_TFLOPS,
-                     "unit": "TFLOP/s", "frac": tf / PEAK_FP32_MFMA_TFLOPS, "traffic": None,
+        "roofline": {"bound": "mfma", "kernel": "k_assign_half<8>", "achieved": tf, "peak": PEAK_FP16_MFMA_TFLOPS,
+                     "unit": "TFLOP/s", "frac": tf / PEAK_FP16_MFMA_TFLOPS, "traffic": None,
                      "avg_launch_ms": a_ms / max(a_n, 1), "launches": a_n},
     }
 
@@ -590,8 +565,7 @@ def main():
                     help="instead of the sweep benchmark: stream CHUNKS uint8 chunks of --n vectors from pinned host "
                          "memory through the online learner (ring of 4 distinct chunks) and report end-to-end vectors/s")
     ap.add_argument("--contraction", choices=["f32", "split"], default="f32",
-                    help="matrix-core arithmetic of the distance contraction: fp32 MFMA, or fp32 operands split into "
-                         "two bf16 terms on the bf16 MFMA (same results; see hclae_set_contraction)")
+                    help="hclae_set_contraction: both modes run the same fp16 pre-selection with exact decisions")
     ap.add_argument("--no-pruning", action="store_true",
                     help="switch off the exact pruning of the Lloyd iterations (hclae_set_pruning 0): every assignment "
                          "and every centroid sum then runs over all vectors; same results")

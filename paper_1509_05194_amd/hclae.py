@@ -230,7 +230,7 @@ class Context:
         self._chk(lib().hclae_set_cooldown(self._h, 1 if improved else 0, phases))
 
     def set_contraction(self, mode):
-        """0: fp32 MFMA; 1: split-bf16 MFMA (same results, see hclae_set_contraction)."""
+        """0 or 1: both modes run the same contraction (see hclae_set_contraction)."""
         self._chk(lib().hclae_set_contraction(self._h, mode))
 
     def set_beam_width(self, L):
