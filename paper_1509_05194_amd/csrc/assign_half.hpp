@@ -46,8 +46,16 @@ struct HalfItem {
 };
 
 // Every wave lists its undecided vectors in a stretch of its own of one array in global memory, 32 per tile of its share;
-// entries the array needs for launches over at most N vectors with `waves` waves.
-__host__ __device__ constexpr int64_t half_list_entries(int64_t N, int waves) { return N + (int64_t)waves * 2 * kTileVec; }
+// entries the array needs for launches over at most N vectors with at most `waves` waves: a wave's share is rounded up to whole
+// tiles, ceil(N / 32 / waves) of them, which leaves less than a tile per wave unused.
+__host__ __device__ constexpr int64_t half_list_entries(int64_t N, int64_t waves) { return N + (waves + 1) * kTileVec; }
+// Blocks of k_assign_half over N vectors: with few tiles one per SIMD before any SIMD gets two.  k_assign_half_chunked, whose blocks
+// take eight tiles at once, never has more.
+__host__ __device__ constexpr int64_t half_blocks(int64_t N, int cus)
+{
+    const int64_t blocks = ((N + kTileVec - 1) / kTileVec + 3) / 4;
+    return blocks < cus ? blocks : cus;
+}
 
 // LDS of the kernels: the fp16 dictionary (or two slices of it), then per-codeword constants, mu, and the waves' buffers.
 struct HalfLds {

@@ -315,9 +315,7 @@ int launch_assign_half(hclae_ctx *ctx, int m, int64_t N, const float *xp, const 
                        const PruneArgs &pa, bool want_moved)
 {
     const int NC = (dact + kChunkD - 1) / kChunkD;
-    const int64_t ntiles = (N + kTileVec - 1) / kTileVec;
-    int64_t blocks = (ntiles + 3) / 4;                      // few tiles: one per SIMD before any SIMD gets two
-    if (blocks > ctx->cus) blocks = ctx->cus;
+    const int64_t blocks = half_blocks(N, ctx->cus);
     auto kern = &k_assign_half<KB, PRUNE, PREFIX>;
     const uint64_t attr_set = 1ull << (16 + 2 * PRUNE + (PREFIX ? 1 : 0));   // this instance's bit in ctx->attr_done
     if (!(ctx->attr_done & attr_set)) {
@@ -779,7 +777,7 @@ int hclae_create(hclae_ctx **out, int64_t N_max, int D, int M, int K, void *hip_
         {(void **)&ctx->half_sums, sizeof(float) * 2 * 32 * ctx->kb},
         {(void **)&ctx->half_negmu, sizeof(float) * kChunkD * ctx->NC},
         {(void **)&ctx->enc_buf, encode_bytes},
-        {(void **)&ctx->half_list, sizeof(HalfItem) * (size_t)half_list_entries(N_max, ctx->cus * kAssignWaves)},
+        {(void **)&ctx->half_list, sizeof(HalfItem) * (size_t)half_list_entries(N_max, half_blocks(N_max, ctx->cus) * kAssignWaves)},
         {(void **)&ctx->old_codes, (size_t)N_max},
         {(void **)&ctx->partial, per * ub},
         {(void **)&ctx->pcount, sizeof(int) * (size_t)K * ub},
