@@ -9,7 +9,8 @@
 // loops over rows run in blocks of columns that stay in registers and are compiled for each width of the host's vector unit.
 // The rotations of several QR sweeps are queued and applied one block of columns after the other, which keeps the block in
 // the first-level cache.  Every element sees the operations of the plain loops in their order, without contraction to fused
-// multiply-adds: the same bits.  D = 128 (covariance of SIFT-like rows, one core of an EPYC): 1969 us as plain loops,
+// multiply-adds: the same bits.  (The pragma for that stands in each function: at file scope it would hold for the rest of the
+// translation unit, device kernels included.)  D = 128 (covariance of SIFT-like rows, one core of an EPYC): 1969 us as plain loops,
 // 854 us (1020 with 256-bit vectors).
 #pragma once
 #include <math.h>
@@ -20,8 +21,6 @@
 #include <vector>
 
 namespace hclae {
-
-#pragma clang fp contract(off)
 
 // One QR sweep: plane rotations (k, k+1) for k = lo..hi-1, in this order; their (c, s) start at pair `at` of the queue.
 struct EigenSweep {
@@ -41,6 +40,7 @@ struct EigenCols {
 template <int W>
 __attribute__((always_inline)) inline int eigen_mul(const double *B, int n, int len, const double *v, double *y, int j)
 {
+#pragma clang fp contract(off)
     using C = EigenCols<W>;
     for (; j + W <= len; j += W) {
         typename C::vec s = {};
@@ -53,6 +53,7 @@ __attribute__((always_inline)) inline int eigen_mul(const double *B, int n, int 
 // B[i][j] -= v[i] p[j] + q[i] x[j]
 __attribute__((always_inline)) inline void eigen_rank2(double *B, int n, int len, const double *x, const double *p)
 {
+#pragma clang fp contract(off)
     for (int i = 0; i < len; ++i) {
         double *bi = B + (size_t)i * n;
         const double vi = x[i], qi = p[i];
@@ -64,6 +65,7 @@ __attribute__((always_inline)) inline void eigen_rank2(double *B, int n, int len
 // Q[i][j] -= (b v[i]) u[j]
 __attribute__((always_inline)) inline void eigen_rank1(double *Q, int n, int len, double b, const double *v, const double *u)
 {
+#pragma clang fp contract(off)
     for (int i = 0; i < len; ++i) {
         double *qi = Q + (size_t)i * n;
         const double bv = b * v[i];
@@ -76,6 +78,7 @@ __attribute__((always_inline)) inline void eigen_rank1(double *Q, int n, int len
 template <int W>
 __attribute__((always_inline)) inline int eigen_rotate(double *V, int n, const EigenSweep *sw, size_t nsw, const double *cs, int j)
 {
+#pragma clang fp contract(off)
     using C = EigenCols<W>;
     for (; j + W <= n; j += W)
         for (size_t q = 0; q < nsw; ++q) {
@@ -126,6 +129,7 @@ HCLAE_EIGEN_LOOPS(EigenAvx512, __attribute__((target("avx512f"))))
 template <typename Loops>
 inline int symmetric_eigen_with(double *A, int n, double *w, double *Vt)
 {
+#pragma clang fp contract(off)
     if (n <= 0) return 0;
     std::vector<double> d(n), e(n > 1 ? n - 1 : 1, 0.0), beta(n, 0.0), p(n), u(n);
     auto row = [&](int i) { return A + (size_t)i * n; };
