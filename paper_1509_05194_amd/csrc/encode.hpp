@@ -19,6 +19,11 @@ namespace hclae {
 constexpr int kPrepThreads = 1024;
 constexpr int kEncodeConsts = 8;                    // floats per dictionary: scale, h, rho, acc, cmax
 
+// Tiles of N < 2^31 vectors, and the blocks that take them: one each up to 2^20, which stride beyond (a launch holds less than
+// 2^32 threads, and a block has up to 512).
+__host__ __device__ constexpr int64_t encode_tiles(int64_t N) { return (N + kTileVec - 1) / kTileVec; }
+__host__ __device__ constexpr int64_t encode_blocks(int64_t N) { return encode_tiles(N) < (1 << 20) ? encode_tiles(N) : (1 << 20); }
+
 // One block per dictionary: fp16 image in the order of half_slot, k-step by k-step; -||C||^2/2 and w per codeword; -mu; the
 // constants (half_constants has the reasons).  Also clears the re-check counter.
 __global__ __launch_bounds__(kPrepThreads) void k_encode_prep(
@@ -253,7 +258,7 @@ __global__ __launch_bounds__(64 * KB, 2) void k_encode_fused(
         wl = wtab[(size_t)m * 32 * KB + 32 * wave + r];
         mu = reinterpret_cast<const float4 *>(negmu + (size_t)m * kChunkD * NC)[p];
     };
-    const int ntiles = (N + kTileVec - 1) / kTileVec;
+    const int ntiles = (int)encode_tiles(N);
     fetch(0);
     for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
         const int n0 = tile * kTileVec;

@@ -659,9 +659,8 @@ int launch_encode_fused(hclae_ctx *ctx, const float *X, int64_t N, const float *
                            img, hn, wtab, negmu, consts, ctx->refine_count);
         HIP_TRY(ctx, hipGetLastError());
     }
-    const int64_t ntiles = (N + kTileVec - 1) / kTileVec;
     Timed t_(ctx, HCLAE_T_ASSIGN);
-    hipLaunchKernelGGL((k_encode_fused<KB, NC>), dim3((unsigned)ntiles), dim3(64 * KB),
+    hipLaunchKernelGGL((k_encode_fused<KB, NC>), dim3((unsigned)encode_blocks(N)), dim3(64 * KB),
                        (size_t)encode_lds(KB, NC).total, ctx->stream,
                        X, C, (int)N, ctx->D, ctx->K, ctx->M, img, hn, wtab, negmu, consts, codes, residue, ctx->refine_count, ctx->work);
     HIP_TRY(ctx, hipGetLastError());

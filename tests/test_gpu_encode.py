@@ -45,3 +45,23 @@ def test_encode_equals_its_steps(kind, N, D, M, K):
     a, v, f = ctx.work_counters()
     assert (a, v) == (M, M * N) and 0 <= ctx.last_refined() <= f <= v
     ctx.close()
+
+
+def test_encode_with_more_tiles_than_blocks():
+    """From 2^20 tiles of 32 vectors a block takes several of them."""
+    from paper_1509_05194_amd import hclae
+    N, D, M, K = (1 << 25) + 32 * 3 + 5, 4, 2, 16
+    g = torch.Generator(device="cuda").manual_seed(3)
+    X = torch.randn((N, D), generator=g, device="cuda")
+    C = torch.randn((M, K, D), generator=g, device="cuda")
+    ctx = hclae.Context(N, D, M, K)
+    codes = torch.full((N, M), 9, dtype=torch.uint8, device="cuda:0")
+    r = torch.full_like(X, 9.0)
+    ctx.encode(X, C, codes, r)
+    want, rw = torch.full_like(codes, 9), X.clone()
+    for m in range(M):
+        ctx.assign(m, rw, C, want)
+        ctx.cool(m, C, want, rw)
+    assert torch.equal(codes, want)
+    assert torch.equal(r, rw)
+    ctx.close()
