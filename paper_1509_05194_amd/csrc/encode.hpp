@@ -5,7 +5,8 @@
 // vectors pay for nothing but launches that way (D = 128, M = 8: 158 us for 64 vectors, 202 us for 10k).  Here a row is read
 // and written once, and the two launches are k_encode_prep, which lays out the fp16 dictionaries, and k_encode_fused: 51 us
 // and 90 us.  What bounds it is the chain of a dictionary's steps (round, contract, decide, subtract, with two or four
-// barriers): about 4.5 us each, eight waves waiting for each other, which is why large calls do not come here (encode_fused()).
+// barriers): about 4.5 us each, eight waves waiting for each other, which is why large calls with many codewords do not come
+// here (encode_fused()).
 //
 // Wave b of the block keeps codewords 32 b .. 32 b + 31 of the running dictionary as MFMA operands in registers (its next
 // operands travel while the vectors are decided); the 32 rows are rounded to fp16 once by all threads and shared through

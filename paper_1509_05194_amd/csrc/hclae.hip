@@ -635,13 +635,36 @@ int encode_chunks(const hclae_ctx *ctx)
     return nc <= 4 && 8 * nc <= 16 * ctx->kb ? nc : 0;
 }
 
-// Which encoder: eight waves that decide 32 vectors in lockstep leave a CU waiting, so for more than 128 codewords the fused
-// encoder is the better one only while a CU has few tiles (K = 256, D = 128, M = 8: 51 us against 158 for 64 vectors, 90 / 202
-// for 10k, 216 / 277 for 40k, 409 / 368 for 80k; the lines cross between 40k and 80k at D = 64 and 256 too).  With fewer
-// waves to a block it always is (K = 100, D = 100, M = 8: 46 / 152 for 10k, 1817 / 2650 for 1M; K = 16: 23 / 60, 251 / 243).
+// Which encoder: the waves of a block decide 32 vectors in lockstep, so the fused encoder's time per vector grows with their
+// number; what it saves, launches and a read and a write of the rows per dictionary, is worth most in small calls and long rows,
+// least where a row is a few cache lines or where four chunks hold mostly padding.  Measured on two kinds of rows, few near-ties
+// and many (M = 8, us fused / dictionary by dictionary):
+//   K > 128       49k vectors: D = 128 235 / 280 (45k) and 289 / 310;  60k: D = 64 241 / 224, D = 128 304 / 331;  80k: D = 128 409 / 368
+//   K in 65..128  D = 16    98k 140 / 187 and 168 / 192, 196k 260 / 235 and 313 / 244;  D = 64  196k 289 / 327 and 385 / 349
+//                 D = 128   196k 401 / 532 and 517 / 556, 262k - and 681 / 691, 392k 790 / 916 and 1020 / 972
+//                 D = 192   98k 361 / 459 and 414 / 487, 196k 733 / 748 and 866 / 787;  D = 208  392k 1481 / 1693 and 1752 / 1854
+//   K in 33..64   D = 16    392k 272 / 304 and 304 / 310, 800k 530 / 443 and 614 / 458;  D = 64  800k 558 / 883 and 721 / 940
+//                 D = 192   98k 386 / 437 and 454 / 455, 196k 818 / 713 and 937 / 744;  D = 256  392k 1596 / 1661 and 1922 / 1776
+//   K <= 32       D = 16    800k 368 / 418 and 400 / 424;  D = 64  800k 390 / 864 and 468 / 896
 bool encode_fused(const hclae_ctx *ctx, int64_t N)
 {
-    return encode_chunks(ctx) != 0 && (ctx->kb < 8 || N <= (int64_t)ctx->cus * 6 * kTileVec);
+    const int nc = encode_chunks(ctx), D = ctx->D;
+    const bool full = D >= 208;                              // of four chunks
+    int tiles_per_cu;                                        // the line, in tiles of 32 vectors
+    switch (nc ? ctx->kb : 0) {
+    case 0: return false;
+    case 1: return true;
+    case 2:
+        if (nc < 4 && D > 16) return true;
+        tiles_per_cu = nc < 4 || full ? 48 : 12;
+        break;
+    case 4:
+        if (full) return true;
+        tiles_per_cu = nc == 2 ? 32 : 16;
+        break;
+    default: tiles_per_cu = 6;
+    }
+    return N <= (int64_t)ctx->cus * tiles_per_cu * kTileVec;
 }
 
 template <int KB, int NC>

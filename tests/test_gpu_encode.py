@@ -65,3 +65,31 @@ def test_encode_with_more_tiles_than_blocks():
     assert torch.equal(codes, want)
     assert torch.equal(r, rw)
     ctx.close()
+
+
+# 256 CUs: the lines lie at 6, 12, 16, 32 and 48 tiles of 32 vectors per CU
+@pytest.mark.parametrize("N,D,K,fused", [(49152, 16, 129, True), (49153, 16, 129, False), (131072, 16, 65, True), (131073, 64, 128, False),
+                                         (262144, 68, 65, True), (262145, 128, 128, False), (131072, 132, 65, True), (131073, 204, 65, False),
+                                         (131073, 208, 65, True), (98304, 132, 33, True), (98305, 204, 64, False), (393216, 208, 33, True),
+                                         (393217, 208, 64, False), (393216, 16, 33, True), (393217, 16, 64, False),
+                                         (400000, 20, 64, True), (400000, 16, 32, True), (100, 260, 20, False), (100, 132, 32, False)])
+def test_encoder_by_size(N, D, K, fused):
+    """Both encoders on either side of the lines between them: one launch that decides, or one per dictionary."""
+    from paper_1509_05194_amd import hclae
+    M = 3
+    g = torch.Generator(device="cuda").manual_seed(N + K)
+    C = torch.randn((M, K, D), generator=g, device="cuda") * torch.tensor([1.0, 0.5, 0.3], device="cuda")[:, None, None]
+    X = torch.randn((N, D), generator=g, device="cuda")
+    ctx = hclae.Context(N, D, M, K)
+    codes, r = torch.full((N, M), 9, dtype=torch.uint8, device="cuda:0"), torch.empty_like(X)
+    ctx.timing_enable(["assign"])
+    ctx.encode(X, C, codes, r)
+    assert ctx.timing_read()["assign"][1] == (1 if fused else M)
+    ctx.timing_enable([])
+    want, rw = torch.full_like(codes, 9), X.clone()
+    for m in range(M):
+        ctx.assign(m, rw, C, want)
+        ctx.cool(m, C, want, rw)
+    assert torch.equal(codes, want)
+    assert torch.equal(r, rw)
+    ctx.close()
