@@ -122,65 +122,66 @@ __global__ __launch_bounds__(kPrepThreads) void k_encode_prep(
 // The nearest of a vector's candidates (bit i of mask[b]: codeword 32 b + i), by one wave; row: its fp32 residual in LDS.
 // As decide_items: fp32 direct form where the two best are further apart than its error, then fp64 in ascending dimension
 // order, lowest index on exact ties.
+// Four candidates at a time: bound by the latency of a round, so sixteen lanes (two loads each at D = 128) take one rather than
+// a half wave (two at a time: vectors with many candidates pay twice the rounds; 10k rows with lognormal norms, D = 64, K = 64,
+// M = 4: 143 us, 224 with a half wave, 64 queries at D = 128 49.4 / 51.5) or eight lanes (115 us, but registers spill at
+// D = 256, K = 128: 920 us for 200k rows instead of 775).
 template <int KB>
 __device__ __forceinline__ int encode_decide(const float *__restrict__ row, const float *__restrict__ Cm, const unsigned *mask, int D, int lane)
 {
     const int d4 = D >> 2;
-    // fp32: a half wave per candidate
-    const int half = lane >> 5, l32 = lane & 31;
-    const float eta = (float)(4 * ((d4 + 31) >> 5) + 8) * 6.1e-8f;
+    // fp32: four candidates at a time, sixteen lanes each
+    const int sub = lane & 15;
+    const float eta = (float)(4 * ((d4 + 15) >> 4) + 8) * 6.1e-8f;
     float best = __builtin_inff(), second = __builtin_inff();
     int kbest = 0, total = 0;
     for (int b = 0; b < KB; ++b) total += __popc(mask[b]);
-    int b = 0;
-    unsigned bits = mask[0];
-    auto next = [&]() {                                             // candidates in ascending order, -1 at the end; uniform
-        while (!bits && b + 1 < KB) bits = mask[++b];
-        if (!bits) return -1;
-        const int k = 32 * b + __ffs(bits) - 1;
-        bits &= bits - 1u;
+    auto nth = [&](int j) {                                         // the j-th candidate, -1 beyond the last
+        int k = -1;
+        for (int w = 0; w < KB; ++w) {
+            unsigned q = mask[w];
+            const int c = __popc(q);
+            if (j >= 0 && j < c) {
+                for (int i = 0; i < j; ++i) q &= q - 1u;
+                k = 32 * w + __ffs(q) - 1;
+            }
+            j -= c;
+        }
         return k;
     };
-    for (int i = 0; i < total; i += 2) {
-        const int k0 = next(), k1 = next();
-        const int k = half ? k1 : k0;
+    for (int j0 = 0; j0 < total; j0 += 4) {
+        const int k = nth(j0 + (lane >> 4));
         const float4 *c4 = reinterpret_cast<const float4 *>(Cm + (size_t)(k < 0 ? 0 : k) * D);
         float s = 0.f;
-        for (int d = l32; d < d4; d += 32) {
+#pragma unroll 2
+        for (int d = sub; d < d4; d += 16) {
             const float4 u = reinterpret_cast<const float4 *>(row)[d], v = c4[d];
             const float e0 = u.x - v.x, e1 = u.y - v.y, e2 = u.z - v.z, e3 = u.w - v.w;
             s = fmaf(e3, e3, fmaf(e2, e2, fmaf(e1, e1, fmaf(e0, e0, s))));
         }
 #pragma unroll
-        for (int o = 16; o > 0; o >>= 1) s += __shfl_xor(s, o, kWave);
-        const float o = __shfl_xor(s, 32, kWave);
-        const float s0 = half ? o : s, s1 = half ? s : o;
-        second = s0 < best ? best : fminf(second, s0);
-        if (s0 < best) { best = s0; kbest = k0; }
-        if (k1 >= 0) {
-            second = s1 < best ? best : fminf(second, s1);
-            if (s1 < best) { best = s1; kbest = k1; }
-        }
+        for (int o = 1; o < 16; o <<= 1) s += __shfl_xor(s, o, kWave);
+        if (k < 0) s = __builtin_inff();
+        second = s < best ? best : fminf(second, s);
+        if (s < best) { best = s; kbest = k; }
+    }
+#pragma unroll
+    for (int o = 16; o < kWave; o <<= 1) {
+        const float ob = __shfl_xor(best, o, kWave), os = __shfl_xor(second, o, kWave);
+        const int ok = __shfl_xor(kbest, o, kWave);
+        second = fminf(fmaxf(best, ob), fminf(second, os));
+        if (ob < best) { best = ob; kbest = ok; }
     }
     if (best * (1.f + eta) < second * (1.f - eta) && second > 1e-25f) return kbest;
     // fp64: a lane per candidate
     double dbest = __builtin_inf();
     int k64 = 0x7fffffff;
     for (int j0 = 0; j0 < total; j0 += kWave) {
-        int j = j0 + lane, k = -1;
-        for (int w = 0; w < KB && k < 0; ++w) {
-            unsigned q = mask[w];
-            const int c = __popc(q);
-            if (j < c) {
-                for (int i = 0; i < j; ++i) q &= q - 1u;
-                k = 32 * w + __ffs(q) - 1;
-            }
-            j -= c;
-        }
+        const int k = nth(j0 + lane);
         if (k < 0) continue;
         const float4 *c4 = reinterpret_cast<const float4 *>(Cm + (size_t)k * D);
         double s = 0.0;
-#pragma unroll 4
+#pragma unroll 2
         for (int d = 0; d < d4; ++d) {
             const float4 u = reinterpret_cast<const float4 *>(row)[d], v = c4[d];
             const double t0 = (double)u.x - (double)v.x, t1 = (double)u.y - (double)v.y;

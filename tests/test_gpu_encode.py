@@ -11,7 +11,7 @@ torch = pytest.importorskip("torch")
 
 # K: 1, 2, 4 and 8 waves to a block; D: 1, 2 and 4 chunks (one that rounds up) and rows too long for the fused kernel;
 # N: one vector, the edges of a 32-vector tile, and above the line where K > 128 goes dictionary by dictionary
-@pytest.mark.parametrize("kind", ["plain", "ties"])
+@pytest.mark.parametrize("kind", ["plain", "ties", "spread"])
 @pytest.mark.parametrize("N,D,M,K", [(1, 4, 1, 1), (31, 16, 4, 16), (33, 64, 3, 32), (65, 100, 2, 20), (95, 60, 3, 33),
                                      (1000, 128, 4, 64), (777, 200, 2, 50), (513, 68, 3, 65), (600, 128, 8, 128),
                                      (64, 256, 2, 100), (1, 128, 8, 256), (2050, 128, 8, 256), (300, 36, 5, 200),
@@ -27,6 +27,10 @@ def test_encode_equals_its_steps(kind, N, D, M, K):
         X[::5] = 0.0
         X[1::9] *= np.float32(1e5)                           # rows beyond the range the dictionaries set
         C[M - 1] = 0.0                                       # every score ties
+    if kind == "spread":                                     # norms over several orders: many candidates
+        f = np.exp(2 * rng.standard_normal((M, K, 1)))
+        C = (C * f).astype(np.float32)
+        X = X * np.exp(2 * rng.standard_normal((N, 1)))
     X = X.astype(np.float32)
     Xg, Cg = to_dev(X), to_dev(C)
     ctx = hclae.Context(N, D, M, K)
