@@ -33,6 +33,9 @@ typedef float floatv2 __attribute__((ext_vector_type(2)));
 constexpr int kHalfStep = 16;                       // dims per fp16 MFMA
 constexpr int kWaveMoved = 128;                     // vectors that changed cluster a wave keeps before it lists them
 constexpr int kRefineLanes = 4;                     // lanes that share an undecided vector in the fp64 decision
+// Candidates from which an undecided vector is scored again in fp32 (rescore_items); its bound grows with D, and for long rows it
+// leaves out little unless fp16 said nothing.
+__host__ __device__ constexpr int rescore_from(int kb, int D) { return D <= 256 ? 8 + 2 * kb : 16 * kb; }
 constexpr int kMuRows = 8;                          // codewords whose mean centres the scores
 constexpr float kHalfMaxNorm = 64000.f;             // a scaled row beyond this may not fit fp16: all codewords are candidates
 
@@ -138,8 +141,10 @@ __device__ __forceinline__ float half_rho(float dsq, float wk, float cmax)
     return cmax > 0.f ? (sqrtf(dsq) * 1.001f + wk * 1.2e-7f) / wk : 0.f;
 }
 
-// A: two units more than the MFMAs, for the norms and for the index bits in a score (decide_half).
-__device__ __forceinline__ float half_acc(int NC) { return (float)(4 * NC + 3) * (17.f * 1.1920929e-7f); }
+// A: two units more than the MFMAs, for the norms and for the index bits in a score (decide_half).  A unit is what one of them
+// may lose of the largest magnitude it adds.
+constexpr float kHalfAccUnit = 17.f * 1.1920929e-7f;
+__device__ __forceinline__ float half_acc(int NC) { return (float)(4 * NC + 3) * kHalfAccUnit; }
 
 // e of a vector, rounded up to fp16 (to nearest of 1.002 e), and not below its smallest normal number.
 __device__ __forceinline__ float half_bound(float x2, float dsq, float xn, const HalfConsts &c)
@@ -324,6 +329,22 @@ __device__ __forceinline__ void mfma_chunk_half(
     }
 }
 
+// Codewords whose score reaches thr, as bitmap words of the lane's half of them, without compare-and-select chains: the sign of
+// score - threshold is shifted into a word (v_alignbit), two instructions per score.
+template <int KB>
+__device__ __forceinline__ void reaching(uint32_t (&mk)[4], const floatx16 (&acc)[KB], float thr)
+{
+    mk[0] = mk[1] = mk[2] = mk[3] = 0u;
+#pragma unroll
+    for (int b = 0; b < KB; ++b) {
+        uint32_t below = 0u;
+#pragma unroll
+        for (int i = 15; i >= 0; --i)
+            below = __builtin_amdgcn_alignbit(below, __float_as_uint(acc[b][i] - thr), 31);   // (below << 1) | sign
+        mk[b >> 1] |= (~below & 0xffffu) << ((b & 1) * 16);
+    }
+}
+
 // What a wave has still to decide (in global memory) and to report (in LDS).
 struct HalfWave {
     HalfItem *items;
@@ -364,19 +385,109 @@ __device__ __forceinline__ void push_moved(HalfWave &w, bool yes, unsigned n, un
     w.nmoved += __popcll(who);
 }
 
+// Narrows the candidates of up to 32 undecided vectors by scores from the fp32 matrix cores, whose bound is 2^-22 D of the
+// magnitudes involved: data that lie far from their mean compared with what tells them apart (groups of clusters a long way from
+// each other, codewords of very different norms, vectors beyond fp16's range) leave the fp16 scores tens of candidates a vector,
+// and the direct form would pay for each of them.  Returns whether half of the candidates or more are left out.
+// Bound: eps (max||c||^2/2 + ||x|| max||c||) is twice the rounding error of a score, D + 2 roundings of 2^-23 of the partial sums.
+// Both operands come from memory, through caches that the other waves share.  Assignment of 200k vectors, D = 128, K = 256, us
+// without / with: two groups 30 standard deviations apart 681 / 266, one codeword 100 times as long as the others 1010 / 660,
+// codewords 10^-4 of the vectors 3178 / 253; where the fp32 bound says no more than the fp16 one (lognormal norms) 978 / 1014.
+// A call, not inlined: few launches come here, and its registers would cost the others 5 to 10 % (N = 1M, D = 128, K = 256).
+template <int KB, int PRUNE>
+__device__ __attribute__((noinline)) bool rescore_items(
+    HalfItem *items, int count, const float *__restrict__ xp, const float *__restrict__ Cm, const float *__restrict__ hneg,
+    int D, int ld, int K, float slack_rel)
+{
+    const int lane = lane_id(), h = lane >> 5, r = lane & 31;
+    HalfItem *it = items + (r < count ? r : 0);
+    const float *xrow = xp + (size_t)it->n * ld;
+    float hmax = 0.f;
+    for (int k = lane; k < K; k += kWave) hmax = fmaxf(hmax, -hneg[k]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) hmax = fmaxf(hmax, __shfl_xor(hmax, o, kWave));
+    floatx16 acc[KB];
+    init_acc<KB>(acc, hneg, h);
+    float x2 = 0.f;
+#pragma unroll 1
+    for (int c0 = 0; c0 < D; c0 += 8) {                             // rows of both operands straight from memory: the caches hold C
+        const int col = c0 + 4 * h;
+        const float4 x = col < D ? *reinterpret_cast<const float4 *>(xrow + col) : make_float4(0.f, 0.f, 0.f, 0.f);
+        float4 a[KB];
+#pragma unroll
+        for (int b = 0; b < KB; ++b) a[b] = load_row_piece(Cm, 32 * b + r, col, K, D, ld);
+        x2 = fmaf(x.x, x.x, x2);
+        x2 = fmaf(x.y, x.y, x2);
+        x2 = fmaf(x.z, x.z, x2);
+        x2 = fmaf(x.w, x.w, x2);
+#pragma unroll
+        for (int b = 0; b < KB; ++b) {
+            acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[b].x, x.x, acc[b], 0, 0, 0);
+            acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[b].y, x.y, acc[b], 0, 0, 0);
+            acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[b].z, x.z, acc[b], 0, 0, 0);
+            acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[b].w, x.w, acc[b], 0, 0, 0);
+        }
+    }
+    x2 += __shfl_xor(x2, 32, kWave);
+    float mx = -__builtin_inff();
+#pragma unroll
+    for (int b = 0; b < KB; ++b)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) mx = fmaxf(mx, acc[b][v]);
+    mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
+    const float eps = 2.02f * (float)(((D + kChunkD - 1) & ~(kChunkD - 1)) + 2) * 1.1920929e-7f;
+    const float margin = eps * (hmax + sqrtf(x2) * sqrtf(2.f * hmax) * 1.000001f);
+    const float thr = mx - margin;
+    uint32_t mk[4];
+    reaching<KB>(mk, acc, thr);
+    const bool usable = fabsf(thr) < 1e37f;                         // else the sums may have left fp32's range
+    uint32_t kept = 0u;                                             // codewords these scores keep and the fp16 scores did not
+    int change = 0;
+    if (r < count && usable) {
+        uint4 *words = reinterpret_cast<uint4 *>(it->mask[h]);
+        const uint4 was = *words;
+        kept = (mk[0] & ~was.x) | (mk[1] & ~was.y) | (mk[2] & ~was.z) | (mk[3] & ~was.w);
+        const uint4 now = make_uint4(was.x & mk[0], was.y & mk[1], was.z & mk[2], was.w & mk[3]);
+        change = __popc(was.x) + __popc(was.y) + __popc(was.z) + __popc(was.w)
+               - 2 * (__popc(now.x) + __popc(now.y) + __popc(now.z) + __popc(now.w));
+        *words = now;
+    }
+    if (PRUNE) {
+        // the codewords left out here have a true score <= out + margin / 2 (the evaluation of this line: see decide_half); those
+        // that only the fp16 scores left out keep the bound those gave
+        float out = -__builtin_inff();
+#pragma unroll
+        for (int b = 0; b < KB; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) out = fmaxf(out, acc[b][v] < thr ? acc[b][v] : out);
+        out = fmaxf(out, __shfl_xor(out, 32, kWave));
+        kept |= (uint32_t)__shfl_xor((int)kept, 32, kWave);
+        if (r < count && h == 0 && usable) {
+            const float slack = slack_rel * (x2 + 2.f * fabsf(mx) + 2.f * fabsf(thr));
+            const float l = sqrtf(fmaxf(0.f, (x2 - 2.f * (out + 0.5001f * margin)) - slack)) * 0.99999f;
+            it->lrest = kept ? fminf(it->lrest, l) : l;
+        }
+    }
+    __threadfence_block();
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) change += __shfl_xor(change, o, kWave);
+    return change >= 0;
+}
+
 // Decides the wave's items among their candidates.
 //
-// First in fp32, direct form, eight lanes per item: the lanes share a row (contiguous pieces), two candidates at a time.  A
-// sum of n non-negative terms accumulated in fp32 is within eta = (n + 6) 2^-24 of itself relatively, so where the best two
-// are further apart than that, the smaller one is the nearest codeword.  What is left (exact and nearly exact ties) is
-// decided in fp64: direct-form squared distances summed in ascending dimension order, smallest wins, exact ties go to the
-// lowest index; kRefineLanes lanes share an item there and a lane takes one candidate at a time.
+// First in fp32, direct form, eight lanes per item (after rescore_items where one of 32 has rescore_from() candidates or more): the
+// lanes share a row (contiguous pieces), two candidates at a time.  A sum of n non-negative terms accumulated in fp32 is within
+// eta = (n + 6) 2^-24 of itself relatively, so where the best two are further apart than that, the smaller one is the nearest
+// codeword.  What is left (exact and nearly exact ties) is decided in fp64: direct-form squared distances summed in ascending
+// dimension order, smallest wins, exact ties go to the lowest index; kRefineLanes lanes share an item there and a lane takes one
+// candidate at a time.
 // PRUNE: the vector's bounds become these distances (the lower one limited by the bound on the codewords left out).
 // Measured at N = 1M, D = 128, K = 256 with a fifth of the vectors undecided: 15 us of the kernel, 55 us with fp64 alone.
-template <int PRUNE>
+template <int KB, int PRUNE>
 __device__ __forceinline__ void decide_items(
-    HalfWave &w, const float *__restrict__ xp, const float *__restrict__ Cm, int D, int ld, int M, int m,
-    uint8_t *__restrict__ codes, const PruneArgs &pa,
+    HalfWave &w, const float *__restrict__ xp, const float *__restrict__ Cm, const float *__restrict__ hneg, int D, int ld, int K,
+    int M, int m, uint8_t *__restrict__ codes, const PruneArgs &pa,
     unsigned long long *__restrict__ moved_list, unsigned *__restrict__ moved_count)
 {
     __threadfence_block();                                          // the items were written by other lanes of the wave
@@ -388,12 +499,21 @@ __device__ __forceinline__ void decide_items(
         const int sub = lane & 7, first = lane & 56;
         const int d4up = (D + 3) >> 2;
         const float eta = (float)(4 * ((d4up + 7) >> 3) + 6) * 6.1e-8f;
+        int rescored = 0;                                           // items up to here have been through rescore_items
         for (int i0 = 0; i0 < w.nitems; i0 += 8) {
             const bool live = i0 + (lane >> 3) < w.nitems;
             const HalfItem *it = w.items + (live ? i0 + (lane >> 3) : 0);
             const unsigned n = it->n, old = it->old;
+            uint32_t word = it->mask[sub >> 2][sub & 3];
+            int total = __popc(live ? word : 0u);
+#pragma unroll
+            for (int o = 1; o < 8; o <<= 1) total += __shfl_xor(total, o, kWave);
+            if (i0 >= rescored && __ballot(total >= rescore_from(KB, D))) {
+                const bool worth = rescore_items<KB, PRUNE>(w.items + i0, min(32, w.nitems - i0), xp, Cm, hneg, D, ld, K, pa.slack);
+                rescored = worth ? i0 + 32 : w.nitems;
+                word = it->mask[sub >> 2][sub & 3];
+            }
             const float lrest = it->lrest;
-            const uint32_t word = it->mask[sub >> 2][sub & 3];
             uint32_t bits = live ? word : 0u;
             const float4 *x = reinterpret_cast<const float4 *>(xp + (size_t)n * ld);
             float best = __builtin_inff(), second = __builtin_inff();
@@ -407,7 +527,7 @@ __device__ __forceinline__ void decide_items(
                 if (sub == src) bits &= bits - 1u;
                 return have ? k : -1;
             };
-            while (__ballot(bits != 0u)) {
+            for (int round = 1; __ballot(bits != 0u); ++round) {
                 const int k0 = next(), k1 = next();
                 const float4 *c0 = reinterpret_cast<const float4 *>(Cm + (size_t)(k0 < 0 ? 0 : k0) * ld);
                 const float4 *c1 = reinterpret_cast<const float4 *>(Cm + (size_t)(k1 < 0 ? 0 : k1) * ld);
@@ -443,6 +563,9 @@ __device__ __forceinline__ void decide_items(
                     second = s1 < best ? best : fminf(second, s1);
                     if (s1 < best) { best = s1; kbest = k1; }
                 }
+                // many candidates, and the two best of the first four cannot be told apart: codewords that are equal (a dictionary
+                // of zeros, or one that counts in two dimensions only), left to fp64
+                if (round == 2 && total > 8 && !(best * (1.f + eta) < second * (1.f - eta))) bits = 0u;
             }
             // (the second condition keeps underflow out: a sum this large has no denormal part that counts)
             const bool sure = best * (1.f + eta) < second * (1.f - eta) && second > 1e-25f;
@@ -556,8 +679,7 @@ __device__ __forceinline__ float mfma_bound_half(
 //
 // The best and the second best of a lane's scores are found on keys: the score with its last four bits replaced by its
 // index in the accumulator block (2^-19 of the score, within h).  Where the second one stays below the threshold the
-// best key names the only candidate; only a tile with an undecided vector builds candidate bitmaps, without compare-and-
-// select chains: the sign of score - threshold is shifted into a word (v_alignbit), two instructions per score.
+// best key names the only candidate; only a tile with an undecided vector builds candidate bitmaps.
 template <int KB, int PRUNE>
 __device__ __forceinline__ void decide_half(
     const floatx16 (&acc)[KB], float x2, float xn, float e, const HalfConsts &c, const float *__restrict__ lds_w, int lane, int n,
@@ -610,15 +732,8 @@ __device__ __forceinline__ void decide_half(
     const uint32_t who = (uint32_t)__ballot(amb && h == 0);
     if (!who) return;
     constexpr int NW = (KB + 1) / 2;
-    uint32_t mk[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int b = 0; b < KB; ++b) {
-        uint32_t below = 0u;
-#pragma unroll
-        for (int i = 15; i >= 0; --i)
-            below = __builtin_amdgcn_alignbit(below, __float_as_uint(acc[b][i] - thr), 31);   // (below << 1) | sign
-        mk[b >> 1] |= (~below & 0xffffu) << ((b & 1) * 16);
-    }
+    uint32_t mk[4];
+    reaching<KB>(mk, acc, thr);
     if (big) {
 #pragma unroll
         for (int i = 0; i < NW; ++i) {
@@ -787,7 +902,7 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign_half(
             step(xb, xa, g + 2 < G);
         }
     }
-    if (w.nitems) decide_items<PRUNE>(w, xp, Cm, D, ld, M, m, codes, pa, moved_list, moved_count);
+    if (w.nitems) decide_items<KB, PRUNE>(w, xp, Cm, hneg, D, ld, K, M, m, codes, pa, moved_list, moved_count);
 
     half_finish<PRUNE>(lds, L, w, amax, refine_count, moved_list, moved_count, work);
 }
@@ -984,7 +1099,7 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign_half_chunked(
         xrow = xrow_n;
         old = old_n;
     }
-    if (w.nitems) decide_items<PRUNE>(w, xp, Cm, D, ld, M, m, codes, pa, moved_list, moved_count);
+    if (w.nitems) decide_items<KB, PRUNE>(w, xp, Cm, hneg, D, ld, K, M, m, codes, pa, moved_list, moved_count);
     half_finish<PRUNE>(lds, L, w, amax, refine_count, moved_list, moved_count, work);
 }
 

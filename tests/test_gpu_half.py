@@ -33,6 +33,19 @@ def _data(kind, N, D, K, rng):
         C[K // 2] *= np.float32(2e3)
     elif kind == "zero":
         C[:] = 0.0
+    # more candidates than fp16 scores can tell apart: they are scored again in fp32
+    elif kind == "groups":               # two groups 30 standard deviations apart
+        C[::2] += np.float32(30.0)
+        X = (C[rng.integers(0, K, N)] + 0.5 * rng.standard_normal((N, D))).astype(np.float32)
+    elif kind == "tiny":                 # codewords far below the vectors
+        C *= np.float32(1e-4)
+        X *= np.float32(rng.choice([0.1, 1.0, 30.0]))
+    elif kind == "spread":               # norms over several orders
+        C *= np.exp(2 * rng.standard_normal((K, 1))).astype(np.float32)
+        X = (C[rng.integers(0, K, N)] * (1 + 0.3 * rng.standard_normal((N, D)))).astype(np.float32)
+    elif kind == "huge":                 # squares beyond fp32
+        C *= np.float32(1e20)
+        X *= np.float32(1e20)
     return X, C
 
 
@@ -42,7 +55,8 @@ SHAPES = [(1, 4, 1), (31, 8, 2), (33, 16, 31), (32, 20, 33), (257, 60, 64), (100
           (4099, 128, 256), (700, 132, 200), (2049, 256, 256), (600, 260, 256), (300, 508, 128), (333, 2048, 32)]
 
 
-@pytest.mark.parametrize("kind", ["plain", "offset", "small", "large", "twins", "wild", "zero"])
+@pytest.mark.parametrize("kind", ["plain", "offset", "small", "large", "twins", "wild", "zero", "groups", "tiny", "spread",
+                                  "huge"])
 @pytest.mark.parametrize("N,D,K", SHAPES)
 def test_codes_equal_fp64_decisions(kind, N, D, K, oracle):
     from paper_1509_05194_amd import hclae
@@ -84,7 +98,7 @@ def test_prefix_codes(dact, oracle):
     assert not np.any((got != want[:, 0]) & (d2 - d1 > 1e-14 * d2))
 
 
-@pytest.mark.parametrize("kind", ["plain", "offset", "twins", "wild"])
+@pytest.mark.parametrize("kind", ["plain", "offset", "twins", "wild", "groups", "tiny", "spread"])
 # N K D on both sides of the line from which a stage keeps bounds (2^23)
 @pytest.mark.parametrize("N,D,K", [(5000 + 7, 128, 256), (3000 + 1, 100, 90), (2500, 16, 33), (20000 + 1, 16, 33),
                                    (2000 + 3, 516, 70), (200 + 3, 516, 70)])
@@ -104,3 +118,31 @@ def test_bounds_never_keep_a_wrong_code(kind, N, D, K):
     for a, b in zip(out[0][:3], out[1][:3]):
         assert torch.equal(a, b)
     assert out[0][3] == out[1][3]
+
+
+def test_many_candidates_do_not_cost_one_by_one():
+    """Where fp16 scores leave every codeword a candidate of every vector (codewords 10^-4 of the vectors), the assignment takes
+    some seven times as long as one without undecided vectors: another pass in fp32.  Deciding among all 256 in the direct form
+    took 80 times as long; 25 lies between the two with room for a slow clock."""
+    from paper_1509_05194_amd import hclae
+    N, D, K = 200000, 128, 256
+    g = torch.Generator(device="cuda").manual_seed(2)
+    X = torch.randn((N, D), generator=g, device="cuda")
+    C = X[:K][None].clone()
+    ctx = hclae.Context(N, D, 1, K)
+    codes = torch.zeros((N, 1), dtype=torch.uint8, device="cuda:0")
+    us = []
+    for f in (1.0, 1e-4):
+        Cf = C * f
+        best = float("inf")
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            ctx.assign(0, X, Cf, codes)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) * 1e3)
+        us.append(best)
+    print("ordinary codewords %.0f us, codewords far below the vectors %.0f us" % tuple(us))
+    assert us[1] < 25 * us[0]
+    ctx.close()
