@@ -33,9 +33,10 @@ typedef float floatv2 __attribute__((ext_vector_type(2)));
 constexpr int kHalfStep = 16;                       // dims per fp16 MFMA
 constexpr int kWaveMoved = 128;                     // vectors that changed cluster a wave keeps before it lists them
 constexpr int kRefineLanes = 4;                     // lanes that share an undecided vector in the fp64 decision
-// Candidates from which an undecided vector is scored again in fp32 (rescore_items); its bound grows with D, and for long rows it
-// leaves out little unless fp16 said nothing.
-__host__ __device__ constexpr int rescore_from(int kb, int D) { return D <= 256 ? 8 + 2 * kb : 16 * kb; }
+// Candidates in one word of an undecided vector's bitmap (32 codewords, 16 of the smallest dictionaries) from which it is scored
+// again in fp32 (rescore_items): six are rare with fewer than some 16 in all, and a look at the words costs no exchange.  The fp32
+// bound grows with D, and for long rows it leaves out little unless fp16 said nothing.
+__host__ __device__ constexpr int rescore_from(int kb, int D) { return D <= 256 ? 6 : kb == 1 ? 13 : 24; }
 constexpr int kMuRows = 8;                          // codewords whose mean centres the scores
 constexpr float kHalfMaxNorm = 64000.f;             // a scaled row beyond this may not fit fp16: all codewords are candidates
 
@@ -476,7 +477,7 @@ __device__ __attribute__((noinline)) bool rescore_items(
 
 // Decides the wave's items among their candidates.
 //
-// First in fp32, direct form, eight lanes per item (after rescore_items where one of 32 has rescore_from() candidates or more): the
+// First in fp32, direct form, eight lanes per item (after rescore_items where one of 32 has many candidates): the
 // lanes share a row (contiguous pieces), two candidates at a time.  A sum of n non-negative terms accumulated in fp32 is within
 // eta = (n + 6) 2^-24 of itself relatively, so where the best two are further apart than that, the smaller one is the nearest
 // codeword.  What is left (exact and nearly exact ties) is decided in fp64: direct-form squared distances summed in ascending
@@ -505,10 +506,7 @@ __device__ __forceinline__ void decide_items(
             const HalfItem *it = w.items + (live ? i0 + (lane >> 3) : 0);
             const unsigned n = it->n, old = it->old;
             uint32_t word = it->mask[sub >> 2][sub & 3];
-            int total = __popc(live ? word : 0u);
-#pragma unroll
-            for (int o = 1; o < 8; o <<= 1) total += __shfl_xor(total, o, kWave);
-            if (i0 >= rescored && __ballot(total >= rescore_from(KB, D))) {
+            if (i0 >= rescored && __ballot(live && __popc(word) >= rescore_from(KB, D))) {
                 const bool worth = rescore_items<KB, PRUNE>(w.items + i0, min(32, w.nitems - i0), xp, Cm, hneg, D, ld, K, pa.slack);
                 rescored = worth ? i0 + 32 : w.nitems;
                 word = it->mask[sub >> 2][sub & 3];
@@ -565,7 +563,12 @@ __device__ __forceinline__ void decide_items(
                 }
                 // many candidates, and the two best of the first four cannot be told apart: codewords that are equal (a dictionary
                 // of zeros, or one that counts in two dimensions only), left to fp64
-                if (round == 2 && total > 8 && !(best * (1.f + eta) < second * (1.f - eta))) bits = 0u;
+                if (round == 2) {
+                    int left = __popc(bits);
+#pragma unroll
+                    for (int o = 1; o < 8; o <<= 1) left += __shfl_xor(left, o, kWave);
+                    if (left > 4 && !(best * (1.f + eta) < second * (1.f - eta))) bits = 0u;
+                }
             }
             // (the second condition keeps underflow out: a sum this large has no denormal part that counts)
             const bool sure = best * (1.f + eta) < second * (1.f - eta) && second > 1e-25f;
