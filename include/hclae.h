@@ -219,9 +219,11 @@ int hclae_online_import(hclae_ctx *ctx, const double *run_sum, const int64_t *ru
 /*
  * Kept for callers: both modes are accepted and give what they always gave, the same codes, dictionaries and residues.
  * The scores x'.c - ||c||^2/2 of the nearest-codeword kernels (Sec. 3.1 / 3.2 assignment, Eq. 3) only pre-select
- * candidates within an error margin, and the decision is a direct-form one in fp64, so no result depends on how they are
- * formed.  One contraction serves both modes: fp16 matrix cores on centred, scaled operands, whose rounding is bounded
- * rigorously by norms measured per vector and per codeword.
+ * candidates within an error margin, and the decision is a direct-form one (in fp32 where the best two are further apart
+ * than that can be wrong, else in fp64), so no result depends on how they are formed.  One contraction serves both modes:
+ * fp16 matrix cores on centred, scaled operands.  Their rounding is bounded by norms measured per vector and per codeword;
+ * what the matrix cores lose in accumulating is bounded by a constant that is four times what was measured on the device,
+ * since no document states it.
  */
 int hclae_set_contraction(hclae_ctx *ctx, int mode);
 
@@ -252,7 +254,7 @@ int hclae_set_pruning(hclae_ctx *ctx, int on);
  *   parent / code DEVICE uint8[N][Ln] = l / k.  err_next, parent and code may be NULL.
  * Cm: DEVICE float[K][D].  1 <= Lc <= L <= HCLAE_MAX_L, N * L < 2^31.
  * Decisions are taken on fp64 direct-form errors of the fp32 rows (candidates pre-selected on the
- * fp16 matrix cores with a rigorous rounding margin).
+ * fp16 matrix cores with the margin of hclae_set_contraction).
  */
 int hclae_beam_step(hclae_ctx *ctx, const float *rows, const double *err, const float *Cm,
                     int64_t N, int D, int K, int Lc, int L,

@@ -5,6 +5,7 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhclae.so")
+PROBE = os.path.join(HERE, "libhclae_probe.so")      # for the tests: single instructions of the contraction
 
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950", "-shared", "-fPIC",
@@ -20,9 +21,10 @@ def sources():
 def build(verbose=False, extra=()):
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     cmd = [hipcc] + HIPCC_FLAGS + list(extra) + ["-o", LIB] + sources()
-    if verbose:
-        print(" ".join(cmd))
-    subprocess.run(cmd, check=True)
+    for c in (cmd, [hipcc] + HIPCC_FLAGS + list(extra) + ["-o", PROBE, os.path.join(CSRC, "probe.hip")]):
+        if verbose:
+            print(" ".join(c))
+        subprocess.run(c, check=True)
     return LIB
 
 

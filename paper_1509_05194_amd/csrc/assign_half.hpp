@@ -12,10 +12,12 @@
 //
 // Bound on the score of codeword k, in the scaled and centred units X, C (X^, C^ the fp16 values that enter the product):
 //   |X.C_k - X^.C^_k| <= ||X - X^|| ||C^_k|| + ||X|| ||C_k - C^_k||  (rounding)
-//                      + A (max||C||^2/2 + ||X|| ||C^_k||)           (accumulation),  A = (D/16 + 3) 17 2^-23:
-// an MFMA adds 16 exact products and the accumulator, and 17 2^-23 of the magnitudes it adds is what 17 addends lose
-// when each is truncated to 24 bits of the largest.  With w_k >= ||C_k||, rho = max ||C_k - C^_k|| / w_k:
-//   E_k = e w_k + h,   e = ||X - X^|| (1 + rho) + ||X|| (rho + A (1 + rho)),   h = A max||C||^2/2.
+//                      + A (max||C||^2/2 + ||X|| ||C^_k|| + t (||X|| + max||C||) + t^2)   (accumulation),
+// A = (D/16 + 3) 17 2^-23, t = 2^-14.  The rounding part is measured and rigorous.  The accumulation part holds if an MFMA, which
+// adds 16 exact products and the accumulator, loses no more than 17 addends do when each is truncated to 24 bits of the largest,
+// where a product counts as if its factors were not below fp16's smallest normal number t (subnormal ones are aligned so).  No
+// document says that; measured on an MI355X over random and adversarial sums it loses less than a quarter of it.  With w_k >= ||C_k||, rho = max ||C_k - C^_k|| / w_k:
+//   E_k = e w_k + h,   e = ||X - X^|| (1 + rho) + ||X|| (rho + A (1 + rho)),   h = A (max||C||^2/2 + t (||X|| + max||C||) + t^2).
 // The matrix cores add e w_k themselves, as one more dimension of the product (X^: e, C^: w_k, both rounded up), so that the
 // accumulators end with U_k, U_k + h an upper bound of the true score; the best one's lower bound is U - 2 e w - h.
 // Per-codeword bounds instead of the largest norm for all leave a third of the undecided vectors (SIFT-shaped data, later
@@ -83,8 +85,9 @@ __host__ __device__ constexpr HalfLds half_lds(int kb, int nc, int slices)
 // Constants of a dictionary in scaled and centred units.
 struct HalfConsts {
     float scale, inv;                               // 2^s, 2^-s
-    float h, rho, acc;                              // A max||C||^2/2, max ||C_k - C^_k|| / w_k, A
+    float h, rho, acc;                              // h but for its term in ||X||, max ||C_k - C^_k|| / w_k, A
     float cmax;                                     // max ||C||
+    float hx;                                       // what a unit of ||X|| adds to h, and to what the index bits do to a key (decide_half)
 };
 
 __device__ __forceinline__ float uniform(float v) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v))); }
@@ -146,6 +149,14 @@ __device__ __forceinline__ float half_rho(float dsq, float wk, float cmax)
 // may lose of the largest magnitude it adds.
 constexpr float kHalfAccUnit = 17.f * 1.1920929e-7f;
 __device__ __forceinline__ float half_acc(int NC) { return (float)(4 * NC + 3) * kHalfAccUnit; }
+
+// h of a dictionary without its term in ||X||, from the largest ||C||^2 and a bound of the largest ||C||.
+__device__ __forceinline__ float half_loss(float acc, float hm, float cmax) { return acc * (0.501f * hm + 6.2e-5f * cmax + 3.8e-9f); }
+
+__device__ __forceinline__ float half_loss_x(float acc, float cmax) { return acc * 6.2e-5f + 2.1e-6f * cmax; }
+
+// w_k rounded up to fp16: to nearest of 1.002 w and a spacing of the subnormal numbers.
+__device__ __forceinline__ _Float16 half_up(float wk) { return (_Float16)(wk * 1.002f + 6e-8f); }
 
 // e of a vector, rounded up to fp16 (to nearest of 1.002 e), and not below its smallest normal number.
 __device__ __forceinline__ float half_bound(float x2, float dsq, float xn, const HalfConsts &c)
@@ -216,7 +227,7 @@ __device__ __forceinline__ HalfConsts half_constants(
     float rho = half_rho(dsq, wk, c.cmax);
     if (holder) {
         const bool real = row < K;
-        const halfx2 up = {(_Float16)(wk * 1.002f), (_Float16)0.f}; // to nearest of 1.002 w: not below w
+        const halfx2 up = {half_up(wk), (_Float16)0.f};
         reinterpret_cast<float *>(lds + L.hneg)[row] = real ? -0.5f * sq : -1e38f;   // finite: index bits in an infinity would be a NaN
         reinterpret_cast<float *>(lds + L.w)[row] = (float)up.x;
         unsigned *aug = reinterpret_cast<unsigned *>(lds + L.waug) + 64 * (row >> 5) + (row & 31);
@@ -234,9 +245,10 @@ __device__ __forceinline__ HalfConsts half_constants(
     // the same in every lane: scalar registers
     c.scale = uniform(scale);
     c.inv = uniform(inv);
-    c.h = uniform(c.acc * 0.5f * hm * 1.002f);
+    c.h = uniform(half_loss(c.acc, hm, c.cmax));
     c.rho = uniform(rho);
     c.cmax = uniform(c.cmax);
+    c.hx = uniform(half_loss_x(c.acc, c.cmax));
     return c;
 }
 
@@ -714,7 +726,8 @@ __device__ __forceinline__ void decide_half(
         mx = fmaxf(mx, mxo);
     }
     code = code < K ? code : 0;                                     // beyond K only with non-finite input
-    const float hh = c.h + 2.1e-6f * (fabsf(mx) + xn * c.cmax) + 1e-36f;   // h, and what the index bits did to the keys (to a zero, too)
+    // h, and what the index bits did to the keys (to a zero, too)
+    const float hh = fmaf(c.hx, xn, fmaf(2.1e-6f, fabsf(mx), c.h)) + 1e-36f;
     const float low = mx - 2.f * e * lds_w[code] - hh;              // lower bound of the best one's true score
     const float thr = low - hh;                                     // candidates: U_k + h >= low
     const bool big = !(x2 < kHalfMaxNorm * kHalfMaxNorm && fabsf(thr) < 1e37f);   // may not fit fp16

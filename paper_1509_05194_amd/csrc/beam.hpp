@@ -49,8 +49,8 @@ __device__ __forceinline__ void beam_select(
         for (int v = 1; v < 16; ++v) bm[b] = __builtin_amdgcn_fmed3f(bm[b], acc[b][v], inf);   // the larger one, see opaque()
         top = fmaxf(top, bm[b]);
     }
-    const float round = c.h + 2.4e-7f * (fabsf(top) + xn * c.cmax) + slack * x2 + 1e-36f;
-    const float down = half_x2 + 2.f * e * c.cmax * 1.01f + round;
+    const float round = c.h + c.acc * 6.2e-5f * xn + 2.4e-7f * (fabsf(top) + xn * c.cmax) + slack * x2 + 1e-36f;
+    const float down = half_x2 + 2.f * e * (c.cmax * 1.01f + 1.2e-7f) + round;
     const bool big = !(x2 < kHalfMaxNorm * kHalfMaxNorm && down < 1e37f);     // may not fit fp16: all codewords are candidates
 #pragma unroll
     for (int b = 0; b < KB; ++b) bm[b] = valid && !big ? bm[b] - down : ninf;

@@ -18,7 +18,7 @@
 namespace hclae {
 
 constexpr int kPrepThreads = 1024;
-constexpr int kEncodeConsts = 8;                    // floats per dictionary: scale, h, rho, acc, cmax
+constexpr int kEncodeConsts = 8;                    // floats per dictionary: scale, h, rho, acc, hx
 
 // Tiles of N < 2^31 vectors, and the blocks that take them: one each up to 2^20, which stride beyond (a launch holds less than
 // 2^32 threads, and a block has up to 512).
@@ -102,7 +102,7 @@ __global__ __launch_bounds__(kPrepThreads) void k_encode_prep(
         const float wk = half_floor(s_sq[k], cmax);
         rho = half_rho(s_dsq[k], wk, cmax);
         hn[(size_t)m * kpad + k] = k < K ? -0.5f * s_sq[k] : -1e38f;
-        wtab[(size_t)m * kpad + k] = k < K ? (float)(_Float16)(wk * 1.002f) : 0.f;
+        wtab[(size_t)m * kpad + k] = k < K ? (float)half_up(wk) : 0.f;
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) rho = fmaxf(rho, __shfl_xor(rho, o, kWave));
@@ -114,8 +114,8 @@ __global__ __launch_bounds__(kPrepThreads) void k_encode_prep(
         c[0] = scale;
         c[2] = rho;
         c[3] = half_acc(NC);
-        c[1] = c[3] * 0.5f * hm * 1.002f;
-        c[4] = cmax;
+        c[1] = half_loss(c[3], hm, cmax);
+        c[4] = half_loss_x(c[3], cmax);
     }
 }
 
@@ -278,7 +278,7 @@ __global__ __launch_bounds__(64 * KB, 2) void k_encode_fused(
             c.h = cc[1];
             c.rho = cc[2];
             c.acc = cc[3];
-            c.cmax = cc[4];
+            c.hx = cc[4];
             // ---- the rows as fp16 operands, with their norms
             const int t16 = p >> 2, g16 = p & 1, hi = (p >> 1) & 1;
             float s[2 * R];
@@ -346,7 +346,7 @@ __global__ __launch_bounds__(64 * KB, 2) void k_encode_fused(
                 mx = fmaxf(mx, o.x);
             }
             code = code < K ? code : 0;
-            const float hh = c.h + 2.1e-6f * (fabsf(mx) + xn * c.cmax) + 1e-36f;
+            const float hh = fmaf(c.hx, xn, fmaf(2.1e-6f, fabsf(mx), c.h)) + 1e-36f;
             const float thr = mx - 2.f * e * lds_w[code] - 2.f * hh;
             const bool big = !(x2 < kHalfMaxNorm * kHalfMaxNorm && fabsf(thr) < 1e37f);
             const bool amb = K > 1 && n0 + r < N && (big || !(m2 < thr));
