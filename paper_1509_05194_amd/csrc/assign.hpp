@@ -1,5 +1,5 @@
-// What the nearest-codeword assignments share (assign_half.hpp holds their kernels), the fp32 contraction that the multi-path
-// scoring and the rotation use, and the distance bounds of a stage.
+// What the nearest-codeword assignments share (assign_half.hpp holds their kernels), the fp32 contraction of the rotation, and the
+// distance bounds of a stage.
 //
 // argmin_k ||x' - c_k||^2 = argmax_k ( x'.c_k - ||c_k||^2/2 ).  The right-hand score is a dense K x D by D x N contraction.
 // The product is oriented codewords x vectors, so a lane ends up holding scores of many codewords for ONE vector and the
@@ -76,13 +76,8 @@ __global__ __launch_bounds__(256) void k_codeword_norms(
     if (lane == 0) hneg[k] = -(float)(0.5 * s);
 }
 
-// LDS image of the codebook in MFMA operand order.  For row block b (32 codewords), k-step s
-// (8 dims) and lane l = 32*h + r, the float4 at index (b*S + s)*64 + l holds
-// C[32b + r][8s + 4h .. 8s + 4h + 3]; a wave's ds_read_b128 of one (b, s) is one contiguous
-// kilobyte (no bank conflicts), and component j of it is the A operand of the MFMA that
-// contracts dims {8s + j, 8s + 4 + j}.
-// Only the first D coordinates of each row (stride ld) enter; the rest of the image is zero, so
-// whatever x' holds beyond D contributes nothing to the scores.
+// Four coordinates of a row from column col: zero beyond the first D coordinates and beyond the first K rows (stride ld), so that
+// whatever the other operand holds there contributes nothing to a product.
 __device__ __forceinline__ float4 load_row_piece(const float *__restrict__ base, int row, int col, int K, int D, int ld)
 {
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -118,26 +113,18 @@ __device__ __forceinline__ void load_x_chunk(
     }
 }
 
-// PREFIX: the chunk ends after `steps` of its eight 8-dim steps (a short prefix of the coordinates counts;
-// the codebook image is zero beyond it, so the steps left out would add nothing).
-template <int KB, bool PREFIX = false>
+// One chunk of the fp32 contraction: lds holds the rows of the other operand in MFMA order (for row block b, 8-dim step s and lane
+// l = 32 h + r the float4 at (b S + s) 64 + l is row 32 b + r, dims 8 s + 4 h .. + 3; component j contracts dims 8 s + j, 8 s + 4 + j).
+template <int KB>
 __device__ __forceinline__ void mfma_chunk(
-    floatx16 (&acc)[KB], const float4 (&x)[8], const float4 *__restrict__ lds, int q, int S, int lane,
-    float &xsq, float &amax, int steps = 8)
+    floatx16 (&acc)[KB], const float4 (&x)[8], const float4 *__restrict__ lds, int S, int lane)
 {
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
-        if (PREFIX && s >= steps) break;
         float4 a[KB];
 #pragma unroll
-        for (int b = 0; b < KB; ++b) a[b] = lds[(b * S + 8 * q + s) * kWave + lane];
+        for (int b = 0; b < KB; ++b) a[b] = lds[(b * S + s) * kWave + lane];
         const float4 xv = x[s];
-        xsq = fmaf(xv.x, xv.x, xsq);
-        xsq = fmaf(xv.y, xv.y, xsq);
-        xsq = fmaf(xv.z, xv.z, xsq);
-        xsq = fmaf(xv.w, xv.w, xsq);
-        amax = fmaxf(fmaxf(amax, fabsf(xv.x)), fabsf(xv.y));      // one v_max3_f32 per two elements
-        amax = fmaxf(fmaxf(amax, fabsf(xv.z)), fabsf(xv.w));
 #pragma unroll
         for (int b = 0; b < KB; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[b].x, xv.x, acc[b], 0, 0, 0);
 #pragma unroll

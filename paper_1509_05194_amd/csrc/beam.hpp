@@ -35,7 +35,7 @@ struct BeamMask {
 constexpr int kBeamHops = 5;                        // 2^5 >= kBeamMaxL
 template <int KB>
 __device__ __forceinline__ void beam_select(
-    const floatx16 (&acc)[KB], float x2, float xn, float e, const HalfConsts &c, float slack, int K,
+    const floatx16 (&acc)[KB], float x2, float xn, float e, const HalfConsts &c, float slack,
     int lane, const int (&next)[kBeamHops], int hops, int Ln, bool valid, BeamMask *__restrict__ out)
 {
     const float ninf = -__builtin_inff();
@@ -81,7 +81,6 @@ __device__ __forceinline__ void beam_select(
     }
     if (big || !(thr > ninf))                            // (bits of codewords beyond K are dropped by the reader)
         mk[0] = mk[1] = mk[2] = mk[3] = ~0u;
-    (void)K;
     if (valid) *reinterpret_cast<uint4 *>(&out->w[lane >> 5][0]) = make_uint4(mk[0], mk[1], mk[2], mk[3]);
 }
 
@@ -145,7 +144,7 @@ __global__ __launch_bounds__(kAssignThreads) void k_beam_score_half(
             const float e = mfma_bound_half<KB>(acc, reinterpret_cast<const unsigned *>(lds + L.waug), xsq, dsq, c, lane, x2, norm);
             const int64_t row = tile * bt.rt + r;
             const bool valid = r < bt.rt && row < nrows;
-            beam_select<KB>(acc, x2, norm, e, c, slack, K, lane, bt.next, bt.hops, Ln, valid, masks + (valid ? row : 0));
+            beam_select<KB>(acc, x2, norm, e, c, slack, lane, bt.next, bt.hops, Ln, valid, masks + (valid ? row : 0));
             init_acc<KB>(acc, lds_h, h);
             xsq = 0.f;
             dsq = 0.f;
@@ -218,7 +217,7 @@ __global__ __launch_bounds__(kAssignThreads) void k_beam_score_half_chunked(
         }
         float x2, norm;
         const float e = mfma_bound_half<KB>(acc, reinterpret_cast<const unsigned *>(lds + L.waug), xsq, dsq, c, lane, x2, norm);
-        beam_select<KB>(acc, x2, norm, e, c, slack, K, lane, bt.next, bt.hops, Ln, valid, masks + (valid ? row : 0));
+        beam_select<KB>(acc, x2, norm, e, c, slack, lane, bt.next, bt.hops, Ln, valid, masks + (valid ? row : 0));
         row = row_n;
         valid = valid_n;
         xrow = xrow_n;

@@ -141,7 +141,6 @@ struct hclae_ctx {
     int beam_L;              // beam width they were sized for
     int sweep_L;             // paths of the re-encode of hclae_sweep, reencode_mode 2
     float *beam_rows[2];     // [beam_cap][beam_L][D] residuals, ping-pong
-    double *beam_err[2];     // [beam_cap][beam_L]
     uint8_t *beam_pre[2];    // [beam_cap][beam_L][M] code prefixes
     BeamMask *beam_mask;     // [beam_cap][beam_L]
     // optional per-kernel timing (HIP events on ctx->stream)
@@ -854,7 +853,7 @@ int hclae_destroy(hclae_ctx *ctx)
                    ctx->pca_grampart, ctx->pca_mean, ctx->pca_mean32, ctx->pca_cov, ctx->pca_R, ctx->pca_xr,
                    ctx->stats_buf, ctx->order_var, ctx->order_idx, ctx->order_tmp,
                    ctx->carry_u, ctx->carry_l, ctx->carry_path, ctx->carry_snap, ctx->carry_Centry, ctx->carry_T, ctx->carry_amax,
-                   ctx->beam_rows[0], ctx->beam_rows[1], ctx->beam_err[0], ctx->beam_err[1],
+                   ctx->beam_rows[0], ctx->beam_rows[1],
                    ctx->beam_pre[0], ctx->beam_pre[1], ctx->beam_mask};
     for (void *p : dev)
         if (p) (void)hipFree(p);
@@ -1308,19 +1307,18 @@ int hclae_online_chunk(hclae_ctx *ctx, const uint8_t *Xu8, int64_t n, int D, flo
 
 static void beam_release(hclae_ctx *ctx)
 {
-    void *dev[] = {ctx->beam_rows[0], ctx->beam_rows[1], ctx->beam_err[0], ctx->beam_err[1],
+    void *dev[] = {ctx->beam_rows[0], ctx->beam_rows[1],
                    ctx->beam_pre[0], ctx->beam_pre[1], ctx->beam_mask};
     for (void *p : dev)
         if (p) (void)hipFree(p);
     ctx->beam_rows[0] = ctx->beam_rows[1] = nullptr;
-    ctx->beam_err[0] = ctx->beam_err[1] = nullptr;
     ctx->beam_pre[0] = ctx->beam_pre[1] = nullptr;
     ctx->beam_mask = nullptr;
     ctx->beam_cap = 0;
     ctx->beam_L = 0;
 }
 
-// Buffers for batches of `cap` vectors with L paths each.  with_state: also the residual, error and
+// Buffers for batches of `cap` vectors with L paths each.  with_state: also the residual and
 // prefix ping-pong buffers (hclae_encode_beam); the single step only needs the candidate bitmaps.
 static int beam_scratch(hclae_ctx *ctx, int64_t cap, int L, bool with_state)
 {
@@ -1336,7 +1334,6 @@ static int beam_scratch(hclae_ctx *ctx, int64_t cap, int L, bool with_state)
     hipError_t e = hipMalloc((void **)&ctx->beam_mask, rows * sizeof(BeamMask));
     for (int i = 0; i < 2 && with_state; ++i) {
         if (e == hipSuccess) e = hipMalloc((void **)&ctx->beam_rows[i], rows * ctx->D * sizeof(float));
-        if (e == hipSuccess) e = hipMalloc((void **)&ctx->beam_err[i], rows * sizeof(double));
         if (e == hipSuccess) e = hipMalloc((void **)&ctx->beam_pre[i], rows * ctx->M);
     }
     if (e != hipSuccess) {
@@ -1446,7 +1443,7 @@ static int enqueue_encode_beam(hclae_ctx *ctx, const float *X, int64_t N, const 
             const bool last = (m == M - 1);
             const int Ln = last ? 1 : beam_next_width(K, Lc, L);    // the answer is the best of the last beam
             float *rows_n = last ? residue + n0 * D : ctx->beam_rows[m & 1];
-            double *err_n = last ? (err ? err + n0 : nullptr) : ctx->beam_err[m & 1];
+            double *err_n = last && err ? err + n0 : nullptr;      // the scoring ranks by the rows: errors in between have no reader
             uint8_t *pre_n = last ? codes + n0 * M : ctx->beam_pre[m & 1];
             rc = enqueue_beam_step(ctx, rows_c, C + (size_t)m * K * D, nb, Lc, Ln, pre_c, pre_n, m,
                                    rows_n, err_n, nullptr, nullptr);

@@ -56,7 +56,6 @@ __global__ __launch_bounds__(kAssignThreads, RES ? 4 : 2) void k_project(
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
         float4 xc[8];
-        float unused_sq = 0.f, unused_max = 0.f;
         for (int q = 0; q < NC; ++q) {
             load_x_chunk(xc, xrow, q, h, D);
             if (!RES) {
@@ -64,7 +63,7 @@ __global__ __launch_bounds__(kAssignThreads, RES ? 4 : 2) void k_project(
                 stage(q, lds_c);
                 __syncthreads();
             }
-            mfma_chunk<KB>(acc, xc, lds_c + (RES ? q * KB * S * kWave : 0), 0, S, lane, unused_sq, unused_max);
+            mfma_chunk<KB>(acc, xc, lds_c + (RES ? q * KB * S * kWave : 0), S, lane);
         }
         if (n_raw < N) {
             float *orow = out + n_raw * D + o0;
