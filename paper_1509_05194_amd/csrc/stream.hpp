@@ -46,7 +46,7 @@ __device__ __forceinline__ void block_absmax(float amax, float *scratch, unsigne
 //            as if it had been stored and reloaded, so the result equals the two passes bit for bit.  By-products:
 //            sum ||e_x||^2 (error after stage m = error before stage j), codes of stage m changed since its entry,
 //            and the code column of stage j saved for its own change count.
-// The rows are read from src, which is r itself in place, or the vectors the greedy encoder starts from.
+// The rows are read from src, which is r itself in place (so neither is __restrict__), or the vectors the greedy encoder starts from.
 // part_err[blockIdx.x], part_chg[blockIdx.x] receive this block's partial sums (fixed order); STATS false: no by-products.
 //
 // A thread works on kStreamUnroll rows at a time, one float4 column of each, in steps (row group, column chunk).
@@ -61,7 +61,7 @@ __device__ __forceinline__ void block_absmax(float amax, float *scratch, unsigne
 // a stage whose first assignment does not read every row and so cannot provide it.
 template <int MODE, bool STATS, int DT = 0, bool AMAX = false>
 __global__ __launch_bounds__(kStreamThreads) void k_row_pass(
-    float *__restrict__ r, const float *src, const uint8_t *__restrict__ codes, const float *__restrict__ Cm, const float *__restrict__ Cj,
+    float *r, const float *src, const uint8_t *__restrict__ codes, const float *__restrict__ Cm, const float *__restrict__ Cj,
     int64_t N, int D_rt, int M, int m, int j_stage, RowGeom g_rt,
     uint8_t *__restrict__ old_codes, double *__restrict__ part_err, long long *__restrict__ part_chg,
     unsigned *__restrict__ absmax_slot = nullptr)
@@ -196,7 +196,7 @@ constexpr int kWideMinD = 768;
 constexpr int kWideRows = 2;
 template <int MODE, bool STATS, bool AMAX = false>
 __global__ __launch_bounds__(kStreamThreads) void k_row_pass_wide(
-    float *__restrict__ r, const float *src, const uint8_t *__restrict__ codes, const float *__restrict__ Cm, const float *__restrict__ Cj,
+    float *r, const float *src, const uint8_t *__restrict__ codes, const float *__restrict__ Cm, const float *__restrict__ Cj,
     int64_t N, int D, int M, int m, int j_stage,
     uint8_t *__restrict__ old_codes, double *__restrict__ part_err, long long *__restrict__ part_chg,
     unsigned *__restrict__ absmax_slot = nullptr)
