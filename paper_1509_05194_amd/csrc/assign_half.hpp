@@ -739,9 +739,10 @@ __device__ __forceinline__ void decide_half(
         codes[(size_t)n * M + m] = (uint8_t)code;
         if (PRUNE) {
             // d^2 = ||X||^2 - 2 score.  slack covers the fp32 evaluation: x2 is a chain of D/2 fused multiply-adds per lane
-            // (relative error <= (D/2 + 1) 2^-24, all terms positive), the rest a handful of roundings; pa.slack = (D/2 + 16) 2^-23
-            pa.bu[n] = K > 1 ? sqrtf(fmaxf(0.f, (x2 - 2.f * low) + slack)) * 1.00001f * c.inv : __builtin_inff();
-            pa.bl[n] = K > 1 ? sqrtf(fmaxf(0.f, (x2 - 2.f * (m2 + hh)) - slack)) * 0.99999f * c.inv : 0.f;
+            // (relative error <= (D/2 + 1) 2^-24, all terms positive), the rest a handful of roundings; pa.slack = (D/2 + 16) 2^-23.
+            // (a single codeword has no other one to be nearer than: settled for good)
+            pa.bu[n] = K > 1 ? sqrtf(fmaxf(0.f, (x2 - 2.f * low) + slack)) * 1.00001f * c.inv : 0.f;
+            pa.bl[n] = K > 1 ? sqrtf(fmaxf(0.f, (x2 - 2.f * (m2 + hh)) - slack)) * 0.99999f * c.inv : __builtin_inff();
         }
     }
     if (moved_list) push_moved(w, mine && !amb && old != (unsigned)code, (unsigned)n, old, (unsigned)code, moved_list, moved_count);
