@@ -19,14 +19,12 @@ def data():
     return X, to_dev(X)
 
 
-@pytest.mark.parametrize("contraction", [0, 1], ids=["f32", "splitbf16"])
-def test_gist_fullsize_assign_sampled(data, oracle, contraction):
+def test_gist_fullsize_assign_sampled(data, oracle):
     from paper_1509_05194_amd import hclae
     X, Xg = data
     M = 2
     idx = synth.init_indices(N, M, K)
     ctx = hclae.Context(N, D, M, K)
-    ctx.set_contraction(contraction)
     C = torch.zeros((M, K, D), dtype=torch.float32, device="cuda:0")
     C[0] = Xg[torch.from_numpy(idx[0]).cuda()]
     codes = torch.zeros((N, M), dtype=torch.uint8, device="cuda:0")

@@ -10,8 +10,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 
-@pytest.mark.parametrize("contraction", [0, 1], ids=["f32", "splitbf16"])
-def test_captured_sweep_replays_like_the_eager_call(contraction):
+def test_captured_sweep_replays_like_the_eager_call():
     from paper_1509_05194_amd import hclae
     N, D, M, K, T = 30000 + 7, 128, 3, 256, 4
     X = synth.sift_like(N, D=D)
@@ -20,7 +19,6 @@ def test_captured_sweep_replays_like_the_eager_call(contraction):
     with torch.cuda.stream(s):
         Xg = torch.from_numpy(X).cuda()
         ctx = hclae.Context(N, D, M, K)                   # takes the current stream: s
-        ctx.set_contraction(contraction)
         C = torch.zeros((M, K, D), dtype=torch.float32, device="cuda:0")
         codes = torch.zeros((N, M), dtype=torch.uint8, device="cuda:0")
         r = Xg.clone()

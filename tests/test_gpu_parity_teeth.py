@@ -69,14 +69,12 @@ def _oracle_from(tmp_path, name, text):
 def _fresh_parity_state():
     """The parity module caches oracle states per case: what a planted mistake computes must neither come from
     that cache nor stay in it."""
-    saved, saved_contraction = parity._cache, [m._CONTRACTION for m in (parity, beam, pca)]
+    saved = parity._cache
     parity._cache = {}
-    parity._CONTRACTION = beam._CONTRACTION = pca._CONTRACTION = 0
     try:
         yield
     finally:
         parity._cache = saved
-        parity._CONTRACTION, beam._CONTRACTION, pca._CONTRACTION = saved_contraction
 
 
 def test_parity_slice_passes_against_a_faithful_copy(tmp_path):
