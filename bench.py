@@ -148,7 +148,7 @@ def sweep_bench(args, torch, hclae, synth, dev, gist, extras):
                    "N": N, "D": D, "M": M, "K": K, "iters": T, "queries": Q,
                    "timed_sweep": "first_anneal_sweep",
                    "quant_error_after": E_first},
-        "roofline": {"bound": "mfma", "kernel": "%s (distance contraction on the fp16 matrix cores with rigorous bounds, "
+        "roofline": {"bound": "mfma", "kernel": "%s (distance contraction on the fp16 matrix cores with rounding bounds, "
                                                  "argmin, and the exact decision of what the bounds leave open; the "
                                                  "launches over all N vectors: with the exact shortcuts on, the first "
                                                  "assignment of each stage, which also stores the distance bounds)"

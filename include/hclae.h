@@ -61,7 +61,7 @@ typedef struct {
     double  err_before;      /* (1/N) sum ||e_x||^2 at stage entry                          */
     double  err_after;       /* same at stage exit                                          */
     int64_t codes_changed;   /* vectors whose i_m differs from its value at stage entry     */
-    int64_t refined;         /* vectors of the final assign decided by the fp64 re-check
+    int64_t refined;         /* vectors of the final assign whose scores left several candidates
                                 (with pruning: among the vectors that assign recomputed)    */
     int32_t empty_clusters;  /* codewords with no member at the last centroid update        */
     int32_t iters_run;       /* Lloyd iterations executed                                   */
@@ -125,7 +125,7 @@ int hclae_sweep(hclae_ctx *ctx, const float *X, int64_t N, int D, float *C, int 
  * first sweep as it does there, NULL for the others).  C, codes and residue end with the very
  * bits those calls give; what the single call adds is speed in late sweeps: every stage but the last passes
  * into the next through the fused row pass, from one sweep to the next as well, and (plain Lloyd cool-down with
- * the exact shortcuts on, iters > 0, at least two sweeps that do not seed) each stage keeps the distance bounds it
+ * the exact shortcuts on, N K D > 2^23, iters > 0, at least two sweeps that do not seed) each stage keeps the distance bounds it
  * ends with and starts its next visit from them, widened by how far x' has moved since, so that the first assignment
  * of a stage also runs only over the vectors the bounds cannot settle.  The arrays this needs (16 * M + 8 bytes per
  * vector of N_max) are allocated at the first such call and kept by the ctx.
@@ -175,9 +175,9 @@ int hclae_assign(hclae_ctx *ctx, int m, int64_t N, int D, const float *xp, const
 int hclae_update(hclae_ctx *ctx, int m, int64_t N, int D, const float *xp, float *C,
                  int M, int K, const uint8_t *codes, int32_t *counts);
 
-/* Number of vectors the last hclae_assign (or the last assign inside a stage / encode) sent
- * to the fp64 re-check because their two best fp32 scores were closer than the rounding
- * bound of the fp32 contraction.  Synchronises the stream.  out: HOST. */
+/* Number of vectors that the scores of the last hclae_assign (or the last assign inside a stage / encode)
+ * left undecided, several codewords being closer than the bound of the rounding:
+ * those are decided from the fp32 rows, in fp32 or fp64 (hclae_set_contraction).  Synchronises the stream.  out: HOST. */
 int hclae_last_refined(hclae_ctx *ctx, int64_t *out);
 
 /* ---- online learning (Sec. 3.4: keep fitting learned dictionaries to newly arriving data) ---- */
@@ -232,7 +232,8 @@ int hclae_set_contraction(hclae_ctx *ctx, int mode);
  * every assignment and every centroid sum of a stage run over all N vectors).  x' is fixed during a stage, so
  * (1) per vector an upper bound on the distance to its codeword and a lower bound on the distance to all
  *     others are kept, aged by how far the codewords move in each centroid update (triangle inequality), and
- *     only vectors whose bounds stop separating are assigned again;
+ *     only vectors whose bounds stop separating are assigned again (in stages of more than 2^23 products N K D;
+ *     in smaller ones the assignment of all vectors is the shorter way);
  * (2) the integer totals of the first centroid update are kept and later updates add only the vectors that
  *     changed cluster.
  * The bounds include the rounding bounds of the kernels and the sums are exact integers, so the results are
@@ -246,8 +247,8 @@ int hclae_set_pruning(hclae_ctx *ctx, int on);
 
 /*
  * One dictionary of the multi-path encoding.  The beam of every vector is held as residuals
- * r_l = x - a_l of its Lc kept sums a_l:  rows DEVICE float[N][Lc][D], err DEVICE double[N][Lc] =
- * ||r_l||^2 (NULL means all zero and is allowed when Lc == 1, where it only shifts every score).
+ * r_l = x - a_l of its Lc kept sums a_l:  rows DEVICE float[N][Lc][D].  err DEVICE double[N][Lc] = ||r_l||^2 or NULL;
+ * kept for callers and not read, the candidates are ranked by the rows themselves.
  * All K * Lc candidates are scored by ||r_l - c(k)||^2 (the left-hand side of Eq. 3) and the
  * Ln = min(L, K * Lc) smallest are kept in ascending order, equal errors in (l, k) order:
  *   rows_next DEVICE float[N][Ln][D] = r_l - c(k) (must not alias rows), err_next DEVICE double[N][Ln],
@@ -356,8 +357,8 @@ int hclae_code_stats(hclae_ctx *ctx, const uint8_t *codes, int64_t N, int M, int
 
 /* Work since hclae_create or the last reset, counted on the device: out[0] = nearest-codeword assignments run
  * (Sec. 3.1 cool-down and re-encode, Eq. 3 with one path), out[1] = vectors those assignments recomputed (all N
- * of a full assignment, the listed ones of an assignment the distance bounds pruned), out[2] = vectors decided by
- * the fp64 re-check.  out: HOST int64[3].  reset != 0 zeroes the counters.  Synchronises the stream. */
+ * of a full assignment, the listed ones of an assignment the distance bounds pruned), out[2] = vectors the scores
+ * left undecided.  out: HOST int64[3].  reset != 0 zeroes the counters.  Synchronises the stream. */
 int hclae_work_counters(hclae_ctx *ctx, int64_t *out, int reset);
 
 

@@ -16,11 +16,11 @@ constexpr int kChunkD = 64;                         // dims per register-residen
 
 // Exact pruning of the assignments of one stage (x' fixed, only the dictionary moves).  For every vector
 // the stage keeps an upper bound bu on the distance to its own codeword and a lower bound bl on the
-// distance to every other one, both rigorous (they include the rounding bound of the scores).  When
+// distance to every other one, both widened by the rounding bound of the scores.  When
 // the dictionary moves, bu grows by the drift of the own codeword and bl shrinks by the largest drift
 // of another one (triangle inequality); while bu < bl the own codeword is still the unique nearest
 // and the vector is not recomputed.  The others are listed (k_bounds_step) and go through the same
-// contraction, decision and fp64 re-check as before, which also renews their bounds.  The codes are
+// contraction and decision as before, which also renews their bounds.  The codes are
 // therefore exactly those of full assignments.
 //   PRUNE 0: plain assignment.  1: all vectors, and store their bounds.  2: only active[0..*active_count),
 //   and store their bounds.
@@ -34,7 +34,7 @@ struct PruneArgs {
 // -||c_k||^2 / 2 in fp32 (computed in fp64) over the first D coordinates of rows of stride ld, for
 // k < K; -inf for the padding rows up to kpad.
 // One wave per codeword.  Also resets the two counters the assign that follows will fill
-// (refine_count[0]: re-check entries, refine_count[1]: bits of max |x'|).
+// (refine_count[0]: vectors its scores leave undecided, refine_count[1]: bits of max |x'|).
 // keep_absmax 2: max |x'| was left by the row pass that wrote x', spread over amax_parts[0..64) (block_absmax): the
 // largest word becomes refine_count[1] and the words are cleared for the next such pass.
 // entry_copy (or nullptr): receives the K x D dictionary as it is now (the carried bounds price a stage by how far
@@ -48,7 +48,7 @@ __global__ __launch_bounds__(256) void k_codeword_norms(
     const int lane = lane_id();
     const int k = blockIdx.x * (256 / kWave) + (threadIdx.x >> 6);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        refine_count[0] = 0u;                      // re-check entries
+        refine_count[0] = 0u;                      // undecided vectors
         if (!keep_absmax) refine_count[1] = 0u;    // bits of max |x'|
         if (keep_absmax == 2) {
             unsigned mx = 0u;

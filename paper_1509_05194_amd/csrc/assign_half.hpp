@@ -1,5 +1,6 @@
 // Nearest-codeword assignment (Sec. 3.1/3.2; the per-dictionary step of Eq. 3 with one path) whose scores come from the
-// fp16 matrix cores (v_mfma_f32_32x32x16_f16, 16 times the rate of the fp32 MFMA on gfx950) and whose decisions are fp64.
+// fp16 matrix cores (v_mfma_f32_32x32x16_f16, 16 times the rate of the fp32 MFMA on gfx950) and whose decisions are
+// those of fp64.
 //
 //   argmin_k ||x - c_k||^2 = argmax_k ( (x - mu).(c_k - mu) - ||c_k - mu||^2 / 2 )          for any mu
 //
@@ -811,8 +812,8 @@ __device__ __forceinline__ void half_finish(
     }
 }
 
-// Assignment with the whole dictionary resident in LDS as fp16 (KB * NC <= 32: K = 256 up to D = 256).  Tile schedule and
-// register streaming as in the other resident kernels: a wave owns tiles of 32 vectors, streams them from HBM into operand
+// Assignment with the whole dictionary resident in LDS as fp16 (half_lds within a workgroup's LDS: K <= 32 up to D = 2240, 64 up to 1152,
+// 128 up to 576, 256 up to 256).  A wave owns tiles of 32 vectors, streams them from HBM into operand
 // registers 64 dims at a time with the next chunk in flight, and keeps all 32 KB scores of a vector in accumulators.
 template <int KB, int PRUNE, bool PREFIX>
 __global__ __launch_bounds__(kAssignThreads) void k_assign_half(

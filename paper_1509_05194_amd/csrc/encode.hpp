@@ -26,7 +26,7 @@ __host__ __device__ constexpr int64_t encode_tiles(int64_t N) { return (N + kTil
 __host__ __device__ constexpr int64_t encode_blocks(int64_t N) { return encode_tiles(N) < (1 << 20) ? encode_tiles(N) : (1 << 20); }
 
 // One block per dictionary: fp16 image in the order of half_slot, k-step by k-step; -||C||^2/2 and w per codeword; -mu; the
-// constants (half_constants has the reasons).  Also clears the re-check counter.
+// constants (half_constants has the reasons).  Also clears the counter of undecided vectors.
 __global__ __launch_bounds__(kPrepThreads) void k_encode_prep(
     const float *__restrict__ C, int K, int D, int kb, int NC, char *__restrict__ img, float *__restrict__ hn,
     float *__restrict__ wtab, float *__restrict__ negmu, float *__restrict__ consts, unsigned *__restrict__ refine_count)

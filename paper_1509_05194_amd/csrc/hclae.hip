@@ -105,7 +105,7 @@ struct hclae_ctx {
     float *carry_Centry;         // [K][D] dictionary of the running stage as the stage found it
     float *carry_T;              // [K][K] pair table of the running stage
     unsigned *carry_amax;        // bits of the largest |x'| or |codeword| coordinate of the call so far
-    unsigned long long *work; // [4] work counters: assignments, vectors recomputed, vectors re-checked in fp64
+    unsigned long long *work; // [4] work counters: assignments, vectors recomputed, vectors the scores left undecided
     int64_t *seed_idx;       // [M][K] seed rows of a sweep from all-zero dictionaries (a single stage uses row 0)
     double *part_a, *part_b; // [nparts]
     long long *part_chg;     // [nparts]
@@ -391,7 +391,7 @@ int launch_assign_kb(hclae_ctx *ctx, int m, int64_t N, const float *xp, const fl
     }
 }
 
-// Assumes hneg holds the norms of Cm (over the same dact coordinates) and the re-check counter is zero.
+// Assumes hneg holds the norms of Cm (over the same dact coordinates) and the counter of undecided vectors is zero.
 int launch_assign(hclae_ctx *ctx, int m, int64_t N, const float *xp, const float *Cm, uint8_t *codes,
                   int dact = 0, int ld = 0, int prune = 0)
 {
@@ -425,7 +425,7 @@ int launch_bounds_step(hclae_ctx *ctx, int m, int64_t N, const uint8_t *codes, c
     return HCLAE_OK;
 }
 
-// Accumulate + merge; leaves hneg = norms of the new Cm and the re-check counter at zero.
+// Accumulate + merge; leaves hneg = norms of the new Cm and the counter of undecided vectors at zero.
 // have_absmax: refine_count[1] already holds max |xp| (the assign kernel just ran on the same xp).
 // dnorm: leading coordinates whose squares enter the refreshed codeword norms (0 = all).
 // keep_totals: also store the integer sums, the counts and the code column, so that the following centroid
@@ -474,7 +474,7 @@ int launch_update(hclae_ctx *ctx, int m, int64_t N, const float *xp, float *Cm, 
 
 // Centroid update from the vectors that changed cluster since the last update of this stage (x' unchanged,
 // max |x'| still published): exact, see k_merge.  Leaves hneg and the counters as launch_update does.
-// The re-check kernel of the assignment that just ran (launch_assign with prune 3) has listed those vectors.
+// The assignment that just ran (launch_assign with prune 3 or 4) has listed those vectors.
 int launch_update_moved(hclae_ctx *ctx, int m, int64_t N, const float *xp, float *Cm)
 {
     const int D = ctx->D, K = ctx->K;

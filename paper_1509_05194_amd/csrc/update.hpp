@@ -231,7 +231,7 @@ __global__ __launch_bounds__(256) void k_absmax(const float4 *__restrict__ x, in
 // One block per codeword k: n_k = sum_b pcount[b][k];  C_m[k][d] = 2^-s * (sum_b partial[b][k][d]) / n_k
 // with the integer sum exact (so its order is free: 4 groups of blocks in parallel) and the
 // division in fp64; untouched when n_k == 0.  Then hneg[k] = -||c_k||^2/2 for the next
-// assignment, nk[k] = n_k, and the re-check counter is reset (max |x'| stays: x' has not changed).
+// assignment, nk[k] = n_k, and the counter of undecided vectors is reset (max |x'| stays: x' has not changed).
 constexpr int kMergeGroups = 4;
 constexpr int kMergePairs = 256 / kMergeGroups;     // dim pairs per pass
 __global__ __launch_bounds__(256) void k_merge(

@@ -309,7 +309,7 @@ class Context:
         return out.value
 
     def work_counters(self, reset=False):
-        """(assignments run, vectors they recomputed, vectors decided by the fp64 re-check) since the last reset."""
+        """(assignments run, vectors they recomputed, vectors their scores left undecided) since the last reset."""
         out = (ctypes.c_int64 * 3)()
         self._chk(lib().hclae_work_counters(self._h, out, 1 if reset else 0))
         return int(out[0]), int(out[1]), int(out[2])
