@@ -519,12 +519,13 @@ __device__ __forceinline__ void decide_items(
             const HalfItem *it = w.items + (live ? i0 + (lane >> 3) : 0);
             const unsigned n = it->n, old = it->old;
             uint32_t word = it->mask[sub >> 2][sub & 3];
+            float lrest = it->lrest;                                // read before the branch: behind it, it costs a latency of its own
             if (i0 >= rescored && __ballot(live && __popc(word) >= rescore_from(KB, D))) {
                 const bool worth = rescore_items<KB, PRUNE>(w.items + i0, min(32, w.nitems - i0), xp, Cm, hneg, D, ld, K, pa.slack);
                 rescored = worth ? i0 + 32 : w.nitems;
                 word = it->mask[sub >> 2][sub & 3];
+                lrest = it->lrest;
             }
-            const float lrest = it->lrest;
             uint32_t bits = live ? word : 0u;
             const float4 *x = reinterpret_cast<const float4 *>(xp + (size_t)n * ld);
             float best = __builtin_inff(), second = __builtin_inff();
