@@ -156,7 +156,7 @@ __device__ __forceinline__ void init_acc(floatx16 (&acc)[KB], const float *hneg_
 
 // Between two assignments of a stage: age the bounds by the drift of the dictionary (drift[k] >= the
 // distance codeword k moved in the centroid update, 0 for a kept one) and list the vectors that have to be
-// recomputed.  A block takes kBoundSpan consecutive vectors, stages its entries in LDS and claims its stretch
+// recomputed.  A block takes kBoundThreads U consecutive vectors, stages its entries in LDS and claims its stretch
 // of the list with one counter add (*count must be zero on entry; order is free).
 //
 // One codeword that moves far (a cluster of few members) costs every vector its lower bound.  When the
@@ -166,24 +166,29 @@ __device__ __forceinline__ void init_acc(floatx16 (&acc)[KB], const float *hneg_
 // those few is computed afresh from x' (expanded form in fp32 with its rounding bound) and joins the lower bound.
 // Vectors that this settles get their aged bounds and leave the list.  Eight lanes share a vector.
 // Dynamic LDS: kVolatile rows of D floats.
-constexpr int kBoundSpan = 4096;
+// U, the vectors per thread, is as large as leaves a block for every CU: the ranking of the drifts is a prologue that every block
+// pays for, the second look a chain of gathers that wants every CU.  Measured with 1 / 2 / 4: N = 250k (four sweeps of sixteen
+// dictionaries, D = 128, K = 256, the whole call) 46.8 ms / 47.5 / 51.9, the kernel 11.9 us on average with 1 and 21.9 with 4;
+// N = 1M (training, eight dictionaries) 35.0 / 34.2 / 33.9.  Smaller blocks (512 x 2, 256 x 4 at 250k: 47.7, 50.8) and two vectors
+// at a time per eight lanes in the second look (47.5) are slower.
 constexpr int kBoundThreads = 1024;
+template <int U>
 __global__ __launch_bounds__(kBoundThreads) void k_bounds_step(
     const uint8_t *__restrict__ codes, int64_t N, int M, int m, const float *__restrict__ drift, int K,
     float *__restrict__ bu, float *__restrict__ bl, uint32_t *__restrict__ list, unsigned *__restrict__ count,
     const float *__restrict__ xp, int D, const float *__restrict__ Cm)
 {
+    constexpr int SPAN = kBoundThreads * U;
     extern __shared__ float4 smem4[];
     float *vrow = reinterpret_cast<float *>(smem4);
-    __shared__ uint32_t found[kBoundSpan], kept[kBoundSpan];
+    __shared__ uint32_t found[SPAN], kept[SPAN];
     __shared__ float sdrift[256];
     __shared__ unsigned nfound, nkept, base;
     __shared__ float s_vnorm[kVolatile], s_top[kVolatile + 1];
     __shared__ int s_tk[kVolatile + 1];
     if (threadIdx.x < 256) sdrift[threadIdx.x] = (int)threadIdx.x < K ? drift[threadIdx.x] : 0.f;
     if (threadIdx.x == 0) { nfound = 0u; nkept = 0u; }
-    const int64_t n0 = (int64_t)blockIdx.x * kBoundSpan;
-    constexpr int U = kBoundSpan / kBoundThreads;
+    const int64_t n0 = (int64_t)blockIdx.x * SPAN;
     int c[U];
     float u[U], l[U];
 #pragma unroll
@@ -222,7 +227,7 @@ __global__ __launch_bounds__(kBoundThreads) void k_bounds_step(
     __syncthreads();
     const unsigned nf = nfound;
     // worth a gather of those rows of x'?
-    const bool apart = nf * 8u > (unsigned)kBoundSpan;
+    const bool apart = nf * 8u > (unsigned)SPAN;
     if (!apart) {
         const unsigned nk0 = nkept;
         if (threadIdx.x == 0 && nf + nk0) base = atomicAdd(count, nf + nk0);
@@ -237,6 +242,7 @@ __global__ __launch_bounds__(kBoundThreads) void k_bounds_step(
     }
     __syncthreads();
     {
+        static_assert(kBoundThreads / kWave >= kVolatile, "a wave per row");
         const int w = threadIdx.x >> 6;                             // the first kVolatile waves, one row each
         if (w < kVolatile) {
             double q = 0.0;
@@ -301,6 +307,8 @@ __global__ __launch_bounds__(kBoundThreads) void k_bounds_step(
     __syncthreads();
     for (unsigned i = threadIdx.x; i < nk; i += kBoundThreads) list[base + i] = kept[i];
 }
+
+constexpr int kBoundSpan = 4096;                     // of k_bounds_carry
 
 // ---- Distance bounds carried from one sweep to the next (several sweeps in one call, plain Lloyd cool-down) ----
 // When a sweep comes back to stage m, C_m and column m of the codes are as the stage's last visit left them

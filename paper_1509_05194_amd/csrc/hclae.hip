@@ -411,13 +411,17 @@ int launch_assign(hclae_ctx *ctx, int m, int64_t N, const float *xp, const float
 int launch_bounds_step(hclae_ctx *ctx, int m, int64_t N, const uint8_t *codes, const float *xp, const float *Cm)
 {
     Timed t_(ctx, HCLAE_T_BOUNDS);
-    const uint64_t attr_set = 1ull << 6;        // this call site's bit in ctx->attr_done
+    // vectors per thread: as many as leave a block for every CU (see k_bounds_step)
+    const int64_t per = N / ((int64_t)ctx->cus * kBoundThreads);
+    const int u = per < 1 ? 1 : per < 2 ? 2 : 4, span = kBoundThreads * u;
+    auto kern = u == 1 ? &k_bounds_step<1> : u == 2 ? &k_bounds_step<2> : &k_bounds_step<4>;
+    const uint64_t attr_set = 1ull << (u == 1 ? 4 : u == 2 ? 5 : 6);        // this instance's bit in ctx->attr_done
     if (!(ctx->attr_done & attr_set)) {
-        HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_bounds_step),
+        HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                          hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget - 40 * 1024));
         ctx->attr_done |= attr_set;
     }
-    hipLaunchKernelGGL(k_bounds_step, dim3((unsigned)((N + kBoundSpan - 1) / kBoundSpan)), dim3(kBoundThreads),
+    hipLaunchKernelGGL(kern, dim3((unsigned)((N + span - 1) / span)), dim3(kBoundThreads),
                        (size_t)kVolatile * ctx->D * sizeof(float), ctx->stream,
                        codes, N, ctx->M, m, ctx->drift, ctx->K, ctx->cur_u, ctx->cur_l,
                        ctx->active, ctx->moved_count + 3, xp, ctx->D, Cm);
