@@ -52,12 +52,12 @@ struct HalfItem {
     uint32_t pad;
 };
 
-// Every wave lists its undecided vectors in a stretch of its own of one array in global memory, 32 per tile of its share;
-// entries the array needs for launches over at most N vectors with at most `waves` waves: a wave's share is rounded up to whole
-// tiles, ceil(N / 32 / waves) of them, which leaves less than a tile per wave unused.
+// Every block lists its undecided vectors in a stretch of its own of one array in global memory, 32 per tile of its share; entries the
+// array needs for launches over at most N vectors with at most `waves` waves: a wave's share is rounded up to whole tiles,
+// ceil(N / 32 / waves) of them, which leaves less than a tile per wave unused.
 __host__ __device__ constexpr int64_t half_list_entries(int64_t N, int64_t waves) { return N + (waves + 1) * kTileVec; }
-// Blocks of k_assign_half over N vectors: with few tiles one per SIMD before any SIMD gets two.  k_assign_half_chunked, whose blocks
-// take eight tiles at once, never has more.
+// Blocks of k_assign_half over N vectors: with few tiles, four each (one per SIMD).  k_assign_half_chunked, whose blocks take eight tiles
+// at once, never has more.
 __host__ __device__ constexpr int64_t half_blocks(int64_t N, int cus)
 {
     const int64_t blocks = ((N + kTileVec - 1) / kTileVec + 3) / 4;
@@ -66,7 +66,7 @@ __host__ __device__ constexpr int64_t half_blocks(int64_t N, int cus)
 
 // LDS of the kernels: the fp16 dictionary (or two slices of it), then per-codeword constants, mu, and the waves' buffers.
 struct HalfLds {
-    int img, hneg, w, waug, mu, moved, misc, total; // byte offsets
+    int img, hneg, w, waug, mu, moved, misc, open, total;   // byte offsets
 };
 // slices: 64-dim slices of the dictionary held at a time (all nc of them, or the two of k_assign_half_chunked).
 __host__ __device__ constexpr HalfLds half_lds(int kb, int nc, int slices)
@@ -79,6 +79,7 @@ __host__ __device__ constexpr HalfLds half_lds(int kb, int nc, int slices)
     l.mu = l.waug + 64 * kb * 4;
     l.moved = l.mu + 64 * nc * 4;
     l.misc = l.moved + kAssignWaves * kWaveMoved * 8;
+    l.open = l.misc + 128;
     l.total = l.misc + 256;
     return l;
 }
@@ -307,6 +308,39 @@ __device__ __forceinline__ HalfConsts stage_half(
     return half_constants<KB>(lds, L, odd ? other : mine, odd ? mine : other, row, l32 < 2 * RP && !odd, K, NC, scale, inv);
 }
 
+// STEPS 16-dim steps of a tile's contraction.  base: LDS of the first step's operands (half_slot), of which all STEPS are there; live:
+// steps that count (wave-uniform; the others are not contracted).  vec(t): the vectors' operand of step t; then(t)
+// follows step t's MFMAs, and comes for the steps that do not count too.
+// The dictionary's operands are read kAhead MFMAs ahead, in an order that the scheduler may not change: left to itself, with
+// registers scarce, it reads each one right before its MFMA and waits out the latency of LDS 64 times a tile (pruned assignments of
+// a training at N = 1M, D = 128, K = 256: 88 -> 82 us; 6 or 8 ahead are no faster).
+constexpr int kAhead = 4;
+template <int KB, int STEPS, typename Vec, typename Then>
+__device__ __forceinline__ void contract_half(floatx16 (&acc)[KB], const char *base, int h, int r, int live, Vec vec, Then then)
+{
+    constexpr int n = STEPS * KB, P = kAhead < n ? kAhead : n;
+    const char *slot[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) slot[t] = base + half_slot(t, h, r);
+    halfx8 a[P];
+#pragma unroll
+    for (int i = 0; i < P; ++i) a[i] = *reinterpret_cast<const halfx8 *>(slot[(i / KB) & 3] + i * 1024);
+#pragma unroll
+    for (int t = 0; t < STEPS; ++t) {
+        if (t < live) {
+            const halfx8 w = vec(t);
+#pragma unroll
+            for (int b = 0; b < KB; ++b) {
+                const int i = t * KB + b;
+                acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[i % P], w, acc[b], 0, 0, 0);
+                if (i + P < n) a[i % P] = *reinterpret_cast<const halfx8 *>(slot[((i + P) / KB) & 3] + (i + P) * 1024);
+                __builtin_amdgcn_sched_barrier(0x6);                // arithmetic may pass, MFMAs and memory not
+            }
+        }
+        then(t);
+    }
+}
+
 // One 64-dim chunk of a 32-vector tile: x as load_x_chunk leaves it (lane (g, r): dims 8 s + 4 g .. + 3 of row r for
 // s = 0..7), so k-step t takes x[2t] and x[2t + 1].  steps: k-steps of the chunk that hold coordinates (PREFIX).
 template <int KB, bool PREFIX, bool AMAX>
@@ -343,6 +377,64 @@ __device__ __forceinline__ void mfma_chunk_half(
     }
 }
 
+// A value of lane l and of lane l ^ 32: the low half's and the high half's.
+__device__ __forceinline__ uint2 both_halves(unsigned v)
+{
+    const auto s = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return make_uint2(s[0], s[1]);
+}
+__device__ __forceinline__ int min_both(int v)
+{
+    const uint2 s = both_halves((unsigned)v);
+    return min((int)s.x, (int)s.y);
+}
+
+// The largest of a lane's sixteen scores of a block with its last four bits replaced by its index (2^-19 of it): two a step
+// (v_maximum3; fmaxf would quiet NaNs one by one first).
+__device__ __forceinline__ float block_key(const floatx16 &a)
+{
+    float m = -__builtin_inff();
+#pragma unroll
+    for (int v = 0; v < 16; v += 2) {
+        const float x = __uint_as_float((__float_as_uint(a[v]) & ~15u) | (unsigned)v);
+        const float y = __uint_as_float((__float_as_uint(a[v + 1]) & ~15u) | (unsigned)(v + 1));
+        m = __builtin_elementwise_maximum(__builtin_elementwise_maximum(m, x), y);
+    }
+    return m;
+}
+
+// Takes thr from every score, on the matrix cores: one more product of at most 4 terms, thr in three fp16 pieces of 11 bits (the
+// remainders are exact, what they leave of thr is below 2^-33 of it and 2^-35).  |thr| < kHalfMaxThr.
+constexpr float kHalfMaxThr = 6e7f;                 // 1024 times fp16's range, and some
+template <int KB>
+__device__ __forceinline__ void subtract_half(floatx16 (&acc)[KB], float thr, int h)
+{
+    const halfx4 one = h == 0 ? (halfx4){(_Float16)1024.f, (_Float16)1.f, (_Float16)0.0009765625f, (_Float16)0.f}
+                              : (halfx4){(_Float16)0.f, (_Float16)0.f, (_Float16)0.f, (_Float16)0.f};
+    const _Float16 a = (_Float16)(thr * -0.0009765625f);
+    const float r = fmaf((float)a, -1024.f, -thr);
+    const _Float16 b = (_Float16)r;
+    const halfx4 w = {a, b, (_Float16)((r - (float)b) * 1024.f), (_Float16)0.f};
+#pragma unroll
+    for (int i = 0; i < KB; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x8f16(one, w, acc[i], 0, 0, 0);
+}
+
+// Scores that are not negative, as bitmap words of the lane's half of the codewords: the sign bits shifted into a word, an
+// instruction per score.
+template <int KB>
+__device__ __forceinline__ void not_negative(uint32_t (&mk)[4], const floatx16 (&acc)[KB])
+{
+    mk[0] = mk[1] = mk[2] = mk[3] = 0u;
+#pragma unroll
+    for (int i = 0; i < (KB + 1) / 2; ++i) {
+        uint32_t below = 0u;
+#pragma unroll
+        for (int v = KB == 1 ? 15 : 31; v >= 0; --v)
+            below = __builtin_amdgcn_alignbit(below, __float_as_uint(acc[2 * i + (v >> 4)][v & 15]), 31);   // (below << 1) | sign
+        mk[i] = KB == 1 ? ~below & 0xffffu : ~below;
+    }
+}
+
 // Codewords whose score reaches thr, as bitmap words of the lane's half of them, without compare-and-select chains: the sign of
 // score - threshold is shifted into a word (v_alignbit), two instructions per score.
 template <int KB>
@@ -359,12 +451,30 @@ __device__ __forceinline__ void reaching(uint32_t (&mk)[4], const floatx16 (&acc
     }
 }
 
-// What a wave has still to decide (in global memory) and to report (in LDS).
-struct HalfWave {
-    HalfItem *items;
-    unsigned long long *moved;                      // [kWaveMoved]
-    int nitems, nmoved;                             // wave-uniform
+// What a block has still to decide: the items are in global memory, these in LDS.
+struct HalfOpen {
+    unsigned items, many, hard;                     // items; one of them has many candidates; items left to fp64
 };
+
+// What a wave has to report (in LDS), and its block has still to decide.
+struct HalfWave {
+    HalfItem *items;                                // the block's
+    HalfOpen *open;
+    unsigned long long *moved;                      // [kWaveMoved]
+    int nmoved;                                     // wave-uniform
+};
+
+// Before the block's first barrier.
+__device__ __forceinline__ HalfWave half_wave(char *lds, const HalfLds &L, HalfItem *items)
+{
+    HalfWave w;
+    w.items = items;
+    w.open = reinterpret_cast<HalfOpen *>(lds + L.open);
+    w.moved = reinterpret_cast<unsigned long long *>(lds + L.moved) + (threadIdx.x >> 6) * kWaveMoved;
+    w.nmoved = 0;
+    if (threadIdx.x == 0) *w.open = HalfOpen{0u, 0u, 0u};
+    return w;
+}
 
 // LDS of one wave: what its lanes wrote is there for all of them (LDS operations of a wave stay in order; this keeps the
 // compiler from moving them).
@@ -488,14 +598,14 @@ __device__ __attribute__((noinline)) bool rescore_items(
     return change >= 0;
 }
 
-// Decides the wave's items among their candidates.
+// Decides the block's items among their candidates; all its waves take part, eight lanes to an item, so that a block with few tiles
+// (short lists, whose vectors are mostly undecided) is done after one round of gathers.
 //
-// First in fp32, direct form, eight lanes per item (after rescore_items where one of 32 has many candidates): the
-// lanes share a row (contiguous pieces), two candidates at a time.  A sum of n non-negative terms accumulated in fp32 is within
-// eta = (n + 6) 2^-24 of itself relatively, so where the best two are further apart than that, the smaller one is the nearest
-// codeword.  What is left (exact and nearly exact ties) is decided in fp64: direct-form squared distances summed in ascending
-// dimension order, smallest wins, exact ties go to the lowest index; kRefineLanes lanes share an item there and a lane takes one
-// candidate at a time.
+// First in fp32, direct form (after rescore_items where one has many candidates): the lanes share a row (contiguous pieces),
+// two candidates at a time.  A sum of n non-negative terms accumulated in fp32 is within eta = (n + 6) 2^-24 of itself relatively,
+// so where the best two are further apart than that, the smaller one is the nearest codeword.  What is left (exact and nearly exact
+// ties) is decided in fp64: direct-form squared distances summed in ascending dimension order, smallest wins, exact ties go to the
+// lowest index; kRefineLanes lanes share an item there and a lane takes one candidate at a time.
 // PRUNE: the vector's bounds become these distances (the lower one limited by the bound on the codewords left out).
 // Measured at N = 1M, D = 128, K = 256 with a fifth of the vectors undecided: 15 us of the kernel, 55 us with fp64 alone.
 template <int KB, int PRUNE>
@@ -504,28 +614,32 @@ __device__ __forceinline__ void decide_items(
     int M, int m, uint8_t *__restrict__ codes, const PruneArgs &pa,
     unsigned long long *__restrict__ moved_list, unsigned *__restrict__ moved_count)
 {
-    __threadfence_block();                                          // the items were written by other lanes of the wave
-    const int lane = lane_id();
+    __syncthreads();                                                // the items were written by all waves
+    const int nitems = (int)w.open->items;
+    if (!nitems) return;
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
     const int d4 = D >> 2;
     const bool want_moved = moved_list != nullptr;
-    int hard = 0;                                                   // items left for fp64, moved to the front
+    if (w.open->many) {
+        for (int i0 = 32 * wave; i0 < nitems; i0 += 32 * kAssignWaves) {
+            const HalfItem *it = w.items + min(i0 + (lane & 31), nitems - 1);
+            const uint4 q = *reinterpret_cast<const uint4 *>(it->mask[lane >> 5]);
+            const int most = max(max(__popc(q.x), __popc(q.y)), max(__popc(q.z), __popc(q.w)));
+            if (!__ballot(most >= rescore_from(KB, D))) continue;
+            if (!rescore_items<KB, PRUNE>(w.items + i0, min(32, nitems - i0), xp, Cm, hneg, D, ld, K, pa.slack)) break;
+        }
+        __syncthreads();
+    }
     {
         const int sub = lane & 7, first = lane & 56;
         const int d4up = (D + 3) >> 2;
         const float eta = (float)(4 * ((d4up + 7) >> 3) + 6) * 6.1e-8f;
-        int rescored = 0;                                           // items up to here have been through rescore_items
-        for (int i0 = 0; i0 < w.nitems; i0 += 8) {
-            const bool live = i0 + (lane >> 3) < w.nitems;
-            const HalfItem *it = w.items + (live ? i0 + (lane >> 3) : 0);
+        for (int i0 = 8 * wave; i0 < nitems; i0 += 8 * kAssignWaves) {
+            const bool live = i0 + (lane >> 3) < nitems;
+            HalfItem *it = w.items + (live ? i0 + (lane >> 3) : 0);
             const unsigned n = it->n, old = it->old;
-            uint32_t word = it->mask[sub >> 2][sub & 3];
-            float lrest = it->lrest;                                // read before the branch: behind it, it costs a latency of its own
-            if (i0 >= rescored && __ballot(live && __popc(word) >= rescore_from(KB, D))) {
-                const bool worth = rescore_items<KB, PRUNE>(w.items + i0, min(32, w.nitems - i0), xp, Cm, hneg, D, ld, K, pa.slack);
-                rescored = worth ? i0 + 32 : w.nitems;
-                word = it->mask[sub >> 2][sub & 3];
-                lrest = it->lrest;
-            }
+            const uint32_t word = it->mask[sub >> 2][sub & 3];
+            const float lrest = it->lrest;                          // read before the branch: behind it, it costs a latency of its own
             uint32_t bits = live ? word : 0u;
             const float4 *x = reinterpret_cast<const float4 *>(xp + (size_t)n * ld);
             float best = __builtin_inff(), second = __builtin_inff();
@@ -587,17 +701,8 @@ __device__ __forceinline__ void decide_items(
             // (the second condition keeps underflow out: a sum this large has no denormal part that counts)
             const bool sure = best * (1.f + eta) < second * (1.f - eta) && second > 1e-25f;
             const bool lead = live && sub == 0;
-            const unsigned long long left = __ballot(lead && !sure);
-            if (live && !sure) {
-                HalfItem *to = w.items + hard + __popcll(left & ((1ull << first) - 1ull));
-                to->mask[sub >> 2][sub & 3] = word;
-                if (sub == 0) {
-                    to->n = n;
-                    to->old = old;
-                    to->lrest = lrest;
-                }
-            }
-            hard += __popcll(left);
+            if (lead) it->pad = sure ? 0u : 1u;
+            if (lead && !sure) atomicAdd(&w.open->hard, 1u);
             if (lead && sure) {
                 codes[(size_t)n * M + m] = (uint8_t)kbest;
                 if (PRUNE) {
@@ -606,14 +711,17 @@ __device__ __forceinline__ void decide_items(
                 }
             }
             if (want_moved) push_moved(w, lead && sure && old != (unsigned)kbest, n, old, (unsigned)kbest, moved_list, moved_count);
-            __threadfence_block();
         }
     }
+    __syncthreads();
+    if (!w.open->hard) return;
     const int sub = lane & (kRefineLanes - 1);
-    for (int i0 = 0; i0 < hard; i0 += kWave / kRefineLanes) {
+    constexpr int per = kWave / kRefineLanes;
+    for (int i0 = per * wave; i0 < nitems; i0 += per * kAssignWaves) {
         const int e = i0 + lane / kRefineLanes;
-        const bool live = e < hard;
-        const HalfItem it = w.items[live ? e : 0];
+        const HalfItem it = w.items[min(e, nitems - 1)];
+        const bool live = e < nitems && it.pad;
+        if (!__ballot(live)) continue;
         int total = 0;
 #pragma unroll
         for (int i = 0; i < 8; ++i) total += __popc(it.mask[i >> 2][i & 3]);
@@ -674,14 +782,12 @@ __device__ __forceinline__ void decide_items(
     }
 }
 
-// Last step of a tile's contraction: the product's extra dimension.  Returns e, and the norms it is made of.
+// Last step of a tile's contraction: the product's extra dimension.  Returns e, from the vector's norms.
 template <int KB>
 __device__ __forceinline__ float mfma_bound_half(
-    floatx16 (&acc)[KB], const unsigned *__restrict__ waug, float xsq, float dsq, const HalfConsts &c, int lane, float &x2, float &xn)
+    floatx16 (&acc)[KB], const unsigned *__restrict__ waug, float x2, float dsq, float xn, const HalfConsts &c, int lane)
 {
-    x2 = xsq + __shfl_xor(xsq, 32, kWave);
-    xn = sqrtf(x2) * 1.001f;
-    const float e = half_bound(x2, dsq + __shfl_xor(dsq, 32, kWave), xn, c);
+    const float e = half_bound(x2, dsq, xn, c);
     const halfx4 w = {(_Float16)e, (_Float16)0.f, (_Float16)0.f, (_Float16)0.f};
 #pragma unroll
     for (int b = 0; b < KB; ++b) {
@@ -694,65 +800,84 @@ __device__ __forceinline__ float mfma_bound_half(
 
 // Decision for the wave's 32 vectors from their upper scores U_k.  old: the code the vector has now.
 //
-// The best and the second best of a lane's scores are found on keys: the score with its last four bits replaced by its
-// index in the accumulator block (2^-19 of the score, within h).  Where the second one stays below the threshold the
-// best key names the only candidate; only a tile with an undecided vector builds candidate bitmaps.
+// The best score is found on keys that carry their index, because its w decides its lower bound (the largest w of its sixteen
+// neighbours instead leaves 2.5 times as many vectors undecided).  The threshold is then taken from the scores by the matrix cores,
+// so that the candidates are sign bits: one and a half instructions per score for the best, one for the bitmap and, where bounds are
+// kept, half of one for the largest score left out (negative floats are smaller as integers the nearer they are to zero, and smaller
+// than any that is not negative).  The second best on keys took one and a half more, and tiles with an undecided vector (nearly all)
+// another two for the bitmap.
 template <int KB, int PRUNE>
 __device__ __forceinline__ void decide_half(
-    const floatx16 (&acc)[KB], float x2, float xn, float e, const HalfConsts &c, const float *__restrict__ lds_w, int lane, int n,
-    int N, int K, int M, int m, unsigned old, uint8_t *__restrict__ codes, const PruneArgs &pa, HalfWave &w,
+    floatx16 (&acc)[KB], float x2, float xn, float e, const HalfConsts &c, const float *__restrict__ lds_w, int lane,
+    int n, int N, int D, int K, int M, int m, unsigned old, uint8_t *__restrict__ codes, const PruneArgs &pa, HalfWave &w,
     unsigned long long *__restrict__ moved_list, unsigned *__restrict__ moved_count)
 {
     const int h = lane >> 5;
-    const float inf = opaque(__builtin_inff());
-    float mx = -__builtin_inff(), m2 = -__builtin_inff();            // best and second best key
-    int blk = 0;
-#pragma unroll
-    for (int b = 0; b < KB; ++b) {                                   // one chain: chains side by side cost registers
-        const float before = mx;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const float key = __uint_as_float((__float_as_uint(acc[b][v]) & ~15u) | (unsigned)v);
-            m2 = __builtin_amdgcn_fmed3f(mx, m2, key);               // m2 <= mx always: the median is the new second
-            mx = __builtin_amdgcn_fmed3f(mx, key, inf);              // the larger one
-        }
-        blk = mx != before ? b : blk;
-    }
-    const int v = (int)(__float_as_uint(mx) & 15u);
-    int code = 32 * blk + 8 * (v >> 2) + 4 * h + (v & 3);
+    float mx = -__builtin_inff();
+    int code = 0;
     {
-        const float mxo = __shfl_xor(mx, 32, kWave), m2o = __shfl_xor(m2, 32, kWave);
-        const int co = __shfl_xor(code, 32, kWave);
-        m2 = fmaxf(fminf(mx, mxo), fmaxf(m2, m2o));
-        if (mxo > mx || (mxo == mx && h == 1)) code = co;            // the two halves agree
-        mx = fmaxf(mx, mxo);
+        int blk = 0;
+#pragma unroll
+        for (int b = 0; b < KB; ++b) {
+            const float k = block_key(acc[b]);
+            blk = k > mx ? b : blk;
+            mx = __builtin_elementwise_maximum(mx, k);
+        }
+        const int v = (int)(__float_as_uint(mx) & 15u);
+        code = 32 * blk + 8 * (v >> 2) + 4 * h + (v & 3);
+        const uint2 s = both_halves(__float_as_uint(mx)), k = both_halves((unsigned)code);
+        const float lo = __uint_as_float(s.x), hi = __uint_as_float(s.y);
+        mx = __builtin_elementwise_maximum(lo, hi);
+        code = (int)(lo >= hi ? k.x : k.y);
+        code = code < K ? code : 0;                                 // beyond K only with non-finite input
     }
-    code = code < K ? code : 0;                                     // beyond K only with non-finite input
-    // h, and what the index bits did to the keys (to a zero, too)
-    const float hh = fmaf(c.hx, xn, fmaf(2.1e-6f, fabsf(mx), c.h)) + 1e-36f;
-    const float low = mx - 2.f * e * lds_w[code] - hh;              // lower bound of the best one's true score
+    // h, what the index bits did to the best key, and what the subtraction of the threshold may lose of the larger of it and a
+    // score that is near it
+    const float hh = fmaf(c.hx, xn, fmaf(4.3e-6f, fabsf(mx), fmaf(4.4e-6f * e, c.cmax, c.h))) + 1e-9f;
+    const float low = mx - 2.f * e * lds_w[code] - hh;   // lower bound of the best one's true score
     const float thr = low - hh;                                     // candidates: U_k + h >= low
-    const bool big = !(x2 < kHalfMaxNorm * kHalfMaxNorm && fabsf(thr) < 1e37f);   // may not fit fp16
-    const bool amb = K > 1 && n < N && (big || !(m2 < thr));
+    const bool big = !(x2 < kHalfMaxNorm * kHalfMaxNorm && fabsf(thr) < kHalfMaxThr);   // may not fit fp16
+    subtract_half<KB>(acc, thr, h);
+    uint32_t mk[4];
+    not_negative<KB>(mk, acc);
+    float m2 = 0.f;                                                 // largest U_k below the threshold
+    bool rest = false;                                              // there is one
+    if (PRUNE) {
+        int s = 0x7fffffff;
+#pragma unroll
+        for (int b = 0; b < KB; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; v += 2) s = min(min(s, __float_as_int(acc[b][v])), __float_as_int(acc[b][v + 1]));
+        s = min_both(s);
+        rest = s < 0;
+        m2 = thr + __int_as_float(s);
+    }
+    // a single candidate is the best one
+    const uint2 count = both_halves((unsigned)(__popc(mk[0]) + __popc(mk[1]) + __popc(mk[2]) + __popc(mk[3])));
+    const bool single = count.x + count.y == 1u;
+    const bool amb = K > 1 && n < N && (big || !single);
     const bool mine = h == 0 && n < N;
-    float slack = 0.f;
-    if (PRUNE) slack = pa.slack * (x2 + 2.f * fabsf(mx) + 2.f * fabsf(m2));
-    if (mine && !amb) {
-        codes[(size_t)n * M + m] = (uint8_t)code;
-        if (PRUNE) {
-            // d^2 = ||X||^2 - 2 score.  slack covers the fp32 evaluation: x2 is a chain of D/2 fused multiply-adds per lane
-            // (relative error <= (D/2 + 1) 2^-24, all terms positive), the rest a handful of roundings; pa.slack = (D/2 + 16) 2^-23.
+    float lrest = __builtin_inff();                                 // lower bound on the distance to what is left out
+    if (PRUNE) {
+        // d^2 = ||X||^2 - 2 score.  slack covers the fp32 evaluation: x2 is a chain of D/2 fused multiply-adds per lane
+        // (relative error <= (D/2 + 1) 2^-24, all terms positive), the rest a handful of roundings; pa.slack = (D/2 + 16) 2^-23.
+        const float slack = pa.slack * (x2 + 2.f * fabsf(mx) + 2.f * fabsf(m2));
+        const float out = m2 + fmaf(2.2e-6f, fabsf(m2), hh);        // the subtraction again, of a score far below the threshold
+        if (rest && !big) lrest = sqrtf(fmaxf(0.f, (x2 - 2.f * out) - slack)) * 0.99999f * c.inv;
+        if (mine && !amb) {
             // (a single codeword has no other one to be nearer than: settled for good)
             pa.bu[n] = K > 1 ? sqrtf(fmaxf(0.f, (x2 - 2.f * low) + slack)) * 1.00001f * c.inv : 0.f;
-            pa.bl[n] = K > 1 ? sqrtf(fmaxf(0.f, (x2 - 2.f * (m2 + hh)) - slack)) * 0.99999f * c.inv : __builtin_inff();
+            pa.bl[n] = K > 1 ? lrest : __builtin_inff();
         }
     }
+    if (mine && !amb) codes[(size_t)n * M + m] = (uint8_t)code;
     if (moved_list) push_moved(w, mine && !amb && old != (unsigned)code, (unsigned)n, old, (unsigned)code, moved_list, moved_count);
     const uint32_t who = (uint32_t)__ballot(amb && h == 0);
     if (!who) return;
+    unsigned at = 0;
+    if (lane == 0) at = atomicAdd(&w.open->items, (unsigned)__popc(who));
+    at = __builtin_amdgcn_readfirstlane(at);
     constexpr int NW = (KB + 1) / 2;
-    uint32_t mk[4];
-    reaching<KB>(mk, acc, thr);
     if (big) {
 #pragma unroll
         for (int i = 0; i < NW; ++i) {
@@ -763,16 +888,16 @@ __device__ __forceinline__ void decide_half(
         }
     }
     if (amb) {
-        HalfItem *it = w.items + w.nitems + __popc(who & ((1u << (lane & 31)) - 1u));
+        HalfItem *it = w.items + at + __popc(who & ((1u << (lane & 31)) - 1u));
         if (h == 0) {
             it->n = (uint32_t)n;
             it->old = old;
-            // codewords left out have a true score <= thr + h
-            it->lrest = PRUNE && !big ? sqrtf(fmaxf(0.f, (x2 - 2.f * (thr + hh)) - slack)) * 0.99999f * c.inv : __builtin_inff();
+            it->lrest = lrest;
         }
         *reinterpret_cast<uint4 *>(it->mask[h]) = make_uint4(mk[0], mk[1], mk[2], mk[3]);
     }
-    w.nitems += __popc(who);
+    const int most = max(max(__popc(mk[0]), __popc(mk[1])), max(__popc(mk[2]), __popc(mk[3])));
+    if (amb && most >= rescore_from(KB, D)) w.open->many = 1u;
 }
 
 // End of a block: what its waves have left, with one atomic each: moved vectors, vectors decided again, max |x'|.
@@ -784,18 +909,17 @@ __device__ __forceinline__ void half_finish(
     const int lane = lane_id(), wave = threadIdx.x >> 6;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, kWave));
-    unsigned *tail = reinterpret_cast<unsigned *>(lds + L.misc);   // [8] moved, [8] decided again, [8] max, [1] base
+    unsigned *tail = reinterpret_cast<unsigned *>(lds + L.misc);   // [8] moved, [8], [8] max, [1] base
     if (lane == 0) {
         tail[wave] = (unsigned)w.nmoved;
-        tail[8 + wave] = (unsigned)w.nitems;
         tail[16 + wave] = __float_as_uint(amax);
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        unsigned nm = 0u, nr = 0u, mxb = 0u;
+        unsigned nm = 0u, mxb = 0u;
+        const unsigned nr = w.open->items;
         for (int i = 0; i < kAssignWaves; ++i) {
             nm += tail[i];
-            nr += tail[8 + i];
             mxb = max(mxb, tail[16 + i]);
         }
         if (nm) tail[24] = atomicAdd(moved_count, nm);
@@ -844,19 +968,13 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign_half(
         work[0] += 1ull;                                            // launches on one stream follow one another
         work[1] += (unsigned long long)listed;
     }
-    if ((int)blockIdx.x * 4 >= ntiles) return;                  // no tile for any wave of this block
+    if ((int)blockIdx.x >= ntiles) return;                      // no tile for any wave of this block
 
-    HalfWave w;
-    w.moved = reinterpret_cast<unsigned long long *>(lds + L.moved) + wave * kWaveMoved;
-    w.nitems = 0;
-    w.nmoved = 0;
-
-    const int nslots = (int)gridDim.x * 4;
-    const int tstride = 2 * nslots;
-    const int t0 = (int)blockIdx.x * 4 + (wave & 3) + nslots * (wave >> 2);
+    const int tstride = (int)gridDim.x * kAssignWaves;
+    const int t0 = (int)blockIdx.x + (int)gridDim.x * wave;     // with few tiles, a block each before any block gets two
+    HalfWave w = half_wave(lds, L, items + (size_t)((ntiles + tstride - 1) / tstride) * kTileVec * kAssignWaves * blockIdx.x);
     const int my_tiles = t0 < ntiles ? (ntiles - t0 + tstride - 1) / tstride : 0;
     const int64_t G = (int64_t)my_tiles * NC;                       // (tile, chunk) steps of this wave
-    w.items = items + (size_t)((ntiles + tstride - 1) / tstride) * kTileVec * (blockIdx.x * kAssignWaves + wave);
 
     // vector behind column r of a tile; N (= "none") for the columns of the ragged tail
     auto vec_of = [&](int tile) -> int {
@@ -902,10 +1020,10 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign_half(
             if (more) load_x_chunk<PREFIX>(xn, row_ptr(n_n), q_n, h, D, 2 * steps_of(q_n));
             mfma_chunk_half<KB, PREFIX, PRUNE != 2>(acc, x, lds + L.img, lds_mu, q, lane, c.scale, xsq, dsq, amax, steps_of(q));
             if (q == NC - 1) {
-                float x2, norm;
-                const float e = mfma_bound_half<KB>(acc, reinterpret_cast<const unsigned *>(lds + L.waug), xsq, dsq, c, lane, x2, norm);
-                decide_half<KB, PRUNE>(acc, x2, norm, e, c, reinterpret_cast<const float *>(lds + L.w), lane, n, N, K, M, m, old,
-                                       codes, pa, w, moved_list, moved_count);
+                const float x2 = xsq + __shfl_xor(xsq, 32, kWave), norm = sqrtf(x2) * 1.001f;
+                const float e = mfma_bound_half<KB>(acc, reinterpret_cast<const unsigned *>(lds + L.waug), x2,
+                                                    dsq + __shfl_xor(dsq, 32, kWave), norm, c, lane);
+                decide_half<KB, PRUNE>(acc, x2, norm, e, c, reinterpret_cast<const float *>(lds + L.w), lane, n, N, D, K, M, m, old, codes, pa, w, moved_list, moved_count);
                 init_acc<KB>(acc, lds_h, h);                        // here and not where the next tile begins: dead until now
                 xsq = 0.f;
                 dsq = 0.f;
@@ -921,7 +1039,7 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign_half(
             step(xb, xa, g + 2 < G);
         }
     }
-    if (w.nitems) decide_items<KB, PRUNE>(w, xp, Cm, hneg, D, ld, K, M, m, codes, pa, moved_list, moved_count);
+    decide_items<KB, PRUNE>(w, xp, Cm, hneg, D, ld, K, M, m, codes, pa, moved_list, moved_count);
 
     half_finish<PRUNE>(lds, L, w, amax, refine_count, moved_list, moved_count, work);
 }
@@ -1066,6 +1184,7 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign_half_chunked(
         if (n >= N) n = gather ? (int)pa.active[rows - 1] : N - 1;  // tail columns re-read the last row
         return xp + (size_t)n * ld;
     };
+    HalfWave w = half_wave(lds, L, items + (size_t)((nbt + gridDim.x - 1) / gridDim.x) * kTileVec * kAssignWaves * blockIdx.x);
     int n = vec_of(blockIdx.x);
     const float *xrow = row_ptr(n);
     unsigned old = moved_list && n < N ? codes[(size_t)n * M + m] : 0u;
@@ -1081,11 +1200,6 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign_half_chunked(
     const bool holder = (int)threadIdx.x < 32 * KB;
     const HalfConsts c = half_constants<KB>(lds, L, holder ? sums[2 * threadIdx.x] : 0.f, holder ? sums[2 * threadIdx.x + 1] : 0.f,
                                             threadIdx.x, holder, K, NC, ldexpf(1.f, s), ldexpf(1.f, -s));
-    HalfWave w;
-    w.moved = reinterpret_cast<unsigned long long *>(lds + L.moved) + wave * kWaveMoved;
-    w.nitems = 0;
-    w.nmoved = 0;
-    w.items = items + (size_t)((nbt + gridDim.x - 1) / gridDim.x) * kTileVec * (blockIdx.x * kAssignWaves + wave);
 
     floatx16 acc[KB];
     float amax = 0.f;
@@ -1110,15 +1224,15 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign_half_chunked(
             __syncthreads();                                        // slice q consumed by all, slice qn complete
             par ^= 1;
         }
-        float x2, norm;
-        const float e = mfma_bound_half<KB>(acc, reinterpret_cast<const unsigned *>(lds + L.waug), xsq, dsq, c, lane, x2, norm);
-        decide_half<KB, PRUNE>(acc, x2, norm, e, c, reinterpret_cast<const float *>(lds + L.w), lane, n, N, K, M, m, old, codes, pa,
-                               w, moved_list, moved_count);
+        const float x2 = xsq + __shfl_xor(xsq, 32, kWave), norm = sqrtf(x2) * 1.001f;
+        const float e = mfma_bound_half<KB>(acc, reinterpret_cast<const unsigned *>(lds + L.waug), x2, dsq + __shfl_xor(dsq, 32, kWave),
+                                            norm, c, lane);
+        decide_half<KB, PRUNE>(acc, x2, norm, e, c, reinterpret_cast<const float *>(lds + L.w), lane, n, N, D, K, M, m, old, codes, pa, w, moved_list, moved_count);
         n = n_n;
         xrow = xrow_n;
         old = old_n;
     }
-    if (w.nitems) decide_items<KB, PRUNE>(w, xp, Cm, hneg, D, ld, K, M, m, codes, pa, moved_list, moved_count);
+    decide_items<KB, PRUNE>(w, xp, Cm, hneg, D, ld, K, M, m, codes, pa, moved_list, moved_count);
     half_finish<PRUNE>(lds, L, w, amax, refine_count, moved_list, moved_count, work);
 }
 

@@ -140,8 +140,9 @@ __global__ __launch_bounds__(kAssignThreads) void k_beam_score_half(
         if (more) load_x_chunk(xn, row_ptr(tile_n), q_n, h, D);
         mfma_chunk_half<KB, false, false>(acc, x, lds + L.img, lds_mu, q, lane, c.scale, xsq, dsq, unused, 4);
         if (q == NC - 1) {
-            float x2, norm;
-            const float e = mfma_bound_half<KB>(acc, reinterpret_cast<const unsigned *>(lds + L.waug), xsq, dsq, c, lane, x2, norm);
+            const float x2 = xsq + __shfl_xor(xsq, 32, kWave), norm = sqrtf(x2) * 1.001f;
+            const float e = mfma_bound_half<KB>(acc, reinterpret_cast<const unsigned *>(lds + L.waug), x2,
+                                                dsq + __shfl_xor(dsq, 32, kWave), norm, c, lane);
             const int64_t row = tile * bt.rt + r;
             const bool valid = r < bt.rt && row < nrows;
             beam_select<KB>(acc, x2, norm, e, c, slack, lane, bt.next, bt.hops, Ln, valid, masks + (valid ? row : 0));
@@ -215,8 +216,9 @@ __global__ __launch_bounds__(kAssignThreads) void k_beam_score_half_chunked(
             __syncthreads();
             par ^= 1;
         }
-        float x2, norm;
-        const float e = mfma_bound_half<KB>(acc, reinterpret_cast<const unsigned *>(lds + L.waug), xsq, dsq, c, lane, x2, norm);
+        const float x2 = xsq + __shfl_xor(xsq, 32, kWave), norm = sqrtf(x2) * 1.001f;
+        const float e = mfma_bound_half<KB>(acc, reinterpret_cast<const unsigned *>(lds + L.waug), x2, dsq + __shfl_xor(dsq, 32, kWave),
+                                            norm, c, lane);
         beam_select<KB>(acc, x2, norm, e, c, slack, lane, bt.next, bt.hops, Ln, valid, masks + (valid ? row : 0));
         row = row_n;
         valid = valid_n;
