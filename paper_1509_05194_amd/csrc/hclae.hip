@@ -14,6 +14,7 @@
 #include "assign_half.hpp"
 #include "encode.hpp"
 #include "stream.hpp"
+#include "rows16.hpp"
 #include "update.hpp"
 #include "pca.hpp"
 #include "eigen.hpp"
@@ -105,6 +106,16 @@ struct hclae_ctx {
     float *carry_Centry;         // [K][D] dictionary of the running stage as the stage found it
     float *carry_T;              // [K][K] pair table of the running stage
     unsigned *carry_amax;        // bits of the largest |x'| or |codeword| coordinate of the call so far
+    // fp16 rows of a stage that keeps bounds (rows16.hpp; allocated on first use, null where that failed: such stages read x')
+    _Float16 *r16_rows;          // [N_max][rows16_ld(D)]
+    float2 *r16_norm;            // [N_max]
+    char *r16_img;               // [4 NC][kb] kilobytes: the running dictionary
+    float *r16_sums;             // [32*kb][2]
+    float *r16_negmu;            // [64*NC]
+    float *r16_consts;           // scale, 1 / scale
+    float *r16_ref;              // [K][D] rows that seed the next stage
+    unsigned *r16_words;         // [kWords16]
+    bool stage16;                // the running stage assigns from them
     unsigned long long *work; // [4] work counters: assignments, vectors recomputed, vectors the scores left undecided
     int64_t *seed_idx;       // [M][K] seed rows of a sweep from all-zero dictionaries (a single stage uses row 0)
     double *part_a, *part_b; // [nparts]
@@ -248,10 +259,21 @@ RowGeom row_geom(int D)
 
 // ---- launches (all on ctx->stream) ------------------------------------------------------
 
+RowPass16 row_pass16(const hclae_ctx *ctx)
+{
+    return {ctx->r16_rows, ctx->r16_norm, ctx->r16_negmu, ctx->r16_consts, rows16_ld(ctx->D)};
+}
+
+MergeImage merge_image(const hclae_ctx *ctx)
+{
+    if (!ctx->stage16) return {};
+    return {ctx->r16_img, ctx->r16_sums, ctx->r16_negmu, ctx->r16_consts, ctx->kb};
+}
+
 // amax (heat only): the pass also publishes max |x'| in refine_count[1] (see k_row_pass).
 template <int SIGN, bool STATS>
 int launch_heat_cool(hclae_ctx *ctx, int m, int64_t N, const float *C, const uint8_t *codes, float *r,
-                     double *part_err, bool amax = false, const float *src = nullptr)
+                     double *part_err, bool amax = false, const float *src = nullptr, bool r16 = false)
 {
     if (!src) src = r;                                      // in place
     const RowGeom g = row_geom(ctx->D);
@@ -263,20 +285,26 @@ int launch_heat_cool(hclae_ctx *ctx, int m, int64_t N, const float *C, const uin
     // the row length of the SIFT-shaped configurations has a kernel of its own (addresses and geometry constant:
     // 179 us instead of 185 us for the stage boundary at N = 1M, D = 128); long rows take k_row_pass_wide
     constexpr bool kCanAmax = SIGN > 0 && STATS;
+    unsigned *slots = r16 ? ctx->r16_words + kWordAmax : amax ? ctx->carry_amax + kAmaxSlots : (unsigned *)nullptr;
+    const RowPass16 o16 = r16 ? row_pass16(ctx) : RowPass16{};
+    amax = amax || r16;
     if (amax && !kCanAmax) return fail(ctx, HCLAE_EINVAL, "row pass: max |x'| is a by-product of the heat pass only");
     if (ctx->D >= kWideMinD) {
-        auto kern = (amax && kCanAmax) ? &k_row_pass_wide<SIGN, STATS, kCanAmax> : &k_row_pass_wide<SIGN, STATS, false>;
+        auto kern = r16 ? &k_row_pass_wide<SIGN, STATS, kCanAmax, kCanAmax>
+                  : amax ? &k_row_pass_wide<SIGN, STATS, kCanAmax> : &k_row_pass_wide<SIGN, STATS, false>;
         hipLaunchKernelGGL(kern, dim3(blocks), dim3(kStreamThreads), 0, ctx->stream,
                            r, src, codes, Cm, (const float *)nullptr, N, ctx->D, ctx->M, m, 0, ctx->old_codes, part_err,
-                           ctx->part_chg, amax ? ctx->carry_amax + kAmaxSlots : (unsigned *)nullptr);
+                           ctx->part_chg, slots, o16);
         HIP_TRY(ctx, hipGetLastError());
         return blocks;
     }
-    auto kern = (amax && kCanAmax) ? (ctx->D == 128 ? &k_row_pass<SIGN, STATS, 128, kCanAmax> : &k_row_pass<SIGN, STATS, 0, kCanAmax>)
-                                   : (ctx->D == 128 ? &k_row_pass<SIGN, STATS, 128, false> : &k_row_pass<SIGN, STATS, 0, false>);
+    const bool d128 = ctx->D == 128;
+    auto kern = r16 ? (d128 ? &k_row_pass<SIGN, STATS, 128, kCanAmax, kCanAmax> : &k_row_pass<SIGN, STATS, 0, kCanAmax, kCanAmax>)
+              : amax ? (d128 ? &k_row_pass<SIGN, STATS, 128, kCanAmax> : &k_row_pass<SIGN, STATS, 0, kCanAmax>)
+                     : (d128 ? &k_row_pass<SIGN, STATS, 128, false> : &k_row_pass<SIGN, STATS, 0, false>);
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(kStreamThreads), 0, ctx->stream,
                        r, src, codes, Cm, (const float *)nullptr, N, ctx->D, ctx->M, m, 0, g, ctx->old_codes, part_err,
-                       ctx->part_chg, amax ? ctx->carry_amax + kAmaxSlots : (unsigned *)nullptr);
+                       ctx->part_chg, slots, o16);
     HIP_TRY(ctx, hipGetLastError());
     return blocks;
 }
@@ -359,6 +387,31 @@ int launch_assign_half_chunked(hclae_ctx *ctx, int m, int64_t N, const float *xp
     return HCLAE_OK;
 }
 
+// The assignments of a stage that has its rows in fp16 (rows16.hpp).
+template <int KB, int PRUNE>
+int launch_assign_rows16(hclae_ctx *ctx, int m, int64_t N, const float *xp, const float *Cm, uint8_t *codes, const PruneArgs &pa,
+                         bool want_moved)
+{
+    const Rows16Args x16 = {ctx->r16_rows, ctx->r16_norm, ctx->r16_consts, ctx->r16_img, ctx->r16_sums, rows16_ld(ctx->D),
+                            rows16_ld(ctx->D) / 16};
+    const bool resident = half_resident(ctx, ctx->D), full = x16.steps % 8 == 0;
+    auto kern = !resident ? &k_assign_rows16_chunked<KB, PRUNE>
+                          : full ? &k_assign_rows16<KB, PRUNE, 8> : &k_assign_rows16<KB, PRUNE, 4>;
+    const int64_t nbt = (N + kTileVec * kAssignWaves - 1) / (kTileVec * kAssignWaves);
+    const int64_t blocks = resident ? half_blocks(N, ctx->cus) : nbt < ctx->cus ? nbt : ctx->cus;
+    const uint64_t attr_set = 1ull << (32 + PRUNE);         // this instance's bit in ctx->attr_done (D is the ctx's)
+    if (!(ctx->attr_done & attr_set)) {
+        HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget));
+        ctx->attr_done |= attr_set;
+    }
+    Timed t_(ctx, PRUNE == 2 ? HCLAE_T_ASSIGN_ACTIVE : HCLAE_T_ASSIGN);
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kAssignThreads), (size_t)half_lds(KB, ctx->NC, resident ? ctx->NC : 2).total,
+                       ctx->stream, xp, Cm, ctx->hneg, x16, (int)N, ctx->D, ctx->K, ctx->M, m, ctx->NC, codes, ctx->refine_count, pa,
+                       want_moved ? ctx->moved_list : (unsigned long long *)nullptr, ctx->moved_count, ctx->work, ctx->half_list);
+    HIP_TRY(ctx, hipGetLastError());
+    return HCLAE_OK;
+}
+
 // prune: 0 plain; 1 all vectors and store the stage's bounds; 2 only the vectors k_bounds_step listed; 3 = 2 and 4 = 0, with the
 // vectors that changed cluster listed (over all D coordinates only; the caller checks).
 template <int KB>
@@ -371,6 +424,9 @@ int launch_assign_kb(hclae_ctx *ctx, int m, int64_t N, const float *xp, const fl
     const int NC = (dact + kChunkD - 1) / kChunkD;
     const int dpad = kChunkD * NC;
     pa.slack = (float)(dpad / 2 + 16) * 1.1920929e-7f;
+    if (ctx->stage16 && prune > 0 && prune < 4)
+        return prune == 1 ? launch_assign_rows16<KB, 1>(ctx, m, N, xp, Cm, codes, pa, false)
+                          : launch_assign_rows16<KB, 2>(ctx, m, N, xp, Cm, codes, pa, prune == 3);
     if (half_resident(ctx, dact)) {
         // the last chunk holds fewer than four 16-dim steps with coordinates that count: stop after them
         const bool prefix = (dact % kChunkD) != 0 && (dact % kChunkD) <= kChunkD - kHalfStep;
@@ -471,7 +527,8 @@ int launch_update(hclae_ctx *ctx, int m, int64_t N, const float *xp, float *Cm, 
                        online ? ctx->run_sum + (size_t)m * K * D : (double *)nullptr,
                        online ? ctx->run_cnt + (size_t)m * K : (long long *)nullptr,
                        keep_totals ? ctx->tot_sum : (long long *)nullptr, keep_totals ? ctx->tot_cnt : (int *)nullptr, 0,
-                       keep_totals ? ctx->moved_count : (unsigned *)nullptr, keep_totals ? ctx->drift : (float *)nullptr);
+                       keep_totals ? ctx->moved_count : (unsigned *)nullptr, keep_totals ? ctx->drift : (float *)nullptr,
+                       merge_image(ctx));
     HIP_TRY(ctx, hipGetLastError());
     return HCLAE_OK;
 }
@@ -501,7 +558,7 @@ int launch_update_moved(hclae_ctx *ctx, int m, int64_t N, const float *xp, float
     hipLaunchKernelGGL(k_merge, dim3(K), dim3(256), 0, ctx->stream,
                        ctx->partial, ctx->pcount, nb, K, D, D, Cm, ctx->hneg, ctx->nk, (int *)nullptr,
                        ctx->refine_count, (double *)nullptr, (long long *)nullptr, ctx->tot_sum, ctx->tot_cnt, 1,
-                       ctx->moved_count, ctx->drift);
+                       ctx->moved_count, ctx->drift, merge_image(ctx));
     HIP_TRY(ctx, hipGetLastError());
     return HCLAE_OK;
 }
@@ -528,6 +585,54 @@ bool bounds_pay(const hclae_ctx *ctx, int64_t N)
     return ctx->pruning && (double)N * ctx->K * ctx->D > 8388608.0;
 }
 
+// Arrays of the fp16 rows, allocated once per ctx at the first stage that keeps bounds.  Where that cannot be (no memory, or the
+// stream is being captured) the stage reads x' itself, with the same results: the caller goes on.
+void rows16_scratch(hclae_ctx *ctx)
+{
+    if (ctx->r16_rows) return;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return;
+    }
+    const size_t n = (size_t)ctx->N_max, rows = n * rows16_ld(ctx->D) * sizeof(_Float16);
+    struct { void **p; size_t bytes; } allocs[] = {
+        {(void **)&ctx->r16_norm, sizeof(float2) * n},
+        {(void **)&ctx->r16_img, (size_t)ctx->NC * ctx->kb * 4096},
+        {(void **)&ctx->r16_sums, sizeof(float) * 2 * 32 * ctx->kb},
+        {(void **)&ctx->r16_negmu, sizeof(float) * kChunkD * ctx->NC},
+        {(void **)&ctx->r16_consts, 256},
+        {(void **)&ctx->r16_ref, sizeof(float) * (size_t)ctx->K * ctx->D},
+        {(void **)&ctx->r16_words, sizeof(unsigned) * kWords16},
+        {(void **)&ctx->r16_rows, rows},                    // last: its presence says that all are there
+    };
+    hipError_t e = hipSuccess;
+    for (auto &a : allocs)
+        if (e == hipSuccess) e = hipMalloc(a.p, a.bytes);
+    // what lies beyond D in a row, and the words, start at zero
+    if (e == hipSuccess && rows16_ld(ctx->D) != ctx->D) e = hipMemsetAsync(ctx->r16_rows, 0, rows, ctx->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(ctx->r16_words, 0, sizeof(unsigned) * kWords16, ctx->stream);
+    if (e == hipSuccess) return;
+    (void)hipGetLastError();
+    for (auto &a : allocs) {
+        if (*a.p) (void)hipFree(*a.p);
+        *a.p = nullptr;
+    }
+}
+
+// Centre and scale of the rows that the coming pass writes for stage `next`: from stage m (Cm; null: the heat pass of `next` itself),
+// with the stage's seeds or null.
+int launch_rows16_ref(hclae_ctx *ctx, const float *Cm, int m, int next, int64_t N, const float *C, const uint8_t *codes,
+                      const float *residue, const int64_t *seeds)
+{
+    Timed t_(ctx, HCLAE_T_NORMS);
+    hipLaunchKernelGGL(k_rows16_ref, dim3((ctx->K + kRefSamples + 3) / 4), dim3(256), 0, ctx->stream,
+                       residue, codes, Cm, C + (size_t)next * ctx->K * ctx->D, N, ctx->D, ctx->K, ctx->M, m, next, ctx->NC, seeds,
+                       ctx->r16_ref, ctx->r16_negmu, ctx->r16_consts, ctx->r16_words);
+    HIP_TRY(ctx, hipGetLastError());
+    return HCLAE_OK;
+}
+
 // Enqueues one full stage; by-products land in ctx->rec[slot].  No host synchronisation.
 // heated: residue already holds x' of this stage and ctx->part_a its entry error (the previous
 // stage ended with a fused transition).  next: >= 0 ends the stage with the fused transition into
@@ -538,25 +643,41 @@ bool bounds_pay(const hclae_ctx *ctx, int64_t N)
 // either, max |x'| comes from the row pass that wrote x' (the first assignment may not read every row).
 // next_amax: the fused pass into the next stage takes max |x'| for it (that stage runs with carry != 0).
 int enqueue_stage(hclae_ctx *ctx, int m, int64_t N, float *C, uint8_t *codes, float *residue, int iters,
-                  const int64_t *seed_dev, int slot, bool heated = false, int next = -1, int carry = 0,
-                  bool next_amax = false)
+                  const int64_t *seed_dev, int slot, bool heated = false, int next = -1, const int64_t *next_seed = nullptr,
+                  int carry = 0, bool next_amax = false)
 {
     const int D = ctx->D, K = ctx->K;
     float *Cm = C + (size_t)m * K * D;
     int rc;
+    const bool prune = iters > 0 && bounds_pay(ctx, N);
+    if (!heated && prune) rows16_scratch(ctx);
+    ctx->stage16 = prune && ctx->r16_rows;                  // the same for all stages of a call
+    struct Done {
+        hclae_ctx *c;
+        ~Done() { c->stage16 = false; }
+    } done{ctx};
     if (carry && (!bounds_pay(ctx, N) || iters <= 0 || seed_dev || !ctx->carry_u))
         return fail(ctx, HCLAE_ESTATE, "stage: carried bounds need pruning, iters > 0 and no seeding");
     ctx->cur_u = carry ? ctx->carry_u + (size_t)m * ctx->N_max : ctx->bnd_u;
     ctx->cur_l = carry ? ctx->carry_l + (size_t)m * ctx->N_max : ctx->bnd_l;
     if (!heated) {
-        const int pb = launch_heat_cool<+1, true>(ctx, m, N, C, codes, residue, ctx->part_a, carry != 0);
+        if (ctx->stage16 && (rc = launch_rows16_ref(ctx, nullptr, 0, m, N, C, codes, residue, seed_dev)) != HCLAE_OK) return rc;
+        const int pb = launch_heat_cool<+1, true>(ctx, m, N, C, codes, residue, ctx->part_a, carry != 0, nullptr, ctx->stage16);
         if (pb < 0) return pb;
     }
     if (seed_dev) {
         hipLaunchKernelGGL(k_seed, dim3(K), dim3(256), 0, ctx->stream, residue, seed_dev, K, D, Cm);
         HIP_TRY(ctx, hipGetLastError());
     }
-    if ((rc = launch_norms(ctx, Cm, 0, 0, carry ? 2 : 0)) != HCLAE_OK) return rc;
+    if (ctx->stage16) {
+        Timed t_(ctx, HCLAE_T_NORMS);
+        hipLaunchKernelGGL(k_rows16_image, dim3(8 * ctx->kb), dim3(256), 0, ctx->stream, Cm, K, D, ctx->kb, ctx->NC, ctx->r16_negmu,
+                           ctx->r16_consts, ctx->r16_img, ctx->r16_sums, ctx->hneg, ctx->refine_count, ctx->r16_words,
+                           carry ? ctx->carry_Centry : (float *)nullptr, carry ? ctx->moved_count + 3 : (unsigned *)nullptr);
+        HIP_TRY(ctx, hipGetLastError());
+    } else if ((rc = launch_norms(ctx, Cm, 0, 0, carry ? 2 : 0)) != HCLAE_OK) {
+        return rc;
+    }
     if (carry == 2) {
         Timed t_(ctx, HCLAE_T_BOUNDS);
         // (8M + 16) 2^-24 sqrt(D), times the largest coordinate seen: the roundings of the passes since the last visit
@@ -571,7 +692,6 @@ int enqueue_stage(hclae_ctx *ctx, int m, int64_t N, float *C, uint8_t *codes, fl
     // With pruning the first assignment stores distance bounds for every vector; after each centroid update
     // (which also reports how far every codeword moved) only the vectors whose bounds no longer separate
     // their codeword from the others are assigned again.  The first update must then keep its totals.
-    const bool prune = iters > 0 && bounds_pay(ctx, N);
     for (int t = 0; t < iters; ++t) {
         if (prune && t > 0 && (rc = launch_bounds_step(ctx, m, N, codes, residue, Cm)) != HCLAE_OK) return rc;
         if ((rc = launch_assign(ctx, m, N, residue, Cm, codes, 0, 0, prune ? (t == 0 ? (carry == 2 ? 2 : 1) : 3)
@@ -597,22 +717,25 @@ int enqueue_stage(hclae_ctx *ctx, int m, int64_t N, float *C, uint8_t *codes, fl
         pa = launch_heat_cool<-1, true>(ctx, m, N, C, codes, residue, ctx->part_b);
         if (pa < 0) return pa;
     } else {
+        const bool r16 = ctx->stage16;
+        if (r16 && (rc = launch_rows16_ref(ctx, Cm, m, next, N, C, codes, residue, next_seed)) != HCLAE_OK) return rc;
         const RowGeom g = row_geom(D);
         pa = heat_cool_blocks(N, D, ctx->cus);
+        unsigned *slots = r16 ? ctx->r16_words + kWordAmax : next_amax ? ctx->carry_amax + kAmaxSlots : (unsigned *)nullptr;
+        const RowPass16 o16 = r16 ? row_pass16(ctx) : RowPass16{};
         Timed t_(ctx, HCLAE_T_TRANSITION);
         if (D >= kWideMinD) {
-            auto kern = next_amax ? &k_row_pass_wide<0, true, true> : &k_row_pass_wide<0, true, false>;
+            auto kern = r16 ? &k_row_pass_wide<0, true, true, true> : next_amax ? &k_row_pass_wide<0, true, true> : &k_row_pass_wide<0, true, false>;
             hipLaunchKernelGGL(kern, dim3(pa), dim3(kStreamThreads), 0, ctx->stream,
                                residue, residue, codes, Cm, C + (size_t)next * K * D, N, D, ctx->M, m, next,
-                               ctx->old_codes, ctx->part_b, ctx->part_chg,
-                               next_amax ? ctx->carry_amax + kAmaxSlots : (unsigned *)nullptr);
+                               ctx->old_codes, ctx->part_b, ctx->part_chg, slots, o16);
         } else {
-            auto kern = next_amax ? (D == 128 ? &k_row_pass<0, true, 128, true> : &k_row_pass<0, true, 0, true>)
+            auto kern = r16 ? (D == 128 ? &k_row_pass<0, true, 128, true, true> : &k_row_pass<0, true, 0, true, true>)
+                      : next_amax ? (D == 128 ? &k_row_pass<0, true, 128, true> : &k_row_pass<0, true, 0, true>)
                                   : (D == 128 ? &k_row_pass<0, true, 128, false> : &k_row_pass<0, true, 0, false>);
             hipLaunchKernelGGL(kern, dim3(pa), dim3(kStreamThreads), 0, ctx->stream,
                                residue, residue, codes, Cm, C + (size_t)next * K * D, N, D, ctx->M, m, next, g,
-                               ctx->old_codes, ctx->part_b, ctx->part_chg,
-                               next_amax ? ctx->carry_amax + kAmaxSlots : (unsigned *)nullptr);
+                               ctx->old_codes, ctx->part_b, ctx->part_chg, slots, o16);
         }
         HIP_TRY(ctx, hipGetLastError());
     }
@@ -856,6 +979,7 @@ int hclae_destroy(hclae_ctx *ctx)
                    ctx->run_sum, ctx->run_cnt, ctx->n0_dev, ctx->pca_rt, ctx->pca_crot, ctx->pca_colpart,
                    ctx->pca_grampart, ctx->pca_mean, ctx->pca_mean32, ctx->pca_cov, ctx->pca_R, ctx->pca_xr,
                    ctx->stats_buf, ctx->order_var, ctx->order_idx, ctx->order_tmp,
+                   ctx->r16_rows, ctx->r16_norm, ctx->r16_img, ctx->r16_sums, ctx->r16_negmu, ctx->r16_consts, ctx->r16_ref, ctx->r16_words,
                    ctx->carry_u, ctx->carry_l, ctx->carry_path, ctx->carry_snap, ctx->carry_Centry, ctx->carry_T, ctx->carry_amax,
                    ctx->beam_rows[0], ctx->beam_rows[1],
                    ctx->beam_pre[0], ctx->beam_pre[1], ctx->beam_mask};
@@ -1099,7 +1223,8 @@ int hclae_sweep(hclae_ctx *ctx, const float *X, int64_t N, int D, float *C, int 
         const bool fuse = (reencode_mode == 0) && ctx->cooldown == HCLAE_COOLDOWN_LLOYD;
         rc = ctx->cooldown == HCLAE_COOLDOWN_IMPROVED
                  ? enqueue_stage_cooldown_pca(ctx, m, N, C, codes, residue, iters, idx, m, nullptr)
-                 : enqueue_stage(ctx, m, N, C, codes, residue, iters, idx, m, fuse && m > 0, (fuse && m + 1 < M) ? m + 1 : -1);
+                 : enqueue_stage(ctx, m, N, C, codes, residue, iters, idx, m, fuse && m > 0, (fuse && m + 1 < M) ? m + 1 : -1,
+                                 idx && m + 1 < M ? idx + K : nullptr);
         if (rc != HCLAE_OK) return rc;
         if (reencode_mode != 0) {
             rc = reencode_mode == 1 ? enqueue_encode(ctx, X, N, C, codes, residue)
@@ -1198,8 +1323,9 @@ int hclae_anneal(hclae_ctx *ctx, int64_t N, int D, float *C, int M, int K, uint8
                 const int mode = !carry || s < first_kept ? 0 : s == first_kept ? 1 : 2;
                 const int s_next = m + 1 < M ? s : s + 1;
                 const bool next_kept = carry && !last && s_next >= first_kept;
+                const int64_t *next_seeds = (init_idx && s_next == 0) ? ctx->seed_idx + (size_t)(m + 1) * K : nullptr;
                 rc = enqueue_stage(ctx, m, N, C, codes, residue, iters, seeds, m, !(s == 0 && m == 0),
-                                   last ? -1 : (m + 1) % M, mode, next_kept);
+                                   last ? -1 : (m + 1) % M, next_seeds, mode, next_kept);
             } else {
                 rc = enqueue_stage_cooldown_pca(ctx, m, N, C, codes, residue, iters, seeds, m, nullptr);
             }

@@ -3,7 +3,7 @@
 // thread moves one float4 per row pass, a wave covers contiguous kilobytes, the K x D
 // codebook (<= 1 MB) stays in L2.
 #pragma once
-#include "common.hpp"
+#include "assign_half.hpp"
 
 namespace hclae {
 
@@ -38,6 +38,22 @@ __device__ __forceinline__ void block_absmax(float amax, float *scratch, unsigne
     }
 }
 
+// Where a row pass leaves the fp16 operands of what it writes (rows16.hpp has their layout), and in which centre and scale.
+struct RowPass16 {
+    _Float16 *rows;                                 // [N][ld]
+    float2 *norm;                                   // [N] {||X||^2, ||X - X^||^2}
+    const float *negmu, *consts;
+    int ld;
+};
+
+// The operands of column c4 of a row; adds to the norms.
+__device__ __forceinline__ void put_rows16(_Float16 *row, int c4, const floatx4 &w, const float4 &neg, float scale,
+                                           float &sq, float &dsq)
+{
+    const halfx4 q = half4(scaled(make_float4(w.x, w.y, w.z, w.w), scale, neg), sq, dsq);
+    __builtin_nontemporal_store(q, reinterpret_cast<halfx4 *>(row + 16 * (c4 >> 2) + 8 * (c4 & 1) + 4 * ((c4 >> 1) & 1)));
+}
+
 // The in-place row passes of a stage (Sec. 3.1), one kernel body:
 //   MODE +1  heat       r_n += C_m[i_m(n)]; by-products: column m of the codes saved (old_codes), sum ||e_x||^2 of the input
 //   MODE -1  new residue r_n -= C_m[i_m(n)]; by-products: sum ||e_x||^2 of the output, codes that differ from old_codes
@@ -59,12 +75,15 @@ __device__ __forceinline__ void block_absmax(float amax, float *scratch, unsigne
 // DT: the row length as a compile-time constant (with the geometry row_geom gives it), or 0: taken from D and g.
 // AMAX (MODE +1 and 0): max |x'| over everything written is merged into absmax_slot[0..kAmaxSlots) (block_absmax), for
 // a stage whose first assignment does not read every row and so cannot provide it.
-template <int MODE, bool STATS, int DT = 0, bool AMAX = false>
+// R16 (MODE +1 and 0, with AMAX): what is written is also left as fp16 operands, with its norms: 24 % more bytes; stage boundary at
+// N = 1M, D = 128 175 -> 225 us (5.7 TB/s as without).  Addresses as a scalar base and a 32-bit offset are what keeps it to 128
+// registers, two blocks per CU: with 64-bit addresses per thread it took 297 us.
+template <int MODE, bool STATS, int DT = 0, bool AMAX = false, bool R16 = false>
 __global__ __launch_bounds__(kStreamThreads) void k_row_pass(
     float *r, const float *src, const uint8_t *__restrict__ codes, const float *__restrict__ Cm, const float *__restrict__ Cj,
     int64_t N, int D_rt, int M, int m, int j_stage, RowGeom g_rt,
     uint8_t *__restrict__ old_codes, double *__restrict__ part_err, long long *__restrict__ part_chg,
-    unsigned *__restrict__ absmax_slot = nullptr)
+    unsigned *__restrict__ absmax_slot, RowPass16 o16)
 {
     __shared__ double red[kStreamThreads / kWave];
     constexpr int U = kStreamUnroll;
@@ -84,72 +103,83 @@ __global__ __launch_bounds__(kStreamThreads) void k_row_pass(
     long long chg = 0;
     float amax = 0.f;
 
-    // rows n0 + u * rows of a group; the loads of a step take rows clamped into range (never used beyond N)
-    auto load_codes = [&](int64_t n0, int (&a)[U], int (&b)[U]) {
+    // Rows nb + ty + u * rows of a group, nb the same for the block: addresses are a scalar base and 32 bits of a thread's own.
+    // The loads of a step take rows clamped into range (never used beyond N).
+    auto last_of = [&](int64_t nb) { return (int)(N - 1 - nb < kStreamThreads * U ? N - 1 - nb : kStreamThreads * U); };
+    auto load_codes = [&](int64_t nb, int (&a)[U], int (&b)[U]) {
+        const uint8_t *at = codes + nb * M;
+        const int last = last_of(nb);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int64_t n = n0 + (int64_t)u * rows;
-            const int64_t nn = n < N ? n : N - 1;
-            a[u] = codes[nn * M + m];
-            if (MODE == 0) b[u] = codes[nn * M + j_stage];
+            const unsigned i = (unsigned)min(ty + u * rows, last) * (unsigned)M;
+            a[u] = at[i + (unsigned)m];
+            if (MODE == 0) b[u] = at[i + (unsigned)j_stage];
         }
     };
-    auto load_rows = [&](int64_t n0, int c4, floatx4 (&v)[U]) {
-        const int cc = c4 < g.d4 ? c4 : g.d4 - 1;
+    auto load_rows = [&](int64_t nb, int c4, floatx4 (&v)[U]) {
+        const floatx4 *at = reinterpret_cast<const floatx4 *>(src + nb * D);
+        const int last = last_of(nb), cc = c4 < g.d4 ? c4 : g.d4 - 1;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t n = n0 + (int64_t)u * rows;
-            const int64_t nn = n < N ? n : N - 1;
-            v[u] = __builtin_nontemporal_load(reinterpret_cast<const floatx4 *>(src + nn * D) + cc);
-        }
+        for (int u = 0; u < U; ++u) v[u] = __builtin_nontemporal_load(at + (unsigned)(min(ty + u * rows, last) * g.d4 + cc));
     };
 
-    int64_t n0 = (int64_t)blockIdx.x * rows * U + ty;
+    const float scale = R16 ? o16.consts[0] : 0.f;
+    float4 neg = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (R16 && tx < g.d4) neg = reinterpret_cast<const float4 *>(o16.negmu)[tx];
+    float sums[2 * U];                                              // R16: norms of the U rows, over the chunks so far
+#pragma unroll
+    for (int i = 0; i < 2 * U; ++i) sums[i] = 0.f;
+    int64_t nb = (int64_t)blockIdx.x * rows * U;
     int chunk = 0;
     floatx4 v[U];
     int cm[U], cj[U];
-    if (n0 < N) {
-        load_codes(n0, cm, cj);
-        load_rows(n0, tx, v);
+    if (nb < N) {
+        load_codes(nb, cm, cj);
+        load_rows(nb, tx, v);
     }
-    while (n0 < N) {
+    while (nb < N) {
         // the step after this one
         int chunk_next = chunk + 1;
-        int64_t n0_next = n0;
-        if (chunk_next == nchunks) { chunk_next = 0; n0_next = n0 + stride; }
+        int64_t nb_next = nb;
+        if (chunk_next == nchunks) { chunk_next = 0; nb_next = nb + stride; }
         floatx4 vn[U];
         int cmn[U], cjn[U];
-        if (n0_next < N) {
-            if (chunk_next == 0) load_codes(n0_next, cmn, cjn);
-            load_rows(n0_next, chunk_next * cw + tx, vn);
+        if (nb_next < N) {
+            if (chunk_next == 0) load_codes(nb_next, cmn, cjn);
+            load_rows(nb_next, chunk_next * cw + tx, vn);
         }
         const int c4 = chunk * cw + tx;
         const bool live = c4 < g.d4;
         const int cc = live ? c4 : g.d4 - 1;
+        const int last = last_of(nb);
         floatx4 a[U], b[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            a[u] = *(reinterpret_cast<const floatx4 *>(Cm + (size_t)cm[u] * D) + cc);
-            if (MODE == 0) b[u] = *(reinterpret_cast<const floatx4 *>(Cj + (size_t)cj[u] * D) + cc);
+            a[u] = reinterpret_cast<const floatx4 *>(Cm)[(unsigned)(cm[u] * g.d4 + cc)];
+            if (MODE == 0) b[u] = reinterpret_cast<const floatx4 *>(Cj)[(unsigned)(cj[u] * g.d4 + cc)];
         }
         if (STATS && tx == 0 && chunk == 0) {
+            uint8_t *oc = old_codes + nb;
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int64_t n = n0 + (int64_t)u * rows;
-                if (n < N) {
-                    if (MODE > 0) old_codes[n] = (uint8_t)cm[u];
-                    if (MODE < 0) chg += (old_codes[n] != (uint8_t)cm[u]);
+                const int i = ty + u * rows;
+                if (i <= last) {
+                    if (MODE > 0) oc[i] = (uint8_t)cm[u];
+                    if (MODE < 0) chg += (oc[i] != (uint8_t)cm[u]);
                     if (MODE == 0) {
-                        chg += (old_codes[n] != (uint8_t)cm[u]);
-                        old_codes[n] = (uint8_t)cj[u];
+                        chg += (oc[i] != (uint8_t)cm[u]);
+                        oc[i] = (uint8_t)cj[u];
                     }
                 }
             }
         }
+        floatx4 *out = reinterpret_cast<floatx4 *>(r + nb * D);
+        _Float16 *out16 = R16 ? o16.rows + nb * o16.ld : nullptr;
+        if (R16 && !(DT && DT <= 256) && nchunks > 1) neg = reinterpret_cast<const float4 *>(o16.negmu)[cc];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int64_t n = n0 + (int64_t)u * rows;
-            if (live && n < N) {
+            const int i = ty + u * rows;
+            if (live && i <= last) {
                 floatx4 w = v[u];
                 if (STATS && MODE > 0)
                     err += (double)w.x * w.x + (double)w.y * w.y + (double)w.z * w.z + (double)w.w * w.w;
@@ -162,8 +192,25 @@ __global__ __launch_bounds__(kStreamThreads) void k_row_pass(
                     amax = fmaxf(fmaxf(amax, fabsf(w.x)), fabsf(w.y));
                     amax = fmaxf(fmaxf(amax, fabsf(w.z)), fabsf(w.w));
                 }
-                __builtin_nontemporal_store(w, reinterpret_cast<floatx4 *>(r + n * D) + c4);
+                __builtin_nontemporal_store(w, out + (unsigned)(i * g.d4 + c4));
+                if (R16) put_rows16(out16 + (unsigned)(i * o16.ld), c4, w, neg, scale, sums[2 * u], sums[2 * u + 1]);
             }
+        }
+        if (R16 && chunk_next == 0) {                               // the threads of a row are lanes of one wave
+            if (DT == 128) {
+                const float s = group_sums<2 * U, 32>(sums);        // lane i: value i
+                const int i = ty + (tx >> 1) * rows;
+                if (tx < 2 * U && i <= last) reinterpret_cast<float *>(o16.norm + nb)[2 * i + (tx & 1)] = s;
+            } else {
+                for (int o = 1; o < cw; o <<= 1)
+#pragma unroll
+                    for (int i = 0; i < 2 * U; ++i) sums[i] += __shfl_xor(sums[i], o, kWave);
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (tx == 0 && ty + u * rows <= last) (o16.norm + nb)[ty + u * rows] = make_float2(sums[2 * u], sums[2 * u + 1]);
+            }
+#pragma unroll
+            for (int i = 0; i < 2 * U; ++i) sums[i] = 0.f;
         }
         if (chunk_next == 0) {
 #pragma unroll
@@ -172,7 +219,7 @@ __global__ __launch_bounds__(kStreamThreads) void k_row_pass(
 #pragma unroll
         for (int u = 0; u < U; ++u) v[u] = vn[u];
         chunk = chunk_next;
-        n0 = n0_next;
+        nb = nb_next;
     }
     if (STATS) {
         const double e = block_sum(err, red);
@@ -191,15 +238,16 @@ __global__ __launch_bounds__(kStreamThreads) void k_row_pass(
 // one row in flight), kWideRows rows per step, steps (row pair, column group) pipelined as in k_row_pass.  Measured at
 // N = 1M, D = 960 (3.84 GB each way): stage boundary 1.39 ms against 1.51 ms for k_row_pass, new residue 1.36 ms
 // against 1.43 ms.  Results are those of k_row_pass bit for bit (the same fp32 operations per element); the error
-// sums differ in their order of additions, which is the same in all three modes here too.
+// sums differ in their order of additions, which is the same in all three modes here too.  Two blocks per CU: the stage boundary with
+// fp16 rows (N = 200k) takes 367 us within 128 registers, 398 us with what the compiler would take.
 constexpr int kWideMinD = 768;
 constexpr int kWideRows = 2;
-template <int MODE, bool STATS, bool AMAX = false>
-__global__ __launch_bounds__(kStreamThreads) void k_row_pass_wide(
+template <int MODE, bool STATS, bool AMAX = false, bool R16 = false>
+__global__ __launch_bounds__(kStreamThreads, 4) void k_row_pass_wide(
     float *r, const float *src, const uint8_t *__restrict__ codes, const float *__restrict__ Cm, const float *__restrict__ Cj,
     int64_t N, int D, int M, int m, int j_stage,
     uint8_t *__restrict__ old_codes, double *__restrict__ part_err, long long *__restrict__ part_chg,
-    unsigned *__restrict__ absmax_slot = nullptr)
+    unsigned *__restrict__ absmax_slot, RowPass16 o16)
 {
     __shared__ double red[kStreamThreads / kWave];
     constexpr int U = 4, R = kWideRows;
@@ -231,7 +279,11 @@ __global__ __launch_bounds__(kStreamThreads) void k_row_pass_wide(
         }
     };
 
-    int64_t n0 = ((int64_t)blockIdx.x * (kStreamThreads / kWave) + (threadIdx.x >> 6)) * R;
+    const float scale = R16 ? o16.consts[0] : 0.f;
+    float sums[2 * R];                                              // R16: norms of the R rows, over the groups so far
+#pragma unroll
+    for (int i = 0; i < 2 * R; ++i) sums[i] = 0.f;
+    int64_t n0 = ((int64_t)blockIdx.x * (kStreamThreads / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * R;   // scalar
     int group = 0;
     floatx4 v[R][U];
     int cm[R], cj[R];
@@ -286,9 +338,17 @@ __global__ __launch_bounds__(kStreamThreads) void k_row_pass_wide(
                             amax = fmaxf(fmaxf(amax, fabsf(w.z)), fabsf(w.w));
                         }
                         __builtin_nontemporal_store(w, reinterpret_cast<floatx4 *>(r + n * D) + c);
+                        if (R16)
+                            put_rows16(o16.rows + n * o16.ld, c, w, reinterpret_cast<const float4 *>(o16.negmu)[c], scale, sums[2 * q], sums[2 * q + 1]);
                     }
                 }
             }
+        }
+        if (R16 && group_next == 0) {
+            const float s = group_sums<2 * R, kWave>(sums);         // lane i: value i
+            if (lane < 2 * R && n0 + (lane >> 1) < N) reinterpret_cast<float *>(o16.norm + n0 + (lane >> 1))[lane & 1] = s;
+#pragma unroll
+            for (int i = 0; i < 2 * R; ++i) sums[i] = 0.f;
         }
         if (group_next == 0) {
 #pragma unroll

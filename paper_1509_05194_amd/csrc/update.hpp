@@ -12,7 +12,7 @@
 // identical bits and no sort or ownership scheme is needed.  Rows are read once, fully
 // coalesced (a wave-instruction covers one 256-byte half row), 16 rows per wave in flight.
 #pragma once
-#include "common.hpp"
+#include "assign_half.hpp"
 
 namespace hclae {
 
@@ -232,6 +232,14 @@ __global__ __launch_bounds__(256) void k_absmax(const float4 *__restrict__ x, in
 // with the integer sum exact (so its order is free: 4 groups of blocks in parallel) and the
 // division in fp64; untouched when n_k == 0.  Then hneg[k] = -||c_k||^2/2 for the next
 // assignment, nk[k] = n_k, and the counter of undecided vectors is reset (max |x'| stays: x' has not changed).
+// image (img null: none): the codeword's fp16 operands for the next assignment in the stage's centre and scale (rows16.hpp), with the
+// squares of the scaled, centred codeword and of its rounding.
+struct MergeImage {
+    char *img;
+    float *sums;
+    const float *negmu, *consts;
+    int kb;
+};
 constexpr int kMergeGroups = 4;
 constexpr int kMergePairs = 256 / kMergeGroups;     // dim pairs per pass
 __global__ __launch_bounds__(256) void k_merge(
@@ -240,9 +248,8 @@ __global__ __launch_bounds__(256) void k_merge(
     int *__restrict__ counts_out, unsigned *__restrict__ refine_count,
     double *__restrict__ run_sum, long long *__restrict__ run_cnt,
     long long *__restrict__ tot_sum, int *__restrict__ tot_cnt, int delta, unsigned *__restrict__ moved_count,
-    float *__restrict__ drift)
+    float *__restrict__ drift, MergeImage image)
 {
-    __shared__ double red[256 / kWave];
     __shared__ long long comb[kMergeGroups][kMergePairs][2];
     __shared__ int s_n;
     const int k = blockIdx.x;
@@ -291,6 +298,8 @@ __global__ __launch_bounds__(256) void k_merge(
     const int b0 = g * per, b1 = min(nblk, b0 + per);
     const int npairs = D >> 1;
     double sq = 0.0, moved2 = 0.0;                                  // ||c||^2 over dnorm dims; ||c_new - c_old||^2
+    float hsq = 0.f, hdsq = 0.f;                                    // of the image
+    const float scale = image.img ? image.consts[0] : 0.f;
     for (int p0 = 0; p0 < npairs; p0 += kMergePairs) {
         const int pr = p0 + l;
         long long s0 = 0, s1 = 0;
@@ -342,15 +351,37 @@ __global__ __launch_bounds__(256) void k_merge(
             // the next assignment may use only the first dnorm coordinates (improved k-means, Sec. 3.2)
             if (2 * pr < dnorm) sq += (double)c.x * c.x;
             if (2 * pr + 1 < dnorm) sq += (double)c.y * c.y;
+            if (image.img) {                                        // half4 of the pair
+                const float2 neg = reinterpret_cast<const float2 *>(image.negmu)[pr];
+                const float wx = fmaf(c.x, scale, neg.x), wy = fmaf(c.y, scale, neg.y);
+                const halfx2 q2 = __builtin_convertvector((floatv2){wx, wy}, halfx2);
+                const float dx = wx - (float)q2.x, dy = wy - (float)q2.y;
+                hsq = fmaf(wx, wx, fmaf(wy, wy, hsq));
+                hdsq = fmaf(dx, dx, fmaf(dy, dy, hdsq));
+                const int p = pr >> 1, t = p >> 2;
+                *reinterpret_cast<halfx2 *>(image.img + (size_t)(t * image.kb + (k >> 5)) * 1024 + half_slot(t, p & 1, k & 31)
+                                            + 8 * ((p >> 1) & 1) + 4 * (pr & 1)) = q2;
+            }
         }
         __syncthreads();
     }
-    sq = block_sum(sq, red);
-    if (drift) {                                                    // how far the codeword moved, rounded up
-        moved2 = block_sum(moved2, red);
-        if (threadIdx.x == 0) drift[k] = (float)(sqrt(moved2) * 1.000001);
+    static_assert(kMergePairs == kWave, "the pairs of group 0 are the first wave");
+    if (threadIdx.x >= kWave) return;
+    sq = wave_sum(sq);
+    if (drift) moved2 = wave_sum(moved2);
+    if (image.img) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            hsq += __shfl_xor(hsq, o, kWave);
+            hdsq += __shfl_xor(hdsq, o, kWave);
+        }
     }
     if (threadIdx.x == 0) {
+        if (drift) drift[k] = (float)(sqrt(moved2) * 1.000001);     // how far the codeword moved, rounded up
+        if (image.img) {
+            image.sums[2 * k] = hsq;
+            image.sums[2 * k + 1] = hdsq;
+        }
         hneg[k] = -(float)(0.5 * sq);
         nk[k] = s_n;
         if (counts_out) counts_out[k] = s_n;
