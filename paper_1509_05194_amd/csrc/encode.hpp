@@ -5,8 +5,8 @@
 // vectors pay for nothing but launches that way (D = 128, M = 8: 158 us for 64 vectors, 202 us for 10k).  Here a row is read
 // and written once, and the two launches are k_encode_prep, which lays out the fp16 dictionaries, and k_encode_fused: 51 us
 // and 90 us.  What bounds it is the chain of a dictionary's steps (round, contract, decide, subtract, with two or four
-// barriers): about 4.5 us each, eight waves waiting for each other, which is why large calls with many codewords do not come
-// here (encode_fused()).
+// barriers): about 4.5 us each, eight waves waiting for each other, which is why large calls do not come here
+// (encoder(); k_encode_wave takes most of them).
 //
 // Wave b of the block keeps codewords 32 b .. 32 b + 31 of the running dictionary as MFMA operands in registers (its next
 // operands travel while the vectors are decided); the 32 rows are rounded to fp16 once by all threads and shared through
@@ -18,7 +18,7 @@
 namespace hclae {
 
 constexpr int kPrepThreads = 1024;
-constexpr int kEncodeConsts = 8;                    // floats per dictionary: scale, h, rho, acc, hx
+constexpr int kEncodeConsts = 8;                    // floats per dictionary: scale, h, rho, acc, hx, cmax
 
 // Tiles of N < 2^31 vectors, and the blocks that take them: one each up to 2^20, which stride beyond (a launch holds less than
 // 2^32 threads, and a block has up to 512).
@@ -26,10 +26,12 @@ __host__ __device__ constexpr int64_t encode_tiles(int64_t N) { return (N + kTil
 __host__ __device__ constexpr int64_t encode_blocks(int64_t N) { return encode_tiles(N) < (1 << 20) ? encode_tiles(N) : (1 << 20); }
 
 // One block per dictionary: fp16 image in the order of half_slot, k-step by k-step; -||C||^2/2 and w per codeword; -mu; the
-// constants (half_constants has the reasons).  Also clears the counter of undecided vectors.
+// constants (half_constants has the reasons); -||c||^2/2 of the codewords as they are.  Also clears the counters of undecided
+// vectors and of tiles given up (k_encode_wave).
 __global__ __launch_bounds__(kPrepThreads) void k_encode_prep(
     const float *__restrict__ C, int K, int D, int kb, int NC, char *__restrict__ img, float *__restrict__ hn,
-    float *__restrict__ wtab, float *__restrict__ negmu, float *__restrict__ consts, unsigned *__restrict__ refine_count)
+    float *__restrict__ wtab, float *__restrict__ negmu, float *__restrict__ consts, float *__restrict__ hneg,
+    unsigned *__restrict__ refine_count)
 {
     __shared__ float s_sq[256], s_dsq[256], s_red[2][kPrepThreads / kWave];
     constexpr int waves = kPrepThreads / kWave;
@@ -37,7 +39,7 @@ __global__ __launch_bounds__(kPrepThreads) void k_encode_prep(
     const int kpad = 32 * kb;
     const float *Cm = C + (size_t)m * K * D;
     img += (size_t)m * NC * kb * 4096;
-    if (m == 0 && threadIdx.x == 0) refine_count[0] = 0u;
+    if (m == 0 && threadIdx.x == 0) refine_count[0] = refine_count[2] = 0u;
     // a lane keeps its float4 column (NC <= 4), a wave takes rows wave, wave + 16, ..., eight of them in flight
     constexpr int U = 8;
     const int p = lane;
@@ -60,8 +62,12 @@ __global__ __launch_bounds__(kPrepThreads) void k_encode_prep(
             const float4 v = load_row_piece(Cm, r0 + u * waves, 4 * p, K, D, D);
             s[u] = v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
         }
-        big = fmaxf(big, group_sums<U, 64>(s));
+        const float mine = group_sums<U, 64>(s);                    // lane i: row r0 + i waves
+        const int row = r0 + (lane & (U - 1)) * waves;
+        if (lane < U && row < K) hneg[(size_t)m * kpad + row] = -0.5f * mine;
+        big = fmaxf(big, mine);
     }
+    for (int k = K + threadIdx.x; k < kpad; k += kPrepThreads) hneg[(size_t)m * kpad + k] = -__builtin_inff();
 #pragma unroll
     for (int o = 1; o < U; o <<= 1) big = fmaxf(big, __shfl_xor(big, o, kWave));
     if (lane == 0) s_red[0][wave] = big;
@@ -116,68 +122,38 @@ __global__ __launch_bounds__(kPrepThreads) void k_encode_prep(
         c[3] = half_acc(NC);
         c[1] = half_loss(c[3], hm, cmax);
         c[4] = half_loss_x(c[3], cmax);
+        c[5] = cmax;
     }
 }
 
-// The nearest of a vector's candidates (bit i of mask[b]: codeword 32 b + i), by one wave; row: its fp32 residual in LDS.
-// As decide_items: fp32 direct form where the two best are further apart than its error, then fp64 in ascending dimension
-// order, lowest index on exact ties.
-// Four candidates at a time: bound by the latency of a round, so sixteen lanes (two loads each at D = 128) take one rather than
-// a half wave (two at a time: vectors with many candidates pay twice the rounds; 10k rows with lognormal norms, D = 64, K = 64,
-// M = 4: 143 us, 224 with a half wave, 64 queries at D = 128 49.4 / 51.5) or eight lanes (115 us, but registers spill at
-// D = 256, K = 128: 920 us for 200k rows instead of 775).
+// The j-th candidate (bit i of mask[b]: codeword 32 b + i), -1 beyond the last.
 template <int KB>
-__device__ __forceinline__ int encode_decide(const float *__restrict__ row, const float *__restrict__ Cm, const unsigned *mask, int D, int lane)
+__device__ __forceinline__ int nth_candidate(const unsigned *mask, int j)
+{
+    int k = -1;
+    for (int w = 0; w < KB; ++w) {
+        unsigned q = mask[w];
+        const int c = __popc(q);
+        if (j >= 0 && j < c) {
+            for (int i = 0; i < j; ++i) q &= q - 1u;
+            k = 32 * w + __ffs(q) - 1;
+        }
+        j -= c;
+    }
+    return k;
+}
+
+// The nearest of a vector's candidates in fp64, by one wave, a lane per candidate; row: its fp32 residual in LDS.
+template <int KB>
+__device__ __forceinline__ int encode_decide_fp64(const float *__restrict__ row, const float *__restrict__ Cm, const unsigned *mask, int D, int lane)
 {
     const int d4 = D >> 2;
-    // fp32: four candidates at a time, sixteen lanes each
-    const int sub = lane & 15;
-    const float eta = (float)(4 * ((d4 + 15) >> 4) + 8) * 6.1e-8f;
-    float best = __builtin_inff(), second = __builtin_inff();
-    int kbest = 0, total = 0;
+    int total = 0;
     for (int b = 0; b < KB; ++b) total += __popc(mask[b]);
-    auto nth = [&](int j) {                                         // the j-th candidate, -1 beyond the last
-        int k = -1;
-        for (int w = 0; w < KB; ++w) {
-            unsigned q = mask[w];
-            const int c = __popc(q);
-            if (j >= 0 && j < c) {
-                for (int i = 0; i < j; ++i) q &= q - 1u;
-                k = 32 * w + __ffs(q) - 1;
-            }
-            j -= c;
-        }
-        return k;
-    };
-    for (int j0 = 0; j0 < total; j0 += 4) {
-        const int k = nth(j0 + (lane >> 4));
-        const float4 *c4 = reinterpret_cast<const float4 *>(Cm + (size_t)(k < 0 ? 0 : k) * D);
-        float s = 0.f;
-#pragma unroll 2
-        for (int d = sub; d < d4; d += 16) {
-            const float4 u = reinterpret_cast<const float4 *>(row)[d], v = c4[d];
-            const float e0 = u.x - v.x, e1 = u.y - v.y, e2 = u.z - v.z, e3 = u.w - v.w;
-            s = fmaf(e3, e3, fmaf(e2, e2, fmaf(e1, e1, fmaf(e0, e0, s))));
-        }
-#pragma unroll
-        for (int o = 1; o < 16; o <<= 1) s += __shfl_xor(s, o, kWave);
-        if (k < 0) s = __builtin_inff();
-        second = s < best ? best : fminf(second, s);
-        if (s < best) { best = s; kbest = k; }
-    }
-#pragma unroll
-    for (int o = 16; o < kWave; o <<= 1) {
-        const float ob = __shfl_xor(best, o, kWave), os = __shfl_xor(second, o, kWave);
-        const int ok = __shfl_xor(kbest, o, kWave);
-        second = fminf(fmaxf(best, ob), fminf(second, os));
-        if (ob < best) { best = ob; kbest = ok; }
-    }
-    if (best * (1.f + eta) < second * (1.f - eta) && second > 1e-25f) return kbest;
-    // fp64: a lane per candidate
     double dbest = __builtin_inf();
     int k64 = 0x7fffffff;
     for (int j0 = 0; j0 < total; j0 += kWave) {
-        const int k = nth(j0 + lane);
+        const int k = nth_candidate<KB>(mask, j0 + lane);
         if (k < 0) continue;
         const float4 *c4 = reinterpret_cast<const float4 *>(Cm + (size_t)k * D);
         double s = 0.0;
@@ -202,6 +178,49 @@ __device__ __forceinline__ int encode_decide(const float *__restrict__ row, cons
     return k64 == 0x7fffffff ? 0 : k64;
 }
 
+// The nearest of a vector's candidates (bit i of mask[b]: codeword 32 b + i), by one wave; row: its fp32 residual in LDS.
+// As decide_items: fp32 direct form where the two best are further apart than its error, then fp64 in ascending dimension
+// order, lowest index on exact ties.
+// Four candidates at a time: bound by the latency of a round, so sixteen lanes (two loads each at D = 128) take one rather than
+// a half wave (two at a time: vectors with many candidates pay twice the rounds; 10k rows with lognormal norms, D = 64, K = 64,
+// M = 4: 143 us, 224 with a half wave, 64 queries at D = 128 49.4 / 51.5) or eight lanes (115 us, but registers spill at
+// D = 256, K = 128: 920 us for 200k rows instead of 775).
+template <int KB>
+__device__ __forceinline__ int encode_decide(const float *__restrict__ row, const float *__restrict__ Cm, const unsigned *mask, int D, int lane)
+{
+    const int d4 = D >> 2;
+    // fp32: four candidates at a time, sixteen lanes each
+    const int sub = lane & 15;
+    const float eta = (float)(4 * ((d4 + 15) >> 4) + 8) * 6.1e-8f;
+    float best = __builtin_inff(), second = __builtin_inff();
+    int kbest = 0, total = 0;
+    for (int b = 0; b < KB; ++b) total += __popc(mask[b]);
+    for (int j0 = 0; j0 < total; j0 += 4) {
+        const int k = nth_candidate<KB>(mask, j0 + (lane >> 4));
+        const float4 *c4 = reinterpret_cast<const float4 *>(Cm + (size_t)(k < 0 ? 0 : k) * D);
+        float s = 0.f;
+#pragma unroll 2
+        for (int d = sub; d < d4; d += 16) {
+            const float4 u = reinterpret_cast<const float4 *>(row)[d], v = c4[d];
+            const float e0 = u.x - v.x, e1 = u.y - v.y, e2 = u.z - v.z, e3 = u.w - v.w;
+            s = fmaf(e3, e3, fmaf(e2, e2, fmaf(e1, e1, fmaf(e0, e0, s))));
+        }
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) s += __shfl_xor(s, o, kWave);
+        if (k < 0) s = __builtin_inff();
+        second = s < best ? best : fminf(second, s);
+        if (s < best) { best = s; kbest = k; }
+    }
+#pragma unroll
+    for (int o = 16; o < kWave; o <<= 1) {
+        const float ob = __shfl_xor(best, o, kWave), os = __shfl_xor(second, o, kWave);
+        const int ok = __shfl_xor(kbest, o, kWave);
+        second = fminf(fmaxf(best, ob), fminf(second, os));
+        if (ob < best) { best = ob; kbest = ok; }
+    }
+    if (best * (1.f + eta) < second * (1.f - eta) && second > 1e-25f) return kbest;
+    return encode_decide_fp64<KB>(row, Cm, mask, D, lane);
+}
 // LDS of k_encode_fused.
 struct EncodeLds {
     int rows16, rows32, best, w, rsq, mask, code, misc, total;      // byte offsets

@@ -13,6 +13,7 @@
 #include "assign.hpp"
 #include "assign_half.hpp"
 #include "encode.hpp"
+#include "encode_wave.hpp"
 #include "stream.hpp"
 #include "rows16.hpp"
 #include "update.hpp"
@@ -761,57 +762,103 @@ int encode_chunks(const hclae_ctx *ctx)
     return nc <= 4 && 8 * nc <= 16 * ctx->kb ? nc : 0;
 }
 
-// Which encoder: the waves of a block decide 32 vectors in lockstep, so the fused encoder's time per vector grows with their
-// number; what it saves, launches and a read and a write of the rows per dictionary, is worth most in small calls and long rows,
-// least where a row is a few cache lines or where four chunks hold mostly padding.  Measured on two kinds of rows, few near-ties
-// and many (M = 8, us fused / dictionary by dictionary):
-//   K > 128       49k vectors: D = 128 235 / 280 (45k) and 289 / 310;  60k: D = 64 241 / 224, D = 128 304 / 331;  80k: D = 128 409 / 368
-//   K in 65..128  D = 16    98k 140 / 187 and 168 / 192, 196k 260 / 235 and 313 / 244;  D = 64  196k 289 / 327 and 385 / 349
-//                 D = 128   196k 401 / 532 and 517 / 556, 262k - and 681 / 691, 392k 790 / 916 and 1020 / 972
-//                 D = 192   98k 361 / 459 and 414 / 487, 196k 733 / 748 and 866 / 787;  D = 208  392k 1481 / 1693 and 1752 / 1854
-//   K in 33..64   D = 16    392k 272 / 304 and 304 / 310, 800k 530 / 443 and 614 / 458;  D = 64  800k 558 / 883 and 721 / 940
-//                 D = 192   98k 386 / 437 and 454 / 455, 196k 818 / 713 and 937 / 744;  D = 256  392k 1596 / 1661 and 1922 / 1776
-//   K <= 32       D = 16    800k 368 / 418 and 400 / 424;  D = 64  800k 390 / 864 and 468 / 896
-bool encode_fused(const hclae_ctx *ctx, int64_t N)
+// Which encoder takes a call: one that has the vectors of a tile decided by all the waves of a block in lockstep (k_encode_fused: shortest
+// for few vectors), one with a tile per wave (k_encode_wave, rows up to 128 coordinates), or the kernels that go dictionary by dictionary.
+// The lines, in tiles of 32 vectors per CU, on two kinds of rows, few near-ties and many (M = 8, us fused / tile per wave / dictionary by
+// dictionary):
+//   K > 128       D = 128  16k 92 / 119 / 216 and 101 / 131 / 219, 32k 165 / 125 / 275 and 184 / 134 / 278, 524k - / 856 / 1309 and - / 943 / 1461
+//                 D = 64   8k 47 / 75 / 174 and 51 / 76 / 173, 16k 77 / 76 / 184 and 83 / 79 / 190;  D = 32  16k 72 / 66 / 171 and 79 / 68 / 172
+//   K in 65..128  D = 128  32k 87 / 99 / 237 and 98 / 106 / 240, 49k 119 / 107 / 282 and 141 / 114 / 293;  D = 64  32k 64 / 65 / 189 and 72 / 69 / 191
+//   K in 33..64   D = 128  49k 89 / 91 / 265 and 104 / 102 / 272, 65k 106 / 102 / 282 and 118 / 111 / 290;  D = 32  32k 41 / 50 / 150 and 46 / 54 / 164,
+//                 49k 62 / 58 / 166 and 71 / 62 / 174
+//   K <= 32       D = 128  49k 77 / 81 / 256 and 88 / 96 / 260, 65k 115 / 87 / 270 and 130 / 101 / 281;  D = 16  32k 44 / 43 / 132 and 48 / 47 / 145
+// and, longer rows (us fused / dictionary by dictionary):
+//   K in 65..128  D = 192  98k 361 / 459 and 414 / 487, 196k 733 / 748 and 866 / 787;  D = 208  392k 1481 / 1693 and 1752 / 1854
+//   K in 33..64   D = 192  98k 386 / 437 and 454 / 455, 196k 818 / 713 and 937 / 744;  D = 256  392k 1596 / 1661 and 1922 / 1776
+enum class Encoder { fused, wave, steps };
+Encoder encoder(const hclae_ctx *ctx, int64_t N)
 {
-    const int nc = encode_chunks(ctx), D = ctx->D;
-    const bool full = D >= 208;                              // of four chunks
-    int tiles_per_cu;                                        // the line, in tiles of 32 vectors
-    switch (nc ? ctx->kb : 0) {
-    case 0: return false;
-    case 1: return true;
-    case 2:
-        if (nc < 4 && D > 16) return true;
-        tiles_per_cu = nc < 4 || full ? 48 : 12;
-        break;
-    case 4:
-        if (full) return true;
-        tiles_per_cu = nc == 2 ? 32 : 16;
-        break;
-    default: tiles_per_cu = 6;
+    const int nc = encode_chunks(ctx);
+    if (!nc) return Encoder::steps;
+    const bool full = ctx->D >= 208;                         // of four chunks
+    int tiles_per_cu;
+    switch (ctx->kb) {
+    case 1: case 2: tiles_per_cu = nc == 1 ? 4 : nc == 2 ? 6 : full ? 48 : 12; break;
+    case 4: tiles_per_cu = nc <= 2 ? 4 : 16; break;
+    default: tiles_per_cu = nc <= 2 ? nc : 6;
     }
-    return N <= (int64_t)ctx->cus * tiles_per_cu * kTileVec;
+    if (N <= (int64_t)ctx->cus * tiles_per_cu * kTileVec || (ctx->kb == 4 && full)) return Encoder::fused;
+    return nc <= 2 ? Encoder::wave : Encoder::steps;
+}
+
+// How many assignments hclae_timing_read counts for a call of k_encode_wave: one per dictionary above the sizes from which a call with so
+// many codewords has counted that way (one up to there), so that a caller's figures per assignment go on meaning the same.
+int encode_timed(const hclae_ctx *ctx, int64_t N)
+{
+    const int tiles_per_cu = ctx->kb == 1 || (ctx->kb == 2 && ctx->D > 16) ? 0 : ctx->kb == 2 ? 48 : ctx->kb == 4 ? (ctx->NC == 2 ? 32 : 16) : 6;
+    return tiles_per_cu && N > (int64_t)ctx->cus * tiles_per_cu * kTileVec ? ctx->M : 1;
+}
+
+// The dictionaries as the encoders that take all of them in one kernel want them (k_encode_prep).
+struct EncodeTables {
+    char *img;
+    float *hn, *wtab, *negmu, *consts, *hneg;
+};
+int launch_encode_prep(hclae_ctx *ctx, const float *C, int NC, EncodeTables *t)
+{
+    const int kb = ctx->kb, kpad = 32 * kb;
+    t->img = ctx->enc_buf;
+    t->hn = reinterpret_cast<float *>(t->img + (size_t)ctx->M * NC * kb * 4096);
+    t->wtab = t->hn + (size_t)ctx->M * kpad;
+    t->negmu = t->wtab + (size_t)ctx->M * kpad;
+    t->consts = t->negmu + (size_t)ctx->M * kChunkD * NC;
+    t->hneg = t->consts + (size_t)ctx->M * kEncodeConsts;
+    Timed t_(ctx, HCLAE_T_NORMS);
+    hipLaunchKernelGGL(k_encode_prep, dim3(ctx->M), dim3(kPrepThreads), 0, ctx->stream, C, ctx->K, ctx->D, kb, NC,
+                       t->img, t->hn, t->wtab, t->negmu, t->consts, t->hneg, ctx->refine_count);
+    HIP_TRY(ctx, hipGetLastError());
+    return HCLAE_OK;
+}
+
+template <int KB, int NC>
+int launch_encode_wave(hclae_ctx *ctx, const float *X, int64_t N, const float *C, uint8_t *codes, float *residue)
+{
+    static_assert(wave_lds(KB, NC).total <= kLdsBudget, "two dictionaries fit LDS");
+    EncodeTables t;
+    int rc = launch_encode_prep(ctx, C, NC, &t);
+    if (rc != HCLAE_OK) return rc;
+    const bool full = ctx->D == kChunkD * NC;
+    auto kern = full ? &k_encode_wave<KB, NC, true, false> : &k_encode_wave<KB, NC, false, false>;
+    auto rest = full ? &k_encode_wave<KB, NC, true, true> : &k_encode_wave<KB, NC, false, true>;
+    const uint64_t attr_set = 1ull << 36;       // this call site's bit in ctx->attr_done (D and K are the ctx's)
+    if (!(ctx->attr_done & attr_set)) {
+        HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget));
+        HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(rest), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget));
+        ctx->attr_done |= attr_set;
+    }
+    const int64_t nbt = (N + kTileVec * kAssignWaves - 1) / (kTileVec * kAssignWaves);
+    for (int i = 1; i < encode_timed(ctx, N); ++i) Timed empty(ctx, HCLAE_T_ASSIGN);
+    Timed t_(ctx, HCLAE_T_ASSIGN);
+    for (auto k : {kern, rest})                 // the tiles that the first gives up are listed in ctx->active
+        hipLaunchKernelGGL(k, dim3((unsigned)(nbt < ctx->cus ? nbt : ctx->cus)), dim3(kAssignThreads), (size_t)wave_lds(KB, NC).total,
+                           ctx->stream, X, C, (int)N, ctx->D, ctx->K, ctx->M, t.img, t.hn, t.wtab, t.negmu, t.consts, t.hneg, codes, residue,
+                           ctx->refine_count, ctx->work, ctx->active, ctx->refine_count + 2);
+    HIP_TRY(ctx, hipGetLastError());
+    return HCLAE_OK;
 }
 
 template <int KB, int NC>
 int launch_encode_fused(hclae_ctx *ctx, const float *X, int64_t N, const float *C, uint8_t *codes, float *residue)
 {
     if (8 * NC > 16 * KB) return fail(ctx, HCLAE_EINVAL, "encode: shape not covered by the fused encoder");
-    const int kpad = 32 * KB;
-    char *img = ctx->enc_buf;
-    float *hn = reinterpret_cast<float *>(img + (size_t)ctx->M * NC * KB * 4096);
-    float *wtab = hn + (size_t)ctx->M * kpad, *negmu = wtab + (size_t)ctx->M * kpad;
-    float *consts = negmu + (size_t)ctx->M * kChunkD * NC;
-    {
-        Timed t_(ctx, HCLAE_T_NORMS);
-        hipLaunchKernelGGL(k_encode_prep, dim3(ctx->M), dim3(kPrepThreads), 0, ctx->stream, C, ctx->K, ctx->D, KB, NC,
-                           img, hn, wtab, negmu, consts, ctx->refine_count);
-        HIP_TRY(ctx, hipGetLastError());
-    }
+    EncodeTables t;
+    int rc = launch_encode_prep(ctx, C, NC, &t);
+    if (rc != HCLAE_OK) return rc;
     Timed t_(ctx, HCLAE_T_ASSIGN);
     hipLaunchKernelGGL((k_encode_fused<KB, NC>), dim3((unsigned)encode_blocks(N)), dim3(64 * KB),
                        (size_t)encode_lds(KB, NC).total, ctx->stream,
-                       X, C, (int)N, ctx->D, ctx->K, ctx->M, img, hn, wtab, negmu, consts, codes, residue, ctx->refine_count, ctx->work);
+                       X, C, (int)N, ctx->D, ctx->K, ctx->M, t.img, t.hn, t.wtab, t.negmu, t.consts, codes, residue,
+                       ctx->refine_count, ctx->work);
     HIP_TRY(ctx, hipGetLastError());
     return HCLAE_OK;
 }
@@ -819,7 +866,8 @@ int launch_encode_fused(hclae_ctx *ctx, const float *X, int64_t N, const float *
 int enqueue_encode(hclae_ctx *ctx, const float *X, int64_t N, const float *C, uint8_t *codes, float *residue)
 {
     const int D = ctx->D, K = ctx->K;
-    switch (encode_fused(ctx, N) ? encode_chunks(ctx) * 16 + ctx->kb : 0) {
+    const Encoder which = encoder(ctx, N);
+    switch (which == Encoder::fused ? encode_chunks(ctx) * 16 + ctx->kb : 0) {
     case 16 + 1: return launch_encode_fused<1, 1>(ctx, X, N, C, codes, residue);
     case 16 + 2: return launch_encode_fused<2, 1>(ctx, X, N, C, codes, residue);
     case 16 + 4: return launch_encode_fused<4, 1>(ctx, X, N, C, codes, residue);
@@ -831,6 +879,17 @@ int enqueue_encode(hclae_ctx *ctx, const float *X, int64_t N, const float *C, ui
     case 64 + 2: return launch_encode_fused<2, 4>(ctx, X, N, C, codes, residue);
     case 64 + 4: return launch_encode_fused<4, 4>(ctx, X, N, C, codes, residue);
     case 64 + 8: return launch_encode_fused<8, 4>(ctx, X, N, C, codes, residue);
+    default: break;
+    }
+    switch (which == Encoder::wave ? encode_chunks(ctx) * 16 + ctx->kb : 0) {
+    case 16 + 1: return launch_encode_wave<1, 1>(ctx, X, N, C, codes, residue);
+    case 16 + 2: return launch_encode_wave<2, 1>(ctx, X, N, C, codes, residue);
+    case 16 + 4: return launch_encode_wave<4, 1>(ctx, X, N, C, codes, residue);
+    case 16 + 8: return launch_encode_wave<8, 1>(ctx, X, N, C, codes, residue);
+    case 32 + 1: return launch_encode_wave<1, 2>(ctx, X, N, C, codes, residue);
+    case 32 + 2: return launch_encode_wave<2, 2>(ctx, X, N, C, codes, residue);
+    case 32 + 4: return launch_encode_wave<4, 2>(ctx, X, N, C, codes, residue);
+    case 32 + 8: return launch_encode_wave<8, 2>(ctx, X, N, C, codes, residue);
     default: break;
     }
     int rc;
@@ -917,7 +976,7 @@ int hclae_create(hclae_ctx **out, int64_t N_max, int D, int M, int K, void *hip_
 
     const size_t enc_nc = (size_t)encode_chunks(ctx);
     const size_t encode_bytes = enc_nc == 0 ? 256 : (size_t)M * (enc_nc * ctx->kb * 4096 + sizeof(float) *
-                                (2 * 32 * ctx->kb + kChunkD * enc_nc + kEncodeConsts));
+                                (3 * 32 * ctx->kb + kChunkD * enc_nc + kEncodeConsts));
     struct { void **p; size_t bytes; } allocs[] = {
         {(void **)&ctx->hneg, sizeof(float) * 32 * ctx->kb},
         {(void **)&ctx->cb_image, half_resident(ctx, D) ? 256 : (size_t)ctx->NC * ctx->kb * 4096},
