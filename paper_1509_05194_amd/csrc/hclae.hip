@@ -414,7 +414,7 @@ int launch_assign_rows16(hclae_ctx *ctx, int m, int64_t N, const float *xp, cons
 }
 
 // prune: 0 plain; 1 all vectors and store the stage's bounds; 2 only the vectors k_bounds_step listed; 3 = 2 and 4 = 0, with the
-// vectors that changed cluster listed (over all D coordinates only; the caller checks).
+// vectors that changed cluster listed (1 to 3 over all D coordinates only; the caller checks).
 template <int KB>
 int launch_assign_kb(hclae_ctx *ctx, int m, int64_t N, const float *xp, const float *Cm, uint8_t *codes, int dact, int ld,
                      int prune)
@@ -454,7 +454,7 @@ int launch_assign(hclae_ctx *ctx, int m, int64_t N, const float *xp, const float
 {
     if (dact <= 0) dact = ctx->D;
     if (ld <= 0) ld = ctx->D;
-    if (dact != ctx->D || ld != ctx->D) prune = 0;
+    if ((dact != ctx->D || ld != ctx->D) && prune != 4) prune = 0;     // bounds are over all coordinates
     switch (ctx->kb) {
     case 1: return launch_assign_kb<1>(ctx, m, N, xp, Cm, codes, dact, ld, prune);
     case 2: return launch_assign_kb<2>(ctx, m, N, xp, Cm, codes, dact, ld, prune);
@@ -496,9 +496,7 @@ int launch_update(hclae_ctx *ctx, int m, int64_t N, const float *xp, float *Cm, 
 {
     const int D = ctx->D, K = ctx->K;
     const int windows = (D + kUpdWindow - 1) / kUpdWindow;
-    int64_t nb = (N + 1023) / 1024;                   // at least 1024 rows per block
-    if (nb > ctx->upd_blocks) nb = ctx->upd_blocks;
-    if (nb < 1) nb = 1;
+    const int nb = full_blocks(N, ctx->upd_blocks);
     int64_t rpb = (N + nb - 1) / nb;
     const size_t lds = upd_lds_bytes(K);
     const uint64_t attr_set = 1ull << 7;        // this call site's bit in ctx->attr_done
@@ -529,7 +527,7 @@ int launch_update(hclae_ctx *ctx, int m, int64_t N, const float *xp, float *Cm, 
                        online ? ctx->run_cnt + (size_t)m * K : (long long *)nullptr,
                        keep_totals ? ctx->tot_sum : (long long *)nullptr, keep_totals ? ctx->tot_cnt : (int *)nullptr, 0,
                        keep_totals ? ctx->moved_count : (unsigned *)nullptr, keep_totals ? ctx->drift : (float *)nullptr,
-                       merge_image(ctx));
+                       merge_image(ctx), N);
     HIP_TRY(ctx, hipGetLastError());
     return HCLAE_OK;
 }
@@ -537,7 +535,7 @@ int launch_update(hclae_ctx *ctx, int m, int64_t N, const float *xp, float *Cm, 
 // Centroid update from the vectors that changed cluster since the last update of this stage (x' unchanged,
 // max |x'| still published): exact, see k_merge.  Leaves hneg and the counters as launch_update does.
 // The assignment that just ran (launch_assign with prune 3 or 4) has listed those vectors.
-int launch_update_moved(hclae_ctx *ctx, int m, int64_t N, const float *xp, float *Cm)
+int launch_update_moved(hclae_ctx *ctx, int m, int64_t N, const float *xp, float *Cm, const uint8_t *codes, int dnorm = 0)
 {
     const int D = ctx->D, K = ctx->K;
     const int windows = (D + kUpdWindow - 1) / kUpdWindow;
@@ -552,14 +550,14 @@ int launch_update_moved(hclae_ctx *ctx, int m, int64_t N, const float *xp, float
         Timed t_(ctx, HCLAE_T_ACCUM_MOVED);
         hipLaunchKernelGGL(k_accumulate_moved, dim3((unsigned)nb, (unsigned)windows), dim3(kUpdThreads), upd_lds_bytes(K),
                            ctx->stream, xp, ctx->moved_list, ctx->moved_count, D, K, ctx->refine_count + 1,
-                           ctx->partial, ctx->pcount, ctx->tot_sum, ctx->tot_cnt);
+                           ctx->partial, ctx->pcount, ctx->tot_sum, ctx->tot_cnt, codes, N, ctx->M, m);
         HIP_TRY(ctx, hipGetLastError());
     }
     Timed t_(ctx, HCLAE_T_MERGE);
     hipLaunchKernelGGL(k_merge, dim3(K), dim3(256), 0, ctx->stream,
-                       ctx->partial, ctx->pcount, nb, K, D, D, Cm, ctx->hneg, ctx->nk, (int *)nullptr,
+                       ctx->partial, ctx->pcount, nb, K, D, dnorm > 0 ? dnorm : D, Cm, ctx->hneg, ctx->nk, (int *)nullptr,
                        ctx->refine_count, (double *)nullptr, (long long *)nullptr, ctx->tot_sum, ctx->tot_cnt, 1,
-                       ctx->moved_count, ctx->drift, merge_image(ctx));
+                       ctx->moved_count, ctx->drift, merge_image(ctx), N);
     HIP_TRY(ctx, hipGetLastError());
     return HCLAE_OK;
 }
@@ -699,7 +697,7 @@ int enqueue_stage(hclae_ctx *ctx, int m, int64_t N, float *C, uint8_t *codes, fl
                                                                              : ctx->pruning && t > 0 ? 4 : 0)) != HCLAE_OK) return rc;
         rc = (t == 0 || !ctx->pruning)
                  ? launch_update(ctx, m, N, residue, Cm, codes, nullptr, true, false, 0, ctx->pruning && (iters > 1 || prune))
-                 : launch_update_moved(ctx, m, N, residue, Cm);
+                 : launch_update_moved(ctx, m, N, residue, Cm, codes);
         if (rc != HCLAE_OK) return rc;
     }
     if (prune && (rc = launch_bounds_step(ctx, m, N, codes, residue, Cm)) != HCLAE_OK) return rc;
@@ -1887,8 +1885,13 @@ static int enqueue_stage_pca(hclae_ctx *ctx, int m, int64_t N, float *C, uint8_t
     for (int i = 0; i < n_dims; ++i) {
         if (iters_per_dim > 0 && (rc = launch_norms(ctx, Cm, dims[i], D, true)) != HCLAE_OK) return rc;
         for (int t = 0; t < iters_per_dim; ++t, ++iters_run) {
-            if ((rc = launch_assign(ctx, m, N, xr, Cm, codes, dims[i], D)) != HCLAE_OK) return rc;
-            if ((rc = launch_update(ctx, m, N, xr, Cm, codes, nullptr, true, false, dims[i])) != HCLAE_OK) return rc;
+            // x^r and its maximum stay for the stage and the sums are over all coordinates, so that here too only the first update
+            // has to sum every vector (exact, see k_merge); each assignment lists what it changes
+            const bool first = iters_run == 0;
+            if ((rc = launch_assign(ctx, m, N, xr, Cm, codes, dims[i], D, first ? 0 : 4)) != HCLAE_OK) return rc;
+            rc = first ? launch_update(ctx, m, N, xr, Cm, codes, nullptr, true, false, dims[i], true)
+                       : launch_update_moved(ctx, m, N, xr, Cm, codes, dims[i]);
+            if (rc != HCLAE_OK) return rc;
         }
     }
     // back: C_m = R^T C'

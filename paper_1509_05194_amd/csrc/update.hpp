@@ -36,12 +36,11 @@ __device__ __forceinline__ int fixed_point_shift(unsigned xmax_bits)
 }
 
 // grid: (vector ranges, 64-dim windows).  partial: int64 [gridDim.x][K][D] (sum of q); pcount: int [gridDim.x][K].
-__global__ __launch_bounds__(kUpdThreads) void k_accumulate(
-    const float *__restrict__ xp, const uint8_t *__restrict__ codes,
-    int64_t N, int D, int K, int M, int m, int64_t rows_per_block, const unsigned *__restrict__ xmax_bits,
+__device__ __forceinline__ void accumulate_rows(
+    float4 *smem4, const float *__restrict__ xp, const uint8_t *__restrict__ codes,
+    int64_t N, int D, int K, int M, int m, int64_t rows_per_block, int shift,
     long long *__restrict__ partial, int *__restrict__ pcount)
 {
-    extern __shared__ float4 smem4[];
     unsigned long long *acc = reinterpret_cast<unsigned long long *>(smem4);   // [K][64]
     unsigned *cnt = reinterpret_cast<unsigned *>(acc + K * kUpdWindow);        // [K]
     const int lane = lane_id();
@@ -49,7 +48,6 @@ __global__ __launch_bounds__(kUpdThreads) void k_accumulate(
     const int d = blockIdx.y * kUpdWindow + lane;                    // this lane's dim
     const bool live = d < D;
     const bool counting = blockIdx.y == 0;
-    const int shift = fixed_point_shift(*xmax_bits);
 
     for (int e = threadIdx.x; e < K * kUpdWindow; e += kUpdThreads) acc[e] = 0ull;
     for (int e = threadIdx.x; e < K; e += kUpdThreads) cnt[e] = 0u;
@@ -107,6 +105,15 @@ __global__ __launch_bounds__(kUpdThreads) void k_accumulate(
         for (int k = threadIdx.x; k < K; k += kUpdThreads) pcount[blockIdx.x * K + k] = (int)cnt[k];
 }
 
+__global__ __launch_bounds__(kUpdThreads) void k_accumulate(
+    const float *__restrict__ xp, const uint8_t *__restrict__ codes,
+    int64_t N, int D, int K, int M, int m, int64_t rows_per_block, const unsigned *__restrict__ xmax_bits,
+    long long *__restrict__ partial, int *__restrict__ pcount)
+{
+    extern __shared__ float4 smem4[];
+    accumulate_rows(smem4, xp, codes, N, D, K, M, m, rows_per_block, fixed_point_shift(*xmax_bits), partial, pcount);
+}
+
 // Blocks (of the x dimension) that the pass over `total` moved vectors uses: 160 rows per block measured best
 // on one MI355X (N = 1M, D = 128: the gather of the rows wants many blocks, the flush of 128 KB of partial sums
 // per block and the merge that reads them want few).  The merge that follows computes the same number.
@@ -125,13 +132,25 @@ __device__ __forceinline__ int moved_blocks(unsigned total, int max_blocks)
 constexpr unsigned kMovedDirect = 1u << 17;         // most additions of one sign
 __device__ __forceinline__ bool moved_direct(unsigned total, int D) { return (unsigned long long)total * (unsigned)D <= kMovedDirect; }
 
+// Whether so many of the N vectors have moved that a pass over all of them, which reads rows in order and adds each once, is shorter
+// than gathering those that moved and adding them twice; the merge asks the same.  N = 1M, D = 128: 86 us against 180 for some 0.7M
+// moved ones.
+__device__ __forceinline__ bool moved_full(unsigned total, int64_t N) { return 3ll * (long long)total > N; }
+
+// Blocks (of the x dimension) of a pass over all N vectors: at least 1024 rows each.
+__host__ __device__ inline int full_blocks(int64_t N, int max_blocks)
+{
+    const int64_t want = (N + 1023) / 1024;
+    return (int)(want < 1 ? 1 : want > max_blocks ? max_blocks : want);
+}
+
 // k_accumulate over the moved vectors only: +q into the new cluster, -q out of the old one, counts likewise.
 // Same grid roles, scale, rounding and partial layout as k_accumulate; the first moved_blocks(count)
-// blocks stride over the list, the others leave at once.
+// blocks stride over the list, the others leave at once.  With a long list (moved_full) it is k_accumulate.
 __global__ __launch_bounds__(kUpdThreads) void k_accumulate_moved(
     const float *__restrict__ xp, const unsigned long long *__restrict__ list, const unsigned *__restrict__ count,
     int D, int K, const unsigned *__restrict__ xmax_bits, long long *__restrict__ partial, int *__restrict__ pcount,
-    long long *__restrict__ tot_sum, int *__restrict__ tot_cnt)
+    long long *__restrict__ tot_sum, int *__restrict__ tot_cnt, const uint8_t *__restrict__ codes, int64_t N, int M, int m)
 {
     extern __shared__ float4 smem4[];
     unsigned long long *acc = reinterpret_cast<unsigned long long *>(smem4);   // [K][64]
@@ -159,6 +178,12 @@ __global__ __launch_bounds__(kUpdThreads) void k_accumulate_moved(
                 atomicAdd(tot_cnt + ko, -1);
             }
         }
+        return;
+    }
+    if (moved_full(total, N)) {
+        const int blocks = full_blocks(N, (int)gridDim.x);
+        if ((int)blockIdx.x < blocks)
+            accumulate_rows(smem4, xp, codes, N, D, K, M, m, (N + blocks - 1) / blocks, shift, partial, pcount);
         return;
     }
     const int used = moved_blocks(total, (int)gridDim.x);
@@ -248,7 +273,7 @@ __global__ __launch_bounds__(256) void k_merge(
     int *__restrict__ counts_out, unsigned *__restrict__ refine_count,
     double *__restrict__ run_sum, long long *__restrict__ run_cnt,
     long long *__restrict__ tot_sum, int *__restrict__ tot_cnt, int delta, unsigned *__restrict__ moved_count,
-    float *__restrict__ drift, MergeImage image)
+    float *__restrict__ drift, MergeImage image, int64_t N)
 {
     __shared__ long long comb[kMergeGroups][kMergePairs][2];
     __shared__ int s_n;
@@ -257,7 +282,12 @@ __global__ __launch_bounds__(256) void k_merge(
     if (k == 0 && threadIdx.x == 0) refine_count[0] = 0u;
     // after a pass over the moved vectors only the blocks that pass used hold partials; the list counter is
     // handed back empty (every block reads it before the last one to arrive resets it)
-    if (delta) nblk = moved_direct(*moved_count, D) ? 0 : moved_blocks(*moved_count, nblk);
+    if (delta) {
+        const unsigned total = *moved_count;
+        if (moved_direct(total, D)) nblk = 0;
+        else if (moved_full(total, N)) { nblk = full_blocks(N, nblk); delta = 0; }      // all vectors were summed
+        else nblk = moved_blocks(total, nblk);
+    }
     // moved_count[3]: the list counter of the pruning step that follows (k_bounds_step)
     if (moved_count) {
         __syncthreads();
