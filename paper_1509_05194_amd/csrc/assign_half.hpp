@@ -389,6 +389,15 @@ __device__ __forceinline__ int min_both(int v)
     return min((int)s.x, (int)s.y);
 }
 
+// The largest of a lane's sixteen scores of a block, two a step (see block_key).
+__device__ __forceinline__ float block_max(const floatx16 &a)
+{
+    float m = a[0];
+#pragma unroll
+    for (int v = 1; v < 15; v += 2) m = __builtin_elementwise_maximum(__builtin_elementwise_maximum(m, a[v]), a[v + 1]);
+    return __builtin_elementwise_maximum(m, a[15]);
+}
+
 // The largest of a lane's sixteen scores of a block with its last four bits replaced by its index (2^-19 of it): two a step
 // (v_maximum3; fmaxf would quiet NaNs one by one first).
 __device__ __forceinline__ float block_key(const floatx16 &a)

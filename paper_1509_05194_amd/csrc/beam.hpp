@@ -39,14 +39,11 @@ __device__ __forceinline__ void beam_select(
     int lane, const int (&next)[kBeamHops], int hops, int Ln, bool valid, BeamMask *__restrict__ out)
 {
     const float ninf = -__builtin_inff();
-    const float inf = opaque(__builtin_inff());
     const float half_x2 = 0.5f * x2;
     float bm[KB], top = ninf;
 #pragma unroll
     for (int b = 0; b < KB; ++b) {
-        bm[b] = acc[b][0];
-#pragma unroll
-        for (int v = 1; v < 16; ++v) bm[b] = __builtin_amdgcn_fmed3f(bm[b], acc[b][v], inf);   // the larger one, see opaque()
+        bm[b] = block_max(acc[b]);
         top = fmaxf(top, bm[b]);
     }
     const float round = c.h + c.acc * 6.2e-5f * xn + 2.4e-7f * (fabsf(top) + xn * c.cmax) + slack * x2 + 1e-36f;
@@ -70,15 +67,9 @@ __device__ __forceinline__ void beam_select(
     }
     const float thr = (tau - round) + half_x2;           // back to the lane's scores
 
-    uint32_t mk[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int b = 0; b < KB; ++b) {
-        uint32_t below = 0u;                             // sign bits of acc - thr, shifted in (v_alignbit)
-#pragma unroll
-        for (int v = 15; v >= 0; --v)
-            below = __builtin_amdgcn_alignbit(below, __float_as_uint(acc[b][v] - thr), 31);
-        mk[b >> 1] |= (~below & 0xffffu) << ((b & 1) * 16);
-    }
+    // (the threshold is subtracted here and not on the matrix cores as in decide_half: they are the busier of the two)
+    uint32_t mk[4];
+    reaching<KB>(mk, acc, thr);
     if (big || !(thr > ninf))                            // (bits of codewords beyond K are dropped by the reader)
         mk[0] = mk[1] = mk[2] = mk[3] = ~0u;
     if (valid) *reinterpret_cast<uint4 *>(&out->w[lane >> 5][0]) = make_uint4(mk[0], mk[1], mk[2], mk[3]);
@@ -100,6 +91,31 @@ struct BeamTile {
         for (int i = 0; i < kBeamHops; ++i) next[i] = (lane & 32) + base + (at + (1 << i)) % Lc;
     }
 };
+
+// mfma_chunk_half with the dictionary's operands read ahead (contract_half) and x refilled in place, with chunk qn of row `next`, as soon
+// as it has been converted: addresses are clamped into the row, and what lies past D is multiplied by zero (mu and the dictionary are
+// zero there).  Here, where ten rows a vector keep the matrix cores busy, it saves a fiftieth of the call (N = 200k, L = 10, D = 128:
+// 6.26 -> 6.14 ms, with the block maxima two scores a step); k_assign_half, which waits for its rows, is 3 % slower with it.
+template <int KB>
+__device__ __forceinline__ void mfma_chunk_refill(
+    floatx16 (&acc)[KB], float4 (&x)[8], const char *__restrict__ img, const float *__restrict__ negmu, int q, int lane,
+    float scale, float &xsq, float &dsq, const float *__restrict__ next, int qn, int D)
+{
+    const int g = lane >> 5, r = lane & 31, last = last_piece(D);
+    const float4 *mu4 = reinterpret_cast<const float4 *>(negmu) + 16 * q + g;
+    auto fetch = [&](int s) { return *reinterpret_cast<const float4 *>(next + min(kChunkD * qn + 8 * s + 4 * g, last)); };
+    contract_half<KB, 4>(acc, img + (size_t)q * 4 * KB * 1024, g, r, 4,
+        [&](int t) {
+            const int col = kChunkD * q + 16 * t + 4 * g;
+            const halfx4 lo = half4(scaled(x[2 * t], col < D ? scale : 0.f, mu4[4 * t]), xsq, dsq);
+            const halfx4 hi = half4(scaled(x[2 * t + 1], col + 8 < D ? scale : 0.f, mu4[4 * t + 2]), xsq, dsq);
+            return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        },
+        [&](int t) {
+            x[2 * t] = fetch(2 * t);
+            x[2 * t + 1] = fetch(2 * t + 1);
+        });
+}
 
 // Scoring with the dictionary resident in LDS as fp16: staging, streaming and bounds of k_assign_half.
 template <int KB>
@@ -125,20 +141,20 @@ __global__ __launch_bounds__(kAssignThreads) void k_beam_score_half(
         if (r >= bt.rt || n >= nrows) n = nrows - 1;     // idle columns re-read the last row
         return rows + n * D;
     };
-    float4 xa[8], xb[8];
-    if (G > 0) load_x_chunk(xa, row_ptr(t0), 0, h, D);   // travels while the dictionary is staged
+    float4 x[8];
+    if (G > 0) load_x_chunk(x, row_ptr(t0), 0, h, D);    // travels while the dictionary is staged
     const HalfConsts c = stage_half<KB>(lds, L, Cm, hneg, K, D, D, NC);
     if (G == 0) return;
     floatx16 acc[KB];
-    float xsq = 0.f, dsq = 0.f, unused = 0.f;
+    float xsq = 0.f, dsq = 0.f;
     int64_t tile = t0;
     int q = 0;
     init_acc<KB>(acc, lds_h, h);
-    auto step = [&](float4 (&x)[8], float4 (&xn)[8], bool more) {
+    for (int64_t i = 0; i < G; ++i) {
         const int q_n = q + 1 == NC ? 0 : q + 1;
         const int64_t tile_n = q_n ? tile : tile + tstride;
-        if (more) load_x_chunk(xn, row_ptr(tile_n), q_n, h, D);
-        mfma_chunk_half<KB, false, false>(acc, x, lds + L.img, lds_mu, q, lane, c.scale, xsq, dsq, unused, 4);
+        const bool more = i + 1 < G;                     // the last step re-reads itself: unused
+        mfma_chunk_refill<KB>(acc, x, lds + L.img, lds_mu, q, lane, c.scale, xsq, dsq, row_ptr(more ? tile_n : tile), more ? q_n : q, D);
         if (q == NC - 1) {
             const float x2 = xsq + __shfl_xor(xsq, 32, kWave), norm = sqrtf(x2) * 1.001f;
             const float e = mfma_bound_half<KB>(acc, reinterpret_cast<const unsigned *>(lds + L.waug), x2,
@@ -152,11 +168,6 @@ __global__ __launch_bounds__(kAssignThreads) void k_beam_score_half(
         }
         tile = tile_n;
         q = q_n;
-    };
-    for (int64_t g = 0; g < G; g += 2) {
-        step(xa, xb, g + 1 < G);
-        if (g + 1 >= G) break;
-        step(xb, xa, g + 2 < G);
     }
 }
 
