@@ -152,7 +152,8 @@ def sweep_bench(args, torch, hclae, synth, dev, gist, extras):
                                                  "argmin, and the exact decision of what the bounds leave open; the "
                                                  "launches over all N vectors: with the exact shortcuts on, the first "
                                                  "assignment of each stage, which also stores the distance bounds)"
-                                                 % ("k_assign_half_chunked<8>" if gist else "k_assign_half<8>"),
+                                                 % (("k_assign_half_chunked<8>" if gist else "k_assign_half<8>") if args.no_pruning else
+                                                    "k_assign_rows16_chunked<8>" if gist else "k_assign_rows16<8>"),
                      "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                      "frac": achieved / peak,
                      "traffic": (ASSIGN_TRAFFIC_BYTES if (N, D, K) == (1_000_000, 128, 256) else
