@@ -29,8 +29,8 @@ MANY_SWEEPS = 20                   # annealing sweeps of the hclae_anneal figure
 
 # HBM bytes per launch of the assign kernel over all vectors, from rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE runs recorded in
 # profiles/da_sweep_*_counters.md (FETCH_SIZE x 2.000, WRITE_SIZE x 1.000; factors from a 512 MB device copy).
-ASSIGN_TRAFFIC_BYTES = 5.658e8   # N=1M, D=128: algorithmic 521e6 (x', codes, bounds)
-ASSIGN_TRAFFIC_BYTES_GIST = 3.985e9   # N=1M, D=960: algorithmic 3.849e9
+ASSIGN_TRAFFIC_BYTES = 3.100e8   # N=1M, D=128: algorithmic 273e6 (fp16 rows, norms, codes, bounds)
+ASSIGN_TRAFFIC_BYTES_GIST = 2.072e9   # N=1M, D=960: algorithmic 1.937e9
 
 
 class State:

@@ -102,6 +102,10 @@ int hclae_anneal_stage(hclae_ctx *ctx, int m, int64_t N, int D, float *C, int M,
                        const int64_t *init_idx, hclae_stage_stats *stats);
 
 /*
+ * (hclae_anneal_stage, hclae_sweep, hclae_anneal with the exact shortcuts on, N K D > 2^23 and iters > 0: the first such call keeps
+ * x' in fp16 as well, in arrays of 32 ceil(D / 16) + 8 bytes per vector of N_max that it allocates and the ctx keeps.  If they cannot be
+ * had, or the stream is being captured, the call runs without them; the results are the same.)
+ *
  * Sec. 3.1, "multiple iterations": hclae_anneal_stage for m = 0..M-1 in order.
  * reencode_mode 0: each stage re-encodes only its own column (keeps E non-increasing).
  * reencode_mode 1: after each stage all M parts are re-encoded greedily from X
@@ -112,8 +116,8 @@ int hclae_anneal_stage(hclae_ctx *ctx, int m, int64_t N, int D, float *C, int M,
  * (mean ||e_x||^2 after each stage).
  * The k-means that cools each stage is the one hclae_set_cooldown chose (plain Lloyd iterations unless set).
  * With the plain cool-down, reencode_mode 0, init_idx == NULL and err_per_stage == NULL the call only enqueues kernels on the
- * context's stream (no allocation, copy, memset or synchronisation; all data-dependent sizes are read on the
- * device), so it may be recorded into a HIP graph on that stream and replayed.
+ * context's stream (apart from that first allocation no allocation, copy, memset or synchronisation; all data-dependent sizes are
+ * read on the device), so it may be recorded into a HIP graph on that stream and replayed.
  */
 int hclae_sweep(hclae_ctx *ctx, const float *X, int64_t N, int D, float *C, int M, int K,
                 uint8_t *codes, float *residue, int iters, int reencode_mode,

@@ -605,9 +605,13 @@ void rows16_scratch(hclae_ctx *ctx)
         {(void **)&ctx->r16_words, sizeof(unsigned) * kWords16},
         {(void **)&ctx->r16_rows, rows},                    // last: its presence says that all are there
     };
-    hipError_t e = hipSuccess;
+    // (another thread may be capturing a stream of its own: an allocation here must not end that)
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    hipError_t e = hipThreadExchangeStreamCaptureMode(&mode);
+    const bool relaxed = e == hipSuccess;
     for (auto &a : allocs)
         if (e == hipSuccess) e = hipMalloc(a.p, a.bytes);
+    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
     // what lies beyond D in a row, and the words, start at zero
     if (e == hipSuccess && rows16_ld(ctx->D) != ctx->D) e = hipMemsetAsync(ctx->r16_rows, 0, rows, ctx->stream);
     if (e == hipSuccess) e = hipMemsetAsync(ctx->r16_words, 0, sizeof(unsigned) * kWords16, ctx->stream);

@@ -72,3 +72,40 @@ def test_dictionaries_that_leave_their_scale(kind):
         X *= np.float32(1e-14)
         C0 *= np.float32(1e-14)
     _same(X, C0, sweeps=2)
+
+
+def test_first_call_under_capture():
+    """While the stream is captured the arrays of the fp16 rows cannot be had: the call reads x' itself, with the same bits, and so do
+    the replays after eager calls that have them."""
+    from paper_1509_05194_amd import hclae
+    N, D, M, K, T = 20000 + 7, 64, 2, 64, 4
+    g = np.random.default_rng(3)
+    X = (g.standard_normal((40, D))[g.integers(0, 40, N)] + 0.3 * g.standard_normal((N, D))).astype(np.float32)
+    C0 = X[g.choice(N, (M, K))] * np.float32(0.5)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        start = [to_dev(C0), torch.zeros((N, M), dtype=torch.uint8, device="cuda:0"), to_dev(X - C0[:, 0].sum(0))]
+        eager = [t.clone() for t in start]
+        ctx = hclae.Context(N, D, M, K)
+        ctx.sweep(*eager, T, want_err=False)
+        torch.cuda.synchronize()
+        other = hclae.Context(N, D, M, K)                 # no call of its own before the captured one
+        run = [t.clone() for t in start]
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            other.sweep(*run, T, want_err=False)
+        for i in range(3):
+            for a, b in zip(run, start):
+                a.copy_(b)
+            graph.replay()
+            torch.cuda.synchronize()
+            for a, b in zip(run, eager):
+                assert torch.equal(a, b), "replay %d" % i
+            again = [t.clone() for t in start]
+            (ctx if i == 0 else other).sweep(*again, T, want_err=False)      # eager work between: other gets its arrays
+            torch.cuda.synchronize()
+            for a, b in zip(again, eager):
+                assert torch.equal(a, b)
+        ctx.close()
+        other.close()
