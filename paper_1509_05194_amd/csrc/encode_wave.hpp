@@ -5,8 +5,7 @@
 // those kernels (N = 1M, D = 128, M = 8, K = 256: 24 passes of 512 MB).  Here it is read once and written once.  The fp16 dictionaries
 // (k_encode_prep) pass through LDS, two of them held: while one is contracted the next travels from L2 into the other by direct
 // loads, for all eight waves of the block together, one barrier per dictionary.  An undecided vector is decided at once, by the two
-// lanes that hold its row: against the best codeword, whose row is gathered anyway for the subtraction, then one more candidate
-// a round.  Scores, bounds and decisions are those of k_assign_half (assign_half.hpp), so the codes are the same fp64 direct-form
+// lanes that hold its row, a candidate a round.  Scores, bounds and decisions are those of k_assign_half (assign_half.hpp), so the codes are the same fp64 direct-form
 // decisions and the residuals the same fp32 subtractions as dictionary by dictionary.
 //
 // Measured (D = 128, M = 8, K = 256, us dictionary by dictionary / here): N = 1M 2451 / 1560, 200k 620 / 424, 49k 317 / 137; D = 64, 100k
