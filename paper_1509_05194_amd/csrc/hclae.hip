@@ -414,7 +414,7 @@ int launch_assign_rows16(hclae_ctx *ctx, int m, int64_t N, const float *xp, cons
 }
 
 // prune: 0 plain; 1 all vectors and store the stage's bounds; 2 only the vectors k_bounds_step listed; 3 = 2 and 4 = 0, with the
-// vectors that changed cluster listed (1 to 3 over all D coordinates only; the caller checks).
+// vectors that changed cluster listed (over all D coordinates only; the caller checks).
 template <int KB>
 int launch_assign_kb(hclae_ctx *ctx, int m, int64_t N, const float *xp, const float *Cm, uint8_t *codes, int dact, int ld,
                      int prune)
@@ -454,7 +454,7 @@ int launch_assign(hclae_ctx *ctx, int m, int64_t N, const float *xp, const float
 {
     if (dact <= 0) dact = ctx->D;
     if (ld <= 0) ld = ctx->D;
-    if ((dact != ctx->D || ld != ctx->D) && prune != 4) prune = 0;     // bounds are over all coordinates
+    if (dact != ctx->D || ld != ctx->D) prune = 0;
     switch (ctx->kb) {
     case 1: return launch_assign_kb<1>(ctx, m, N, xp, Cm, codes, dact, ld, prune);
     case 2: return launch_assign_kb<2>(ctx, m, N, xp, Cm, codes, dact, ld, prune);
@@ -535,7 +535,7 @@ int launch_update(hclae_ctx *ctx, int m, int64_t N, const float *xp, float *Cm, 
 // Centroid update from the vectors that changed cluster since the last update of this stage (x' unchanged,
 // max |x'| still published): exact, see k_merge.  Leaves hneg and the counters as launch_update does.
 // The assignment that just ran (launch_assign with prune 3 or 4) has listed those vectors.
-int launch_update_moved(hclae_ctx *ctx, int m, int64_t N, const float *xp, float *Cm, const uint8_t *codes, int dnorm = 0)
+int launch_update_moved(hclae_ctx *ctx, int m, int64_t N, const float *xp, float *Cm, const uint8_t *codes)
 {
     const int D = ctx->D, K = ctx->K;
     const int windows = (D + kUpdWindow - 1) / kUpdWindow;
@@ -555,7 +555,7 @@ int launch_update_moved(hclae_ctx *ctx, int m, int64_t N, const float *xp, float
     }
     Timed t_(ctx, HCLAE_T_MERGE);
     hipLaunchKernelGGL(k_merge, dim3(K), dim3(256), 0, ctx->stream,
-                       ctx->partial, ctx->pcount, nb, K, D, dnorm > 0 ? dnorm : D, Cm, ctx->hneg, ctx->nk, (int *)nullptr,
+                       ctx->partial, ctx->pcount, nb, K, D, D, Cm, ctx->hneg, ctx->nk, (int *)nullptr,
                        ctx->refine_count, (double *)nullptr, (long long *)nullptr, ctx->tot_sum, ctx->tot_cnt, 1,
                        ctx->moved_count, ctx->drift, merge_image(ctx), N);
     HIP_TRY(ctx, hipGetLastError());
@@ -1889,13 +1889,11 @@ static int enqueue_stage_pca(hclae_ctx *ctx, int m, int64_t N, float *C, uint8_t
     for (int i = 0; i < n_dims; ++i) {
         if (iters_per_dim > 0 && (rc = launch_norms(ctx, Cm, dims[i], D, true)) != HCLAE_OK) return rc;
         for (int t = 0; t < iters_per_dim; ++t, ++iters_run) {
-            // x^r and its maximum stay for the stage and the sums are over all coordinates, so that here too only the first update
-            // has to sum every vector (exact, see k_merge); each assignment lists what it changes
-            const bool first = iters_run == 0;
-            if ((rc = launch_assign(ctx, m, N, xr, Cm, codes, dims[i], D, first ? 0 : 4)) != HCLAE_OK) return rc;
-            rc = first ? launch_update(ctx, m, N, xr, Cm, codes, nullptr, true, false, dims[i], true)
-                       : launch_update_moved(ctx, m, N, xr, Cm, codes, dims[i]);
-            if (rc != HCLAE_OK) return rc;
+            // Every update sums all vectors: on a prefix most of them go on moving, and whether summing those alone is shorter depends
+            // on the data, not on sizes (a stage of 10 iterations, us all / moved: integers in 256 groups, N = 300k, D = 128, K = 256
+            // 2533 / 2472; rows of rank 64, D = 64, K = 256, N = 300k 1435 / 1530, D = 32, K = 64, N = 30k 855 / 988)
+            if ((rc = launch_assign(ctx, m, N, xr, Cm, codes, dims[i], D)) != HCLAE_OK) return rc;
+            if ((rc = launch_update(ctx, m, N, xr, Cm, codes, nullptr, true, false, dims[i])) != HCLAE_OK) return rc;
         }
     }
     // back: C_m = R^T C'
