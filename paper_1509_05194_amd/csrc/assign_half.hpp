@@ -64,6 +64,47 @@ __host__ __device__ constexpr int64_t half_blocks(int64_t N, int cus)
     return blocks < cus ? blocks : cus;
 }
 
+// Which tile a block of k_assign_half takes in its slot-th place (wave w has the places w, w + 8, ...).  ls < 0: tiles in order over the
+// blocks, so that with few of them every block has one before any has two.  ls >= 0: so within each XCD, and a stretch of 2^ls tiles
+// belongs to the XCD whose row-pass blocks take those rows (blocks go round the eight XCDs in order): what the pass left in that L2 is
+// read from there, and the other way round.  A chunk of the online learner, D = 128, us in order / so: N = 49k, K = 20 534 / 466, K = 256
+// 752 / 702; N = 1M, K = 256, beyond the L2s, 4596 / 4593; encoding N = 60k, D = 192, K = 256 438 / 406.
+__host__ __device__ constexpr int half_tile(int block, int slot, int grid, int ls)
+{
+    if (ls < 0) return block + grid * slot;
+    const int i = slot * (grid >> 3) + (block >> 3);
+    return ((((i >> ls) << 3) | (block & 7)) << ls) | (i & ((1 << ls) - 1));
+}
+// Tiles below ntiles among the places of a wave.
+__host__ __device__ constexpr int half_tiles_of(int block, int wave, int ntiles, int grid, int ls)
+{
+    int first = block + grid * wave, end = ntiles, step = grid;
+    if (ls >= 0) {
+        const int rounds = ntiles >> (ls + 3), rest = ntiles - (rounds << (ls + 3)) - ((block & 7) << ls);
+        step = grid >> 3;
+        first = wave * step + (block >> 3);
+        end = (rounds << ls) + (rest < 0 ? 0 : rest < (1 << ls) ? rest : 1 << ls);      // tiles of the block's XCD
+    }
+    step *= kAssignWaves;
+    return first < end ? (end - first + step - 1) / step : 0;
+}
+// No block has more tiles than this.
+__host__ __device__ constexpr int half_share(int ntiles, int grid, int ls)
+{
+    if (ls < 0) return (ntiles + grid - 1) / grid;
+    const int step = grid >> 3;
+    return ((((ntiles >> (ls + 3)) + 1) << ls) + step - 1) / step;
+}
+// ls of a launch: with a block on every CU, if a stretch is no larger than half a round of blocks (half_list_entries has room for the
+// tiles that one XCD may have more than another).  pass_rows: consecutive rows that a block of the row pass takes.
+__host__ __device__ constexpr int half_order(int grid, int cus, int pass_rows)
+{
+    if (grid != cus || grid % 8 || pass_rows < kTileVec || 2 * (pass_rows / kTileVec) > grid) return -1;
+    int ls = 0;
+    while ((2 << ls) * kTileVec <= pass_rows) ++ls;
+    return ls;
+}
+
 // LDS of the kernels: the fp16 dictionary (or two slices of it), then per-codeword constants, mu, and the waves' buffers.
 struct HalfLds {
     int img, hneg, w, waug, mu, moved, misc, open, total;   // byte offsets
@@ -955,7 +996,7 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign_half(
     int N, int D, int ld, int K, int M, int m, int NC,
     uint8_t *__restrict__ codes, unsigned *__restrict__ refine_count, PruneArgs pa,
     unsigned long long *__restrict__ moved_list, unsigned *__restrict__ moved_count, unsigned long long *__restrict__ work,
-    HalfItem *__restrict__ items)
+    HalfItem *__restrict__ items, int ls)
 {
     extern __shared__ float4 smem4[];
     char *lds = reinterpret_cast<char *>(smem4);
@@ -979,10 +1020,10 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign_half(
     }
     if ((int)blockIdx.x >= ntiles) return;                      // no tile for any wave of this block
 
-    const int tstride = (int)gridDim.x * kAssignWaves;
-    const int t0 = (int)blockIdx.x + (int)gridDim.x * wave;     // with few tiles, a block each before any block gets two
-    HalfWave w = half_wave(lds, L, items + (size_t)((ntiles + tstride - 1) / tstride) * kTileVec * kAssignWaves * blockIdx.x);
-    const int my_tiles = t0 < ntiles ? (ntiles - t0 + tstride - 1) / tstride : 0;
+    if (PRUNE == 2) ls = -1;                                    // listed vectors lie anywhere
+    const int t0 = half_tile(blockIdx.x, wave, gridDim.x, ls);
+    HalfWave w = half_wave(lds, L, items + (size_t)half_share(ntiles, gridDim.x, ls) * kTileVec * blockIdx.x);
+    const int my_tiles = half_tiles_of(blockIdx.x, wave, ntiles, gridDim.x, ls);
     const int64_t G = (int64_t)my_tiles * NC;                       // (tile, chunk) steps of this wave
 
     // vector behind column r of a tile; N (= "none") for the columns of the ragged tail
@@ -999,7 +1040,7 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign_half(
     float amax = 0.f;
     const int steps_last = PREFIX ? (D - kChunkD * (NC - 1) + kHalfStep - 1) / kHalfStep : 4;
     auto steps_of = [&](int qq) { return (PREFIX && qq == NC - 1) ? steps_last : 4; };
-    int tile = t0, n = N;
+    int slot = wave, n = N;
     unsigned old = 0u;
     float4 xa[8], xb[8];
     if (G > 0) {                                                    // the first chunk travels while the dictionary is staged
@@ -1015,14 +1056,14 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign_half(
         init_acc<KB>(acc, lds_h, h);
         // one step: contract x (chunk q of the tile) while the next step's chunk travels into xn
         auto step = [&](float4 (&x)[8], float4 (&xn)[8], bool more) {
-            int tile_n = tile, n_n = n;
+            int n_n = n;
             unsigned old_n = old;
             int q_n = q + 1;
             if (q_n == NC) {
                 q_n = 0;
-                tile_n = tile + tstride;
+                slot += kAssignWaves;
                 if (more) {
-                    n_n = vec_of(tile_n);
+                    n_n = vec_of(half_tile(blockIdx.x, slot, gridDim.x, ls));
                     if (want_moved) old_n = n_n < N ? codes[(size_t)n_n * M + m] : 0u;
                 }
             }
@@ -1037,7 +1078,6 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign_half(
                 xsq = 0.f;
                 dsq = 0.f;
             }
-            tile = tile_n;
             n = n_n;
             old = old_n;
             q = q_n;

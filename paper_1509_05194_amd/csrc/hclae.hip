@@ -258,6 +258,12 @@ RowGeom row_geom(int D)
     return g;
 }
 
+// Consecutive rows that a block of the row pass takes.
+int row_pass_rows(int D)
+{
+    return D >= kWideMinD ? (kStreamThreads / kWave) * kWideRows : (kStreamThreads >> row_geom(D).lcw) * kStreamUnroll;
+}
+
 // ---- launches (all on ctx->stream) ------------------------------------------------------
 
 RowPass16 row_pass16(const hclae_ctx *ctx)
@@ -354,7 +360,7 @@ int launch_assign_half(hclae_ctx *ctx, int m, int64_t N, const float *xp, const 
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kAssignThreads), (size_t)half_lds(KB, NC, NC).total, ctx->stream,
                        xp, Cm, ctx->hneg, (int)N, dact, ld, ctx->K, ctx->M, m, NC, codes, ctx->refine_count, pa,
                        want_moved ? ctx->moved_list : (unsigned long long *)nullptr, ctx->moved_count, ctx->work,
-                       ctx->half_list);
+                       ctx->half_list, half_order((int)blocks, ctx->cus, row_pass_rows(ctx->D)));
     HIP_TRY(ctx, hipGetLastError());
     return HCLAE_OK;
 }
