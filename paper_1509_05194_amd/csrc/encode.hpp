@@ -26,8 +26,10 @@ __host__ __device__ constexpr int64_t encode_tiles(int64_t N) { return (N + kTil
 __host__ __device__ constexpr int64_t encode_blocks(int64_t N) { return encode_tiles(N) < (1 << 20) ? encode_tiles(N) : (1 << 20); }
 
 // One block per dictionary: fp16 image in the order of half_slot, k-step by k-step; -||C||^2/2 and w per codeword; -mu; the
-// constants (half_constants has the reasons); -||c||^2/2 of the codewords as they are.  Also clears the counters of undecided
-// vectors and of tiles given up (k_encode_wave).
+// constants (half_constants has the reasons).  Also clears the counters of undecided vectors and of tiles given up (k_encode_wave).
+// NORMS: a second block per dictionary leaves -||c||^2/2 of the codewords as they are, from 64-bit sums (-inf beyond K), for scores from
+// the fp32 matrix cores; within the other blocks the same sums cost small calls, which never ask for such scores, 1 %.
+template <bool NORMS>
 __global__ __launch_bounds__(kPrepThreads) void k_encode_prep(
     const float *__restrict__ C, int K, int D, int kb, int NC, char *__restrict__ img, float *__restrict__ hn,
     float *__restrict__ wtab, float *__restrict__ negmu, float *__restrict__ consts, float *__restrict__ hneg,
@@ -35,9 +37,18 @@ __global__ __launch_bounds__(kPrepThreads) void k_encode_prep(
 {
     __shared__ float s_sq[256], s_dsq[256], s_red[2][kPrepThreads / kWave];
     constexpr int waves = kPrepThreads / kWave;
-    const int m = blockIdx.x, lane = lane_id(), wave = threadIdx.x >> 6;
+    const int M = NORMS ? gridDim.x / 2 : gridDim.x, m = NORMS && (int)blockIdx.x >= M ? blockIdx.x - M : blockIdx.x;
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
     const int kpad = 32 * kb;
     const float *Cm = C + (size_t)m * K * D;
+    if (NORMS && (int)blockIdx.x >= M) {
+        for (int row = wave; row < kpad; row += waves) {
+            const float4 v = load_row_piece(Cm, row, 4 * lane, K, D, D);
+            const double s = wave_sum((double)v.x * v.x + (double)v.y * v.y + (double)v.z * v.z + (double)v.w * v.w);
+            if (lane == 0) hneg[(size_t)m * kpad + row] = row < K ? -(float)(0.5 * s) : -__builtin_inff();
+        }
+        return;
+    }
     img += (size_t)m * NC * kb * 4096;
     if (m == 0 && threadIdx.x == 0) refine_count[0] = refine_count[2] = 0u;
     // a lane keeps its float4 column (NC <= 4), a wave takes rows wave, wave + 16, ..., eight of them in flight
@@ -62,12 +73,8 @@ __global__ __launch_bounds__(kPrepThreads) void k_encode_prep(
             const float4 v = load_row_piece(Cm, r0 + u * waves, 4 * p, K, D, D);
             s[u] = v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
         }
-        const float mine = group_sums<U, 64>(s);                    // lane i: row r0 + i waves
-        const int row = r0 + (lane & (U - 1)) * waves;
-        if (lane < U && row < K) hneg[(size_t)m * kpad + row] = -0.5f * mine;
-        big = fmaxf(big, mine);
+        big = fmaxf(big, group_sums<U, 64>(s));
     }
-    for (int k = K + threadIdx.x; k < kpad; k += kPrepThreads) hneg[(size_t)m * kpad + k] = -__builtin_inff();
 #pragma unroll
     for (int o = 1; o < U; o <<= 1) big = fmaxf(big, __shfl_xor(big, o, kWave));
     if (lane == 0) s_red[0][wave] = big;

@@ -812,6 +812,7 @@ struct EncodeTables {
     char *img;
     float *hn, *wtab, *negmu, *consts, *hneg;
 };
+template <bool NORMS>
 int launch_encode_prep(hclae_ctx *ctx, const float *C, int NC, EncodeTables *t)
 {
     const int kb = ctx->kb, kpad = 32 * kb;
@@ -822,7 +823,7 @@ int launch_encode_prep(hclae_ctx *ctx, const float *C, int NC, EncodeTables *t)
     t->consts = t->negmu + (size_t)ctx->M * kChunkD * NC;
     t->hneg = t->consts + (size_t)ctx->M * kEncodeConsts;
     Timed t_(ctx, HCLAE_T_NORMS);
-    hipLaunchKernelGGL(k_encode_prep, dim3(ctx->M), dim3(kPrepThreads), 0, ctx->stream, C, ctx->K, ctx->D, kb, NC,
+    hipLaunchKernelGGL(k_encode_prep<NORMS>, dim3(NORMS ? 2 * ctx->M : ctx->M), dim3(kPrepThreads), 0, ctx->stream, C, ctx->K, ctx->D, kb, NC,
                        t->img, t->hn, t->wtab, t->negmu, t->consts, t->hneg, ctx->refine_count);
     HIP_TRY(ctx, hipGetLastError());
     return HCLAE_OK;
@@ -833,7 +834,7 @@ int launch_encode_wave(hclae_ctx *ctx, const float *X, int64_t N, const float *C
 {
     static_assert(wave_lds(KB, NC).total <= kLdsBudget, "two dictionaries fit LDS");
     EncodeTables t;
-    int rc = launch_encode_prep(ctx, C, NC, &t);
+    int rc = launch_encode_prep<true>(ctx, C, NC, &t);
     if (rc != HCLAE_OK) return rc;
     const bool full = ctx->D == kChunkD * NC;
     auto kern = full ? &k_encode_wave<KB, NC, true, false> : &k_encode_wave<KB, NC, false, false>;
@@ -860,7 +861,7 @@ int launch_encode_fused(hclae_ctx *ctx, const float *X, int64_t N, const float *
 {
     if (8 * NC > 16 * KB) return fail(ctx, HCLAE_EINVAL, "encode: shape not covered by the fused encoder");
     EncodeTables t;
-    int rc = launch_encode_prep(ctx, C, NC, &t);
+    int rc = launch_encode_prep<false>(ctx, C, NC, &t);
     if (rc != HCLAE_OK) return rc;
     Timed t_(ctx, HCLAE_T_ASSIGN);
     hipLaunchKernelGGL((k_encode_fused<KB, NC>), dim3((unsigned)encode_blocks(N)), dim3(64 * KB),

@@ -1,6 +1,6 @@
 // Support for the tests: single instructions of the distance contraction, so that what the rounding bounds of assign_half.hpp
-// take for granted about them can be measured.  Built next to the library, not part of it.
-#include "assign_half.hpp"
+// take for granted about them can be measured, and tables that no entry point returns.  Built next to the library, not part of it.
+#include "encode.hpp"
 
 namespace {
 
@@ -46,5 +46,21 @@ int hclae_probe_mfma(int k, const void *A, const void *B, const float *acc, floa
 
 // What the bounds allow one of them, relative to the largest magnitude it adds: half_acc, and the 2^-23 per term of rescore_items.
 float hclae_probe_allowance(int k) { return k == 2 ? 2.f * 1.1920929e-7f : kHalfAccUnit; }
+
+// -||c||^2/2 of M dictionaries as k_encode_prep leaves them, out [M][32 kb] with the smallest kb of 1, 2, 4, 8 that holds K; D <= 256.
+int hclae_probe_encode_norms(const float *C, int M, int K, int D, float *out)
+{
+    if (!C || !out || M < 1 || K < 1 || K > 256 || D < 4 || D > 256 || D % 4) return -1;
+    const int kb = K <= 32 ? 1 : K <= 64 ? 2 : K <= 128 ? 4 : 8, NC = (D + kChunkD - 1) / kChunkD, nc = NC == 3 ? 4 : NC;
+    char *buf = nullptr;
+    const size_t img = (size_t)M * nc * kb * 4096, tab = (size_t)M * 32 * kb, mu = (size_t)M * kChunkD * nc;
+    if (hipMalloc((void **)&buf, img + sizeof(float) * (2 * tab + mu + M * kEncodeConsts + 4)) != hipSuccess) return -3;
+    float *hn = reinterpret_cast<float *>(buf + img), *w = hn + tab, *negmu = w + tab, *consts = negmu + mu;
+    hipLaunchKernelGGL(k_encode_prep<true>, dim3(2 * M), dim3(kPrepThreads), 0, 0, C, K, D, kb, nc, buf, hn, w, negmu, consts, out,
+                       reinterpret_cast<unsigned *>(consts + M * kEncodeConsts));
+    const bool ok = hipGetLastError() == hipSuccess && hipDeviceSynchronize() == hipSuccess;
+    (void)hipFree(buf);
+    return ok ? 0 : -3;
+}
 
 }
