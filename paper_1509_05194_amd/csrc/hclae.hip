@@ -799,14 +799,6 @@ Encoder encoder(const hclae_ctx *ctx, int64_t N)
     return nc <= 2 ? Encoder::wave : Encoder::steps;
 }
 
-// How many assignments hclae_timing_read counts for a call of k_encode_wave: one per dictionary above the sizes from which a call with so
-// many codewords has counted that way (one up to there), so that a caller's figures per assignment go on meaning the same.
-int encode_timed(const hclae_ctx *ctx, int64_t N)
-{
-    const int tiles_per_cu = ctx->kb == 1 || (ctx->kb == 2 && ctx->D > 16) ? 0 : ctx->kb == 2 ? 48 : ctx->kb == 4 ? (ctx->NC == 2 ? 32 : 16) : 6;
-    return tiles_per_cu && N > (int64_t)ctx->cus * tiles_per_cu * kTileVec ? ctx->M : 1;
-}
-
 // The dictionaries as the encoders that take all of them in one kernel want them (k_encode_prep).
 struct EncodeTables {
     char *img;
@@ -846,13 +838,13 @@ int launch_encode_wave(hclae_ctx *ctx, const float *X, int64_t N, const float *C
         ctx->attr_done |= attr_set;
     }
     const int64_t nbt = (N + kTileVec * kAssignWaves - 1) / (kTileVec * kAssignWaves);
-    for (int i = 1; i < encode_timed(ctx, N); ++i) Timed empty(ctx, HCLAE_T_ASSIGN);
-    Timed t_(ctx, HCLAE_T_ASSIGN);
-    for (auto k : {kern, rest})                 // the tiles that the first gives up are listed in ctx->active
+    for (auto k : {kern, rest}) {               // the tiles that the first gives up are listed in ctx->active
+        Timed t_(ctx, HCLAE_T_ASSIGN);
         hipLaunchKernelGGL(k, dim3((unsigned)(nbt < ctx->cus ? nbt : ctx->cus)), dim3(kAssignThreads), (size_t)wave_lds(KB, NC).total,
                            ctx->stream, X, C, (int)N, ctx->D, ctx->K, ctx->M, t.img, t.hn, t.wtab, t.negmu, t.consts, t.hneg, codes, residue,
                            ctx->refine_count, ctx->work, ctx->active, ctx->refine_count + 2);
-    HIP_TRY(ctx, hipGetLastError());
+        HIP_TRY(ctx, hipGetLastError());
+    }
     return HCLAE_OK;
 }
 

@@ -10,7 +10,7 @@ torch = pytest.importorskip("torch")
 
 
 # K: 1, 2, 4 and 8 waves to a block; D: 1, 2 and 4 chunks (one that rounds up) and rows too long for the fused kernel;
-# N: one vector, the edges of a 32-vector tile, and above the line where K > 128 goes dictionary by dictionary
+# N: one vector, the edges of a 32-vector tile, and a call that the encoder with a tile per wave takes
 @pytest.mark.parametrize("kind", ["plain", "ties", "spread"])
 @pytest.mark.parametrize("N,D,M,K", [(1, 4, 1, 1), (31, 16, 4, 16), (33, 64, 3, 32), (65, 100, 2, 20), (95, 60, 3, 33),
                                      (1000, 128, 4, 64), (777, 200, 2, 50), (513, 68, 3, 65), (600, 128, 8, 128),
@@ -71,14 +71,19 @@ def test_encode_with_more_tiles_than_blocks():
     ctx.close()
 
 
-# 256 CUs: the lines lie at 6, 12, 16, 32 and 48 tiles of 32 vectors per CU
-@pytest.mark.parametrize("N,D,K,fused", [(49152, 16, 129, True), (49153, 16, 129, False), (131072, 16, 65, True), (131073, 64, 128, False),
-                                         (262144, 68, 65, True), (262145, 128, 128, False), (131072, 132, 65, True), (131073, 204, 65, False),
-                                         (131073, 208, 65, True), (98304, 132, 33, True), (98305, 204, 64, False), (393216, 208, 33, True),
-                                         (393217, 208, 64, False), (393216, 16, 33, True), (393217, 16, 64, False),
-                                         (400000, 20, 64, True), (400000, 16, 32, True), (100, 260, 20, False), (100, 132, 32, False)])
-def test_encoder_by_size(N, D, K, fused):
-    """Both encoders on either side of the lines between them: one launch that decides, or one per dictionary."""
+# 256 CUs.  Three ways to encode, told apart by the launches that decide: one (a tile for all waves of a block), two (a tile per wave; the
+# second takes up what the first leaves) or one per dictionary.  Rows of up to 64 and 128 coordinates change from the first to the
+# second above 4 and 6 tiles of 32 vectors per CU (K <= 64), 4 (K <= 128), 1 and 2; longer ones from the first to the third above 12 and,
+# from D = 208 on, 48 (K <= 64), 16 and never (K <= 128), 6.  N: at the line and one more
+@pytest.mark.parametrize("N,D,K,launches", [
+    (32768, 64, 32, 1), (32769, 64, 32, 2), (32769, 16, 33, 2), (49152, 68, 32, 1), (49153, 128, 64, 2),
+    (32768, 16, 65, 1), (32769, 16, 65, 2), (32768, 128, 128, 1), (32769, 128, 128, 2), (32769, 68, 65, 2),
+    (8192, 64, 129, 1), (8193, 64, 129, 2), (8193, 4, 256, 2), (16384, 68, 129, 1), (16385, 128, 256, 2), (400000, 20, 64, 2),
+    (98304, 132, 33, 1), (98305, 204, 64, 3), (393216, 208, 33, 1), (393217, 208, 64, 3),
+    (131072, 132, 65, 1), (131073, 204, 65, 3), (131073, 208, 65, 1), (49152, 132, 140, 1), (49153, 256, 140, 3),
+    (100, 260, 20, 3), (100, 132, 32, 3)])
+def test_encoder_by_size(N, D, K, launches):
+    """The encoders on either side of the lines between them."""
     from paper_1509_05194_amd import hclae
     M = 3
     g = torch.Generator(device="cuda").manual_seed(N + K)
@@ -88,7 +93,7 @@ def test_encoder_by_size(N, D, K, fused):
     codes, r = torch.full((N, M), 9, dtype=torch.uint8, device="cuda:0"), torch.empty_like(X)
     ctx.timing_enable(["assign"])
     ctx.encode(X, C, codes, r)
-    assert ctx.timing_read()["assign"][1] == (1 if fused else M)
+    assert ctx.timing_read()["assign"][1] == launches
     ctx.timing_enable([])
     want, rw = torch.full_like(codes, 9), X.clone()
     for m in range(M):
