@@ -712,11 +712,27 @@ __device__ __forceinline__ void decide_items(
                     const float a = u.x - v.x, b = u.y - v.y, c = u.z - v.z, d = u.w - v.w;
                     return fmaf(d, d, fmaf(c, c, fmaf(b, b, fmaf(a, a, s))));
                 };
-#pragma unroll 4
-                for (int d = sub; d < d4; d += 8) {
-                    const float4 u = x[d];
-                    s0 = term(s0, u, c0[d]);
-                    s1 = term(s1, u, c1[d]);
+                int d = sub;
+                for (; d + 24 < d4; d += 32) {
+                    float4 u[4], v[4], w[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        u[i] = x[d + 8 * i];
+                        v[i] = c0[d + 8 * i];
+                        w[i] = c1[d + 8 * i];
+                    }
+                    __builtin_amdgcn_sched_barrier(0);              // twelve loads in flight: k_encode_rest takes twice as long with two
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        s0 = term(s0, u[i], v[i]);
+                        s1 = term(s1, u[i], w[i]);
+                    }
+                }
+                for (; d < d4; d += 8) {
+                    const float4 u = x[d], v = c0[d], w = c1[d];
+                    __builtin_amdgcn_sched_barrier(0);
+                    s0 = term(s0, u, v);
+                    s1 = term(s1, u, w);
                 }
                 if ((D & 3) && sub == (d4 & 7)) {                   // D need not be a multiple of 4
                     for (int d = 4 * d4; d < D; ++d) {

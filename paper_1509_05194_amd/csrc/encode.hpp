@@ -50,7 +50,7 @@ __global__ __launch_bounds__(kPrepThreads) void k_encode_prep(
         return;
     }
     img += (size_t)m * NC * kb * 4096;
-    if (m == 0 && threadIdx.x == 0) refine_count[0] = refine_count[2] = 0u;
+    if (m == 0 && threadIdx.x == 0) refine_count[0] = refine_count[2] = refine_count[3] = 0u;
     // a lane keeps its float4 column (NC <= 4), a wave takes rows wave, wave + 16, ..., eight of them in flight
     constexpr int U = 8;
     const int p = lane;

@@ -829,8 +829,8 @@ int launch_encode_wave(hclae_ctx *ctx, const float *X, int64_t N, const float *C
     int rc = launch_encode_prep<true>(ctx, C, NC, &t);
     if (rc != HCLAE_OK) return rc;
     const bool full = ctx->D == kChunkD * NC;
-    auto kern = full ? &k_encode_wave<KB, NC, true, false> : &k_encode_wave<KB, NC, false, false>;
-    auto rest = full ? &k_encode_wave<KB, NC, true, true> : &k_encode_wave<KB, NC, false, true>;
+    auto kern = full ? &k_encode_wave<KB, NC, true> : &k_encode_wave<KB, NC, false>;
+    auto rest = &k_encode_rest<KB, NC>;
     const uint64_t attr_set = 1ull << 36;       // this call site's bit in ctx->attr_done (D and K are the ctx's)
     if (!(ctx->attr_done & attr_set)) {
         HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget));
@@ -838,13 +838,20 @@ int launch_encode_wave(hclae_ctx *ctx, const float *X, int64_t N, const float *C
         ctx->attr_done |= attr_set;
     }
     const int64_t nbt = (N + kTileVec * kAssignWaves - 1) / (kTileVec * kAssignWaves);
-    for (auto k : {kern, rest}) {               // the tiles that the first gives up are listed in ctx->active
+    uint2 *given = reinterpret_cast<uint2 *>(ctx->active);      // the tiles that the first launch leaves to the second
+    unsigned *counts = ctx->refine_count + 2;
+    {
         Timed t_(ctx, HCLAE_T_ASSIGN);
-        hipLaunchKernelGGL(k, dim3((unsigned)(nbt < ctx->cus ? nbt : ctx->cus)), dim3(kAssignThreads), (size_t)wave_lds(KB, NC).total,
-                           ctx->stream, X, C, (int)N, ctx->D, ctx->K, ctx->M, t.img, t.hn, t.wtab, t.negmu, t.consts, t.hneg, codes, residue,
-                           ctx->refine_count, ctx->work, ctx->active, ctx->refine_count + 2);
+        hipLaunchKernelGGL(kern, dim3((unsigned)(nbt < ctx->cus ? nbt : ctx->cus)), dim3(kAssignThreads), (size_t)wave_lds(KB, NC).total,
+                           ctx->stream, X, C, (int)N, ctx->D, ctx->K, ctx->M, t.img, t.hn, t.wtab, t.negmu, t.consts, codes, residue,
+                           ctx->refine_count, ctx->work, given, counts);
         HIP_TRY(ctx, hipGetLastError());
     }
+    Timed t_(ctx, HCLAE_T_ASSIGN);
+    hipLaunchKernelGGL(rest, dim3((unsigned)half_blocks(N, ctx->cus)), dim3(kAssignThreads), (size_t)half_lds(KB, NC, NC).total,
+                       ctx->stream, X, C, (int)N, ctx->D, ctx->K, ctx->M, t.img, t.hn, t.wtab, t.negmu, t.consts, t.hneg, codes, residue,
+                       ctx->refine_count, ctx->work, given, counts, ctx->half_list);
+    HIP_TRY(ctx, hipGetLastError());
     return HCLAE_OK;
 }
 

@@ -69,3 +69,19 @@ def test_large_calls_equal_small_ones(N, D, M, K):
 @pytest.mark.parametrize("N,D,M,K", [(20000 + 3, 128, 2, 256), (9000 + 1, 52, 3, 140), (34000, 100, 2, 96)])
 def test_many_candidates_and_ties(kind, N, D, M, K):
     _same_as_small_calls(*_data(kind, N, D, M, K, np.random.default_rng(K)), 4000)
+
+
+@pytest.mark.parametrize("kind", ["groups", "tiny", "zero", "some", "late"])
+@pytest.mark.parametrize("N,D,M,K", [(140000 + 5, 128, 1, 256), (140000 + 5, 64, 3, 200), (210000, 76, 2, 33), (80000 + 31, 20, 5, 130)])
+def test_tiles_left_to_the_second_launch(kind, N, D, M, K):
+    """Several rounds of tiles: all left from the first round on, or from some dictionary on, or few of them (at different dictionaries)."""
+    rng = np.random.default_rng(N + D)
+    X, C = _data(kind if kind in ("groups", "tiny", "zero") else "plain", N, D, M, K, rng)
+    if kind == "some":                                   # vectors between all the codewords of one dictionary
+        C[1:] *= np.float32(0.3)
+        for m in range(M):
+            X[100 + 700 * m::5000] = C[:m].sum(0)[0] if m else 0
+            C[m, K // 2:] *= np.float32(1e-3)
+    elif kind == "late":
+        C[M // 2 + (M > 1):] *= np.float32(1e-4)
+    _same_as_small_calls(X, C, 8000)
