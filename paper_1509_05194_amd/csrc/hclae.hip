@@ -772,31 +772,53 @@ int encode_chunks(const hclae_ctx *ctx)
 
 // Which encoder takes a call: one that has the vectors of a tile decided by all the waves of a block in lockstep (k_encode_fused: shortest
 // for few vectors), one with a tile per wave (k_encode_wave, rows up to 128 coordinates), or the kernels that go dictionary by dictionary.
-// The lines, in tiles of 32 vectors per CU, on two kinds of rows, few near-ties and many (M = 8, us fused / tile per wave / dictionary by
-// dictionary):
-//   K > 128       D = 128  16k 92 / 119 / 216 and 101 / 131 / 219, 32k 165 / 125 / 275 and 184 / 134 / 278, 524k - / 856 / 1309 and - / 943 / 1461
-//                 D = 64   8k 47 / 75 / 174 and 51 / 76 / 173, 16k 77 / 76 / 184 and 83 / 79 / 190;  D = 32  16k 72 / 66 / 171 and 79 / 68 / 172
-//   K in 65..128  D = 128  32k 87 / 99 / 237 and 98 / 106 / 240, 49k 119 / 107 / 282 and 141 / 114 / 293;  D = 64  32k 64 / 65 / 189 and 72 / 69 / 191
-//   K in 33..64   D = 128  49k 89 / 91 / 265 and 104 / 102 / 272, 65k 106 / 102 / 282 and 118 / 111 / 290;  D = 32  32k 41 / 50 / 150 and 46 / 54 / 164,
-//                 49k 62 / 58 / 166 and 71 / 62 / 174
-//   K <= 32       D = 128  49k 77 / 81 / 256 and 88 / 96 / 260, 65k 115 / 87 / 270 and 130 / 101 / 281;  D = 16  32k 44 / 43 / 132 and 48 / 47 / 145
-// and, longer rows (us fused / dictionary by dictionary):
-//   K in 65..128  D = 192  98k 361 / 459 and 414 / 487, 196k 733 / 748 and 866 / 787;  D = 208  392k 1481 / 1693 and 1752 / 1854
-//   K in 33..64   D = 192  98k 386 / 437 and 454 / 455, 196k 818 / 713 and 937 / 744;  D = 256  392k 1596 / 1661 and 1922 / 1776
+// k_encode_wave takes its tiles in rounds of eight per CU, and a round that is begun costs nearly as much as a full one; k_encode_fused's time grows
+// with the tiles.  The line between them is therefore so many tiles per CU for every round the call would have: the higher, the
+// fewer waves a block of the fused kernel has, and for long rows, where its waves wait for each other least.  A single dictionary gains nothing from
+// rows that stay on chip and two gain little, unless the row pass of the steps has rows that are no whole cache lines.  Measured, us fused / tile per wave / dictionary by dictionary:
+//   M = 8, K = 256  D = 128  16k 95 / 122 / 221, 24k 134 / 126 / 245, 66k 327 / 152 / 317, 80k 392 / 240 / 345, 400k 1823 / 775 / 1015
+//                   D = 64   9k 69 / 74 / 176, 16k 77 / 77 / 190, 24k 107 / 81 / 208, 80k 299 / 147 / 264
+//          K = 128  D = 128  33k 90 / 102 / 207, 49k 125 / 111 / 231, 80k 189 / 186 / 293;  D = 64  33k 68 / 69 / 180, 49k 94 / 77 / 200
+//          K = 64   D = 128  66k 114 / 102 / 233, 80k 127 / 154 / 272, 200k 259 / 285 / 492, 400k 483 / 482 / 889
+//                   D = 64   80k 89 / 98 / 205, 200k 178 / 176 / 318, 262k 219 / 182 / 374;  D = 32  49k 65 / 61 / 159, 200k 167 / 152 / 236
+//                   D = 16   33k 52 / 52 / 149, 49k 69 / 59 / 160, 200k 179 / 137 / 209
+//          K = 32   D = 128  49k 78 / 83 / 195, 66k 114 / 84 / 222, 80k 122 / 126 / 256;  D = 64, K = 16  66k 61 / 62 / 178, 800k 391 / 440 / 872
+//                   D = 16   33k 50 / 48 / 140, 80k 85 / 68 / 163
+//   M = 2, K = 256  D = 128  24k 54 / 59 / 65, 66k 117 / 80 / 81, 200k 311 / 170 / 152;  D = 64  131k 167 / 79 / 84, 200k 245 / 108 / 104
+//          K = 128  D = 128  80k 65 / 68 / 74, 131k 95 / 80 / 100;  D = 32  131k 69 / 54 / 58, 400k 170 / 106 / 98;  K = 64  D = 64  131k 48 / 51 / 64
+//   M = 1, K = 256  D = 128  9k 28 / 38 / 27, 200k 194 / 115 / 75;  K = 128  33k 29 / 36 / 30, 66k 42 / 41 / 35;  K = 64  66k 34 / 35 / 35, 131k 48 / 51 / 46
+//   M = 2, K = 256  D = 80  200k 300 / 137 / 146;  K = 128  D = 20  150k 72 / 49 / 61;  M = 1, K = 128, D = 100  131k 65 / 58 / 62, 200k 87 / 78 / 83
+//   M = 1  D = 64   K = 16  66k 25 / 26 / 28, 262k 46 / 55 / 47;  D = 16   K = 64  33k 30 / 31 / 23, 200k 94 / 54 / 31
+// and, longer rows (fused / dictionary by dictionary):
+//   M = 8, K in 65..128  D = 192  98k 361 / 459 and 414 / 487, 196k 733 / 748 and 866 / 787;  D = 208  392k 1481 / 1693 and 1752 / 1854
+//          K in 33..64   D = 192  98k 386 / 437 and 454 / 455, 196k 818 / 713 and 937 / 744;  D = 256  392k 1596 / 1661 and 1922 / 1776
 enum class Encoder { fused, wave, steps };
 Encoder encoder(const hclae_ctx *ctx, int64_t N)
 {
-    const int nc = encode_chunks(ctx);
+    const int nc = encode_chunks(ctx), kb = ctx->kb, D = ctx->D, M = ctx->M;
     if (!nc) return Encoder::steps;
-    const bool full = ctx->D >= 208;                         // of four chunks
-    int tiles_per_cu;
-    switch (ctx->kb) {
-    case 1: case 2: tiles_per_cu = nc == 1 ? 4 : nc == 2 ? 6 : full ? 48 : 12; break;
-    case 4: tiles_per_cu = nc <= 2 ? 4 : 16; break;
-    default: tiles_per_cu = nc <= 2 ? nc : 6;
+    const int64_t tiles = encode_tiles(N), cus = ctx->cus;
+    if (nc > 2) {
+        const bool full = D >= 208;                          // of four chunks
+        const int line = kb == 2 ? (full ? 48 : 12) : kb == 4 ? 16 : 6;
+        return tiles <= cus * line || (kb == 4 && full) ? Encoder::fused : Encoder::steps;
     }
-    if (N <= (int64_t)ctx->cus * tiles_per_cu * kTileVec || (ctx->kb == 4 && full)) return Encoder::fused;
-    return nc <= 2 ? Encoder::wave : Encoder::steps;
+    const bool lines = D % 32 == 0 || D <= 16;               // rows of whole cache lines, or nearly: the row pass takes them best
+    if (M == 1) {
+        if (kb <= 2 && (!lines || (kb == 1 && nc == 1 && D > 32))) return Encoder::fused;
+        return tiles <= cus * (kb == 8 ? 1 : kb == 4 || D <= 16 ? 4 : 8) ? Encoder::fused : Encoder::steps;
+    }
+    const int64_t rounds = (tiles + kAssignWaves * cus - 1) / (kAssignWaves * cus);
+    if (M == 2 && lines && (kb == 8 || D <= (kb == 1 ? 16 : 32)) && rounds > (kb == 8 && nc == 2 ? 1 : 2)) return Encoder::steps;
+    const bool few = M < 4;                                  // what a call pays once is a larger share
+    int line;                                                // half tiles per CU and round; 16: never the tile per wave
+    switch (kb) {
+    case 1: line = nc == 2 ? 12 : D <= 24 ? 8 : 16; break;
+    case 2: line = D <= 32 ? 9 : D <= 48 ? 10 : nc == 1 && few ? 16 : nc == 2 && D < 96 ? 11 : few ? 14 : 13; break;
+    case 4: line = nc == 1 ? 8 : few && D >= 96 ? 12 : 9; break;
+    default: line = nc == 2 ? (M == 2 ? 6 : 5) : few ? 4 : 3;
+    }
+    return 2 * tiles <= line * rounds * cus ? Encoder::fused : Encoder::wave;
 }
 
 // The dictionaries as the encoders that take all of them in one kernel want them (k_encode_prep).

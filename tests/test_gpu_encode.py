@@ -71,29 +71,36 @@ def test_encode_with_more_tiles_than_blocks():
     ctx.close()
 
 
-# 256 CUs.  Three ways to encode, told apart by the launches that decide: one (a tile for all waves of a block), two (a tile per wave; the
-# second takes up what the first leaves) or one per dictionary.  Rows of up to 64 and 128 coordinates change from the first to the
-# second above 4 and 6 tiles of 32 vectors per CU (K <= 64), 4 (K <= 128), 1 and 2; longer ones from the first to the third above 12 and,
-# from D = 208 on, 48 (K <= 64), 16 and never (K <= 128), 6.  N: at the line and one more
-@pytest.mark.parametrize("N,D,K,launches", [
-    (32768, 64, 32, 1), (32769, 64, 32, 2), (32769, 16, 33, 2), (49152, 68, 32, 1), (49153, 128, 64, 2),
-    (32768, 16, 65, 1), (32769, 16, 65, 2), (32768, 128, 128, 1), (32769, 128, 128, 2), (32769, 68, 65, 2),
-    (8192, 64, 129, 1), (8193, 64, 129, 2), (8193, 4, 256, 2), (16384, 68, 129, 1), (16385, 128, 256, 2), (400000, 20, 64, 2),
-    (98304, 132, 33, 1), (98305, 204, 64, 3), (393216, 208, 33, 1), (393217, 208, 64, 3),
-    (131072, 132, 65, 1), (131073, 204, 65, 3), (131073, 208, 65, 1), (49152, 132, 140, 1), (49153, 256, 140, 3),
-    (100, 260, 20, 3), (100, 132, 32, 3)])
-def test_encoder_by_size(N, D, K, launches):
+# 256 CUs: 8192 vectors are a tile of 32 for each, 65536 a round of k_encode_wave.  Each line of the choice, at it and one vector on: F a tile for
+# all waves of a block (one launch decides), W a tile per wave (two), S dictionary by dictionary (one each, and a row pass each)
+@pytest.mark.parametrize("N,D,M,K,way", [
+    (8192, 128, 1, 256, "F"), (8193, 64, 1, 129, "S"), (8193, 20, 1, 256, "S"), (32768, 16, 1, 128, "F"), (32769, 100, 1, 65, "S"),
+    (65536, 32, 1, 33, "F"), (65537, 128, 1, 32, "S"), (32769, 16, 1, 16, "S"), (300000, 36, 1, 32, "F"), (300000, 20, 1, 64, "F"),
+    (65536, 128, 2, 256, "W"), (65537, 96, 2, 129, "S"), (65537, 68, 2, 129, "W"), (131072, 64, 2, 256, "W"), (131073, 64, 2, 129, "S"),
+    (131073, 32, 2, 64, "S"), (131073, 36, 2, 64, "W"), (131073, 16, 2, 32, "S"), (131073, 28, 2, 32, "F"),
+    (24576, 128, 2, 256, "F"), (24577, 68, 2, 256, "W"), (20480, 128, 3, 256, "F"), (20481, 128, 4, 129, "W"), (16384, 64, 3, 256, "F"),
+    (16385, 4, 3, 256, "W"), (12288, 64, 4, 256, "F"), (12289, 64, 4, 256, "W"),
+    (49152, 96, 3, 65, "F"), (49153, 128, 3, 128, "W"), (36864, 128, 4, 128, "F"), (36865, 92, 3, 65, "W"), (73728, 128, 4, 128, "F"),
+    (73729, 100, 4, 128, "W"), (32768, 64, 3, 128, "F"), (32769, 16, 4, 65, "W"),
+    (36864, 32, 3, 64, "F"), (36865, 16, 4, 33, "W"), (40960, 48, 4, 64, "F"), (40961, 36, 3, 64, "W"), (53248, 64, 4, 64, "F"),
+    (53249, 128, 4, 64, "W"), (300000, 64, 3, 64, "F"), (57344, 128, 3, 64, "F"), (57345, 128, 3, 33, "W"), (45056, 92, 4, 64, "F"),
+    (45057, 68, 3, 64, "W"), (49152, 128, 4, 32, "F"), (49153, 68, 3, 32, "W"), (32768, 24, 4, 32, "F"), (32769, 4, 3, 16, "W"),
+    (300000, 28, 4, 16, "F"),
+    (98304, 132, 3, 33, "F"), (98305, 204, 3, 64, "S"), (393216, 208, 3, 33, "F"), (393217, 208, 3, 64, "S"),
+    (131072, 132, 3, 65, "F"), (131073, 204, 3, 65, "S"), (131073, 208, 3, 65, "F"), (49152, 132, 3, 140, "F"), (49153, 256, 3, 140, "S"),
+    (100, 260, 3, 20, "S"), (100, 132, 3, 32, "S")])
+def test_encoder_by_size(N, D, M, K, way):
     """The encoders on either side of the lines between them."""
     from paper_1509_05194_amd import hclae
-    M = 3
     g = torch.Generator(device="cuda").manual_seed(N + K)
-    C = torch.randn((M, K, D), generator=g, device="cuda") * torch.tensor([1.0, 0.5, 0.3], device="cuda")[:, None, None]
+    C = torch.randn((M, K, D), generator=g, device="cuda") * torch.tensor([1.0, 0.5, 0.3, 0.2][:M], device="cuda")[:, None, None]
     X = torch.randn((N, D), generator=g, device="cuda")
     ctx = hclae.Context(N, D, M, K)
     codes, r = torch.full((N, M), 9, dtype=torch.uint8, device="cuda:0"), torch.empty_like(X)
-    ctx.timing_enable(["assign"])
+    ctx.timing_enable(["assign", "cool"])
     ctx.encode(X, C, codes, r)
-    assert ctx.timing_read()["assign"][1] == launches
+    times = ctx.timing_read()
+    assert (times["assign"][1], times["cool"][1]) == {"F": (1, 0), "W": (2, 0), "S": (M, M)}[way]
     ctx.timing_enable([])
     want, rw = torch.full_like(codes, 9), X.clone()
     for m in range(M):
