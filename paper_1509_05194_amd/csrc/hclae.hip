@@ -306,7 +306,8 @@ int launch_heat_cool(hclae_ctx *ctx, int m, int64_t N, const float *C, const uin
         return blocks;
     }
     const bool d128 = ctx->D == 128;
-    auto kern = r16 ? (d128 ? &k_row_pass<SIGN, STATS, 128, kCanAmax, kCanAmax> : &k_row_pass<SIGN, STATS, 0, kCanAmax, kCanAmax>)
+    auto kern = r16 ? (d128 ? &k_row_pass<SIGN, STATS, 128, kCanAmax, kCanAmax>
+                       : g.d4 == 1 << g.lcw ? &k_row_pass<SIGN, STATS, kOneChunk, kCanAmax, kCanAmax> : &k_row_pass<SIGN, STATS, 0, kCanAmax, kCanAmax>)
               : amax ? (d128 ? &k_row_pass<SIGN, STATS, 128, kCanAmax> : &k_row_pass<SIGN, STATS, 0, kCanAmax>)
                      : (d128 ? &k_row_pass<SIGN, STATS, 128, false> : &k_row_pass<SIGN, STATS, 0, false>);
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(kStreamThreads), 0, ctx->stream,
@@ -739,7 +740,8 @@ int enqueue_stage(hclae_ctx *ctx, int m, int64_t N, float *C, uint8_t *codes, fl
                                residue, residue, codes, Cm, C + (size_t)next * K * D, N, D, ctx->M, m, next,
                                ctx->old_codes, ctx->part_b, ctx->part_chg, slots, o16);
         } else {
-            auto kern = r16 ? (D == 128 ? &k_row_pass<0, true, 128, true, true> : &k_row_pass<0, true, 0, true, true>)
+            auto kern = r16 ? (D == 128 ? &k_row_pass<0, true, 128, true, true>
+                               : g.d4 == 1 << g.lcw ? &k_row_pass<0, true, kOneChunk, true, true> : &k_row_pass<0, true, 0, true, true>)
                       : next_amax ? (D == 128 ? &k_row_pass<0, true, 128, true> : &k_row_pass<0, true, 0, true>)
                                   : (D == 128 ? &k_row_pass<0, true, 128, false> : &k_row_pass<0, true, 0, false>);
             hipLaunchKernelGGL(kern, dim3(pa), dim3(kStreamThreads), 0, ctx->stream,

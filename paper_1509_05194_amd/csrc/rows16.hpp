@@ -2,8 +2,8 @@
 //
 // The assignment of assign_half.hpp reads x' in fp32, centres, scales and rounds it, every time: up to eleven times a stage, and it
 // is the reads that hold it (N = 1M, D = 128: 512 MB of an HBM pass, 85 of some 150 us).  A stage that keeps distance bounds
-// therefore has the pass that writes x' write the rounded rows X^ beside it, with ||X||^2 and ||X - X^||^2 per vector (24 % more
-// bytes in that pass), and all its assignments read those: half of the bytes and no conversion.  The centre mu and the scale are those of the
+// therefore has the pass that writes x' write the rounded rows X^ beside it, with ||X||^2 and ||X - X^||^2 per vector (25 to
+// 29 % more bytes in that pass), and all its assignments read those: half of the bytes and no conversion.  The centre mu and the scale are those of the
 // dictionary as the stage finds it and stay for the stage: the bounds hold for any.  The dictionary's image follows from them too,
 // codeword by codeword, so the merge writes it where it writes the codeword, and an assignment copies 64 KB into LDS instead of
 // rounding 128 KB in every block.  Undecided vectors are decided from x' in fp32 as before: the codes are the same.

@@ -72,14 +72,20 @@ __device__ __forceinline__ void put_rows16(_Float16 *row, int c4, const floatx4 
 // bytes takes 193 us); the launch shape (512 threads, 32 blocks per CU, about two steps per block) is the best of
 // a sweep of shapes.  All three modes share the geometry, so a thread adds the same squares in the same order in
 // the stage boundary as in the separate new-residue pass: the error sums are the same bits.
-// DT: the row length as a compile-time constant (with the geometry row_geom gives it), or 0: taken from D and g.
+// DT: the row length as a compile-time constant (with the geometry row_geom gives it), kOneChunk: rows of one column chunk (D a power of two up
+// to 256), or 0: whatever D and g say.
 // AMAX (MODE +1 and 0): max |x'| over everything written is merged into absmax_slot[0..kAmaxSlots) (block_absmax), for
 // a stage whose first assignment does not read every row and so cannot provide it.
-// R16 (MODE +1 and 0, with AMAX): what is written is also left as fp16 operands, with its norms: 24 % more bytes; stage boundary at
+// R16 (MODE +1 and 0, with AMAX): what is written is also left as fp16 operands, with its norms: 25 to 29 % more bytes; stage boundary at
 // N = 1M, D = 128 175 -> 225 us (5.7 TB/s as without).  Addresses as a scalar base and a 32-bit offset are what keeps it to 128
-// registers, two blocks per CU: with 64-bit addresses per thread it took 297 us.
+// registers, two blocks per CU: with 64-bit addresses per thread it took 297 us.  Rows of one chunk stay there at other lengths too, those of
+// several (136 registers, one block) do not: held to 128 they spill, which costs D = 100 and 764 as much as it gives D = 192.  Boundary,
+// us without the operands / 130 registers and a norm at a time / now: D = 16, N = 12.5M 325 / 537 / 429; D = 32, 6.25M 292 / 460 / 378;
+// D = 64, 3.1M 284 / 449 / 366; D = 256, 0.78M 268 / 456 / 355; D = 100, 2M 472 / 823 / 837; D = 192, 1.04M 293 / 487 / 464; D = 512, 0.39M
+// 261 / 383 / 363; D = 764, 0.26M 314 / 423 / 402.
+constexpr int kOneChunk = -1;
 template <int MODE, bool STATS, int DT = 0, bool AMAX = false, bool R16 = false>
-__global__ __launch_bounds__(kStreamThreads) void k_row_pass(
+__global__ __launch_bounds__(kStreamThreads, R16 && DT < 0 ? 4 : 1) void k_row_pass(
     float *r, const float *src, const uint8_t *__restrict__ codes, const float *__restrict__ Cm, const float *__restrict__ Cj,
     int64_t N, int D_rt, int M, int m, int j_stage, RowGeom g_rt,
     uint8_t *__restrict__ old_codes, double *__restrict__ part_err, long long *__restrict__ part_chg,
@@ -87,9 +93,9 @@ __global__ __launch_bounds__(kStreamThreads) void k_row_pass(
 {
     __shared__ double red[kStreamThreads / kWave];
     constexpr int U = kStreamUnroll;
-    const int D = DT ? DT : D_rt;
+    const int D = DT > 0 ? DT : D_rt;
     RowGeom g = g_rt;
-    if (DT) {
+    if (DT > 0) {
         g.d4 = DT / 4;
         g.lcw = DT >= 256 ? 6 : DT >= 128 ? 5 : DT >= 64 ? 4 : DT >= 32 ? 3 : DT >= 16 ? 2 : DT >= 8 ? 1 : 0;
     }
@@ -97,7 +103,7 @@ __global__ __launch_bounds__(kStreamThreads) void k_row_pass(
     const int tx = threadIdx.x & (cw - 1);
     const int ty = threadIdx.x >> g.lcw;
     const int rows = kStreamThreads >> g.lcw;
-    const int nchunks = (g.d4 + cw - 1) >> g.lcw;
+    const int nchunks = DT ? 1 : (g.d4 + cw - 1) >> g.lcw;
     const int64_t stride = (int64_t)gridDim.x * rows * U;
     double err = 0.0;
     long long chg = 0;
@@ -149,7 +155,7 @@ __global__ __launch_bounds__(kStreamThreads) void k_row_pass(
             load_rows(nb_next, chunk_next * cw + tx, vn);
         }
         const int c4 = chunk * cw + tx;
-        const bool live = c4 < g.d4;
+        const bool live = DT || c4 < g.d4;
         const int cc = live ? c4 : g.d4 - 1;
         const int last = last_of(nb);
         floatx4 a[U], b[U];
@@ -175,7 +181,7 @@ __global__ __launch_bounds__(kStreamThreads) void k_row_pass(
         }
         floatx4 *out = reinterpret_cast<floatx4 *>(r + nb * D);
         _Float16 *out16 = R16 ? o16.rows + nb * o16.ld : nullptr;
-        if (R16 && !(DT && DT <= 256) && nchunks > 1) neg = reinterpret_cast<const float4 *>(o16.negmu)[cc];
+        if (R16 && nchunks > 1) neg = reinterpret_cast<const float4 *>(o16.negmu)[cc];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int i = ty + u * rows;
@@ -197,8 +203,10 @@ __global__ __launch_bounds__(kStreamThreads) void k_row_pass(
             }
         }
         if (R16 && chunk_next == 0) {                               // the threads of a row are lanes of one wave
-            if (DT == 128) {
-                const float s = group_sums<2 * U, 32>(sums);        // lane i: value i
+            if (DT == 128 || cw >= 2 * U) {
+                float s = group_sums<2 * U, DT == 128 ? 32 : 2 * U>(sums);      // lane i: value i
+                if (DT != 128)
+                    for (int o = 2 * U; o < cw; o <<= 1) s += __shfl_xor(s, o, kWave);
                 const int i = ty + (tx >> 1) * rows;
                 if (tx < 2 * U && i <= last) reinterpret_cast<float *>(o16.norm + nb)[2 * i + (tx & 1)] = s;
             } else {

@@ -29,7 +29,7 @@ def _same(X, C0, idx=None, sweeps=3):
         assert np.array_equal(x, y), name
 
 
-@pytest.mark.parametrize("N,D,K", [(200000 + 1, 4, 256), (150000, 20, 33), (140000 + 31, 60, 64), (140000 + 7, 72, 65),
+@pytest.mark.parametrize("N,D,K", [(200000 + 1, 4, 256), (150000 + 3, 16, 64), (150000, 20, 33), (140000 + 31, 60, 64), (140000 + 3, 64, 256), (140000 + 7, 72, 65),
                                    (3001, 128, 100), (140000 + 1, 128, 256), (140000 + 1, 132, 256), (2000, 132, 256),
                                    (70000 + 33, 256, 256), (140000 + 5, 260, 256), (70000, 764, 32), (70000 + 3, 768, 200),
                                    (500 + 9, 1028, 33), (70000, 2304, 30)])
