@@ -166,11 +166,12 @@ __device__ __forceinline__ void init_acc(floatx16 (&acc)[KB], const float *hneg_
 // those few is computed afresh from x' (expanded form in fp32 with its rounding bound) and joins the lower bound.
 // Vectors that this settles get their aged bounds and leave the list.  Eight lanes share a vector.
 // Dynamic LDS: kVolatile rows of D floats.
-// U, the vectors per thread, is as large as leaves a block for every CU: the ranking of the drifts is a prologue that every block
-// pays for, the second look a chain of gathers that wants every CU.  Measured with 1 / 2 / 4: N = 250k (four sweeps of sixteen
-// dictionaries, D = 128, K = 256, the whole call) 46.8 ms / 47.5 / 51.9, the kernel 11.9 us on average with 1 and 21.9 with 4;
-// N = 1M (training, eight dictionaries) 35.0 / 34.2 / 33.9.  Smaller blocks (512 x 2, 256 x 4 at 250k: 47.7, 50.8) and two vectors
-// at a time per eight lanes in the second look (47.5) are slower.
+// U, the vectors per thread: the fewest of 1, 2 and 4 with which no CU has a second block (4 beyond).  The ranking of the drifts is a prologue
+// that every block pays for, so fewer and larger blocks win once they would run one after another; below that the second look, a chain of
+// gathers, wants the CUs.  Measured, us with 1 / 2 / 4 (two sweeps of four dictionaries, D = 128, K = 256, 256 CUs): N = 150k 9.4 / 9.7 / 11.7,
+// 300k 11.0 / 9.1 / 9.3, 400k 12.0 / 9.5 / 9.6, 524k 13.3 / 10.6 / 10.3, 600k 14.4 / 12.2 / 10.2, 800k 17.7 / 14.0 / 11.6, 1M 20.9 / 15.7 /
+// 13.6, 2.2M 35.8 / 24.9 / 22.0; D = 32, K = 64: 300k 11.2 / 9.1 / 9.3, 600k 14.9 / 12.2 / 10.4.  Smaller blocks (512 x 2, 256 x 4 at 250k) and
+// two vectors at a time per eight lanes in the second look are slower.
 constexpr int kBoundThreads = 1024;
 template <int U>
 __global__ __launch_bounds__(kBoundThreads) void k_bounds_step(

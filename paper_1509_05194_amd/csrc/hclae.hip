@@ -475,8 +475,8 @@ int launch_assign(hclae_ctx *ctx, int m, int64_t N, const float *xp, const float
 int launch_bounds_step(hclae_ctx *ctx, int m, int64_t N, const uint8_t *codes, const float *xp, const float *Cm)
 {
     Timed t_(ctx, HCLAE_T_BOUNDS);
-    // vectors per thread: as many as leave a block for every CU (see k_bounds_step)
-    const int64_t per = N / ((int64_t)ctx->cus * kBoundThreads);
+    // vectors per thread: the fewest with which no CU has a second block (see k_bounds_step)
+    const int64_t per = (N - 1) / ((int64_t)ctx->cus * kBoundThreads);
     const int u = per < 1 ? 1 : per < 2 ? 2 : 4, span = kBoundThreads * u;
     auto kern = u == 1 ? &k_bounds_step<1> : u == 2 ? &k_bounds_step<2> : &k_bounds_step<4>;
     const uint64_t attr_set = 1ull << (u == 1 ? 4 : u == 2 ? 5 : 6);        // this instance's bit in ctx->attr_done

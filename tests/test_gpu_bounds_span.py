@@ -9,7 +9,7 @@ from paper_1509_05194_amd import hclae, synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("blocks,more", [(1, 0), (2, -1), (2, 0), (4, 1)])
+@pytest.mark.parametrize("blocks,more", [(1, 0), (1, 1), (2, -1), (2, 0), (2, 1), (4, 1)])
 def test_bounds_by_number_of_vectors(blocks, more):
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     N, D, M, K = 1024 * cus * blocks + more, 8, 2, 32
