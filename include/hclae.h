@@ -102,9 +102,11 @@ int hclae_anneal_stage(hclae_ctx *ctx, int m, int64_t N, int D, float *C, int M,
                        const int64_t *init_idx, hclae_stage_stats *stats);
 
 /*
- * (hclae_anneal_stage, hclae_sweep, hclae_anneal with the exact shortcuts on, N K D > 2^23 and iters > 0: the first such call keeps
- * x' in fp16 as well, in arrays of 32 ceil(D / 16) + 8 bytes per vector of N_max that it allocates and the ctx keeps.  If they cannot be
- * had, or the stream is being captured, the call runs without them; the results are the same.)
+ * (Memory of hclae_anneal_stage, hclae_sweep and hclae_anneal beyond what hclae_create allocates: with the exact shortcuts on, N K D > 2^23
+ * and iters > 0 they keep x' in fp16 as well, in arrays of 32 ceil(D / 16) + 8 bytes per vector of N_max and some hundred kilobytes, which
+ * the first such call allocates and hclae_destroy frees; a program that wants neither the memory nor the allocation turns the shortcuts off with
+ * hclae_set_pruning before it.  If there is no memory for them, these calls run without them from then on; while the
+ * stream is being captured, that call does.  The results are the same.)
  *
  * Sec. 3.1, "multiple iterations": hclae_anneal_stage for m = 0..M-1 in order.
  * reencode_mode 0: each stage re-encodes only its own column (keeps E non-increasing).

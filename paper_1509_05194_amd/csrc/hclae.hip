@@ -117,6 +117,7 @@ struct hclae_ctx {
     float *r16_ref;              // [K][D] rows that seed the next stage
     unsigned *r16_words;         // [kWords16]
     bool stage16;                // the running stage assigns from them
+    bool r16_none;               // there was no memory for them: not asked for again
     unsigned long long *work; // [4] work counters: assignments, vectors recomputed, vectors the scores left undecided
     int64_t *seed_idx;       // [M][K] seed rows of a sweep from all-zero dictionaries (a single stage uses row 0)
     double *part_a, *part_b; // [nparts]
@@ -591,11 +592,11 @@ bool bounds_pay(const hclae_ctx *ctx, int64_t N)
     return ctx->pruning && (double)N * ctx->K * ctx->D > 8388608.0;
 }
 
-// Arrays of the fp16 rows, allocated once per ctx at the first stage that keeps bounds.  Where that cannot be (no memory, or the
-// stream is being captured) the stage reads x' itself, with the same results: the caller goes on.
+// Arrays of the fp16 rows, allocated once per ctx at the first stage that keeps bounds.  Where that cannot be (no memory, which is then not
+// asked for again, or the stream is being captured) the stage reads x' itself, with the same results: the caller goes on.
 void rows16_scratch(hclae_ctx *ctx)
 {
-    if (ctx->r16_rows) return;
+    if (ctx->r16_rows || ctx->r16_none) return;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(ctx->stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
         (void)hipGetLastError();
@@ -623,6 +624,7 @@ void rows16_scratch(hclae_ctx *ctx)
     if (e == hipSuccess && rows16_ld(ctx->D) != ctx->D) e = hipMemsetAsync(ctx->r16_rows, 0, rows, ctx->stream);
     if (e == hipSuccess) e = hipMemsetAsync(ctx->r16_words, 0, sizeof(unsigned) * kWords16, ctx->stream);
     if (e == hipSuccess) return;
+    ctx->r16_none = true;
     (void)hipGetLastError();
     for (auto &a : allocs) {
         if (*a.p) (void)hipFree(*a.p);

@@ -109,3 +109,29 @@ def test_first_call_under_capture():
                 assert torch.equal(a, b)
         ctx.close()
         other.close()
+
+
+def test_without_memory_for_the_rows():
+    """A context made for more vectors than the device has room for in fp16: its trainings read x' itself, with the same bits, call after
+    call, and the second call leaves the free memory as it was."""
+    N, D, M, K = 4000, 2304, 2, 32
+    assert N * K * D > 2 ** 23                             # else the stage keeps no bounds
+    from paper_1509_05194_amd import hclae
+    n_max = torch.cuda.get_device_properties(0).total_memory // (2 * D) + 1
+    g = np.random.default_rng(5)
+    X = (g.standard_normal((20, D))[g.integers(0, 20, N)] + 0.3 * g.standard_normal((N, D))).astype(np.float32)
+    idx = np.stack([g.choice(N, K, replace=False) for _ in range(M)]).astype(np.int64)
+    out = []
+    for size in (N, n_max):
+        ctx = hclae.Context(size, D, M, K)
+        free = []
+        for _ in range(2):
+            C, codes, r = torch.zeros((M, K, D), device="cuda"), torch.zeros((N, M), dtype=torch.uint8, device="cuda"), to_dev(X)
+            ctx.anneal(C, codes, r, 4, 2, init_idx=idx)
+            out.append([t.cpu().numpy() for t in (C, codes, r)])
+            free.append(torch.cuda.mem_get_info()[0])
+        assert abs(free[0] - free[1]) < 2 ** 26
+        ctx.close()
+    for other in out[1:]:
+        for a, b in zip(out[0], other):
+            assert np.array_equal(a, b)
