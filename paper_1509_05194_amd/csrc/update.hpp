@@ -133,9 +133,11 @@ constexpr unsigned kMovedDirect = 1u << 17;         // most additions of one sig
 __device__ __forceinline__ bool moved_direct(unsigned total, int D) { return (unsigned long long)total * (unsigned)D <= kMovedDirect; }
 
 // Whether so many of the N vectors have moved that a pass over all of them, which reads rows in order and adds each once, is shorter
-// than gathering those that moved and adding them twice; the merge asks the same.  N = 1M, D = 128: 86 us against 180 for some 0.7M
-// moved ones.
-__device__ __forceinline__ bool moved_full(unsigned total, int64_t N) { return 3ll * (long long)total > N; }
+// than gathering those that moved and adding them twice; the merge asks the same.  Both with their merges, us moved / all, by the
+// share that moved: N = 1M, D = 128, K = 256 0.16 76 / 109, 0.33 122 / 110, 0.49 170 / 110; N = 200k 0.14 39 / 49, 0.19 47 / 48, 0.34 58 / 47;
+// N = 1M, D = 32 0.20 63 / 72, 0.39 88 / 69; N = 300k, D = 64, K = 64 0.13 43 / 46, 0.24 53 / 48; N = 100k, D = 960 0.21 90 / 101, 0.27 104 /
+// 100, 0.34 112 / 98; N = 1M, D = 16, K = 16 0.14 54 / 61, 0.23 63 / 62.  A quarter lies between for all.
+__device__ __forceinline__ bool moved_full(unsigned total, int64_t N) { return 4ll * (long long)total > N; }
 
 // Blocks (of the x dimension) of a pass over all N vectors: at least 1024 rows each.
 __host__ __device__ inline int full_blocks(int64_t N, int max_blocks)
