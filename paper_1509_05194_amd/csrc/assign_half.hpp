@@ -453,6 +453,33 @@ __device__ __forceinline__ float block_key(const floatx16 &a)
     return m;
 }
 
+// The best of a vector's scores on keys (mx) and its codeword, the same in both lanes that share the vector.
+template <int KB>
+__device__ __forceinline__ int best_half(const floatx16 (&acc)[KB], int h, int K, float &mx)
+{
+    mx = -__builtin_inff();
+    int blk = 0;
+#pragma unroll
+    for (int b = 0; b < KB; ++b) {
+        const float k = block_key(acc[b]);
+        blk = k > mx ? b : blk;
+        mx = __builtin_elementwise_maximum(mx, k);
+    }
+    const int v = (int)(__float_as_uint(mx) & 15u);
+    const uint2 s = both_halves(__float_as_uint(mx)), k = both_halves((unsigned)(32 * blk + 8 * (v >> 2) + 4 * h + (v & 3)));
+    const float lo = __uint_as_float(s.x), hi = __uint_as_float(s.y);
+    mx = __builtin_elementwise_maximum(lo, hi);
+    const int code = (int)(lo >= hi ? k.x : k.y);
+    return code < K ? code : 0;                                     // beyond K only with non-finite input
+}
+
+// What a score may be off: h, what the index bits did to the best key, and what the subtraction of the threshold may lose of the larger
+// of it and a score that is near it.
+__device__ __forceinline__ float margin_half(const HalfConsts &c, float mx, float xn, float e)
+{
+    return fmaf(c.hx, xn, fmaf(4.3e-6f, fabsf(mx), fmaf(4.4e-6f * e, c.cmax, c.h))) + 1e-9f;
+}
+
 // Takes thr from every score, on the matrix cores: one more product of at most 4 terms, thr in three fp16 pieces of 11 bits (the
 // remainders are exact, what they leave of thr is below 2^-33 of it and 2^-35).  |thr| < kHalfMaxThr.
 constexpr float kHalfMaxThr = 6e7f;                 // 1024 times fp16's range, and some
@@ -514,7 +541,7 @@ struct HalfWave {
     int nmoved;                                     // wave-uniform
 };
 
-// Before the block's first barrier.
+// A barrier of the block comes between this and the first use of what it sets.
 __device__ __forceinline__ HalfWave half_wave(char *lds, const HalfLds &L, HalfItem *items)
 {
     HalfWave w;
@@ -879,27 +906,9 @@ __device__ __forceinline__ void decide_half(
     unsigned long long *__restrict__ moved_list, unsigned *__restrict__ moved_count)
 {
     const int h = lane >> 5;
-    float mx = -__builtin_inff();
-    int code = 0;
-    {
-        int blk = 0;
-#pragma unroll
-        for (int b = 0; b < KB; ++b) {
-            const float k = block_key(acc[b]);
-            blk = k > mx ? b : blk;
-            mx = __builtin_elementwise_maximum(mx, k);
-        }
-        const int v = (int)(__float_as_uint(mx) & 15u);
-        code = 32 * blk + 8 * (v >> 2) + 4 * h + (v & 3);
-        const uint2 s = both_halves(__float_as_uint(mx)), k = both_halves((unsigned)code);
-        const float lo = __uint_as_float(s.x), hi = __uint_as_float(s.y);
-        mx = __builtin_elementwise_maximum(lo, hi);
-        code = (int)(lo >= hi ? k.x : k.y);
-        code = code < K ? code : 0;                                 // beyond K only with non-finite input
-    }
-    // h, what the index bits did to the best key, and what the subtraction of the threshold may lose of the larger of it and a
-    // score that is near it
-    const float hh = fmaf(c.hx, xn, fmaf(4.3e-6f, fabsf(mx), fmaf(4.4e-6f * e, c.cmax, c.h))) + 1e-9f;
+    float mx;
+    const int code = best_half<KB>(acc, h, K, mx);
+    const float hh = margin_half(c, mx, xn, e);
     const float low = mx - 2.f * e * lds_w[code] - hh;   // lower bound of the best one's true score
     const float thr = low - hh;                                     // candidates: U_k + h >= low
     const bool big = !(x2 < kHalfMaxNorm * kHalfMaxNorm && fabsf(thr) < kHalfMaxThr);   // may not fit fp16

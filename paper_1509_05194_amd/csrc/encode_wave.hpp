@@ -1,5 +1,5 @@
 // Greedy encoding (Sec. 3.3, Eq. 3 with one path) of large calls with rows of up to 128 coordinates, in one kernel: a wave takes 32
-// vectors through ALL M dictionaries, the residual rows staying in its registers in between (K > 128 and D > 64: but for 14 to 17 registers'
+// vectors through ALL M dictionaries, the residual rows staying in its registers in between (K > 128 and D > 64: but for 13 to 15 registers'
 // worth in scratch memory).
 //
 // Dictionary by dictionary a row crosses HBM three times per dictionary (assignment, residue in, residue out), which is what holds
@@ -164,26 +164,10 @@ __global__ __launch_bounds__(kAssignThreads) void k_encode_wave(
                 }
             }
             // the best, the threshold and the candidates: decide_half has the reasons
-            float mx = -inf;
-            int code = 0;
-            {
-                int blk = 0;
-#pragma unroll
-                for (int i = 0; i < KB; ++i) {
-                    const float k = block_key(acc[i]);
-                    blk = k > mx ? i : blk;
-                    mx = __builtin_elementwise_maximum(mx, k);
-                }
-                const int v = (int)(__float_as_uint(mx) & 15u);
-                code = 32 * blk + 8 * (v >> 2) + 4 * h + (v & 3);
-                const uint2 s = both_halves(__float_as_uint(mx)), k = both_halves((unsigned)code);
-                const float lo = __uint_as_float(s.x), hi = __uint_as_float(s.y);
-                mx = __builtin_elementwise_maximum(lo, hi);
-                code = (int)(lo >= hi ? k.x : k.y);
-                code = code < K ? code : 0;
-            }
+            float mx;
+            int code = best_half<KB>(acc, h, K, mx);
             const float *Cm = C + (size_t)m * K * D;
-            const float hh = fmaf(c.hx, xn, fmaf(4.3e-6f, fabsf(mx), fmaf(4.4e-6f * e, c.cmax, c.h))) + 1e-9f;
+            const float hh = margin_half(c, mx, xn, e);
             const float thr = mx - 2.f * e * lds_w[code] - 2.f * hh;
             const bool big = !(x2 < kHalfMaxNorm * kHalfMaxNorm && fabsf(thr) < kHalfMaxThr);
             subtract_half<KB>(acc, thr, h);

@@ -153,7 +153,7 @@ struct Rows16Args {
 };
 
 // k_assign_half over the fp16 rows, the dictionary resident in LDS.  A wave owns tiles of 32 vectors; up to eight k-steps (128 dims)
-// of a row, 256 bytes, are in flight while the ones before are contracted.  FULL: the steps are a multiple of eight.
+// of a row, 256 bytes, are in flight while the ones before are contracted.  UNIT: so many, 8 where the row's steps are a multiple of it, else 4.
 template <int KB, int PRUNE, int UNIT>
 __global__ __launch_bounds__(kAssignThreads) void k_assign_rows16(
     const float *__restrict__ xp, const float *__restrict__ Cm, const float *__restrict__ hneg, Rows16Args x16,
