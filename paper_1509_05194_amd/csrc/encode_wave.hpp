@@ -10,7 +10,7 @@
 // decisions and the residuals the same fp32 subtractions as dictionary by dictionary.
 //
 // Measured (D = 128, M = 8, K = 256, us dictionary by dictionary / here): N = 1M 2480 / 1630, 200k 620 / 420, 49k 237 / 131; D = 64, 100k
-// 288 / 140.  Of the 1630, 930 are the arithmetic (MFMAs and VALU in turn, two waves to a SIMD), some 250 the rows to subtract (gathered
+// 288 / 140 (calls in a row; the kernel alone 1690 when it runs once).  Of the 1630, 930 are the arithmetic (MFMAs and VALU in turn, two waves to a SIMD), some 250 the rows to subtract (gathered
 // from L2, 16 bytes a lane; through LDS with contiguous reads it is no faster), 230 the dictionaries' way into LDS and the barriers,
 // 200 the undecided vectors.  Tiles whose vectors have many candidates go on in a second launch (k_encode_rest), which decides them with all
 // the waves of a block; data that consist of such (N = 200k, M = 8, us dictionary by dictionary / here): groups 30 standard deviations apart
