@@ -96,7 +96,9 @@ struct BeamTile {
 // as it has been converted: addresses are clamped into the row, and what lies past D is multiplied by zero (mu and the dictionary are
 // zero there).  Here, where ten rows a vector keep the matrix cores busy, it saves a fiftieth of the call (N = 200k, L = 10, D = 128:
 // 6.26 -> 6.14 ms, with the block maxima two scores a step); k_assign_half, which waits for its rows, is 3 % slower with it.
-template <int KB>
+// USE: an instance for each kernel that has it; shared with k_encode_rest the compiler puts it together in another order, and this kernel's
+// calls take 1 % longer (5.95 -> 6.00 ms).
+template <int KB, int USE = 0>
 __device__ __forceinline__ void mfma_chunk_refill(
     floatx16 (&acc)[KB], float4 (&x)[8], const char *__restrict__ img, const float *__restrict__ negmu, int q, int lane,
     float scale, float &xsq, float &dsq, const float *__restrict__ next, int qn, int D)

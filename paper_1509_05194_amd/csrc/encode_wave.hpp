@@ -373,7 +373,7 @@ __global__ __launch_bounds__(kAssignThreads) void k_encode_rest(
             while (j < places) {
                 const int q_n = q + 1 == NC ? 0 : q + 1, j_n = q_n ? j : skip(j + 1);
                 const int n_n = q_n ? n : vec_of(j_n < places ? j_n : j);       // after the last step the row again: unused
-                mfma_chunk_refill<KB>(acc, x, lds + L.img, reinterpret_cast<const float *>(lds + L.mu), q, lane, c.scale, xsq, dsq, row_ptr(n_n), q_n, D);
+                mfma_chunk_refill<KB, 1>(acc, x, lds + L.img, reinterpret_cast<const float *>(lds + L.mu), q, lane, c.scale, xsq, dsq, row_ptr(n_n), q_n, D);
                 if (q_n == 0) {
                     const float x2 = xsq + __shfl_xor(xsq, 32, kWave), norm = sqrtf(x2) * 1.001f;
                     const float e = mfma_bound_half<KB>(acc, reinterpret_cast<const unsigned *>(lds + L.waug), x2,
