@@ -95,7 +95,9 @@ struct BeamTile {
 // mfma_chunk_half with the dictionary's operands read ahead (contract_half) and x refilled in place, with chunk qn of row `next`, as soon
 // as it has been converted: addresses are clamped into the row, and what lies past D is multiplied by zero (mu and the dictionary are
 // zero there).  Here, where ten rows a vector keep the matrix cores busy, it saves a fiftieth of the call (N = 200k, L = 10, D = 128:
-// 6.26 -> 6.14 ms, with the block maxima two scores a step); k_assign_half, which waits for its rows, is 3 % slower with it.
+// 6.26 -> 6.14 ms, with the block maxima two scores a step).  For K > 128 only: with fewer codewords a step has too few MFMAs to hide what it
+// sends for, and two buffers are shorter (a launch, N = 100k, L = 10, us so / two buffers: K = 21, D = 92 96 / 78, D = 128 110 / 104, K = 54, D = 92
+// 88 / 79, K = 100, D = 192 157 / 153); k_assign_half, which waits for its rows, is 3 % slower with it.
 // USE: an instance for each kernel that has it; shared with k_encode_rest the compiler puts it together in another order, and this kernel's
 // calls take 1 % longer (5.95 -> 6.00 ms).
 template <int KB, int USE = 0>
@@ -152,11 +154,17 @@ __global__ __launch_bounds__(kAssignThreads) void k_beam_score_half(
     int64_t tile = t0;
     int q = 0;
     init_acc<KB>(acc, lds_h, h);
-    for (int64_t i = 0; i < G; ++i) {
+    // one step: contract x (chunk q of the tile), with the chunk after it on its way into xn, and select where it was the tile's last
+    auto step = [&](float4 (&x)[8], float4 (&xn)[8], bool more) {
         const int q_n = q + 1 == NC ? 0 : q + 1;
         const int64_t tile_n = q_n ? tile : tile + tstride;
-        const bool more = i + 1 < G;                     // the last step re-reads itself: unused
-        mfma_chunk_refill<KB>(acc, x, lds + L.img, lds_mu, q, lane, c.scale, xsq, dsq, row_ptr(more ? tile_n : tile), more ? q_n : q, D);
+        if constexpr (KB == 8) {                         // xn is x; the last step re-reads itself: unused
+            mfma_chunk_refill<KB>(acc, x, lds + L.img, lds_mu, q, lane, c.scale, xsq, dsq, row_ptr(more ? tile_n : tile), more ? q_n : q, D);
+        } else {
+            float unused = 0.f;
+            if (more) load_x_chunk(xn, row_ptr(tile_n), q_n, h, D);
+            mfma_chunk_half<KB, false, false>(acc, x, lds + L.img, lds_mu, q, lane, c.scale, xsq, dsq, unused, 4);
+        }
         if (q == NC - 1) {
             const float x2 = xsq + __shfl_xor(xsq, 32, kWave), norm = sqrtf(x2) * 1.001f;
             const float e = mfma_bound_half<KB>(acc, reinterpret_cast<const unsigned *>(lds + L.waug), x2,
@@ -170,6 +178,16 @@ __global__ __launch_bounds__(kAssignThreads) void k_beam_score_half(
         }
         tile = tile_n;
         q = q_n;
+    };
+    if constexpr (KB == 8) {
+        for (int64_t i = 0; i < G; ++i) step(x, x, i + 1 < G);
+    } else {
+        float4 y[8];
+        for (int64_t i = 0; i < G; i += 2) {
+            step(x, y, i + 1 < G);
+            if (i + 1 >= G) break;
+            step(y, x, i + 2 < G);
+        }
     }
 }
 
