@@ -1027,7 +1027,7 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign_half(
     char *lds = reinterpret_cast<char *>(smem4);
     const HalfLds L = half_lds(KB, NC, NC);
     const int lane = lane_id();
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);      // scalar, and the tile order with it: 469 -> 461 us, N = 8M, D = 32
     const int h = lane >> 5;
     const int r = lane & 31;
     const float *lds_h = reinterpret_cast<const float *>(lds + L.hneg);
