@@ -244,7 +244,7 @@ __global__ __launch_bounds__(kStreamThreads, R16 && DT < 0 ? 4 : 1) void k_row_p
 // The same passes for long rows (D >= kWideMinD): a wave owns whole rows.  Lane l takes float4 columns l, l + 64,
 // l + 128, l + 192 of a group of 256 columns (one contiguous kilobyte of the row per wave-instruction, up to 4 KB of
 // one row in flight), kWideRows rows per step, steps (row pair, column group) pipelined as in k_row_pass.  Measured at
-// N = 1M, D = 960 (3.84 GB each way): stage boundary 1.39 ms against 1.51 ms for k_row_pass, new residue 1.36 ms
+// N = 1M, D = 960 (3.84 GB each way): stage boundary 1.39 ms against 1.51 ms for k_row_pass (with fp16 rows 1.83), new residue 1.36 ms
 // against 1.43 ms.  Results are those of k_row_pass bit for bit (the same fp32 operations per element); the error
 // sums differ in their order of additions, which is the same in all three modes here too.  Two blocks per CU: the stage boundary with
 // fp16 rows (N = 200k) takes 367 us within 128 registers, 398 us with what the compiler would take.
